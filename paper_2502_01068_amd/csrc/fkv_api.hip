@@ -19,7 +19,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
-  size_t partial, rowstat, scores_group, scores_tsp, counters, fused_part, fused_lse, sel_long, sel_coop, dec_part, wout_o, wout_ms, total;
+  size_t partial, rowstat, scores_group, scores_tsp, counters, fused_part, fused_lse, sel_long, sel_coop, dec_part, dec_count, wout_o, wout_ms, total;
   int max_stat_blocks;
 };
 
@@ -37,7 +37,8 @@ WsLayout ws_layout(int64_t max_tokens, int32_t max_seqs) {
   w.fused_lse = off;    off += align_up(kFusedLseBytes);
   w.sel_long = off;     off += align_up((size_t)kLongMaxInst * kLongStateWords * sizeof(uint32_t));
   w.sel_coop = off;     off += align_up(kCoopBoxBytes);
-  w.dec_part = off;     off += align_up((size_t)max_seqs * kMaxKvHeads * kMaxReal * kDecodeMaxSplits * (kHeadDim + 2) * sizeof(float));
+  w.dec_part = off;     off += align_up((size_t)2 * kDecodeMaxBlocks * kDecodeSlotFloats * sizeof(float));
+  w.dec_count = off;    off += align_up((size_t)max_seqs * kMaxKvHeads * sizeof(unsigned));
   const size_t wout_slots = (size_t)kWoutBlocks + (size_t)kMaxVGroups * max_seqs;
   w.wout_o = off;       off += align_up(wout_slots * kRowsPerGroup * kHeadDim * sizeof(float));
   w.wout_ms = off;      off += align_up(wout_slots * kRowsPerGroup * sizeof(float2));
@@ -585,6 +586,7 @@ int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_
   }
   const bool counted = e == hipSuccess;
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.counters, 0, kNumCounters * sizeof(unsigned));
+  if (e == hipSuccess) e = hipMemset(c->ws + c->lay.dec_count, 0, (size_t)max_seqs * kMaxKvHeads * sizeof(unsigned));
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.fused_part, 0xFF, kFusedPartBytes);  // every mailbox empty
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.fused_lse, 0xFF, kFusedLseBytes);
   if (e == hipSuccess) e = reset_select_exchange(c);
@@ -800,7 +802,6 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
   }
   DecodeArgs a{};
   int64_t tot = 0;
-  int n_max = 0;
   a.off[0] = 0;
   for (int b = 0; b < r.n_seq; ++b) {
     if (n_per_seq[b] < 1) return FKV_EINVAL;
@@ -808,7 +809,6 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
     tot += n_per_seq[b];
     if (tot > INT32_MAX) return FKV_EINVAL;
     a.off[b + 1] = (int)tot;
-    if (n_per_seq[b] > n_max) n_max = n_per_seq[b];
   }
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out)) return FKV_EALIGN;
   if (!ctx) return FKV_ENULL;
@@ -819,6 +819,7 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
   a.v = static_cast<const uint16_t *>(v);
   a.out = out;
   a.part = reinterpret_cast<float *>(ctx->ws + ctx->lay.dec_part);
+  a.count = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.dec_count);
   const bool token_major = pg || kv_layout == FKV_KV_TOKEN_MAJOR;
   a.tok_stride = token_major ? (int64_t)r.Hkv * kHeadDim : kHeadDim;
   a.head_stride = token_major ? kHeadDim : tot * kHeadDim;
@@ -829,16 +830,11 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
     a.n_pages = (int)pg->n_pages;
   }
   a.Hq = r.Hq; a.Hkv = r.Hkv; a.G = r.G; a.n_seq = r.n_seq;
-  a.V = r.V; a.vsh = r.vsh;
-  int splits = (n_max + 63) / 64;  // at least 64 tokens per block, at most decode_max_splits() blocks per head
-  if (splits < 1) splits = 1;
-  if (splits > decode_max_splits()) splits = decode_max_splits();
-  a.n_split = splits;
   const float scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.0f / sqrtf((float)shape->head_dim);
   a.scale_log2e = scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
   Timed t(ctx, st, KID_DECODE);
-  const hipError_t e = launch_decode(a, st);
+  const hipError_t e = launch_decode(a, ctx->n_cu > 0 ? ctx->n_cu : 256, st);
   return e == hipSuccess ? FKV_OK : hip_fail(e);
 }
 }  // namespace

@@ -2,227 +2,385 @@
 // compacted cache KVCompress leaves behind (Algorithm 1 returns it; Sec. 5.3 measures decoding over
 // it).  out[h] = sum_t softmax_t(scale * q[h].k[g(h),t]) * v[g(h),t], every cached token visible.
 //
-// The work is a pure stream of K and V (512 B per cached token and KV head, ~1 flop per byte), so
-// it runs on the vector ALUs: 16 lanes cover one token's 256-byte row with one 128-bit load each,
-// a wave takes 4 tokens per step, the G query heads of the KV group share every K / V load.  Tokens
-// are split over blocks (flash-decoding style); each block keeps a running (max, sum, weighted V
-// sum) per head, and a second small launch merges the splits in a fixed order.
+// Bound: the bytes of K and V (512 B per cached token and KV head).  Both contractions run on the matrix
+// cores (16x16x32 tiles, the G <= 8 query heads of a KV head on the N side), where they take a few per
+// cent of the time the bytes take; as vector dot products they were what the kernel waited for.
+//   S = K . Q^T  A operand = 16 tokens x 32 of the 128 columns, read from a wave-private 8 KiB LDS tile that
+//                128-bit LDS-direct loads fill with whole rows (16 lanes per row, XOR swizzle on the
+//                global side; loading the operand layout itself touches 64 bytes of 16 rows per
+//                instruction and cost 10 % on token-major caches).  The result leaves head n = lane % 16
+//                on the lane and 8 tokens of the tile in its registers: the softmax is per lane, only the
+//                running maximum is shared between the 4 lanes of a head.
+//   O^T += V^T . P  B operand = the probabilities as the first contraction left them (the token order inside
+//                a contraction is free as long as both operands agree).  A operand: lane (c, q) loads
+//                column chunk c (8 values) of those same 8 tokens into registers, whole rows per
+//                instruction; the 8x8 block is transposed inside the lane (32 byte permutes), so operand j
+//                holds d = 8 c + j.
+// Probabilities enter as three bf16 pieces that add up to the fp32 value.  A wave keeps one tile of 32
+// tokens (16 KiB of K and V) in flight while it works on the one before it; one block of 4 waves per CU is
+// enough for that (more resident waves were slower: 256 / 512 / 1024 blocks took 57 / 61 / 68 us for 304 MB).
+//
+// The tiles of all rows (row = KV head of a sequence) form one line that is cut into equal shares, one per
+// block, so ragged batches leave no CU idle.  Rows cut by a share's end are folded by the last block
+// that finishes a piece of them, in piece order (reproducible): one launch per call, nothing waits.
+//
+// Measured (device time per call, before -> after): 2048 tokens, 1 sequence 11.0 -> 8.0 us; 32768 tokens 35.5 ->
+// 26.9 us (5.0 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 56.3 us (5.4 TB/s).
+#include <algorithm>
+#include <type_traits>
+
+#include "fkv_dpp.h"
 #include "fkv_internal.h"
+
 
 namespace fkv {
 
-constexpr int kDecThreads = 256;
-constexpr int kDecWaves = kDecThreads / 64;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
+
+constexpr int kDecTile = 32;                  // tokens a wave works on at a time
 constexpr float kDecNegBig = -1.0e30f;
 
-int decode_max_splits(void) { return kDecodeMaxSplits; }
-
 __device__ __forceinline__ float dec_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-__device__ __forceinline__ void unpack8(const u32x4 &w, float (&f)[8]) {
-  f[0] = bf16_lo(w[0]); f[1] = bf16_hi(w[0]); f[2] = bf16_lo(w[1]); f[3] = bf16_hi(w[1]);
-  f[4] = bf16_lo(w[2]); f[5] = bf16_hi(w[2]); f[6] = bf16_lo(w[3]); f[7] = bf16_hi(w[3]);
+
+// Maximum / sum over the 4 lanes that hold the same head (16 lanes apart), in every lane.
+__device__ __forceinline__ float quad_max(float x) {
+  unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  u = __float_as_uint(x);
+  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  u = __float_as_uint(x);
+  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Sum over the 16 lanes of a DPP row (= the lanes that share a token), result in every lane of the
-// row, on the vector ALU (row rotations; no LDS crossbar traffic).  Every lane adds the same pairs
-// at every level, so the 16 results are bit-identical.
-__device__ __forceinline__ float row_sum16(float x) {
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false));  // row_ror:8
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, false));  // row_ror:4
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xF, 0xF, false));  // row_ror:2
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xF, 0xF, false));  // row_ror:1
-  return x;
+// The K tile's operands: waits until at most the 8 youngest loads (the V tile's) are outstanding, reads and waits for
+// the reads, so that the tile may be overwritten.  One asm block: for an ordinary LDS read the compiler would
+// wait for every outstanding load, the V tile's too.
+__device__ __forceinline__ void read_k_tile(u32x4 (&r)[8], const uint32_t (&addr)[4]) {
+  asm volatile(
+      "s_waitcnt vmcnt(8)\n\t"
+      "ds_read_b128 %0, %8\n\t"
+      "ds_read_b128 %1, %9\n\t"
+      "ds_read_b128 %2, %10\n\t"
+      "ds_read_b128 %3, %11\n\t"
+      "ds_read_b128 %4, %8 offset:4096\n\t"
+      "ds_read_b128 %5, %9 offset:4096\n\t"
+      "ds_read_b128 %6, %10 offset:4096\n\t"
+      "ds_read_b128 %7, %11 offset:4096\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+      : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
+      : "memory");
 }
 
-struct DecState {  // running softmax of one head over this lane's tokens, for the lane's 8 columns
-  float m, l, acc[8];
-};
-__device__ __forceinline__ void dec_merge(DecState &a, float m2, float l2, const float (&acc2)[8]) {
-  const float mn = fmaxf(a.m, m2);
-  const float ca = dec_exp2(a.m - mn), cb = dec_exp2(m2 - mn);
-  a.l = a.l * ca + l2 * cb;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc[i] = a.acc[i] * ca + acc2[i] * cb;
-  a.m = mn;
+__device__ __forceinline__ void agent_store2(float *p, float x, float y) {
+  const float2 v = make_float2(x, y);
+  unsigned long long bits;
+  __builtin_memcpy(&bits, &v, sizeof bits);
+  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 agent_load2(const float *p) {
+  const unsigned long long bits =
+      __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float2 v;
+  __builtin_memcpy(&v, &bits, sizeof v);
+  return v;
 }
 
-// grid (n_split, V, B), one block per split and virtual group; partial results part[((b*Hq + h)*n_split + s)*(128+2)]: 128 weighted sums, max, sum
-template <bool kPaged>
-__global__ __launch_bounds__(kDecThreads) void k_decode_partial(DecodeArgs a) {
-  __shared__ float lds[kDecWaves][kMaxGroup][16][10];
-  const int s = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c = lane & 15, tq = lane >> 4;
-  const int n = a.off[b + 1] - a.off[b];
-  int chunk = (n + a.n_split - 1) / a.n_split;
-  chunk = (chunk + 15) / 16 * 16;
-  const int t0 = s * chunk, t1 = min(n, t0 + chunk);
-  const int kvh = vg_kv_head(a, g), h0 = vg_head0(a, g), n_h = vg_heads(a, g);
+// The work of a launch is a line of 32-token tiles, row after row (a row = one KV head of one sequence); block i
+// of N takes tiles [i T / N, (i + 1) T / N).  A row that lies inside one block is finished there; the pieces of a row
+// that is cut go to partial slots, at most two per block (2 i: a piece that does not begin its row, 2 i + 1: one that does).
+__device__ __forceinline__ int64_t dec_first_tile(int64_t block, int64_t tiles, int64_t n_blocks) { return block * tiles / n_blocks; }
+__device__ __forceinline__ int dec_block_of(int64_t tile, int64_t tiles, int64_t n_blocks) {
+  return (int)(((tile + 1) * n_blocks - 1) / tiles);
+}
 
-  float qf[kMaxGroup][8];
+template <bool kPaged, int kWaves>
+__global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
+  constexpr int kThr = kWaves * 64;
+  constexpr int kTileBytes = kDecTile * kHeadDim * 2;
+  __shared__ __attribute__((aligned(16))) uint8_t k_lds[kWaves][kTileBytes];
+  __shared__ __attribute__((aligned(16))) float o_lds[kWaves][kMaxReal][kHeadDim];
+  __shared__ float m_lds[kWaves][16], l_lds[kWaves][16];
+  __shared__ float w_lds[kMaxReal][kDecodeMaxSplits];
+  __shared__ unsigned last_lds;
+  typedef __attribute__((address_space(1))) const void *gptr_t;
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, q = lane >> 4;
+  const int G = a.G;
+  const int64_t n_blocks = gridDim.x;
+  int64_t at = dec_first_tile(blockIdx.x, a.tiles, n_blocks);
+  const int64_t at_end = dec_first_tile((int64_t)blockIdx.x + 1, a.tiles, n_blocks);
+  uint8_t *stage = k_lds[wave];
+  // Row c of the first contraction's A operand is token 4 (c % 4) + c / 4 of a half tile, so that row 4 q + r of
+  // its result is token 4 r + q: the tokens whose V rows one load instruction brings to lane group q in turn.
+  const int kt = 4 * (c & 3) + (c >> 2);
+  uint32_t k_addr[4];
 #pragma unroll
-  for (int hl = 0; hl < kMaxGroup; ++hl) {
-    if (hl < n_h) {
-      const u32x4 w = *reinterpret_cast<const u32x4 *>(a.q + ((size_t)b * a.Hq + h0 + hl) * kHeadDim + c * 8);
-      unpack8(w, qf[hl]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) qf[hl][i] = 0.f;
-    }
-  }
-  DecState st[kMaxGroup];
-#pragma unroll
-  for (int hl = 0; hl < kMaxGroup; ++hl) {
-    st[hl].m = kDecNegBig;
-    st[hl].l = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) st[hl].acc[i] = 0.f;
-  }
-  const size_t first = kPaged ? 0 : (size_t)a.off[b];  // a paged sequence is addressed through its block table
-  const uint16_t *kb = a.k + (size_t)kvh * a.head_stride + first * a.tok_stride + c * 8;
-  const uint16_t *vb = a.v + (size_t)kvh * a.head_stride + first * a.tok_stride + c * 8;
-  const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
+  for (int s = 0; s < 4; ++s) k_addr[s] = (uint32_t)(uintptr_t)(lptr_t)stage + kt * 256 + (((4 * s + q) ^ kt) << 4);
+  int b = 0;
 
-  constexpr int kU = 4;  // token steps whose loads are in flight together
-  for (int tb = t0 + wave * 4; tb < t1; tb += kDecWaves * 4 * kU) {  // uniform per wave
-    u32x4 kw[kU], vw[kU];
+  while (at < at_end) {
+    // ---- the piece [tile0, tile1) of row (b, kvh)
+    while (at >= (int64_t)a.tile0[b + 1] * a.Hkv) ++b;
+    const int row_tiles = a.tile0[b + 1] - a.tile0[b];
+    const int64_t seq_at = (int64_t)a.tile0[b] * a.Hkv;
+    const int kvh = (int)((at - seq_at) / row_tiles);
+    const int64_t row_at = seq_at + (int64_t)kvh * row_tiles;
+    const int tile0 = (int)(at - row_at), tile1 = (int)min((int64_t)row_tiles, at_end - row_at);
+    const int n = a.off[b + 1] - a.off[b];
+
+    // B operand of the first contraction: head n = c, columns 8 (4 s + q) .. + 7 in step s
+    bf16x8 qb[4];
+    {
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(a.q + ((size_t)b * a.Hq + (size_t)kvh * G + (c < G ? c : 0)) * kHeadDim) + q;
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      int t = min(tb + u * kDecWaves * 4 + tq, t1 - 1);
-      if (kPaged) {  // physical slot; an entry outside the pool is clamped into it (never out of bounds)
-        const int page = min(max(table[t >> a.page_shift], 0), a.n_pages - 1);
-        t = (page << a.page_shift) + (t & ((1 << a.page_shift) - 1));
+      for (int s = 0; s < 4; ++s) {
+        u32x4 w = src[4 * s];
+        if (c >= G) w = (u32x4){0u, 0u, 0u, 0u};
+        qb[s] = __builtin_bit_cast(bf16x8, w);
       }
-      kw[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kb + (size_t)t * a.tok_stride));
-      vw[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + (size_t)t * a.tok_stride));
     }
+    const size_t first = kPaged ? 0 : (size_t)a.off[b];  // a paged sequence is addressed through its block table
+    const uint16_t *kb = a.k + (size_t)kvh * a.head_stride + first * a.tok_stride;
+    const uint16_t *vb = a.v + (size_t)kvh * a.head_stride + first * a.tok_stride + c * 8;
+    const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
+
+    // Page of this lane's token (lane % 32) of a tile; an entry outside the pool is clamped into it.
+    auto page_of = [&](int tile) { return table[min(tile * kDecTile + (lane & 31), n - 1) >> a.page_shift]; };
+    auto slot_of = [&](int tile, int page) {
+      const int t = min(tile * kDecTile + (lane & 31), n - 1);
+      return (min(max(page, 0), a.n_pages - 1) << a.page_shift) + (t & ((1 << a.page_shift) - 1));
+    };
+    u32x4 vr[8];
+    // Load i of a tile covers its tokens 4 i .. 4 i + 3, one per 16 lanes.  `slot`: page slots of the tile's
+    // tokens, one per lane (paged cache only).
+    auto token_of = [&](int i, int tile, int slot) {
+      return kPaged ? __shfl(slot, 4 * i + q) : min(tile * kDecTile + 4 * i + q, n - 1);
+    };
+    auto load_k = [&](int tile, int slot) {
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const bool valid = tb + u * kDecWaves * 4 + tq < t1;
-      float kf[8], vf[8];
-      unpack8(kw[u], kf);
-      unpack8(vw[u], vf);
-#pragma unroll
-      for (int hl = 0; hl < kMaxGroup; ++hl) {
-        float dot = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) dot += qf[hl][i] * kf[i];
-        dot = row_sum16(dot);  // the 16 lanes of this token
-        const float z = dot * a.scale_log2e;
-        const float mn = valid ? fmaxf(st[hl].m, z) : st[hl].m;
-        const float corr = dec_exp2(st[hl].m - mn);
-        const float p = valid ? dec_exp2(z - mn) : 0.f;
-        st[hl].l = st[hl].l * corr + p;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) st[hl].acc[i] = st[hl].acc[i] * corr + p * vf[i];
-        st[hl].m = mn;
+      for (int i = 0; i < 8; ++i) {
+        const uint16_t *src = kb + (size_t)token_of(i, tile, slot) * a.tok_stride + ((c ^ ((4 * i + q) & 15)) << 3);
+        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stage + i * 1024), 16, 0, 2);
       }
+    };
+    auto load_v = [&](int tile, int slot) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + (size_t)token_of(i, tile, slot) * a.tok_stride));
+    };
+
+    floatx4 o[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    float m = kDecNegBig, l = 0.f;
+
+    int tile = tile0 + wave;
+    int slot = 0, page_next = 0;
+    {
+      const int t = min(tile, tile1 - 1);  // a wave without a tile of its own loads one all the same: no branch around the loads
+      if (kPaged) {
+        const int page = page_of(t);
+        page_next = page_of(t + kWaves);
+        slot = slot_of(t, page);
+      }
+      load_k(t, slot);
+      load_v(t, slot);
     }
-  }
-  // merge the 4 token groups of the wave (same columns, lanes 16 and 32 apart), fixed order
+    // One tile; kMore: the loads of the wave's next one go out as their registers and LDS become free (a
+    // compile-time flag, so that the waits count exactly what is in flight).
+    auto step = [&](auto more_t) {
+      constexpr bool kMore = decltype(more_t)::value;
+      u32x4 kr[8];
+      read_k_tile(kr, k_addr);
+      if constexpr (kPaged && kMore) {
+        slot = slot_of(tile + kWaves, page_next);
+        page_next = page_of(tile + 2 * kWaves);
+      }
+      if constexpr (kMore) load_k(tile + kWaves, slot);
+      floatx4 acc[2];
 #pragma unroll
-  for (int off = 16; off < 64; off <<= 1) {
+      for (int h = 0; h < 2; ++h) {
+        acc[h] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int hl = 0; hl < kMaxGroup; ++hl) {
-      const float m2 = __shfl_xor(st[hl].m, off), l2 = __shfl_xor(st[hl].l, off);
-      float acc2[8];
+        for (int s = 0; s < 4; ++s)
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[4 * h + s]), qb[s], acc[h], 0, 0, 0);
+      }
+
+      // acc[h][r] = logit of head c and token 16 h + 4 r + q of the tile
+      float z[8];
+      float tmax = kDecNegBig;
+      const bool edge = (tile + 1) * kDecTile > n;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc2[i] = __shfl_xor(st[hl].acc[i], off);
-      // both partners compute merge(lower, upper) so that they agree bit for bit
-      DecState lo = st[hl];
-      if (lane & off) {
-        DecState up = st[hl];
-        lo.m = m2; lo.l = l2;
+      for (int i = 0; i < 8; ++i) {
+        z[i] = acc[i >> 2][i & 3] * a.scale_log2e;
+        if (edge && tile * kDecTile + 4 * i + q >= n) z[i] = kDecNegBig;
+        tmax = fmaxf(tmax, z[i]);
+      }
+      tmax = quad_max(tmax);
+      const float m_new = fmaxf(m, tmax);
+      const float alpha = dec_exp2(m - m_new);
+      m = m_new;
+      float psum = 0.f;
+      bf16x8 p0, p1, p2;  // p = p0 + p1 + p2, 8 bits each
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lo.acc[i] = acc2[i];
-        dec_merge(lo, up.m, up.l, up.acc);
+      for (int i = 0; i < 8; ++i) {
+        const float p = dec_exp2(z[i] - m_new);
+        psum += p;
+        p0[i] = (__bf16)p;
+        const float r1 = p - (float)p0[i];
+        p1[i] = (__bf16)r1;
+        p2[i] = (__bf16)(r1 - (float)p1[i]);
+      }
+      l = l * alpha + psum;
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] *= alpha;
+      }
+
+      u32x4 va[8];  // va[j]: the 8 tokens' values of column 8 c + j
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          va[2 * w][i] = __builtin_amdgcn_perm(vr[2 * i + 1][w], vr[2 * i][w], 0x05040100u);
+          va[2 * w + 1][i] = __builtin_amdgcn_perm(vr[2 * i + 1][w], vr[2 * i][w], 0x07060302u);
+        }
+      if constexpr (kMore) load_v(tile + kWaves, slot);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bf16x8 vj = __builtin_bit_cast(bf16x8, va[j]);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p2, o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p1, o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p0, o[j], 0, 0, 0);
+      }
+    };
+    for (; tile + kWaves < tile1; tile += kWaves) step(std::true_type{});  // uniform per wave
+    if (tile < tile1) step(std::false_type{});
+
+    // ---- the waves' states into LDS: lane (head c, q) holds d = 32 q + 8 r + j in o[j][r]
+    l = quad_sum(l);
+    if (c < G) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j4 = 0; j4 < 2; ++j4)
+          *reinterpret_cast<float4 *>(&o_lds[wave][c][32 * q + 8 * r + 4 * j4]) =
+              make_float4(o[4 * j4][r], o[4 * j4 + 1][r], o[4 * j4 + 2][r], o[4 * j4 + 3][r]);
+      if (q == 0) { m_lds[wave][c] = m; l_lds[wave][c] = l; }
+    }
+    __syncthreads();
+    const bool whole = tile0 == 0 && tile1 == row_tiles;  // this block has the entire row
+    float *part = a.part + (2 * (size_t)blockIdx.x + (tile0 == 0 ? 1 : 0)) * kDecodeSlotFloats;
+    float *out = a.out + ((size_t)b * a.Hq + (size_t)kvh * G) * kHeadDim;
+    for (int e = tid; e < G * (kHeadDim / 2); e += kThr) {
+      const int h = e >> 6, d = (e & 63) * 2;
+      float M = m_lds[0][h];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) M = fmaxf(M, m_lds[w][h]);
+      float L = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float f = dec_exp2(m_lds[w][h] - M);
+        const float2 ov = *reinterpret_cast<const float2 *>(&o_lds[w][h][d]);
+        L += f * l_lds[w][h];
+        x += f * ov.x;
+        y += f * ov.y;
+      }
+      if (whole) {
+        *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x / L, y / L);
       } else {
-        dec_merge(lo, m2, l2, acc2);
+        agent_store2(part + h * kHeadDim + d, x, y);
+        if (d == 0) agent_store2(part + kMaxReal * kHeadDim + 2 * h, M, L);
       }
-      st[hl] = lo;
     }
-  }
-  if (tq == 0) {
-#pragma unroll
-    for (int hl = 0; hl < kMaxGroup; ++hl) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) lds[wave][hl][c][i] = st[hl].acc[i];
-      lds[wave][hl][c][8] = st[hl].m;
-      lds[wave][hl][c][9] = st[hl].l;
+    at = row_at + tile1;
+    if (whole) {
+      __syncthreads();  // the next piece reuses the tables
+      continue;
     }
-  }
-  __syncthreads();
-  if (wave == 0 && tq == 0) {
-#pragma unroll
-    for (int hl = 0; hl < kMaxGroup; ++hl) {
-      if (hl >= n_h) continue;
-      DecState r = st[hl];
-      for (int w = 1; w < kDecWaves; ++w) {
-        float acc2[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc2[i] = lds[w][hl][c][i];
-        dec_merge(r, lds[w][hl][c][8], lds[w][hl][c][9], acc2);
+
+    // ---- count this piece; the last one of the row folds them
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int blk0 = dec_block_of(row_at, a.tiles, n_blocks);
+    const int n_split = dec_block_of(row_at + row_tiles - 1, a.tiles, n_blocks) - blk0 + 1;
+    unsigned *count = a.count + b * kMaxKvHeads + kvh;
+    if (tid == 0) {
+      const unsigned old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_lds = old + 1u == (unsigned)n_split ? 1u : 0u;
+    }
+    __syncthreads();
+    if (last_lds != 0u) {
+      if (tid == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+      // piece p of the row lies in block blk0 + p; only the first one begins the row
+      const float *src = a.part + 2 * (size_t)blk0 * kDecodeSlotFloats;
+      auto piece = [&](int p) { return src + (size_t)(p == 0 ? 1 : 2 * p) * kDecodeSlotFloats; };
+      for (int hw = wave; hw < G; hw += kWaves) {  // one wave per head, lane = piece: the pieces' weights
+        const float2 ml = agent_load2(piece(min(lane, n_split - 1)) + kMaxReal * kHeadDim + 2 * hw);
+        const float mp = lane < n_split ? ml.x : kDecNegBig;
+        const float f = dec_exp2(mp - wave_fmax(mp));
+        const float L = wave_fsum(lane < n_split ? ml.y * f : 0.f);
+        w_lds[hw][lane] = lane < n_split ? f / L : 0.f;
       }
-      float *dst = a.part + (((size_t)b * a.Hq + h0 + hl) * a.n_split + s) * (kHeadDim + 2);
+      __syncthreads();
+      constexpr int kBatch = 16;  // partial rows in flight per thread
+      for (int e = tid; e < G * (kHeadDim / 2); e += kThr) {
+        const int h = e >> 6, d = (e & 63) * 2;
+        float x = 0.f, y = 0.f;
+        for (int s0 = 0; s0 < n_split; s0 += kBatch) {
+          float2 v[kBatch];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dst[c * 8 + i] = r.acc[i];
-      if (c == 0) { dst[kHeadDim] = r.m; dst[kHeadDim + 1] = r.l; }
+          for (int i = 0; i < kBatch; ++i) v[i] = agent_load2(piece(min(s0 + i, n_split - 1)) + h * kHeadDim + d);
+#pragma unroll
+          for (int i = 0; i < kBatch; ++i) {  // past the last piece the weight is 0
+            const float f = w_lds[h][s0 + i];
+            x += v[i].x * f;
+            y += v[i].y * f;
+          }
+        }
+        *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x, y);
+      }
     }
+    __syncthreads();
   }
 }
 
-// grid (Hq, B), 512 threads: 4 split groups x 128 output columns.  Every thread first learns the
-// splits' (max, sum) pairs (one load each, all in flight together), then sums its share of the
-// splits' weighted rows with the loads of a round issued together; the 4 groups meet in LDS.
-__global__ __launch_bounds__(4 * kHeadDim) void k_decode_combine(DecodeArgs a) {
-  __shared__ float w_lds[kDecodeMaxSplits];
-  __shared__ float o_lds[4][kHeadDim];
-  __shared__ float l_tot;
-  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const int col = tid & (kHeadDim - 1), grp = tid >> 7;
-  const float *src = a.part + ((size_t)b * a.Hq + h) * a.n_split * (kHeadDim + 2);
-  if (tid < 64) {  // one wave: lane = split
-    const bool live = tid < a.n_split;
-    const float m = live ? src[tid * (kHeadDim + 2) + kHeadDim] : kDecNegBig;
-    const float l = live ? src[tid * (kHeadDim + 2) + kHeadDim + 1] : 0.f;
-    float M = m;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
-    const float w = dec_exp2(m - M);
-    float L = l * w;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) L += __shfl_xor(L, off);
-    w_lds[tid] = w;
-    if (tid == 0) l_tot = L;
+// Tiles of every sequence (a.tile0, a.tiles), the blocks to spread them over, and the launch.
+hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
+  constexpr int kWaves = 4;
+  int64_t tiles = 0, longest = 1;
+  a.tile0[0] = 0;
+  for (int b = 0; b < a.n_seq; ++b) {
+    const int64_t t = (a.off[b + 1] - a.off[b] + kDecTile - 1) / kDecTile;
+    tiles += t;
+    longest = std::max(longest, t);
+    a.tile0[b + 1] = (int)tiles;
   }
-  __syncthreads();
-  float o = 0.f;
-  const int per = (a.n_split + 3) / 4;
-  const int s0 = grp * per, s1 = min(a.n_split, s0 + per);
-  for (int sb = s0; sb < s1; sb += 8) {
-    float v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = src[(size_t)min(sb + i, s1 - 1) * (kHeadDim + 2) + col];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (sb + i < s1) o += v[i] * w_lds[sb + i];
-  }
-  o_lds[grp][col] = o;
-  __syncthreads();
-  if (grp == 0)
-    a.out[((size_t)b * a.Hq + h) * kHeadDim + col] = (((o_lds[0][col] + o_lds[1][col]) + o_lds[2][col]) + o_lds[3][col]) / l_tot;
-}
-
-hipError_t launch_decode(const DecodeArgs &a, hipStream_t s) {
+  a.tiles = tiles * a.Hkv;
+  // One block per CU, with a tile for each of its waves.  Two per CU where a block goes through several short
+  // rows: each row begins with the latency of its first loads, which the other block then covers
+  // (512 rows of 10 tiles: 24.7 instead of 27 us; of 23 tiles: no difference; of 56 tiles: 88 instead of 80 us).
+  const int rows = a.n_seq * a.Hkv;
+  const int per_cu = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
+  int64_t blocks = std::min<int64_t>(std::min(per_cu * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
+  // a row is cut into at most kDecodeMaxSplits pieces: the fold keeps a weight for each
+  blocks = std::max<int64_t>(1, std::min(blocks, a.tiles * (kDecodeMaxSplits - 2) / longest));
+  const dim3 grid((unsigned)blocks);
   if (a.block_table)
-    hipLaunchKernelGGL(k_decode_partial<true>, dim3(a.n_split, a.V, a.n_seq), dim3(kDecThreads), 0, s, a);
+    hipLaunchKernelGGL((k_decode<true, kWaves>), grid, dim3(kWaves * 64), 0, s, a);
   else
-    hipLaunchKernelGGL(k_decode_partial<false>, dim3(a.n_split, a.V, a.n_seq), dim3(kDecThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_decode_combine, dim3(a.Hq, a.n_seq), dim3(4 * kHeadDim), 0, s, a);
+    hipLaunchKernelGGL((k_decode<false, kWaves>), grid, dim3(kWaves * 64), 0, s, a);
   return hipGetLastError();
 }
 

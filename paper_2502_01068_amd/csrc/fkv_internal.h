@@ -186,24 +186,27 @@ int select_long_threshold(void);
 hipError_t launch_select_long(const SelectArgs &a, int rows, int max_slices, hipStream_t s);
 
 // ---- decode attention over the cache ----------------------------------------------------
-constexpr int kDecodeMaxSplits = 64;
+constexpr int kDecodeMaxSplits = 64;    // pieces one (sequence, KV head) row is cut into
+constexpr int kDecodeMaxBlocks = 1024;  // blocks per launch, two partial slots each
+constexpr int kDecodeSlotFloats = kMaxReal * kHeadDim + 32;  // one block's partial: [G][d] weighted sums, then (max, sum) pairs; whole cache lines
 struct DecodeArgs {
   const uint16_t *q;     // [B][Hq][d]
   const uint16_t *k, *v; // element (b, g, t) at g*head_stride + (off[b] + t)*tok_stride
   float *out;            // [B][Hq][d]
-  float *part;           // [B][Hq][n_split][d + 2]
+  float *part;           // [2 * blocks][kDecodeSlotFloats]
+  unsigned *count;       // [B][kMaxKvHeads]: blocks that finished, zero between launches
   int64_t tok_stride, head_stride;
-  int Hq, Hkv, G, n_split, n_seq;
-  int V, vsh;            // virtual groups, as in ScoreArgs
+  int Hq, Hkv, G, n_seq;
   float scale_log2e;
-  int off[FKV_MAX_SEQS + 1];
+  int off[FKV_MAX_SEQS + 1];     // token prefix sums
+  int tile0[FKV_MAX_SEQS + 1];   // prefix sums of the sequences' 32-token tiles
+  int64_t tiles;                 // tiles of the launch: those of every (sequence, KV head)
   // paged cache (block_table != nullptr): k, v are page pools [n_pages][page_size][Hkv][d]; logical
   // token t of sequence b lives in page block_table[b*max_pages + t/page_size], slot t % page_size
   const int32_t *block_table;
   int max_pages, page_shift, n_pages;
 };
-int decode_max_splits(void);
-hipError_t launch_decode(const DecodeArgs &a, hipStream_t s);
+hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s);
 
 // ---- attention output of the window rows ------------------------------------------------
 constexpr int kWoutBlocks = 256;  // blocks a launch aims for (one per CU: 128 KiB of LDS each)

@@ -1,0 +1,42 @@
+"""Decode attention where its work is cut: rows that end inside a block's share, rows of one tile, tiles
+with one token, more rows than blocks, and one long row next to short ones."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_01068_amd import binding as fk
+from paper_2502_01068_amd import workloads as wl
+from parity import dev_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = fk.Context(max_total_tokens=4096, max_seqs=64)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("ns,Hq,Hkv", [
+    ([31], 32, 8), ([33], 32, 8), ([1, 32, 1], 7, 1), ([4097], 32, 8), ([9000], 4, 1), ([20000], 8, 1),
+    ([30000, 1, 65], 32, 8), ([37] * 64, 32, 8), ([5 * i + 1 for i in range(64)], 64, 8), ([640] * 33, 32, 8),
+])
+def test_decode_cut_rows(ctx, ns, Hq, Hkv):
+    print("case: decode split n=%s.. (%d) Hq=%d Hkv=%d" % (ns[:4], len(ns), Hq, Hkv), flush=True)
+    B, d, tot = len(ns), 128, sum(ns)
+    q = wl.normal_bf16(70, 0, "q_win", (B, Hq, d))
+    k, v = (wl.normal_bf16(70, 0, n, (tot, Hkv, d)) for n in ("k", "v"))
+    shape = fk.make_shape([max(n, 8) for n in ns], n_q_heads=Hq, n_kv_heads=Hkv)
+    dq, dk, dv = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    first = ctx.fkv_decode_attention(shape, dq, dk, dv, ns, "token_major")
+    second = ctx.fkv_decode_attention(shape, dq, dk, dv, ns, "token_major")
+    assert torch.equal(first, second)
+    out, o = first.cpu().numpy().astype(np.float64), 0
+    for b, n in enumerate(ns):
+        if b < 4 or b == B - 1:
+            ref = np.asarray(oracle.decode_attention(q[b], k[o:o + n], v[o:o + n], "token_major", None, "f64"), np.float64)
+            err = np.abs(out[b] - ref) / np.abs(ref).max(axis=-1, keepdims=True)
+            assert err.max() <= 1e-5, "seq %d: %.3g" % (b, err.max())
+        o += n
