@@ -298,25 +298,38 @@ ScoreWs ws_of(fkv_ctx *ctx) {
   return w;
 }
 
+// Tokens per block of a launch that cuts every sequence (less its last `skip` tokens) into equal ranges, each computed
+// with `halo` more tokens in full 32-token sub-tiles: the fewest sub-tiles from `lo` to `hi` whose blocks fill the CUs
+// once (as many times as needed when even shares of `hi` do not fit).  One block is resident per CU, so a few blocks more
+// than that would be a second, nearly empty wave: the 8 sequences of 8192-16384 tokens took 59 us instead of 38
+// in the scores pass.  Shares that end inside a sub-tile (256 instead of 244 blocks at 131072 tokens, 256
+// instead of 213 at 32768) were 1 us slower: the last round trip is paid in full for a few tokens.
+int even_share(const Resolved &r, int skip, int halo, int n_cu, int lo, int hi) {
+  if (n_cu <= 0) n_cu = 256;
+  auto blocks = [&](int sub) {
+    const int share = sub * 32 - halo;
+    int64_t t = 0;
+    for (int b = 0; b < r.n_seq; ++b) t += (r.cu[b + 1] - r.cu[b] - skip + share - 1) / share;
+    return t;
+  };
+  const int64_t target = std::max<int64_t>(1, (blocks(hi) + n_cu - 1) / n_cu) * n_cu;
+  int sub = lo;
+  while (sub < hi && blocks(sub) > target) ++sub;
+  return sub * 32 - halo;
+}
+
 // Second pass of the two-pass score kernels: probabilities from the per-row normalisers in
 // a.rowstat, window sum, pooling, head means.  Tiles overlap by the pooling halo.
 int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, hipStream_t st) {
-  const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
-  {
-    int sub = scores_sub_short();
-    const int64_t per_cu = (r.sum_p + n_cu - 1) / n_cu + 2 * a.pool_r;
-    if (per_cu > (int64_t)sub * 32) sub = (int)((per_cu + 31) / 32);
-    const int sub_max = r.V > kMaxKvHeads ? scores_sub_wide() : scores_sub_long();
-    if (sub > sub_max) sub = sub_max;
-    while (sub * 32 - 2 * a.pool_r < 1) ++sub;
-    a.tile_sub = sub;
-  }
-  const int tout = a.tile_sub * 32 - 2 * a.pool_r;
+  const int sub_max = r.V > kMaxKvHeads ? scores_sub_wide() : scores_sub_long();
+  const int own = even_share(r, r.W, 2 * a.pool_r, w.n_cu, scores_sub_short(), sub_max);
+  a.tile_own = own;
+  a.tile_sub = (own + 2 * a.pool_r + 31) / 32;
   int nb = 0;
   for (int b = 0; b < r.n_seq; ++b) {
     a.map.blk[b] = nb;
     const int P = r.cu[b + 1] - r.cu[b] - r.W;
-    nb += (P + tout - 1) / tout;
+    nb += (P + own - 1) / own;
   }
   a.map.blk[r.n_seq] = nb;
   if (nb > 0) {
@@ -380,16 +393,8 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
   if (r.sum_p == 0) return FKV_OK;
 
   // pass 1: softmax statistics of every window row over all L keys.  Blocks take at least
-  // stats_chunk_tokens() tokens, more when that keeps the launch near one block per CU (the Q
-  // load and the fold at the end of a block are paid once per block).
-  const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
-  {
-    const int64_t per_cu = (r.total + n_cu - 1) / n_cu;
-    int chunk = (int)((per_cu + 31) / 32 * 32);
-    if (chunk < stats_chunk_tokens()) chunk = stats_chunk_tokens();
-    if (chunk > 1024) chunk = 1024;
-    a.chunk = chunk;
-  }
+  // stats_chunk_tokens() tokens (the Q load and the fold at the end of a block are paid once per block).
+  a.chunk = even_share(r, 0, 0, w.n_cu, stats_chunk_tokens() / 32, 32);
   int nb = 0;
   for (int b = 0; b < r.n_seq; ++b) {
     a.map.blk[b] = nb;

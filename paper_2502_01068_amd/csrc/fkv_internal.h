@@ -84,8 +84,9 @@ struct ScoreArgs {
   int causal;
   int pool_r;             // pooling radius (kernel = 2r+1)
   int pool_mode;          // FKV_POOL_AVG / FKV_POOL_MAX
-  int chunk;              // tokens per block in the stats launch (multiple of 32)
-  int tile_sub;           // 32-token sub-tiles per block in the scores launch
+  int chunk;              // tokens per block in the stats launch
+  int tile_own;           // tokens each block of the scores launch owns
+  int tile_sub;           // 32-token sub-tiles that hold them and the pooling halo
   int k_cached;           // scores launch: K was streamed by the launch just before (read it with plain loads)
   int64_t sum_p;          // row stride of scores_group
 };

@@ -26,6 +26,7 @@ int scores_sub_short(void) { return kScoresSubShort; }
 int scores_sub_long(void) { return kScoresSubLong; }
 int scores_sub_wide(void) { return kScoresSubWide; }
 
+template <int kVg>
 __global__ __launch_bounds__(kThreads) void k_stats(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -36,38 +37,46 @@ __global__ __launch_bounds__(kThreads) void k_stats(ScoreArgs a) {
   const int P = Lb - a.W;
   const int t0 = ((int)blockIdx.x - a.map.blk[b]) * a.chunk;
   const int t1 = min(Lb, t0 + a.chunk);
-  const int n_sub = (t1 - t0 + kSub - 1) / kSub;
   uint8_t *stage = stage_all + wave * kStageBytes;
+  const int g = wave * kVg;
+  if (g >= a.V) return;
 
   FKV_TICK(16);
-  for (int g = wave; g < a.V; g += kWaves) {
-    bf16x8 qa[8];
-    load_q(a, b, g, lane, qa);
-    float mx[16], sm[16];
+  bf16x8 qa[kVg][8];
+  float mx[kVg][16], sm[kVg][16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { mx[r] = kNegBig; sm[r] = 0.f; }
-
-    stream_head<true>(a, qa, tok_base, Lb, g, t0, n_sub, stage, lane, [&](int st, const floatx16 &acc) {
-      const int tok = t0 + st * kSub + n;
-      const bool valid = tok < t1;
+  for (int v = 0; v < kVg; ++v) {
+    load_q(a, b, g + v, lane, qa[v]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int w = hi * 4 + (r & 3);
-        const bool ok = valid && (!a.causal || tok <= P + w);
-        // online softmax with one exponential per element: e = 2^-|z - max|
-        const float z = ok ? acc[r] * a.scale_log2e : kNegBig;
-        const float d = z - mx[r];
-        const float e = fast_exp2(-fabsf(d));
-        sm[r] = d > 0.f ? sm[r] * e + 1.f : sm[r] + (ok ? e : 0.f);
-        mx[r] = fmaxf(mx[r], z);
-      }
-    });
-    FKV_TICK(17);
-    const float2 ms = fold_rows(mx, sm, reinterpret_cast<float *>(stage), lane);
-    if (lane < 32)
-      a.partial[(size_t)(g * kRowsPerGroup + lane) * a.partial_stride + blockIdx.x] = ms;
-    FKV_TICK(18);
+    for (int r = 0; r < 16; ++r) { mx[v][r] = kNegBig; sm[v][r] = 0.f; }
   }
+
+  stream_head<true, kVg>(a, qa, tok_base, Lb, g, t0, t1 - t0, stage, lane, [&](int st, const floatx16 (&acc)[kVg]) {
+    const int tok = t0 + st * kSub + n;
+    const bool valid = tok < t1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int w = hi * 4 + (r & 3);
+      const bool ok = valid && (!a.causal || tok <= P + w);
+#pragma unroll
+      for (int v = 0; v < kVg; ++v) {
+        // online softmax with one exponential per element: e = 2^-|z - max|
+        const float z = ok ? acc[v][r] * a.scale_log2e : kNegBig;
+        const float d = z - mx[v][r];
+        const float e = fast_exp2(-fabsf(d));
+        sm[v][r] = d > 0.f ? sm[v][r] * e + 1.f : sm[v][r] + (ok ? e : 0.f);
+        mx[v][r] = fmaxf(mx[v][r], z);
+      }
+    }
+  });
+  FKV_TICK(17);
+#pragma unroll
+  for (int v = 0; v < kVg; ++v) {
+    const float2 ms = fold_rows(mx[v], sm[v], reinterpret_cast<float *>(stage), lane);
+    if (lane < 32)
+      a.partial[(size_t)((g + v) * kRowsPerGroup + lane) * a.partial_stride + blockIdx.x] = ms;
+  }
+  FKV_TICK(18);
 }
 
 // One wave per softmax row: grid.x = ceil(B*Hkv*32 / 4), 256 threads.  Lane l folds partials
@@ -101,12 +110,12 @@ __global__ __launch_bounds__(256) void k_combine(ScoreArgs a) {
   }
 }
 
-// kMaxSub 32-token sub-tiles per block at most; a.tile_sub of them are used (host-chosen so that
-// the launch is about one block per CU).  The window sums go straight into their own LDS array,
+// kMaxSub 32-token sub-tiles per block at most.  A block owns a.tile_own tokens (host-chosen so that the
+// launch is one block per CU) and computes them and the pooling halo.  The window sums go straight into their own LDS array,
 // next to the waves' staging tiles.
-template <int kMaxSub, int kGroups, bool kStreaming = true>
+template <int kMaxSub, int kVg, bool kStreaming = true>
 __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a) {
-  constexpr int kSlots = kMaxSub * kSub;
+  constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
   __shared__ float g_sum[kGroups][kSlots];               // per virtual group sums of pooled head scores
@@ -118,34 +127,39 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a) {
   const int Lb = a.map.cu[b + 1] - tok_base;
   const int P = Lb - a.W;
   const int r = a.pool_r;
-  const int n_sub = a.tile_sub;
-  const int tout = n_sub * kSub - 2 * r;
-  const int j0 = ((int)blockIdx.x - a.map.blk[b]) * tout - r;  // first computed token (may be < 0)
+  const int o0 = ((int)blockIdx.x - a.map.blk[b]) * a.tile_own, o1 = min(P, o0 + a.tile_own);  // owned tokens
+  const int j0 = o0 - r;  // first computed token (may be < 0)
   uint8_t *stage = stage_all + wave * kStageBytes;
 
   FKV_TICK(24);
-  for (int g = wave; g < a.V; g += kWaves) {
-    bf16x8 qa[8];
-    load_q(a, b, g, lane, qa);
-    float cst[16];
-    const float *rs = a.rowstat + ((size_t)b * a.V + g) * kRowsPerGroup;
+  const int g = wave * kVg;
+  if (g < a.V) {
+    bf16x8 qa[kVg][8];
+    float cst[kVg][16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) cst[q] = rs[(q >> 2) * 8 + hi * 4 + (q & 3)];
+    for (int v = 0; v < kVg; ++v) {
+      load_q(a, b, g + v, lane, qa[v]);
+      const float *rs = a.rowstat + ((size_t)b * a.V + g + v) * kRowsPerGroup;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) cst[v][q] = rs[(q >> 2) * 8 + hi * 4 + (q & 3)];
+    }
 
-    stream_head<kStreaming>(a, qa, tok_base, Lb, g, j0, n_sub, stage, lane, [&](int st, const floatx16 &acc) {
+    stream_head<kStreaming, kVg>(a, qa, tok_base, Lb, g, j0, o1 + r - j0, stage, lane, [&](int st, const floatx16 (&acc)[kVg]) {
       const int tok = j0 + st * kSub + n;
       const bool inb = tok >= 0 && tok < P;  // only prefix tokens are scored
 #pragma unroll
-      for (int hl = 0; hl < 4; ++hl) {
-        float sum = 0.f;
+      for (int v = 0; v < kVg; ++v)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const float e = fast_exp2(acc[hl * 4 + rr] * a.scale_log2e - cst[hl * 4 + rr]);
-          sum += (hi * 4 + rr < a.W) ? e : 0.f;
+        for (int hl = 0; hl < 4; ++hl) {
+          float sum = 0.f;
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) {
+            const float e = fast_exp2(acc[v][hl * 4 + rr] * a.scale_log2e - cst[v][hl * 4 + rr]);
+            sum += (hi * 4 + rr < a.W) ? e : 0.f;
+          }
+          sum = add_across_halves(sum);  // other half of the window rows
+          if (hi == 0 && hl < vg_heads(a, g + v)) s_head[(g + v) * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
         }
-        sum = add_across_halves(sum);  // other half of the window rows
-        if (hi == 0 && hl < vg_heads(a, g)) s_head[g * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
-      }
     });
   }
   FKV_TICK(25);
@@ -153,12 +167,18 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a) {
   FKV_TICK(26);
 
   const int col0 = tok_base - b * a.W;  // column of this sequence's token 0 in the score rows
-  pool_and_write<kSlots>(a, s_head, g_sum, j0, j0 + r, min(j0 + r + tout, P), col0);
+  pool_and_write<kSlots>(a, s_head, g_sum, j0, o0, o1, col0);
   FKV_TICK(27);
 }
 
+// One wave per virtual group of up to 4 heads; with more than 8 of those (5 to 8 heads per KV head, more than 4
+// KV heads) a wave takes both groups of its KV head, so that K is read once per pass: 64 / 8 heads at 20001 tokens
+// 69 -> 61 us per compress call, at 60000 tokens 101 -> 88 us.
 hipError_t launch_stats(const ScoreArgs &a, int n_blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_stats, dim3(n_blocks), dim3(kThreads), 0, s, a);
+  if (a.V > kMaxKvHeads)
+    hipLaunchKernelGGL(k_stats<2>, dim3(n_blocks), dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_stats<1>, dim3(n_blocks), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_combine(const ScoreArgs &a, hipStream_t s) {
@@ -168,13 +188,13 @@ hipError_t launch_combine(const ScoreArgs &a, hipStream_t s) {
 }
 hipError_t launch_scores(const ScoreArgs &a, int n_blocks, hipStream_t s) {
   if (a.V > kMaxKvHeads)  // twice the heads in LDS: half the tile
-    hipLaunchKernelGGL((k_scores<kScoresSubWide, kMaxVGroups>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2>), dim3(n_blocks), dim3(kThreads), 0, s, a);
   else if (a.tile_sub <= kScoresSubShort && !a.k_cached)
-    hipLaunchKernelGGL((k_scores<kScoresSubShort, kMaxKvHeads>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_scores<kScoresSubShort, 1>), dim3(n_blocks), dim3(kThreads), 0, s, a);
   else if (!a.k_cached)
-    hipLaunchKernelGGL((k_scores<kScoresSubLong, kMaxKvHeads>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1>), dim3(n_blocks), dim3(kThreads), 0, s, a);
   else  // K was just read by the launch before: plain loads, so that what the caches still hold is used
-    hipLaunchKernelGGL((k_scores<kScoresSubLong, kMaxKvHeads, false>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, false>), dim3(n_blocks), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -50,29 +50,33 @@ __device__ __forceinline__ void load_q(const A &a, int b, int g, int lane, bf16x
   }
 }
 
-// Streams the K rows of virtual group g's KV head for `n_sub` consecutive 32-token sub-tiles starting at
-// sequence-local token `first` (tokens are clamped into [0, Lb-1] for the load; the caller masks
-// what lies outside its range).  fn(st, acc) receives the raw logits of sub-tile st:
+// Streams the K rows of virtual group g's KV head for `n_slots` consecutive tokens, in 32-token sub-tiles, starting at
+// sequence-local token `first`.  Loads are clamped to the range's tokens inside the sequence; the caller masks
+// what lies outside.  fn(st, acc) receives the raw logits of sub-tile st:
 // acc[r] = q_row(m) . k(token first + st*32 + lane%32) with m = (r/4)*8 + (lane/32)*4 + r%4,
 // i.e. head r/4 of the group and window row (lane/32)*4 + r%4.
+// kVg = 2: g and g + 1 are the two virtual groups of one KV head; both take their logits from the same tile.
 // kStreaming marks the loads non-temporal.  Measured at 131072 tokens: both passes of the two-pass
 // kernels gain from it together (-6 us per layer), the single-pass kernel does not.
-template <bool kStreaming = false, typename F>
-__device__ __forceinline__ void stream_head(const ScoreArgs &a, const bf16x8 (&qa)[8], int tok_base, int Lb, int g,
-                                            int first, int n_sub, uint8_t *stage, int lane, F fn) {
+// At 131072 tokens the stream runs at the rate of the same loads without any work between
+// them (45 us for 268 MB); two or three tiles in flight per wave and the softmax work left out changed nothing.
+template <bool kStreaming = false, int kVg = 1, typename F>
+__device__ __forceinline__ void stream_head(const ScoreArgs &a, const bf16x8 (&qa)[kVg][8], int tok_base, int Lb, int g,
+                                            int first, int n_slots, uint8_t *stage, int lane, F fn) {
+  const int n_sub = (n_slots + kSub - 1) / kSub;
   const int c = lane & 15;        // 16-byte column of the 256-byte head row
   const int tq = lane >> 4;       // token within a quad of 4 tokens per load instruction
   const int n = lane & 31, hi = lane >> 5;
-  const uint16_t *kbase = a.k + (size_t)vg_kv_head(a, g) * kHeadDim + c * 8;
   const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
+  const uint16_t *kbase = a.k + (size_t)tok_base * tok_stride + (size_t)vg_kv_head(a, g) * kHeadDim + c * 8;
+  const int t_last = min(first + n_slots, Lb) - 1;
 
   u32x4 nxt[8];
   auto issue = [&](int st) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      int t = first + st * kSub + i * 4 + tq;
-      t = min(max(t, 0), Lb - 1);
-      const u32x4 *src = reinterpret_cast<const u32x4 *>(kbase + (size_t)(tok_base + t) * tok_stride);
+      const int t = min(max(first + st * kSub + i * 4 + tq, 0), t_last);
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(kbase + (size_t)t * tok_stride);
       nxt[i] = kStreaming ? __builtin_nontemporal_load(src) : *src;
     }
   };
@@ -87,11 +91,16 @@ __device__ __forceinline__ void stream_head(const ScoreArgs &a, const bf16x8 (&q
     }
     if (st + 1 < n_sub) issue(st + 1);
     wave_lds_sync();
-    floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    floatx16 acc[kVg];
+#pragma unroll
+    for (int v = 0; v < kVg; ++v)
+      acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const u32x4 kb = *reinterpret_cast<const u32x4 *>(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s], __builtin_bit_cast(bf16x8, kb), acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < kVg; ++v)
+        acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][s], __builtin_bit_cast(bf16x8, kb), acc[v], 0, 0, 0);
     }
     fn(st, acc);
   }
