@@ -12,6 +12,9 @@ namespace fkv {
 
 constexpr int kDppRowShr = 0x110;   // + n: lane i reads lane i - n of its row
 constexpr int kDppRowRor = 0x120;   // + n: lane i reads lane (i - n) mod 16 of its row
+constexpr int kDppQuadXor1 = 0xB1;  // lane i of a quad reads lane i ^ 1,
+constexpr int kDppQuadXor2 = 0x4E;  // lane i ^ 2
+constexpr int kDppHalfMirror = 0x141;  // lane i of 8 reads lane 7 - i
 constexpr int kDppBcast15 = 0x142;  // lane 15 of each row to every lane of the next row
 constexpr int kDppBcast31 = 0x143;  // lane 31 to every lane of rows 2 and 3
 

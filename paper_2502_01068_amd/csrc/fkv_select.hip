@@ -2,9 +2,9 @@
 // order-preserving integer image of the fp32 scores, then an ordered compaction, so the
 // output is ascending, has exactly k entries and equal scores go to the lower index.
 //
-// One 1024-thread block per (row, sequence).  Each thread holds 8, 16 or 32 keys (by row
-// length) read with coalesced 128-bit loads.  Rows of up to 32768 keys stay in registers for
-// the whole kernel; longer rows are processed in 32768-key chunks re-read from L2 per pass.
+// Rows of up to 32768 keys take one 1024-thread block each with the keys in registers (k_select below); longer
+// ones the kernels of fkv_select_coop.hip / fkv_select_long.hip, or, where those do not take the call, one
+// block that goes through the row in 32768-key chunks re-read from L2 per pass (select_row).  That one:
 //   1. the row's smallest and largest key bound the search interval [lo, lo + 2^s); histogram
 //      passes of up to 11 bits of (key - lo), most significant first, narrow it down to the key
 //      T of the (k-W)-th largest prefix score.  Taking digits relative to the row's own range
@@ -14,21 +14,19 @@
 //      run on that list.  Keys equal to the interval's lower end are never histogrammed (a row
 //      may hold thousands of them: probabilities that underflowed to zero); their count is the
 //      difference between the interval's key count and the histogram's total;
-//   2. a scan of the per-item keep counts (in-wave through an LDS table, across waves through
-//      wave totals) gives every kept key its output offset in index order: all keys > T and
-//      the first `need_eq` keys == T by index.
+//   2. a scan of the per-item keep counts gives every kept key its output offset in index order: all
+//      keys > T and the first `need_eq` keys == T by index.
 #include "fkv_select_common.h"
 
 namespace fkv {
 
-template <bool kResident, int kKpt>
 __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32_t *out, uint32_t *hist,
                                            uint32_t *wsum, uint32_t *bcast, uint32_t *scan_tbl) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
   const float *base = sc - mis;
-  constexpr int kChunk = kSelThreads * kKpt;
-  const int n_chunks = kResident ? 1 : (P + mis + kChunk - 1) / kChunk;
+  constexpr int kKpt = kMaxKpt, kChunk = kSelThreads * kKpt;
+  const int n_chunks = (P + mis + kChunk - 1) / kChunk;
   uint32_t key[kKpt];
   FKV_TICK(0);
   FKV_BTICK(0);
@@ -87,7 +85,7 @@ __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32
     const int shift = s - min(11, s);
     clear_hist();
     for (int ch = 0; ch < n_chunks; ++ch) {
-      if (!kResident) load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
+      load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
       const uint32_t span = s >= 32 ? 0xFFFFFFFFu : ((1u << s) - 1u);
 #pragma unroll
       for (int e = 0; e < kKpt; ++e) {
@@ -108,7 +106,7 @@ __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32
     uint32_t *cand = scan_tbl;  // free until the compaction
     const uint32_t span = (1u << s) - 1u;  // s <= 21 here
     for (int ch = 0; ch < n_chunks; ++ch) {
-      if (!kResident) load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
+      load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
       // Valid keys lie in [0x007FFFFF, 0xFF800000] and span < 2^21, so a key below lo (or an empty
       // slot) wraps above span: one unsigned compare per key.  A wave reserves list space for all its
       // candidates with one LDS atomic (a scan over the lanes' counts gives each lane its place).
@@ -151,7 +149,7 @@ __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32
       const uint32_t span = (s >= 32) ? 0xFFFFFFFFu : ((1u << s) - 1u);  // candidates: key - lo <= span
       clear_hist();
       for (int ch = 0; ch < n_chunks; ++ch) {
-        if (!kResident) load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
+        load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
 #pragma unroll
         for (int e = 0; e < kKpt; ++e) {  // keys equal to lo are left to pick_bin's total, as in the first pass
           const uint32_t rel = key[e] - lo;
@@ -173,47 +171,248 @@ __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32
   // ---- ordered compaction.  Index order inside a wave is (q, lane, e).
   uint32_t run_gt = 0, run_eq = 0;
   for (int ch = 0; ch < n_chunks; ++ch) {
-    if (!kResident) load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
+    load_keys<kKpt>(base, mis, P, ch * kChunk, wave, lane, key);
     compact_chunk<kKpt>(key, T, need_eq, run_gt, run_eq, ch * kChunk - mis, out, scan_tbl, wsum, bcast + 8);
   }
   FKV_TICK(3);
   FKV_BTICK(3);
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
-  __shared__ uint32_t hist[kBins + 32];  // + spare words for key slots that are not counted (never read; one
-                                         // per bank, so they do not pile onto one address)
-  __shared__ __attribute__((aligned(16))) uint32_t scan_tbl[kSelWaves * 64 * kMaxKpt];  // 128 KiB: scan tables / output staging
-  __shared__ uint32_t wsum[2 * kSelWaves];
-  __shared__ uint32_t bcast[8 + 64];  // broadcast slots, then one sink word per lane
+// ---- rows of up to 32768 keys: everything in registers -----------------------------------------
+// One 1024-thread block per row, kKpt keys per thread.  Bound by instruction issue and by the latency of the
+// steps between block barriers (one block per row leaves most of the chip idle whatever is done), so per key
+// there are: the order-preserving image (4), min / max (2), histogram address and LDS atomic (5), two tests
+// against the threshold's bin (5) and the compaction (7: masks stay scalar, lane prefixes from v_mbcnt), and seven
+// barriers in the usual case.
+//   1. the row's smallest and largest key; 2048 bins over that range, one LDS atomic per key.  Keys equal to
+//      the interval's smallest are not counted (a row may hold thousands of probabilities that underflowed to
+//      zero): they are what the total lacks.
+//   2. the threshold's bin; while it holds more than kListCap keys (ties, very long tails) it is binned again
+//   3. its keys are listed in LDS, a thread each ranks them by a sweep over the list
+//   4. ordered compaction, staged per wave in LDS.
+// Per launch inside a compress call, before -> after: 2040 keys 7.5 -> 5.6 us, 6546 8.7 -> 7.8, 12281 (max pooling)
+// 12.2 -> 10.8, 32 rows of 16376 10.5 -> 9.0.  At 16376 keys: loading 1.8 us, range 0.7, histogram 1.1, bin 0.4,
+// list 1.5, rank 0.7, compaction 1.5 (2.4 GHz clock).
+constexpr int kListCap = 256;
 
+template <int kKpt>
+struct SelectLds {
+  uint32_t hist[kBins + 64];               // first: 16-byte aligned; + one spare word per lane for slots that are not counted
+  uint32_t list[kListCap];                 // keys of the threshold's interval, relative to its smallest,
+  uint32_t list_wave[kListCap];            // and the waves that hold them
+  uint32_t tot[kSelWaves], cnt[kSelWaves]; // wave totals: histogram scan, keys kept for sure
+  uint32_t kmax, not_kmin, n_list, pick[3];
+  int32_t stage[kSelWaves][64 * kKpt + 64];  // kept indices of each wave, then a word per lane for dropped ones
+};
+
+template <int kKpt>
+__device__ __forceinline__ void select_resident(const float *sc, int P, int kp, int32_t *out, SelectLds<kKpt> &s) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
+  uint32_t key[kKpt];
+  load_keys<kKpt>(sc - mis, mis, P, 0, wave, lane, key);
+  for (int i = tid; i < kBins / 4; i += kSelThreads) *reinterpret_cast<u32x4 *>(&s.hist[4 * i]) = u32x4{0u, 0u, 0u, 0u};
+  if (tid < kListCap / 4) *reinterpret_cast<u32x4 *>(&s.list[4 * tid]) = u32x4{0u, 0u, 0u, 0u};
+  if (tid < 3) (&s.kmax)[tid] = 0u;  // kmax, not_kmin, n_list
+  __syncthreads();
+
+  {
+    uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+    const int v_wave = wave * (64 * kKpt);
+    if (v_wave >= mis && v_wave + 64 * kKpt <= mis + P) {
+#pragma unroll
+      for (int e = 0; e < kKpt; ++e) {
+        kmax = max(kmax, key[e]);
+        kmin = min(kmin, key[e]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < kKpt; ++e) {
+        kmax = max(kmax, key[e]);
+        kmin = min(kmin, key[e] != 0u ? key[e] : 0xFFFFFFFFu);  // 0: no element
+      }
+    }
+    kmax = wave_max_to_last(kmax);
+    kmin = wave_min_to_last(kmin);
+    if (lane == 63) {
+      atomicMax(&s.kmax, kmax);
+      atomicMax(&s.not_kmin, ~kmin);
+    }
+  }
+  __syncthreads();
+  // the interval [base, base + span] holds n_in keys, among them the `remaining`-th largest one of it: the threshold
+  uint32_t base = uniform(~s.not_kmin), span = uniform(s.kmax) - base;
+  uint32_t n_in = (uint32_t)P, remaining = (uint32_t)kp;
+  uint32_t T, need_eq = 0;      // kept: keys > T and the first need_eq keys == T
+  uint32_t before_gt, before_eq = 0;  // keys > T and == T in the waves before this one
+
+  // What the other waves hold of a key class: one word per wave through LDS.
+  auto exchange = [&](uint32_t mine) {
+    if (lane == 0) s.cnt[wave] = mine;
+    __syncthreads();
+    return wave_prefix(s.cnt, lane, wave).before;
+  };
+  auto settle = [&](uint32_t t, uint32_t eq) {  // the threshold is known without the list
+    T = t;
+    need_eq = eq;
+    uint32_t mine = count_keys<kKpt>(key, [&](uint32_t k) { return k > t; });
+    if (eq != 0u) mine |= count_keys<kKpt>(key, [&](uint32_t k) { return k == t; }) << 16;
+    const uint32_t b = exchange(mine);
+    before_gt = b & 0xFFFFu;
+    before_eq = b >> 16;
+  };
+
+  while (true) {
+    if (n_in == remaining) { settle(base - 1u, 0u); break; }  // the whole interval
+    if (span == 0u) { settle(base, remaining); break; }
+    if (n_in <= (uint32_t)kListCap) {
+      uint64_t in[kKpt];
+      uint32_t mine = 0, above = 0;
+#pragma unroll
+      for (int e = 0; e < kKpt; ++e) {
+        in[e] = __builtin_amdgcn_ballot_w64(key[e] - base <= span);
+        mine += __popcll(in[e]);
+        above += key[e] > base + span ? 1u : 0u;
+      }
+      if (mine != 0u) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s.n_list, mine);
+        at = uniform(at);
+#pragma unroll
+        for (int q = 0; q < kKpt / 4; ++q)
+          if ((in[4 * q] | in[4 * q + 1] | in[4 * q + 2] | in[4 * q + 3]) != 0ull) {
+#pragma unroll
+            for (int e = 4 * q; e < 4 * q + 4; ++e) {
+              if (key[e] - base <= span) {
+                const uint32_t to = lanes_before(in[e], at);
+                s.list[to] = key[e] - base + 1u;
+                s.list_wave[to] = wave;
+              }
+              at += __popcll(in[e]);
+            }
+          }
+      }
+      before_gt = exchange(wave_last(wave_sum_to_last(above)));
+      // one list key per thread: its rank from a sweep over the list, four keys per read (unused entries are 0)
+      if ((uint32_t)tid < n_in) {
+        const uint32_t x = s.list[tid];
+        uint32_t gt = 0, ge = 0;
+        for (uint32_t j = 0; j < n_in; j += 4) {
+          const u32x4 y = *reinterpret_cast<const u32x4 *>(&s.list[j]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            gt += y[i] > x ? 1u : 0u;
+            ge += y[i] >= x ? 1u : 0u;
+          }
+        }
+        if (gt < remaining && remaining <= ge) {  // x is the threshold (equal keys write the same words)
+          s.pick[0] = ge == remaining ? x - 1u : x;
+          s.pick[1] = ge == remaining ? 0u : remaining - gt;
+        }
+      }
+      __syncthreads();
+      const uint32_t t = uniform(s.pick[0]);
+      need_eq = uniform(s.pick[1]);
+      T = base + t - 1u;
+      for (uint32_t j = 0; j < n_in; j += 64) {  // kept and tied list keys of the waves before this one
+        const bool live = j + lane < n_in && s.list_wave[j + lane] < (uint32_t)wave;
+        const uint32_t x = live ? s.list[j + lane] : 0u;
+        before_gt += __popcll(__builtin_amdgcn_ballot_w64(live && x > t));
+        if (need_eq != 0u) before_eq += __popcll(__builtin_amdgcn_ballot_w64(live && x == t));
+      }
+      break;
+    }
+    const int shift = max(21 - __clz((span - 1u) | 1u), 0);  // 2048 bins for keys base + 1 .. base + span
+    const uint32_t spare = (uint32_t)kBins + lane;
+#pragma unroll
+    for (int e = 0; e < kKpt; ++e) {
+      // empty slots and what lies below the interval or on its smallest key wrap above span
+      const uint32_t rel = key[e] - (base + 1u);
+      atomicAdd(&s.hist[rel < span ? rel >> shift : spare], 1u);
+    }
+    __syncthreads();
+    // thread t owns bins 2 (1023 - t), + 1: thread order runs from the top bin down
+    const int pair = kSelThreads - 1 - tid;
+    const uint2 h = *reinterpret_cast<const uint2 *>(&s.hist[2 * pair]);
+    *reinterpret_cast<uint2 *>(&s.hist[2 * pair]) = make_uint2(0u, 0u);
+    const uint32_t mine = h.x + h.y;
+    const uint32_t run = wave_scan_add(mine);
+    if (lane == 63) s.tot[wave] = run;
+    __syncthreads();
+    const WavePrefix wp = wave_prefix(s.tot, lane, wave);
+    if (remaining > wp.total) {  // the threshold is the interval's smallest key
+      settle(base, remaining - wp.total);
+      break;
+    }
+    const uint32_t above = wp.before + run - mine;
+    if (above < remaining && remaining <= above + mine) {
+      const bool top = remaining <= above + h.y;
+      s.pick[0] = 2 * pair + (top ? 1 : 0);
+      s.pick[1] = remaining - above - (top ? 0u : h.y);
+      s.pick[2] = top ? h.y : h.x;
+    }
+    __syncthreads();
+    const uint32_t at = uniform(s.pick[0]) << shift;
+    base += 1u + at;
+    span = min((1u << shift) - 1u, span - 1u - at);
+    remaining = uniform(s.pick[1]);
+    n_in = uniform(s.pick[2]);
+  }
+
+  compact_wave<kKpt>(key, T, need_eq, before_gt, before_eq, wave, -mis, out, s.stage[wave]);
+}
+
+struct SelectRow {
+  const float *sc;
+  int32_t *out;
+  int P, k, kp;
+};
+__device__ __forceinline__ SelectRow locate_row(const SelectArgs &a) {
   int row = blockIdx.x;
   const int set_id = (a.n_sets > 1 && row >= a.set[0].n_rows) ? 1 : 0;
   if (set_id) row -= a.set[0].n_rows;
   const SelectRowSet &rs = a.set[set_id];
   const int b = blockIdx.y;
-  const int Lb = a.cu[b + 1] - a.cu[b];
-  const int P = Lb - a.W;
-  const int k = rs.cnt_off[b + 1] - rs.cnt_off[b];
-  const int kp = k - a.W;  // prefix tokens to keep
-  const float *sc = rs.scores + (size_t)row * rs.row_stride + (a.cu[b] - b * a.W);
-  int32_t *out = rs.idx_out + (size_t)row * rs.cnt_off[a.n_seq] + rs.cnt_off[b];
+  SelectRow r;
+  r.P = a.cu[b + 1] - a.cu[b] - a.W;
+  r.k = rs.cnt_off[b + 1] - rs.cnt_off[b];
+  r.kp = r.k - a.W;  // prefix tokens to keep
+  r.sc = rs.scores + (size_t)row * rs.row_stride + (a.cu[b] - b * a.W);
+  r.out = rs.idx_out + (size_t)row * rs.cnt_off[a.n_seq] + rs.cnt_off[b];
+  return r;
+}
 
-  if (a.long_state != nullptr && P + 3 > kSelThreads * kMaxKpt) return;  // taken by the multi-block chain
+// Rows of at most 1024 kKpt - 3 keys; longer ones of the call are left to another launch.
+template <int kKpt>
+__global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
+  __shared__ __attribute__((aligned(16))) SelectLds<kKpt> lds;
+  const SelectRow r = locate_row(a);
+  if (r.P + 3 > kSelThreads * kKpt) return;
   if (a.err != nullptr && *a.err != 0u) {  // the scores are invalid: no index may look usable
-    for (int i = threadIdx.x; i < k; i += kSelThreads) out[i] = -1;
+    for (int i = threadIdx.x; i < r.k; i += kSelThreads) r.out[i] = -1;
     return;
   }
-  if ((int)threadIdx.x < a.W) out[kp + threadIdx.x] = P + threadIdx.x;  // window tokens are always kept
-  if (kp <= 0) return;
-  if (P + 3 <= kSelThreads * 8)
-    select_row<true, 8>(sc, P, kp, out, hist, wsum, bcast, scan_tbl);
-  else if (P + 3 <= kSelThreads * 16)
-    select_row<true, 16>(sc, P, kp, out, hist, wsum, bcast, scan_tbl);
-  else if (P + 3 <= kSelThreads * 32)
-    select_row<true, 32>(sc, P, kp, out, hist, wsum, bcast, scan_tbl);
-  else
-    select_row<false, 32>(sc, P, kp, out, hist, wsum, bcast, scan_tbl);
+  if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;  // window tokens are always kept
+  if (r.kp > 0) select_resident<kKpt>(r.sc, r.P, r.kp, r.out, lds);
+}
+
+// Longer rows on one block each, re-read from the caches pass by pass: only for calls with more such rows than the
+// launch chain has state for.
+__global__ __launch_bounds__(kSelThreads) void k_select_chunks(SelectArgs a) {
+  __shared__ uint32_t hist[kBins + 32];  // + spare words for key slots that are not counted (never read; one
+                                         // per bank, so they do not pile onto one address)
+  __shared__ __attribute__((aligned(16))) uint32_t scan_tbl[kSelWaves * 64 * kMaxKpt];  // 128 KiB: scan tables / output staging
+  __shared__ uint32_t wsum[2 * kSelWaves];
+  __shared__ uint32_t bcast[8 + 64];  // broadcast slots, then one sink word per lane
+  const SelectRow r = locate_row(a);
+  if (r.P + 3 <= kSelThreads * kMaxKpt) return;
+  if (a.err != nullptr && *a.err != 0u) {
+    for (int i = threadIdx.x; i < r.k; i += kSelThreads) r.out[i] = -1;
+    return;
+  }
+  if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;
+  if (r.kp > 0) select_row(r.sc, r.P, r.kp, r.out, hist, wsum, bcast, scan_tbl);
 }
 
 hipError_t launch_select(SelectArgs a, uint32_t *long_state, const SelectCoop *coop, hipStream_t s) {
@@ -224,25 +423,38 @@ hipError_t launch_select(SelectArgs a, uint32_t *long_state, const SelectCoop *c
     a.long_state = nullptr;
     if (coop != nullptr && try_launch_select_coop(a, rows, *coop, s, &e)) return e;
   }
-  // Rows over one chunk go to the multi-block chain when the call's row instances fit its state.
-  int max_slices = 0;
-  bool any_short = false;
+  // Rows over one block's registers go to the multi-block chain when the call's row instances fit its state.
+  int max_slices = 0, max_short = 0;
   for (int b = 0; b < a.n_seq; ++b) {
     const int P = a.cu[b + 1] - a.cu[b] - a.W;
     if (P + 3 > select_long_threshold())
       max_slices = max(max_slices, (P + 3 + select_long_chunk() - 1) / select_long_chunk());
     else
-      any_short = true;
+      max_short = max(max_short, P + 3);
   }
-  const bool use_long = long_state != nullptr && max_slices > 0 && max_slices <= kLongMaxSlices &&
+  const bool use_long = max_slices > 0 && long_state != nullptr && max_slices <= kLongMaxSlices &&
                         (int64_t)rows * a.n_seq <= kLongMaxInst;
   a.long_state = use_long ? long_state : nullptr;
+  const dim3 grid(rows, a.n_seq), block(kSelThreads);
   hipError_t e = hipSuccess;
-  if (!use_long || any_short) {
-    hipLaunchKernelGGL(k_select, dim3(rows, a.n_seq), dim3(kSelThreads), 0, s, a);
+  if (max_short > 0) {  // keys per thread by the longest of these rows
+    if (max_short <= kSelThreads * 4)
+      hipLaunchKernelGGL(k_select<4>, grid, block, 0, s, a);
+    else if (max_short <= kSelThreads * 8)
+      hipLaunchKernelGGL(k_select<8>, grid, block, 0, s, a);
+    else if (max_short <= kSelThreads * 16)
+      hipLaunchKernelGGL(k_select<16>, grid, block, 0, s, a);
+    else if (max_short <= kSelThreads * 24)
+      hipLaunchKernelGGL(k_select<24>, grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL(k_select<32>, grid, block, 0, s, a);
     e = hipGetLastError();
   }
   if (e == hipSuccess && use_long) e = launch_select_long(a, rows, max_slices, s);
+  if (e == hipSuccess && max_slices > 0 && !use_long) {
+    hipLaunchKernelGGL(k_select_chunks, grid, block, 0, s, a);
+    e = hipGetLastError();
+  }
   return e;
 }
 

@@ -15,9 +15,8 @@ constexpr int kBins = 2048;
 // Monotone map fp32 -> uint32 (larger float <=> larger key), valid for any non-NaN input;
 // -0.0 and +0.0 compare equal as floats, so both get the key of +0.0.  No valid key is 0.
 __device__ __forceinline__ uint32_t order_key(float f) {
-  uint32_t u = __float_as_uint(f);
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(f + 0.0f);  // -0.0 + 0.0 = +0.0
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
 // Key layout of a chunk of 1024*kKpt keys (kKpt keys per thread): wave w owns virtual positions
@@ -33,6 +32,16 @@ template <int kKpt>
 __device__ __forceinline__ void load_keys(const float *base, int mis, int P, int v_chunk, int wave, int lane,
                                           uint32_t (&key)[kKpt]) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int v_wave = __builtin_amdgcn_readfirstlane(v_chunk + wave * (64 * kKpt));
+  if (v_wave >= mis && v_wave + 64 * kKpt <= mis + P) {  // the wave's whole range holds keys
+#pragma unroll
+    for (int q = 0; q < kKpt / 4; ++q) {
+      const f32x4 f = *reinterpret_cast<const f32x4 *>(base + v_wave + q * 256 + lane * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key[4 * q + e] = order_key(f[e]);
+    }
+    return;
+  }
 #pragma unroll
   for (int q = 0; q < kKpt / 4; ++q) {
     const int v = v_chunk + slot_pos<kKpt>(wave, lane, q);
@@ -110,9 +119,7 @@ __device__ __forceinline__ BinPick pick_bin(const uint32_t *hist, uint32_t *wsum
 // keys came before, in index order.  run_gt / run_eq count what earlier chunks kept / saw and are
 // advanced.  scan_tbl: kSelWaves*64*kMaxKpt words, wsum: kSelWaves words, sink: 64 words of LDS.
 // Index order inside a wave is (q, lane, e).  Contains block barriers.
-// kCoherentOut: the indices leave as agent-scope atomic stores (straight to device memory instead of
-// resting in the writing CU's L2), for kernels whose blocks order their output among themselves.
-template <int kKpt, bool kCoherentOut = false>
+template <int kKpt>
 __device__ __forceinline__ void compact_chunk(const uint32_t (&key)[kKpt], uint32_t T, uint32_t need_eq,
                                               uint32_t &run_gt, uint32_t &run_eq, int i_chunk, int32_t *out,
                                               uint32_t *scan_tbl, uint32_t *wsum, uint32_t *sink) {
@@ -184,15 +191,93 @@ __device__ __forceinline__ void compact_chunk(const uint32_t (&key)[kKpt], uint3
       }
     }
     wave_sync_lds();
-    for (uint32_t o = lane; o < wave_end - wave_base; o += 64) {
-      if (kCoherentOut)
-        __hip_atomic_store(out + wave_base + o, stg[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        out[wave_base + o] = stg[o];
-    }
+    for (uint32_t o = lane; o < wave_end - wave_base; o += 64) out[wave_base + o] = stg[o];
     __syncthreads();  // the tables are rewritten by the next chunk
     run_gt += total & 0xFFFFu;
     run_eq += total >> 16;
+}
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
+// Sum of the block's wave totals before this wave, and over all waves; `tot` holds one word per wave.
+struct WavePrefix { uint32_t before, total; };
+__device__ __forceinline__ WavePrefix wave_prefix(const uint32_t *tot, int lane, int wave) {
+  static_assert(kSelWaves == 16, "one DPP row");
+  uint32_t x = tot[lane & 15];
+  x += dpp_u32<kDppRowShr + 1>(0u, x);
+  x += dpp_u32<kDppRowShr + 2>(0u, x);
+  x += dpp_u32<kDppRowShr + 4>(0u, x);
+  x += dpp_u32<kDppRowShr + 8>(0u, x);
+  WavePrefix p;
+  p.total = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+  p.before = wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)x, wave - 1);
+  return p;
+}
+__device__ __forceinline__ uint32_t lanes_before(uint64_t mask, uint32_t add) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, add));
+}
+
+
+// Ordered compaction of one wave's keys: appends to `out` the indices (+ i_base) of all keys > T and of keys == T
+// while fewer than need_eq equal keys came before, in index order ((q, lane, e) for key 4 q + e).  before_gt /
+// before_eq: keys > T / == T of the row before this wave.  stage: 64 kKpt + 64 words of LDS of this wave's own.  The
+// masks of kept keys stay scalar; a key's place is a lane prefix over them (v_mbcnt).
+// kCoherentOut: the indices leave as agent-scope atomic stores (straight to device memory instead of
+// resting in the writing CU's L2), for kernels whose blocks order their output among themselves.
+template <int kKpt, bool kCoherentOut = false>
+__device__ __forceinline__ void compact_wave(const uint32_t (&key)[kKpt], uint32_t T, uint32_t need_eq, uint32_t before_gt,
+                                             uint32_t before_eq, int wave, int i_base, int32_t *out, int32_t *stage) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t first = before_gt + min(before_eq, need_eq);  // this wave's first output
+  uint32_t n_out = 0, eq_seen = before_eq;
+#pragma unroll
+  for (int q = 0; q < kKpt / 4; ++q) {
+    bool kept[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) kept[e] = key[4 * q + e] > T;
+    if (need_eq != 0u) {
+      uint32_t rank = eq_seen;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rank = lanes_before(__builtin_amdgcn_ballot_w64(key[4 * q + e] == T), rank);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool eq = key[4 * q + e] == T;
+        eq_seen += __popcll(__builtin_amdgcn_ballot_w64(eq));
+        kept[e] = kept[e] || (eq && rank < need_eq);
+        rank += eq ? 1u : 0u;
+      }
+    }
+    uint64_t m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = __builtin_amdgcn_ballot_w64(kept[e]);
+    uint32_t at = n_out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) at = lanes_before(m[e], at);
+    const int i0 = slot_pos<kKpt>(wave, lane, q) + i_base;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      stage[kept[e] ? at : 64u * kKpt + lane] = i0 + e;  // a dropped key goes to the lane's spare word
+      at += kept[e] ? 1u : 0u;
+      n_out += __popcll(m[e]);
+    }
+  }
+  wave_sync_lds();
+  for (uint32_t o = lane; o < n_out; o += 64) {
+    if (kCoherentOut)
+      __hip_atomic_store(out + first + o, stage[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      out[first + o] = stage[o];
+  }
+}
+
+// Keys of the wave that satisfy pred, as a scalar.
+template <int kKpt, typename F>
+__device__ __forceinline__ uint32_t count_keys(const uint32_t (&key)[kKpt], F pred) {
+  uint32_t n = 0;
+#pragma unroll
+  for (int e = 0; e < kKpt; ++e) n += pred(key[e]) ? 1u : 0u;
+  return wave_last(wave_sum_to_last(n));
 }
 
 }  // namespace fkv

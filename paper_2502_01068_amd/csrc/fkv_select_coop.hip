@@ -44,7 +44,7 @@ template <int kKpt, int kSl>
 __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopArgs c) {
   constexpr int kChunk = kSelThreads * kKpt;  // keys per block
   __shared__ uint32_t hist[kBins + 32];  // + one spare word per bank for key slots that are not counted
-  __shared__ __attribute__((aligned(16))) uint32_t scan_tbl[kSelWaves * 64 * kMaxKpt];  // 128 KiB: peers' histogram words [slice][thread], then scan tables / output staging
+  __shared__ __attribute__((aligned(16))) uint32_t scan_tbl[kSelWaves * (64 * kMaxKpt + 64)];  // 128 KiB: peers' histogram words [slice][thread], then scan tables / output staging
   __shared__ uint32_t wsum[2 * kSelWaves];
   __shared__ uint32_t bcast[8 + 64];
   __shared__ uint32_t slice_cnt[kCoopMaxSlices];  // keys of each slice inside the current interval
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
                                 // 3 a wave gave up, 4 outcome of the finish count, 5 list length of this slice
   static_assert(kCoopMaxSlices * kSelThreads <= kSelWaves * 64 * kMaxKpt, "peer staging fits the scan table");
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wave_s = __builtin_amdgcn_readfirstlane(wave);
   FKV_TICK(6);
   int b = 0;
   while (b + 1 < a.n_seq && (int)blockIdx.x >= c.blk[b + 1]) ++b;
@@ -214,6 +214,35 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
     // interval take no part): sets lo to the threshold key; whole = every key >= lo is kept.
     auto finish_on_list = [&](uint32_t cand, bool &whole) {
       whole = false;
+      if (n_in <= 128u) {
+        // few keys: 8 threads rank each of them by a sweep over the list (unused entries are 0)
+        uint32_t *list = scan_tbl + kCoopMaxSlices * kSelThreads;
+        __syncthreads();
+        if (tid < 128) list[tid] = (uint32_t)tid < n_in ? cand : 0u;
+        __syncthreads();
+        const uint32_t x = list[tid >> 3];
+        uint32_t rank = 0;  // keys above x (low half), keys above or equal (high half)
+        for (uint32_t j = 4 * (tid & 7); j < n_in; j += 32) {
+          const u32x4 y = *reinterpret_cast<const u32x4 *>(list + j);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) rank += (y[i] > x ? 1u : 0u) + (y[i] >= x ? 0x10000u : 0u);
+        }
+        rank += dpp_u32<kDppQuadXor1>(0u, rank);
+        rank += dpp_u32<kDppQuadXor2>(0u, rank);
+        rank += dpp_u32<kDppHalfMirror>(0u, rank);
+        const uint32_t gt = rank & 0xFFFFu, ge = rank >> 16;
+        if (x != 0u && gt < remaining && remaining <= ge) {  // x is the threshold (equal keys write the same words)
+          bcast[0] = x;
+          bcast[1] = remaining - gt;
+          bcast[2] = ge == remaining ? 1u : 0u;
+        }
+        __syncthreads();
+        lo = bcast[0];
+        remaining = bcast[1];
+        whole = bcast[2] != 0u;
+        span = 0u;
+        return;
+      }
       if (span > 0u) {
         // first pass over 8192 bins (behind the staged histogram words): with a few hundred keys in the interval
         // the threshold's bin then holds one key, or only ties, and the search is over
@@ -421,8 +450,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
 
     // ---- ordered compaction of this slice; earlier slices' kept / tied keys give the start
     __syncthreads();
-    uint32_t run_gt = gt_before, run_eq = eq_before;
-    compact_chunk<kKpt, true>(key, T, need_eq, run_gt, run_eq, v0 - mis, out, scan_tbl, wsum, bcast + 8);
+    {
+      uint32_t mine = count_keys<kKpt>(key, [&](uint32_t x) { return x > T; });
+      if (need_eq != 0u) mine |= count_keys<kKpt>(key, [&](uint32_t x) { return x == T; }) << 16;
+      if (lane == 0) wsum[wave] = mine;
+      __syncthreads();
+      const uint32_t before = wave_prefix(wsum, lane, wave_s).before;
+      compact_wave<kKpt, true>(key, T, need_eq, gt_before + (before & 0xFFFFu), eq_before + (before >> 16), wave_s, v0 - mis, out,
+                               reinterpret_cast<int32_t *>(scan_tbl) + wave_s * (64 * kKpt + 64));
+    }
     FKV_TICK(5);
     FKV_BTICK(3);
     return true;
