@@ -1,8 +1,12 @@
-"""ctypes binding of libfastkv_select (argument marshalling only; every step runs in the HIP kernels).
+"""Binding of libfastkv_select (argument marshalling only; every step runs in the HIP kernels).
 
 Functions carry the names of the C ABI in ``include/fastkv_select.h``.  torch is used for
 device memory and the current stream; tensors must live on the context's GPU.  A missing
 library is an error: there is no fallback path.
+
+The wrappers a program calls per layer and per token hand their arguments to ``_native`` (csrc/fkv_torch.cpp),
+which checks them, allocates what is missing and makes the library call; it returns None for anything
+that is not a correct call, and the ctypes code below then makes the same call and reports what is wrong.
 """
 import ctypes
 import os
@@ -49,16 +53,23 @@ class FkvError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def load():
     """Open libfastkv_select.so (built in-tree by build.py) and declare its signatures."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise FileNotFoundError("libfastkv_select.so is not built: run `python -m paper_2502_01068_amd.build` "
                                 "(or __graft_entry__.build()); there is no fallback path")
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise FileNotFoundError("_native.so is not built for this torch: run `python -m paper_2502_01068_amd.build` "
+                                "(or __graft_entry__.build()); there is no fallback path") from e
+    _native = native
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
     shp, pi32 = ctypes.POINTER(FkvShape), ctypes.POINTER(ctypes.c_int32)
@@ -106,6 +117,7 @@ def load():
     lib.fkv_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_float), pi32, i32]
     for name in EXPORTS:
         getattr(lib, name)  # raises AttributeError if a declared symbol is missing
+    _native.bind(FkvShape, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
     _lib = lib
     return lib
 
@@ -250,6 +262,7 @@ class Context:
         h = ctypes.c_void_p()
         _check(lib.fkv_create(ctypes.byref(h), self.device, int(max_total_tokens), int(max_seqs)), "fkv_create")
         self.handle = h
+        self._h = h.value
         self.max_total_tokens = int(max_total_tokens)
 
     def close(self):
@@ -257,6 +270,7 @@ class Context:
             torch.cuda.synchronize(self.device)
             load().fkv_destroy(self.handle)
             self.handle = None
+            self._h = 0
 
     def __del__(self):
         try:
@@ -272,6 +286,9 @@ class Context:
 
     def fkv_score_window(self, shape, q_win, k, scores_group=None, scores_tsp=None, want_tsp=True):
         """-> (scores_group [Hkv, sum P] fp32, scores_tsp [sum P] fp32 or None)"""
+        done = _native.score_window(self._h, self.device, shape, q_win, k, scores_group, scores_tsp, bool(want_tsp))
+        if done is not None:
+            return done
         n = _Sizes(shape)
         dev = k.device
         if scores_group is None:
@@ -287,6 +304,9 @@ class Context:
 
     def fkv_select_topk(self, shape, scores, k_per_seq, idx_out=None):
         """scores [n_rows, sum P] (or [sum P]) -> idx [n_rows, sum k] int32"""
+        done = _native.select_topk(self._h, self.device, shape, scores, k_per_seq, idx_out)
+        if done is not None:
+            return done
         counts, arr = _counts(shape, k_per_seq)
         n = _Sizes(shape)
         n_rows = 1 if scores.dim() == 1 else scores.shape[0]
@@ -301,6 +321,9 @@ class Context:
 
     def fkv_gather_rows(self, shape, x, idx, k_per_seq, out=None):
         """x [sum L, ...] -> out [sum k, ...] (rows copied bit for bit)"""
+        done = _native.gather_rows(self._h, self.device, shape, x, idx, k_per_seq, out)
+        if done is not None:
+            return done
         counts, arr = _counts(shape, k_per_seq)
         n = _Sizes(shape)
         row_bytes = x.stride(0) * x.element_size()
@@ -315,6 +338,9 @@ class Context:
         return out
 
     def fkv_gather_kv(self, shape, k, v, idx_kv, budget_per_seq, k_out=None, v_out=None):
+        done = _native.gather_kv(self._h, self.device, shape, k, v, idx_kv, budget_per_seq, k_out, v_out)
+        if done is not None:
+            return done
         counts, arr = _counts(shape, budget_per_seq)
         n = _Sizes(shape)
         tot = sum(counts)
@@ -345,6 +371,9 @@ class Context:
     def fkv_compress_kv(self, shape, q_win, k, v, budget_per_seq, x=None, k_tsp_per_seq=None, out=None):
         """One layer of Algorithm 1.  Returns dict(k_out, v_out, idx_kv[, x_out, idx_tsp]).
         Pass `out` (a dict from a previous call of the same shape and counts) to reuse the output buffers."""
+        done = _native.compress_kv(self._h, self.device, shape, q_win, k, v, budget_per_seq, x, k_tsp_per_seq, out)
+        if done is not None:
+            return done
         b_counts, b_arr = _counts(shape, budget_per_seq)
         n = _Sizes(shape)
         tsp = x is not None
@@ -367,6 +396,9 @@ class Context:
 
     def fkv_score_heads(self, shape, q_win, k, scores_head=None):
         """-> scores_head [Hq, sum P] fp32: pooled per-head scores (Eq. 1), no head averaging"""
+        done = _native.score_heads(self._h, self.device, shape, q_win, k, scores_head)
+        if done is not None:
+            return done
         n = _Sizes(shape)
         if scores_head is None:
             scores_head = torch.empty((shape.n_q_heads, n.sum_p), dtype=torch.float32, device=k.device)
@@ -377,6 +409,9 @@ class Context:
         return scores_head
 
     def fkv_gather_kv_per_head(self, shape, k, v, idx_head, budget_per_seq, k_out=None, v_out=None):
+        done = _native.gather_kv_per_head(self._h, self.device, shape, k, v, idx_head, budget_per_seq, k_out, v_out)
+        if done is not None:
+            return done
         counts, arr = _counts(shape, budget_per_seq)
         n = _Sizes(shape)
         tot = sum(counts)
@@ -395,6 +430,9 @@ class Context:
 
     def fkv_decode_attention(self, shape, q, k, v, n_per_seq, layout="compact", out=None):
         """q [B,Hq,d] bf16; k, v [Hkv,sum n,d] ("compact") or [sum n,Hkv,d] ("token_major") -> out [B,Hq,d] fp32"""
+        done = _native.decode_attention(self._h, self.device, shape, q, k, v, n_per_seq, layout, out)
+        if done is not None:
+            return done
         counts = [int(c) for c in ([n_per_seq] * shape.n_seq if isinstance(n_per_seq, int) else n_per_seq)]
         if len(counts) != shape.n_seq:
             raise ValueError("need one token count per sequence")
@@ -411,6 +449,9 @@ class Context:
 
     def fkv_window_output(self, shape, q_win, k, v, out=None):
         """q_win [B,W,Hq,d], k, v [sum L,Hkv,d] bf16 -> attention output of the window rows [B,W,Hq,d] fp32"""
+        done = _native.window_output(self._h, self.device, shape, q_win, k, v, out)
+        if done is not None:
+            return done
         n = _Sizes(shape)
         if out is None:
             out = torch.empty((shape.n_seq, shape.window, shape.n_q_heads, shape.head_dim), dtype=torch.float32,
@@ -423,6 +464,9 @@ class Context:
     def fkv_score_window_output(self, shape, q_win, k, v, scores_group=None, scores_tsp=None, out=None, want_tsp=True):
         """Scores and the window rows' attention output in one call (V read once, K twice, no grid exchange)
         -> (scores_group [Hkv, sum P], scores_tsp [sum P] or None, out [B,W,Hq,d] fp32)"""
+        done = _native.score_window_output(self._h, self.device, shape, q_win, k, v, scores_group, scores_tsp, out, bool(want_tsp))
+        if done is not None:
+            return done
         n = _Sizes(shape)
         dev = k.device
         if scores_group is None:
@@ -464,6 +508,9 @@ class Context:
 
     def fkv_compress_kv_paged(self, shape, q_win, k, v, budget_per_seq, block_table, k_pages, v_pages, idx_kv=None):
         """score -> per-KV-head select -> kept K/V rows into the pages; returns idx_kv [Hkv, sum budget]"""
+        done = _native.compress_kv_paged(self._h, self.device, shape, q_win, k, v, budget_per_seq, block_table, k_pages, v_pages, idx_kv)
+        if done is not None:
+            return done
         counts, arr = _counts(shape, budget_per_seq)
         n = _Sizes(shape)
         if idx_kv is None:
@@ -478,6 +525,9 @@ class Context:
 
     def fkv_decode_attention_paged(self, shape, q, k_pages, v_pages, block_table, n_per_seq, out=None):
         """q [B,Hq,d] bf16; k_pages, v_pages [n_pages,page_size,Hkv,d]; block_table [B,max_pages] -> out [B,Hq,d] fp32"""
+        done = _native.decode_attention_paged(self._h, self.device, shape, q, k_pages, v_pages, block_table, n_per_seq, out)
+        if done is not None:
+            return done
         counts = [int(c) for c in ([n_per_seq] * shape.n_seq if isinstance(n_per_seq, int) else n_per_seq)]
         if len(counts) != shape.n_seq:
             raise ValueError("need one token count per sequence")
