@@ -10,6 +10,7 @@
 
 namespace fkv {
 
+constexpr int kDppRowShl = 0x100;   // + n: lane i reads lane i + n of its row
 constexpr int kDppRowShr = 0x110;   // + n: lane i reads lane i - n of its row
 constexpr int kDppRowRor = 0x120;   // + n: lane i reads lane (i - n) mod 16 of its row
 constexpr int kDppQuadXor1 = 0xB1;  // lane i of a quad reads lane i ^ 1,
@@ -87,6 +88,47 @@ __device__ __forceinline__ float half_sum(float x) {
   const unsigned u = __float_as_uint(x);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// half_sum of 16 values at once, scattered: lane q of each 16-lane row returns the sum of x[q] over its wave half.  At
+// every level a lane keeps the half of the values its lane bit names and adds its partner's, so 15 exchanges
+// do the work of 64; the pairs added are those of half_sum (addition commutes), so the sums have the same bits.
+__device__ __forceinline__ float half_sum_scatter(const float (&x)[16], int lane) {
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float lo = x[k] + dpp_f32<kDppRowShl + 8>(0.f, x[k]), hi = x[k + 8] + dpp_f32<kDppRowShr + 8>(0.f, x[k + 8]);
+    a[k] = (lane & 8) ? hi : lo;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float lo = a[k] + dpp_f32<kDppRowShl + 4>(0.f, a[k]), hi = a[k + 4] + dpp_f32<kDppRowShr + 4>(0.f, a[k + 4]);
+    b[k] = (lane & 4) ? hi : lo;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const float lo = b[k] + dpp_f32<kDppQuadXor2>(0.f, b[k]), hi = b[k + 2] + dpp_f32<kDppQuadXor2>(0.f, b[k + 2]);
+    c[k] = (lane & 2) ? hi : lo;
+  }
+  const float lo = c[0] + dpp_f32<kDppQuadXor1>(0.f, c[0]), hi = c[1] + dpp_f32<kDppQuadXor1>(0.f, c[1]);
+  const unsigned u = __float_as_uint((lane & 1) ? hi : lo);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// One of two registers by a lane bit.  (Written as a choice between two elements of an array the compiler makes it a
+// lane-dependent index and moves the array to LDS.)
+__device__ __forceinline__ float lane_pick(bool second, float x, float y) {
+  asm("" : "+v"(x), "+v"(y));
+  return second ? y : x;
+}
+// x[lane % 16].
+__device__ __forceinline__ float pick16(const float (&x)[16], int lane) {
+  float a[8], b[4];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) a[k] = lane_pick((lane & 8) != 0, x[k], x[k + 8]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) b[k] = lane_pick((lane & 4) != 0, a[k], a[k + 4]);
+  return lane_pick((lane & 1) != 0, lane_pick((lane & 2) != 0, b[0], b[2]), lane_pick((lane & 2) != 0, b[1], b[3]));
 }
 
 // Maximum / sum over the 64 lanes as a wave-uniform value (fixed order: reproducible).

@@ -97,7 +97,7 @@ constexpr int kLseRowsPerBlock = kMaxKvHeads * kRowsPerGroup;  // result boxes p
 constexpr int kCtrError = 0;          // sticky error flag of the context
 constexpr int kNumCounters = 64;
 struct FusedArgs {
-  float2 *part;            // [Hkv*32][kMaxFusedBlocks]: (max, sum) of a softmax row over one block's tokens, log2 units
+  float2 *part;            // [kMaxFusedBlocks][kLseRowsPerBlock]: (max, sum) of a softmax row over one block's tokens, log2 units
   float *lse;              // [kMaxFusedBlocks][kLseRowsPerBlock]: log-sum-exp of each row, one copy per block
   unsigned *err;           // the context's sticky error flag
   int n_wg;                // blocks of the launch (all resident at once)

@@ -156,6 +156,11 @@ __device__ __forceinline__ void stream_head_direct(const ScoreArgs &a, const bf1
   }
 }
 
+// Block barrier that orders LDS accesses only.  __syncthreads also waits for the acknowledgement of every
+// outstanding global store (about 1 us to device memory); where none of those has to be visible behind the
+// barrier that wait is pure latency.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Folds the per-lane running (max, sum) pairs of a wave's 32 softmax rows over the 32 token
 // lanes, through a wave-private LDS transpose (`scratch` >= 4480 bytes, 4-byte aligned).
 // In: mx[r], sm[r] of row m = (r/4)*8 + (lane/32)*4 + r%4 for token lane%32.
@@ -221,27 +226,38 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   for (int g = threadIdx.x >> 6; g < a.V; g += n_waves) {  // one wave per virtual group
     const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
     if (r == 3) {
-      // kernel 7 (the paper's): the 7 taps of all heads of the group are independent LDS reads, in flight together
+      // kernel 7 (the paper's): two neighbouring tokens per lane, whose 8 taps are four 8-byte LDS reads per head (o0 - j0 is
+      // r: the first tap of owned token jj is slot jj)
+      typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 #pragma unroll 1
-      for (int jj = lane; jj < own; jj += 64) {
-        const int c = o0 + jj - j0;  // slot of the pooled token
-        float p[kMaxGroup];
+      for (int jj = 2 * lane; jj < own; jj += 128) {
+        float p[kMaxGroup][2];
 #pragma unroll
         for (int hl = 0; hl < kMaxGroup; ++hl) {
-          const float *row = s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + c;
-          const float v0 = row[-3], v1 = row[-2], v2 = row[-1], v3 = row[0], v4 = row[1], v5 = row[2], v6 = row[3];
-          p[hl] = is_max ? fmaxf(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)), fmaxf(fmaxf(v4, v5), v6))
-                         : ((((((v0 + v1) + v2) + v3) + v4) + v5) + v6) * inv_k;
+          const float2 *row = reinterpret_cast<const float2 *>(s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + jj);
+          const float2 v01 = row[0], v23 = row[1], v45 = row[2], v67 = row[3];
+          const float v[8] = {v01.x, v01.y, v23.x, v23.y, v45.x, v45.y, v67.x, v67.y};
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            p[hl][i] = is_max ? fmaxf(fmaxf(fmaxf(v[i], v[i + 1]), fmaxf(v[i + 2], v[i + 3])), fmaxf(fmaxf(v[i + 4], v[i + 5]), v[i + 6]))
+                              : ((((((v[i] + v[i + 1]) + v[i + 2]) + v[i + 3]) + v[i + 4]) + v[i + 5]) + v[i + 6]) * inv_k;
         }
-        float gs = 0.f;
+        const bool both = jj + 1 < own;
+        auto put = [&](float *dst, float x, float y) {
+          if (both) *reinterpret_cast<f32x2u *>(dst) = f32x2u{x, y};
+          else *dst = x;
+        };
+        float gs[2] = {0.f, 0.f};
 #pragma unroll
         for (int hl = 0; hl < kMaxGroup; ++hl)
           if (hl < n_h) {
-            if (a.scores_head) a.scores_head[(size_t)(h0 + hl) * a.sum_p + col0 + o0 + jj] = p[hl];
-            gs += p[hl];
+            if (a.scores_head) put(a.scores_head + (size_t)(h0 + hl) * a.sum_p + col0 + o0 + jj, p[hl][0], p[hl][1]);
+            gs[0] += p[hl][0];
+            gs[1] += p[hl][1];
           }
-        g_sum[g][jj] = gs;
-        if (a.scores_group && !split) a.scores_group[(size_t)g * a.sum_p + col0 + o0 + jj] = gs * inv_g;
+        g_sum[g][jj] = gs[0];
+        if (both) g_sum[g][jj + 1] = gs[1];
+        if (a.scores_group && !split) put(a.scores_group + (size_t)g * a.sum_p + col0 + o0 + jj, gs[0] * inv_g, gs[1] * inv_g);
       }
       continue;
     }
@@ -269,7 +285,7 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
     }
   }
   if (a.scores_tsp == nullptr && !(split && a.scores_group)) return;
-  __syncthreads();
+  lds_barrier();
   if (split && a.scores_group) {
     for (int i = threadIdx.x; i < own * a.Hkv; i += blockDim.x) {
       const int kv = i / own, jj = i - kv * own;

@@ -9,11 +9,17 @@
 //
 //   phase 1  stream the block's K rows (owned range plus pooling halo), keep raw logits in
 //            registers, fold running (max, sum) of the owned tokens per softmax row
-//   phase 2  every block posts its 256 row partials; each softmax row has one owner wave somewhere
-//            in the grid that collects the row's partials from all blocks of the sequence, folds
-//            them in a fixed order (bit-reproducible) and posts the row's log-sum-exp to every
-//            block of the sequence
+//   phase 2  every block posts its 256 row partials, a line of memory per 8 rows; each group of 8 rows has one owner
+//            block somewhere in the grid that collects the group's partials from all blocks of the
+//            sequence, folds them in a fixed order (bit-reproducible) and posts the rows' log-sum-exps to
+//            every block of the sequence.  What the exchange costs is transactions: with one owner wave per
+//            row every partial and every result was one of its own (109 000 at 213 blocks; with groups 14 000),
+//            6.6 us from the last post to the last result instead of 3.5.  Groups of 16 rows (two folds per
+//            wave) were 1.2 us slower, of 4 or 2 rows no faster.
 //   phase 3  probabilities from the kept logits, window sum, LDS pooling, head means, write
+//
+// Per launch, before -> after the grouped exchange, the scattered row sums and the barriers that leave stores
+// in flight: 2048 tokens 15.0 -> 13.4 us, 6554 18.0 -> 16.4, 12289 20.5 -> 17.9, 32768 28.4 -> 25.0.
 //
 // Used when the batch fits the resident grid (about 64K tokens on 256 CUs); longer inputs take
 // the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
@@ -27,7 +33,8 @@ namespace fkv {
 constexpr int kFusedSubShort = 5;  // sub-tiles (of 32 tokens) a block keeps in registers: the variant for inputs
 constexpr int kFusedSubLong = 8;   // that fit 5 per block carries less register-select work per logit
 constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
-constexpr int kBoxChunks = kMaxFusedBlocks / 64;  // 64-block chunks an owner wave collects
+constexpr int kBoxChunks = kMaxFusedBlocks / 64;  // 64-block chunks an owner wave folds
+constexpr int kOwnRows = 8;                       // softmax rows per owner block, one per wave
 
 int fused_slots(void) { return kFusedSlotsMax; }
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more
@@ -56,6 +63,9 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   constexpr int kFusedSlots = kFusedSub * kSub;
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[kWaves * kStageBytes];
   __shared__ float cst_lds[kWaves][kRowsPerGroup];
+  __shared__ float2 part_lds[kOwnRows][kMaxFusedBlocks];  // owner blocks: partials of their rows, by block
+  __shared__ float lse_lds[kOwnRows];
+  __shared__ unsigned own_late[kWaves];
   __shared__ unsigned flag_lds[1];
   float(*s_head)[kFusedSlots] = reinterpret_cast<float(*)[kFusedSlots]>(lds_all);  // [Hkv*4][slots]
   float(*g_sum)[kFusedSlots] =
@@ -81,12 +91,10 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   const int g = wave;
   const bool has_group = g < a.V;  // the host takes this kernel only for V <= 8 (one wave per virtual group)
 
-  // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
-  // (fkv_clear_error) every launch only marks its scores invalid.
-  if (*f.err != 0u) {
-    poison_scores(a, col0, o0, o1);
-    return;
-  }
+  // The error flag, on its way while K is streamed and looked at before anything is posted.  Written out: for a load
+  // of a uniform value the compiler waits on the spot (0.7 us before the first K load).
+  unsigned poisoned;
+  asm volatile("global_load_dword %0, %1, %2 sc1" : "=v"(poisoned) : "v"(0), "s"(f.err) : "memory");
   if (threadIdx.x == 0) flag_lds[0] = 1u;
 
   FKV_TICK(32);
@@ -125,73 +133,96 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
     FKV_TICK(33);
     FKV_WTICK(0);
     // fold over the 32 token lanes of each wave half: registers only
-    float srow[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
+    float srow[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) srow[q] = half_sum(sm[q] * fast_exp2(mx[q] - mloc[q]));
+    for (int q = 0; q < 16; ++q) srow[q] = sm[q] * fast_exp2(mx[q] - mloc[q]);
+    // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
+    const float ps = half_sum_scatter(srow, lane), pm = pick16(mloc, lane);
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(poisoned));
     // lanes 0-15 post the 16 rows of the low half, lanes 32-47 those of the high half
-    float pm = mloc[0], ps = srow[0];
-#pragma unroll
-    for (int q = 1; q < 16; ++q)
-      if ((lane & 15) == q) { pm = mloc[q]; ps = srow[q]; }
-    if ((lane & 31) < 16) {
+    if ((lane & 31) < 16 && poisoned == 0u) {
       const int q = lane & 15;
       const int row = g * kRowsPerGroup + (q >> 2) * 8 + hi * 4 + (q & 3);
-      box_post(f.part + (size_t)row * kMaxFusedBlocks + blockIdx.x, make_float2(pm, ps));
+      box_post(f.part + (size_t)blockIdx.x * kLseRowsPerBlock + row, make_float2(pm, ps));
     }
+  }
+  // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
+  // (fkv_clear_error) every launch only marks its scores invalid.
+  if (!has_group) asm volatile("s_waitcnt vmcnt(0)" : "+v"(poisoned));
+  if (poisoned != 0u) {
+    poison_scores(a, col0, o0, o1);
+    return;
   }
   FKV_TICK(34);
   FKV_BTICK(1);
   FKV_WTICK(1);
 
-  // ---- phase 2a: owner duty.  Softmax row t = (sequence, row) belongs to block t mod n_wg; a block
-  // spreads its rows over its waves.  The owner collects the row's partial from every block of the
-  // sequence, folds them and posts the log-sum-exp into each of those blocks' result boxes.
+  // ---- phase 2a: owner duty.  A group of kOwnRows softmax rows of a sequence belongs to one block, group t to
+  // block t mod n_wg.  That block's waves collect the rows' partials from every block of the sequence, fold a row
+  // each and post the log-sum-exps into those blocks' result boxes.
   bool wave_ok = true;
   {
-    const int rows_per_seq = a.V * kRowsPerGroup;
-    const int n_tasks = a.map.n_seq * rows_per_seq;
-    for (int t = (int)blockIdx.x + wave * f.n_wg; t < n_tasks; t += kWaves * f.n_wg) {
-      const int tb = t / rows_per_seq, row = t - tb * rows_per_seq;
+    const int groups_per_seq = a.V * (kRowsPerGroup / kOwnRows);
+    const int n_groups = a.map.n_seq * groups_per_seq;
+    for (int t = (int)blockIdx.x; t < n_groups; t += f.n_wg) {  // block-uniform
+      const int tb = t / groups_per_seq, row0 = (t - tb * groups_per_seq) * kOwnRows;
       const int blk0 = a.map.blk[tb], nb = a.map.blk[tb + 1] - blk0;
-      float2 *src = f.part + (size_t)row * kMaxFusedBlocks + blk0;
-      const int n_it = (nb + 63) >> 6;
-      unsigned long long v[kBoxChunks];
+      constexpr int kPerPass = kWaves * (64 / kOwnRows);  // blocks the block's lanes cover at a time
+      constexpr int kPasses = kMaxFusedBlocks / kPerPass;
+      const int i0 = wave * (64 / kOwnRows) + lane / kOwnRows, rl = lane % kOwnRows;
+      float2 *src = f.part + (size_t)blk0 * kLseRowsPerBlock + row0 + rl;
+      unsigned long long v[kPasses];
 #pragma unroll
-      for (int i = 0; i < kBoxChunks; ++i) v[i] = kEmpty64;
+      for (int i = 0; i < kPasses; ++i) v[i] = kEmpty64;
       BoundedWait wait(f.timeout_ticks);
       while (true) {
         bool missing = false;
 #pragma unroll
-        for (int i = 0; i < kBoxChunks; ++i)
-          if (i < n_it && i * 64 + lane < nb && v[i] == kEmpty64) v[i] = box_peek(src + i * 64 + lane);
+        for (int i = 0; i < kPasses; ++i)
+          if (i * kPerPass + i0 < nb && v[i] == kEmpty64) v[i] = box_peek(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
 #pragma unroll
-        for (int i = 0; i < kBoxChunks; ++i)
-          if (i < n_it && i * 64 + lane < nb && v[i] == kEmpty64) missing = true;
+        for (int i = 0; i < kPasses; ++i)
+          if (i * kPerPass + i0 < nb && v[i] == kEmpty64) missing = true;
         if (!__any(missing)) break;
         if (wait.expired()) { wave_ok = false; break; }
       }
-      if (!wave_ok) break;
-      float m = kNegBig, s = 0.f;
+      if (wave_ok) {
 #pragma unroll
-      for (int i = 0; i < kBoxChunks; ++i)
-        if (i < n_it && i * 64 + lane < nb) {
-          box_clear(src + i * 64 + lane);
-          float2 pv;
-          __builtin_memcpy(&pv, &v[i], sizeof pv);
-          const float mn = fmaxf(m, pv.x);
-          s = s * fast_exp2(m - mn) + pv.y * fast_exp2(pv.x - mn);
-          m = mn;
-        }
-      const float mw = wave_fmax(m);
-      const float sw = wave_fsum(s * fast_exp2(m - mw));
-      const int vg = row >> 5, rr = row & 31;
-      const bool row_ok = (rr >> 3) < vg_heads(a, vg) && (rr & 7) < a.W;
-      const float lse = row_ok ? mw + __log2f(sw) : 0.f;
+        for (int i = 0; i < kPasses; ++i)
+          if (i * kPerPass + i0 < nb) {
+            box_clear(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
+            __builtin_memcpy(&part_lds[rl][i * kPerPass + i0], &v[i], sizeof v[i]);
+          }
+      }
+      if (lane == 0) own_late[wave] = wave_ok ? 0u : 1u;
+      lds_barrier();
+      bool late = false;
 #pragma unroll
-      for (int i = 0; i < kBoxChunks; ++i)
-        if (i < n_it && i * 64 + lane < nb) box_post(f.lse + (size_t)(blk0 + i * 64 + lane) * kLseRowsPerBlock + row, lse);
+      for (int w = 0; w < kWaves; ++w) late = late || own_late[w] != 0u;
+      if (late) { wave_ok = false; break; }  // the whole block
+      if (wave < kOwnRows) {
+        float m = kNegBig, s = 0.f;
+#pragma unroll
+        for (int i = 0; i < kBoxChunks; ++i)
+          if (i * 64 + lane < nb) {
+            const float2 pv = part_lds[wave][i * 64 + lane];
+            const float mn = fmaxf(m, pv.x);
+            s = s * fast_exp2(m - mn) + pv.y * fast_exp2(pv.x - mn);
+            m = mn;
+          }
+        const float mw = wave_fmax(m);
+        const float sw = wave_fsum(s * fast_exp2(m - mw));
+        const int row = row0 + wave, in_group = row & (kRowsPerGroup - 1);
+        const bool row_ok = (in_group >> 3) < vg_heads(a, row / kRowsPerGroup) && (in_group & 7) < a.W;
+        if (lane == 0) lse_lds[wave] = row_ok ? mw + __log2f(sw) : 0.f;
+      }
+      lds_barrier();
+      const float lse = lse_lds[rl];
+#pragma unroll
+      for (int i = 0; i < kPasses; ++i)
+        if (i * kPerPass + i0 < nb) box_post(f.lse + (size_t)(blk0 + i * kPerPass + i0) * kLseRowsPerBlock + row0 + rl, lse);
     }
   }
   FKV_TICK(35);
@@ -226,15 +257,18 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   }
   FKV_BTICK(2);
   FKV_WTICK(3);
-  __syncthreads();  // every wave has left its staging tile (phase 3 reuses them); flag_lds is initialised
+  lds_barrier();  // every wave has left its staging tile (phase 3 reuses them); flag_lds is initialised
   if (!wave_ok && lane == 0) flag_lds[0] = 0u;
   FKV_TICK(37);
 
   // ---- phase 3: probabilities from the kept logits, window sums into LDS
   if (has_group && wave_ok) {
-    float fac[16];  // 2^(block reference - global log-sum-exp) per row
+    float fac[16];  // 2^(block reference - global log-sum-exp) per row, 0 for rows the window does not have
 #pragma unroll
-    for (int q = 0; q < 16; ++q) fac[q] = fast_exp2(mloc[q] - cst_lds[wave][(q >> 2) * 8 + hi * 4 + (q & 3)]);
+    for (int q = 0; q < 16; ++q) {
+      fac[q] = fast_exp2(mloc[q] - cst_lds[wave][(q >> 2) * 8 + hi * 4 + (q & 3)]);
+      if (hi * 4 + (q & 3) >= a.W) fac[q] = 0.f;
+    }
 #pragma unroll
     for (int st = 0; st < kFusedSub; ++st) {
       if (st < n_sub) {
@@ -244,14 +278,14 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
         for (int hl = 0; hl < 4; ++hl) {
           float sum = 0.f;
 #pragma unroll
-          for (int rr = 0; rr < 4; ++rr) sum += (hi * 4 + rr < a.W) ? z[st][hl * 4 + rr] * fac[hl * 4 + rr] : 0.f;
+          for (int rr = 0; rr < 4; ++rr) sum += z[st][hl * 4 + rr] * fac[hl * 4 + rr];
           sum = add_across_halves(sum);  // other half of the window rows
           if (hi == 0 && hl < vg_heads(a, g)) s_head[g * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
         }
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
   FKV_TICK(40);
   const bool grid_ok = flag_lds[0] != 0u;
   if (grid_ok) {
