@@ -48,8 +48,8 @@
  *
  * Supported shapes: head_dim = 128; 1 <= W <= 8; Hq = G*Hkv with 1 <= G <= 8;
  * 1 <= Hkv <= 8; odd pool_kernel <= 31; B <= FKV_MAX_SEQS.  Anything else returns
- * FKV_EUNSUPPORTED.  (Groups of more than 4 query heads take two passes of the matrix tile
- * per KV head; with more than 8 such half-groups the two-pass score kernels are used.)
+ * FKV_EUNSUPPORTED.  (Groups of more than 4 query heads take two virtual
+ * groups of the matrix tile per KV head.)
  */
 #ifndef FASTKV_SELECT_H
 #define FASTKV_SELECT_H
@@ -295,13 +295,15 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
                     int32_t *idx_kv, const void *x, size_t x_row_bytes,
                     const int32_t *k_tsp_per_seq, void *x_out, int32_t *idx_tsp, void *stream);
 
-/* Which kernels compute the scores.  0 (default): the single-pass kernel (K read once; all its
- * blocks must be resident at once, about 64K tokens per call on 256 CUs) when the batch fits,
- * else the two-pass kernels; 1: always two-pass; 2: single-pass or FKV_EUNSUPPORTED.  Both give
- * the same scores up to fp32 summation order. */
+/* Which kernels compute the scores.  0 (default): when the batch fits, a kernel whose blocks are all resident at
+ * once: the single-pass kernel (K read once; about 61K tokens per call on 256 CUs), else, unless several contexts
+ * exist on the device, the one that keeps the logits of part of the tokens and reads the rest of K again (about
+ * 137K tokens; 72K with more than 4 query heads per KV head and more than 4 KV heads); else the two-pass kernels.
+ * 1: always two-pass; 2: single-pass or FKV_EUNSUPPORTED.  All give the same scores up to fp32 summation
+ * order.  What is said here about single-pass launches holds for both resident kernels. */
 int fkv_set_score_path(fkv_ctx *ctx, int mode);
 
-/* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 16384 keys
+/* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 24576 keys
  * are cut into at most 8 slices (8192, 16384 or 32768 keys each, by row length), one block per slice,
  * and the blocks of a row agree on the threshold through device memory inside one launch, when every
  * block of the call can be resident at once (rows x slices x sequences <= compute units, rows up to

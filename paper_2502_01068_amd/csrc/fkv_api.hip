@@ -77,6 +77,12 @@ hipError_t gated_launch(int device, hipStream_t st, F &&launch) {
   return e;
 }
 
+bool several_contexts(int device) {
+  FusedGate &gate = g_gate[device & 15];
+  std::lock_guard<std::mutex> lock(gate.mu);
+  return gate.n_ctx > 1;
+}
+
 // Scratch memory and launch parameters the score kernels need besides the caller's tensors: a
 // view of a context's workspace, or of the library's static scratch array.
 struct ScoreWs {
@@ -231,10 +237,10 @@ void fill_map(const Resolved &r, SeqMap *m) {
 // of work it owns max(0, W - r) tokens fewer.  A CU streams K at a fixed rate, so the time of the pass
 // follows the most tokens any block computes; the share found below is evened out inside each sequence.  blk[b] = first
 // block of sequence b (blk[n_seq] = blocks in all), n_sub_max = 32-token sub-tiles the largest block
-// computes.  False if no layout fits (more than fused_slots() computed tokens per block needed).
-bool plan_fused(const Resolved &r, int pool_r, int max_blocks, int *blk, int *own, int *n_sub_max) {
+// computes.  False if no layout fits (more than `slots` computed tokens per block needed).
+bool plan_fused(const Resolved &r, int pool_r, int slots, int max_blocks, int *blk, int *own, int *n_sub_max) {
   const int last_less = r.W > pool_r ? r.W - pool_r : 0;
-  const int own_cap = fused_slots() - 2 * pool_r;
+  const int own_cap = slots - 2 * pool_r;
   if (own_cap <= last_less || max_blocks < 1) return false;
   // fewest blocks of a sequence at a share of at most `share` tokens per block, and the share they get:
   // the largest o <= share whose remainder P - (nb - 1) o fits the last block
@@ -258,7 +264,7 @@ bool plan_fused(const Resolved &r, int pool_r, int max_blocks, int *blk, int *ow
   // exchange was measured to favour.  Otherwise the smallest share that fits max_blocks (the blocks
   // needed fall as the share grows: bisect).
   int lo = 0;
-  for (int n_sub = 1; n_sub * 32 <= fused_slots() && lo == 0; ++n_sub) {
+  for (int n_sub = 1; n_sub * 32 <= slots && lo == 0; ++n_sub) {
     const int share = n_sub * 32 - 2 * pool_r;
     if (share > last_less && need(share) <= std::min(max_blocks, fused_preferred_blocks(n_sub))) lo = share;
   }
@@ -370,8 +376,15 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
   if (w.fused_part != nullptr) {
     FusedArgs f{};
     int total = 0;
-    const bool fits = w.score_path != 1 && r.V <= kMaxKvHeads &&
-                      plan_fused(r, a.pool_r, std::min(w.n_cu, kMaxFusedBlocks), a.map.blk, f.own, &f.n_sub_max);
+    const int max_blocks = std::min(w.n_cu, kMaxFusedBlocks);
+    bool keep = false;
+    bool fits = w.score_path != 1 && r.V <= kMaxKvHeads &&
+                plan_fused(r, a.pool_r, fused_slots(), max_blocks, a.map.blk, f.own, &f.n_sub_max);
+    if (!fits && w.score_path == 0 && !several_contexts(w.device)) {
+      // Longer inputs and wide groups: part of the logits kept, the rest of K read again.  Not while several contexts
+      // exist on the device: resident launches of different contexts are chained, the two-pass kernels overlap.
+      keep = fits = plan_fused(r, a.pool_r, keep_sub_max(r.V) * 32, max_blocks, a.map.blk, f.own, &f.n_sub_max);
+    }
     if (fits) total = a.map.blk[r.n_seq];
     if (w.score_path == 2 && !(fits && total > 0)) return FKV_EUNSUPPORTED;
     if (fits && total > 0) {
@@ -381,8 +394,8 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
       f.n_wg = total;
       f.timeout_ticks = w.wait_ticks;
       const hipError_t e = gated_launch(w.device, st, [&] {
-        Timed t(w.prof, st, KID_SCORE_FUSED);
-        return launch_score_fused(a, f, st);
+        Timed t(w.prof, st, KID_SCORE_FUSED);  // both resident score kernels
+        return keep ? launch_score_keep(a, f, st) : launch_score_fused(a, f, st);
       });
       return e == hipSuccess ? FKV_OK : hip_fail(e);
     }
@@ -424,12 +437,9 @@ hipError_t enqueue_select(fkv_ctx *ctx, const SelectArgs &a, hipStream_t st) {
   coop.max_blocks = std::min(ctx->n_cu_select, kCoopMaxBlocks);
   coop.mode = ctx->select_path;
   Timed t(ctx, st, KID_SELECT);
-  if (coop.max_blocks > 0 && coop.mode == 0) {
-    // While several contexts exist on the device, resident launches are chained one after the other;
-    // the select gains less from its resident kernel than concurrent calls lose by that.
-    std::lock_guard<std::mutex> lock(g_gate[ctx->device & 15].mu);
-    if (g_gate[ctx->device & 15].n_ctx > 1) coop.mode = 1;
-  }
+  // While several contexts exist on the device, resident launches are chained one after the other;
+  // the select gains less from its resident kernel than concurrent calls lose by that.
+  if (coop.max_blocks > 0 && coop.mode == 0 && several_contexts(ctx->device)) coop.mode = 1;
   if (coop.max_blocks <= 0 || coop.mode == 1) return launch_select(a, long_state, nullptr, st);
   return gated_launch(ctx->device, st, [&] { return launch_select(a, long_state, &coop, st); });
 }
@@ -743,7 +753,7 @@ int fkv_score_plan(const fkv_shape *shape, int32_t max_blocks, int32_t *first_bl
   if (!first_block || !own || !n_sub_max) return FKV_ENULL;
   if (max_blocks < 1) return FKV_EINVAL;
   int blk[FKV_MAX_SEQS + 1], o[FKV_MAX_SEQS], ns = 0;
-  if (r.V > kMaxKvHeads || !plan_fused(r, shape->pool_kernel / 2, std::min(max_blocks, kMaxFusedBlocks), blk, o, &ns))
+  if (r.V > kMaxKvHeads || !plan_fused(r, shape->pool_kernel / 2, fused_slots(), std::min(max_blocks, kMaxFusedBlocks), blk, o, &ns))
     return FKV_EUNSUPPORTED;
   for (int b = 0; b <= r.n_seq; ++b) first_block[b] = blk[b];
   for (int b = 0; b < r.n_seq; ++b) own[b] = o[b];

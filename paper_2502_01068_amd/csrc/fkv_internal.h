@@ -93,7 +93,7 @@ struct ScoreArgs {
 
 // Single-pass (resident grid) score kernel: per-launch plan and the mailboxes of its grid exchange.
 constexpr int kMaxFusedBlocks = 256;  // upper bound on resident blocks (one per CU) the mailboxes hold
-constexpr int kLseRowsPerBlock = kMaxKvHeads * kRowsPerGroup;  // result boxes per block: one per softmax row
+constexpr int kLseRowsPerBlock = kMaxVGroups * kRowsPerGroup;  // boxes per block: one per softmax row
 constexpr int kCtrError = 0;          // sticky error flag of the context
 constexpr int kNumCounters = 64;
 struct FusedArgs {
@@ -105,7 +105,7 @@ struct FusedArgs {
   unsigned long long timeout_ticks;  // bound of every wait of the exchange, 100 MHz ticks
   int own[FKV_MAX_SEQS];             // prefix tokens owned by each block of sequence b
 };
-constexpr size_t kFusedPartBytes = (size_t)kMaxKvHeads * kRowsPerGroup * kMaxFusedBlocks * sizeof(float2);
+constexpr size_t kFusedPartBytes = (size_t)kMaxFusedBlocks * kLseRowsPerBlock * sizeof(float2);
 constexpr size_t kFusedLseBytes = (size_t)kMaxFusedBlocks * kLseRowsPerBlock * sizeof(float);
 // Virtual-group helpers (a = any args struct with Hkv, G, vsh).
 template <typename A> __host__ __device__ inline int vg_kv_head(const A &a, int v) { return v >> a.vsh; }
@@ -120,6 +120,8 @@ int fused_slots(void);
 int fused_preferred_blocks(int n_sub);
 int score_fused_max_blocks_per_cu(void);
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
+int keep_sub_max(int v_groups);
+hipError_t launch_score_keep(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
 
 int stats_chunk_tokens(void);
 int scores_sub_short(void);

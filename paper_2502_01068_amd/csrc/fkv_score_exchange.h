@@ -1,0 +1,151 @@
+// The grid exchange of the resident score kernels: every block posts the (max, sum) of each softmax row over its
+// tokens, owner blocks fold the rows and post their log-sum-exps back to every block of the sequence.
+#pragma once
+
+#include "fkv_dpp.h"
+#include "fkv_mailbox.h"
+#include "fkv_score_common.h"
+
+namespace fkv {
+
+constexpr int kBoxChunks = kMaxFusedBlocks / 64;  // 64-block chunks an owner wave folds
+constexpr int kOwnRows = 8;                       // softmax rows per owner block, one per wave
+
+struct ExchangeLds {
+  float2 part[kOwnRows][kMaxFusedBlocks];  // owner blocks: partials of their rows, by block
+  float lse[kOwnRows];
+  unsigned late[kWaves];
+};
+
+// Writes NaN into every score this block owns: a call whose exchange failed must not leave
+// plausible numbers behind.
+__device__ __forceinline__ void poison_scores(const ScoreArgs &a, int col0, int o0, int o1) {
+  const float nan = __uint_as_float(0x7FC00000u);
+  const int own = o1 - o0;
+  for (int i = threadIdx.x; i < own; i += blockDim.x) {
+    const size_t col = (size_t)col0 + o0 + i;
+    if (a.scores_group)
+      for (int g = 0; g < a.Hkv; ++g) a.scores_group[(size_t)g * a.sum_p + col] = nan;
+    if (a.scores_head)
+      for (int h = 0; h < a.Hq; ++h) a.scores_head[(size_t)h * a.sum_p + col] = nan;
+    if (a.scores_tsp) a.scores_tsp[col] = nan;
+  }
+}
+
+// The error flag, on its way while K is streamed (flag_arrived before it is looked at).  Written out: for a load of a
+// uniform value the compiler waits on the spot (0.7 us before the first K load).
+__device__ __forceinline__ unsigned request_flag(const unsigned *err) {
+  unsigned v;
+  asm volatile("global_load_dword %0, %1, %2 sc1" : "=v"(v) : "v"(0), "s"(err) : "memory");
+  return v;
+}
+__device__ __forceinline__ void flag_arrived(unsigned &v) { asm volatile("s_waitcnt vmcnt(0)" : "+v"(v)); }
+
+// Folds a wave's per-lane (max, sum) pairs of a virtual group's 32 rows over the token lanes and posts them.  mloc[q]:
+// the block's maximum of row (q / 4) * 8 + hi * 4 + q % 4, in every lane.
+__device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
+                                              int g, int lane, unsigned &poisoned) {
+#pragma unroll
+  for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
+  float srow[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) srow[q] = sm[q] * fast_exp2(mx[q] - mloc[q]);
+  // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
+  const float ps = half_sum_scatter(srow, lane), pm = pick16(mloc, lane);
+  flag_arrived(poisoned);
+  // lanes 0-15 post the 16 rows of the low half, lanes 32-47 those of the high half
+  if ((lane & 31) < 16 && poisoned == 0u) {
+    const int q = lane & 15;
+    const int row = g * kRowsPerGroup + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3);
+    box_post(f.part + (size_t)blockIdx.x * kLseRowsPerBlock + row, make_float2(pm, ps));
+  }
+}
+
+// Owner duty of a block.  A group of kOwnRows softmax rows of a sequence belongs to one block, group t to block
+// t mod n_wg.  That block's waves collect the rows' partials from every block of the sequence, fold a row
+// each and post the log-sum-exps into those blocks' result boxes.  Contains block barriers in blocks that own a group.
+// False if a wait ran out (block-uniform).
+__device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &f, ExchangeLds &x, int wave, int lane) {
+  bool wave_ok = true;
+  const int groups_per_seq = a.V * (kRowsPerGroup / kOwnRows);
+  const int n_groups = a.map.n_seq * groups_per_seq;
+  for (int t = (int)blockIdx.x; t < n_groups; t += f.n_wg) {  // block-uniform
+    const int tb = t / groups_per_seq, row0 = (t - tb * groups_per_seq) * kOwnRows;
+    const int blk0 = a.map.blk[tb], nb = a.map.blk[tb + 1] - blk0;
+    constexpr int kPerPass = kWaves * (64 / kOwnRows);  // blocks the block's lanes cover at a time
+    constexpr int kPasses = kMaxFusedBlocks / kPerPass;
+    const int i0 = wave * (64 / kOwnRows) + lane / kOwnRows, rl = lane % kOwnRows;
+    float2 *src = f.part + (size_t)blk0 * kLseRowsPerBlock + row0 + rl;
+    unsigned long long v[kPasses];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) v[i] = kEmpty64;
+    BoundedWait wait(f.timeout_ticks);
+    while (true) {
+      bool missing = false;
+#pragma unroll
+      for (int i = 0; i < kPasses; ++i)
+        if (i * kPerPass + i0 < nb && v[i] == kEmpty64) v[i] = box_peek(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
+#pragma unroll
+      for (int i = 0; i < kPasses; ++i)
+        if (i * kPerPass + i0 < nb && v[i] == kEmpty64) missing = true;
+      if (!__any(missing)) break;
+      if (wait.expired()) { wave_ok = false; break; }
+    }
+    if (wave_ok) {
+#pragma unroll
+      for (int i = 0; i < kPasses; ++i)
+        if (i * kPerPass + i0 < nb) {
+          box_clear(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
+          __builtin_memcpy(&x.part[rl][i * kPerPass + i0], &v[i], sizeof v[i]);
+        }
+    }
+    if (lane == 0) x.late[wave] = wave_ok ? 0u : 1u;
+    lds_barrier();
+    bool late = false;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) late = late || x.late[w] != 0u;
+    if (late) { wave_ok = false; break; }  // the whole block
+    if (wave < kOwnRows) {
+      float m = kNegBig, s = 0.f;
+#pragma unroll
+      for (int i = 0; i < kBoxChunks; ++i)
+        if (i * 64 + lane < nb) {
+          const float2 pv = x.part[wave][i * 64 + lane];
+          const float mn = fmaxf(m, pv.x);
+          s = s * fast_exp2(m - mn) + pv.y * fast_exp2(pv.x - mn);
+          m = mn;
+        }
+      const float mw = wave_fmax(m);
+      const float sw = wave_fsum(s * fast_exp2(m - mw));
+      const int row = row0 + wave, in_group = row & (kRowsPerGroup - 1);
+      const bool row_ok = (in_group >> 3) < vg_heads(a, row / kRowsPerGroup) && (in_group & 7) < a.W;
+      if (lane == 0) x.lse[wave] = row_ok ? mw + __log2f(sw) : 0.f;
+    }
+    lds_barrier();
+    const float lse = x.lse[rl];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i)
+      if (i * kPerPass + i0 < nb) box_post(f.lse + (size_t)(blk0 + i * kPerPass + i0) * kLseRowsPerBlock + row0 + rl, lse);
+  }
+  return wave_ok;
+}
+
+// The log-sum-exps of a virtual group's 32 rows from the block's result boxes, into dst (LDS, 32 floats).  Wave-uniform
+// result: false if the wait ran out.
+__device__ __forceinline__ bool collect_lse(const FusedArgs &f, int g, int lane, float *dst) {
+  float *box = f.lse + (size_t)blockIdx.x * kLseRowsPerBlock + g * kRowsPerGroup + (lane & 31);
+  unsigned bits = kEmpty32;
+  BoundedWait wait(f.timeout_ticks);
+  while (true) {
+    if (lane < 32 && bits == kEmpty32) bits = box_peek(box);
+    if (!__any(lane < 32 && bits == kEmpty32)) break;
+    if (wait.expired()) return false;
+  }
+  if (lane < 32) {
+    box_clear(box);
+    dst[lane] = __uint_as_float(bits);
+  }
+  return true;
+}
+
+}  // namespace fkv

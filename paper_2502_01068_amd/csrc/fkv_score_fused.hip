@@ -24,48 +24,27 @@
 // Used when the batch fits the resident grid (about 64K tokens on 256 CUs); longer inputs take
 // the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
 // for within the time limit raises the context's error flag, and its block writes NaN scores.
-#include "fkv_dpp.h"
-#include "fkv_mailbox.h"
-#include "fkv_score_common.h"
+#include "fkv_score_exchange.h"
 
 namespace fkv {
 
 constexpr int kFusedSubShort = 5;  // sub-tiles (of 32 tokens) a block keeps in registers: the variant for inputs
 constexpr int kFusedSubLong = 8;   // that fit 5 per block carries less register-select work per logit
 constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
-constexpr int kBoxChunks = kMaxFusedBlocks / 64;  // 64-block chunks an owner wave folds
-constexpr int kOwnRows = 8;                       // softmax rows per owner block, one per wave
 
 int fused_slots(void) { return kFusedSlotsMax; }
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more
 // sub-tile per block (fewer, longer blocks): the exchange gets slower with the number of blocks.
 // Swept over 2048 .. 49152 tokens (e.g. 6554 tokens: 64 blocks 21.1 us, 113 blocks 18.0, 160 blocks
 // 18.6, 256 blocks 18.4; 32768 tokens: 213 blocks 28.3, 256 blocks 28.7).
-int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : 224; }
-
-// Writes NaN into every score this block owns: a call whose exchange failed must not leave
-// plausible numbers behind.
-__device__ __forceinline__ void poison_scores(const ScoreArgs &a, int col0, int o0, int o1) {
-  const float nan = __uint_as_float(0x7FC00000u);
-  const int own = o1 - o0;
-  for (int i = threadIdx.x; i < own; i += blockDim.x) {
-    const size_t col = (size_t)col0 + o0 + i;
-    if (a.scores_group)
-      for (int g = 0; g < a.Hkv; ++g) a.scores_group[(size_t)g * a.sum_p + col] = nan;
-    if (a.scores_head)
-      for (int h = 0; h < a.Hq; ++h) a.scores_head[(size_t)h * a.sum_p + col] = nan;
-    if (a.scores_tsp) a.scores_tsp[col] = nan;
-  }
-}
+int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : n_sub * kSub <= kFusedSlotsMax ? 224 : kMaxFusedBlocks; }
 
 template <int kFusedSub>
 __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs f) {
   constexpr int kFusedSlots = kFusedSub * kSub;
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[kWaves * kStageBytes];
   __shared__ float cst_lds[kWaves][kRowsPerGroup];
-  __shared__ float2 part_lds[kOwnRows][kMaxFusedBlocks];  // owner blocks: partials of their rows, by block
-  __shared__ float lse_lds[kOwnRows];
-  __shared__ unsigned own_late[kWaves];
+  __shared__ ExchangeLds xch;
   __shared__ unsigned flag_lds[1];
   float(*s_head)[kFusedSlots] = reinterpret_cast<float(*)[kFusedSlots]>(lds_all);  // [Hkv*4][slots]
   float(*g_sum)[kFusedSlots] =
@@ -91,10 +70,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   const int g = wave;
   const bool has_group = g < a.V;  // the host takes this kernel only for V <= 8 (one wave per virtual group)
 
-  // The error flag, on its way while K is streamed and looked at before anything is posted.  Written out: for a load
-  // of a uniform value the compiler waits on the spot (0.7 us before the first K load).
-  unsigned poisoned;
-  asm volatile("global_load_dword %0, %1, %2 sc1" : "=v"(poisoned) : "v"(0), "s"(f.err) : "memory");
+  unsigned poisoned = request_flag(f.err);
   if (threadIdx.x == 0) flag_lds[0] = 1u;
 
   FKV_TICK(32);
@@ -132,25 +108,11 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
     });
     FKV_TICK(33);
     FKV_WTICK(0);
-    // fold over the 32 token lanes of each wave half: registers only
-#pragma unroll
-    for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
-    float srow[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) srow[q] = sm[q] * fast_exp2(mx[q] - mloc[q]);
-    // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
-    const float ps = half_sum_scatter(srow, lane), pm = pick16(mloc, lane);
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(poisoned));
-    // lanes 0-15 post the 16 rows of the low half, lanes 32-47 those of the high half
-    if ((lane & 31) < 16 && poisoned == 0u) {
-      const int q = lane & 15;
-      const int row = g * kRowsPerGroup + (q >> 2) * 8 + hi * 4 + (q & 3);
-      box_post(f.part + (size_t)blockIdx.x * kLseRowsPerBlock + row, make_float2(pm, ps));
-    }
+    fold_and_post(f, mx, sm, mloc, g, lane, poisoned);
   }
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
   // (fkv_clear_error) every launch only marks its scores invalid.
-  if (!has_group) asm volatile("s_waitcnt vmcnt(0)" : "+v"(poisoned));
+  if (!has_group) flag_arrived(poisoned);
   if (poisoned != 0u) {
     poison_scores(a, col0, o0, o1);
     return;
@@ -159,72 +121,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   FKV_BTICK(1);
   FKV_WTICK(1);
 
-  // ---- phase 2a: owner duty.  A group of kOwnRows softmax rows of a sequence belongs to one block, group t to
-  // block t mod n_wg.  That block's waves collect the rows' partials from every block of the sequence, fold a row
-  // each and post the log-sum-exps into those blocks' result boxes.
-  bool wave_ok = true;
-  {
-    const int groups_per_seq = a.V * (kRowsPerGroup / kOwnRows);
-    const int n_groups = a.map.n_seq * groups_per_seq;
-    for (int t = (int)blockIdx.x; t < n_groups; t += f.n_wg) {  // block-uniform
-      const int tb = t / groups_per_seq, row0 = (t - tb * groups_per_seq) * kOwnRows;
-      const int blk0 = a.map.blk[tb], nb = a.map.blk[tb + 1] - blk0;
-      constexpr int kPerPass = kWaves * (64 / kOwnRows);  // blocks the block's lanes cover at a time
-      constexpr int kPasses = kMaxFusedBlocks / kPerPass;
-      const int i0 = wave * (64 / kOwnRows) + lane / kOwnRows, rl = lane % kOwnRows;
-      float2 *src = f.part + (size_t)blk0 * kLseRowsPerBlock + row0 + rl;
-      unsigned long long v[kPasses];
-#pragma unroll
-      for (int i = 0; i < kPasses; ++i) v[i] = kEmpty64;
-      BoundedWait wait(f.timeout_ticks);
-      while (true) {
-        bool missing = false;
-#pragma unroll
-        for (int i = 0; i < kPasses; ++i)
-          if (i * kPerPass + i0 < nb && v[i] == kEmpty64) v[i] = box_peek(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
-#pragma unroll
-        for (int i = 0; i < kPasses; ++i)
-          if (i * kPerPass + i0 < nb && v[i] == kEmpty64) missing = true;
-        if (!__any(missing)) break;
-        if (wait.expired()) { wave_ok = false; break; }
-      }
-      if (wave_ok) {
-#pragma unroll
-        for (int i = 0; i < kPasses; ++i)
-          if (i * kPerPass + i0 < nb) {
-            box_clear(src + (size_t)(i * kPerPass + i0) * kLseRowsPerBlock);
-            __builtin_memcpy(&part_lds[rl][i * kPerPass + i0], &v[i], sizeof v[i]);
-          }
-      }
-      if (lane == 0) own_late[wave] = wave_ok ? 0u : 1u;
-      lds_barrier();
-      bool late = false;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) late = late || own_late[w] != 0u;
-      if (late) { wave_ok = false; break; }  // the whole block
-      if (wave < kOwnRows) {
-        float m = kNegBig, s = 0.f;
-#pragma unroll
-        for (int i = 0; i < kBoxChunks; ++i)
-          if (i * 64 + lane < nb) {
-            const float2 pv = part_lds[wave][i * 64 + lane];
-            const float mn = fmaxf(m, pv.x);
-            s = s * fast_exp2(m - mn) + pv.y * fast_exp2(pv.x - mn);
-            m = mn;
-          }
-        const float mw = wave_fmax(m);
-        const float sw = wave_fsum(s * fast_exp2(m - mw));
-        const int row = row0 + wave, in_group = row & (kRowsPerGroup - 1);
-        const bool row_ok = (in_group >> 3) < vg_heads(a, row / kRowsPerGroup) && (in_group & 7) < a.W;
-        if (lane == 0) lse_lds[wave] = row_ok ? mw + __log2f(sw) : 0.f;
-      }
-      lds_barrier();
-      const float lse = lse_lds[rl];
-#pragma unroll
-      for (int i = 0; i < kPasses; ++i)
-        if (i * kPerPass + i0 < nb) box_post(f.lse + (size_t)(blk0 + i * kPerPass + i0) * kLseRowsPerBlock + row0 + rl, lse);
-    }
-  }
+  bool wave_ok = owner_duty(a, f, xch, wave, lane);
   FKV_TICK(35);
   FKV_WTICK(2);
 
@@ -242,18 +139,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 
   // ---- phase 2b: collect the log-sum-exp of this wave's 32 rows from the block's result box
   if (has_group && wave_ok) {
-    float *box = f.lse + (size_t)blockIdx.x * kLseRowsPerBlock + g * kRowsPerGroup + (lane & 31);
-    unsigned bits = kEmpty32;
-    BoundedWait wait(f.timeout_ticks);
-    while (true) {
-      if (lane < 32 && bits == kEmpty32) bits = box_peek(box);
-      if (!__any(lane < 32 && bits == kEmpty32)) break;
-      if (wait.expired()) { wave_ok = false; break; }
-    }
-    if (wave_ok && lane < 32) {
-      box_clear(box);
-      cst_lds[wave][lane] = __uint_as_float(bits);
-    }
+    wave_ok = collect_lse(f, g, lane, cst_lds[wave]);
   }
   FKV_BTICK(2);
   FKV_WTICK(3);

@@ -1,0 +1,226 @@
+// Window-attention scores (Sec. 4.2 Eq. 1-2, App. B.1) of inputs whose logits do not all fit on the chip: the grid is
+// resident like that of fkv_score_fused.hip, but a block keeps only the logits of its last tiles in registers while the
+// grid agrees on the softmax normalisers, and streams its first tiles of K a second time afterwards.
+//
+//   phase 1  stream the block's tiles (owned tokens plus pooling halo): running (max, sum) of the owned tokens per
+//            softmax row; raw logits of the last kKeep tiles stay in registers
+//   phase 2  grid exchange of the row statistics (fkv_score_exchange.h); the first tile of phase 3 is on its way
+//   phase 3  probabilities of the tiles streamed again and, between their loads, of the kept ones; window sums to LDS
+//   phase 4  pooling, head means, scores
+//
+// Against the two-pass kernels (fkv_score.hip), which read K twice and need three launches, K's second read shrinks
+// by the kept part and a launch boundary (the statistics' way through memory and back) becomes the exchange:
+// 131072 tokens (17 tiles per block, 8 kept) 102 -> 80 us, 8 sequences of 8192-16384 tokens 87 -> 61 us.  With more than
+// 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and keeps 2 tiles of each:
+// 64 / 8 heads at 20001 tokens 39 -> 25 us.
+// A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not.
+#include <type_traits>
+
+#include "fkv_score_exchange.h"
+
+namespace fkv {
+
+constexpr int kKeepSub = 17, kKeepSubWide = 9;  // tiles per block: the window sums of all heads wait for the pooling in LDS
+
+int keep_sub_max(int v_groups) { return v_groups > kMaxKvHeads ? kKeepSubWide : kKeepSub; }
+
+template <int kVg, int kKeep, int kMaxSub>
+__global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs f) {
+  constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
+  __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
+  __shared__ __attribute__((aligned(16))) float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
+  __shared__ float g_sum[kGroups][kSlots];
+  __shared__ float cst_lds[kGroups][kRowsPerGroup];
+  __shared__ unsigned late_lds[kWaves];
+  static_assert(sizeof(ExchangeLds) <= sizeof(s_head), "the exchange's tables lie where the window sums go later");
+  ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(s_head);
+  typedef __attribute__((address_space(1))) const void *gptr_t;
+  typedef __attribute__((address_space(3))) void *lptr_t;
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = lane & 31, hi = lane >> 5;
+  const int b = find_seq(a.map, blockIdx.x);
+  const int tok_base = a.map.cu[b];
+  const int Lb = a.map.cu[b + 1] - tok_base;
+  const int P = Lb - a.W;
+  const int r = a.pool_r;
+  const int local = (int)blockIdx.x - a.map.blk[b];
+  const int o0 = local * f.own[b], o1 = min(P, o0 + f.own[b]);            // owned prefix tokens
+  const bool last = local == a.map.blk[b + 1] - a.map.blk[b] - 1;         // also owns the window columns
+  const int c0 = o0 - r, c1 = last ? max(Lb, o1 + r) : o1 + r;            // computed tokens
+  const int n_sub = (c1 - c0 + kSub - 1) / kSub;                          // <= kMaxSub (host guarantees)
+  const int n_keep = min(n_sub, kKeep), n_re = n_sub - n_keep;
+  const int col0 = tok_base - b * a.W;
+  const int g = wave * kVg;
+  const bool has_group = g < a.V;
+  uint8_t *stage = stage_all + wave * kStageBytes;
+  unsigned poisoned = request_flag(f.err);
+
+  bf16x8 qa[kVg][8];
+  const int c = lane & 15, tq = lane >> 4;
+  const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
+  const uint16_t *kbase = a.k + (size_t)tok_base * tok_stride + (size_t)vg_kv_head(a, has_group ? g : 0) * kHeadDim;
+  // Tile st of the block into the wave's LDS tile (see stream_head_direct); token slots past the range are not loaded.
+  // Tiles that will be read again are loaded plainly, all others non-temporal: 131072 tokens 2 us less than with every
+  // load non-temporal, 4 us less than with none.
+  typedef std::integral_constant<int, 0> first_t;
+  typedef std::integral_constant<int, 2> rest_t;
+  auto issue = [&](int st, auto aux_t) {
+    constexpr int kAux = decltype(aux_t)::value;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (st * kSub + i * 4 >= c1 - c0) break;  // wave-uniform
+      const int slot = i * 4 + tq;
+      const int t = min(max(c0 + st * kSub + slot, 0), Lb - 1);
+      __builtin_amdgcn_global_load_lds((gptr_t)(kbase + (size_t)t * tok_stride + ((c ^ (slot & 15)) << 3)),
+                                       (lptr_t)(stage + i * 1024), 16, 0, kAux);
+    }
+  };
+  // Logits of the tile that was requested last; the LDS tile is free afterwards.
+  auto logits = [&](floatx16 (&acc)[kVg]) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+    wave_lds_sync();
+#pragma unroll
+    for (int v = 0; v < kVg; ++v)
+      acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const u32x4 kb = *reinterpret_cast<const u32x4 *>(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
+#pragma unroll
+      for (int v = 0; v < kVg; ++v)
+        acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][s], __builtin_bit_cast(bf16x8, kb), acc[v], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): every lane's operands have left the tile
+    wave_lds_sync();
+  };
+
+  // ---- phase 1
+  floatx16 z[kKeep][kVg];
+  if (has_group) {
+#pragma unroll
+    for (int v = 0; v < kVg; ++v) load_q(a, b, g + v, lane, qa[v]);
+    float mx[kVg][16], sm[kVg][16];
+#pragma unroll
+    for (int v = 0; v < kVg; ++v)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) { mx[v][q] = kNegBig; sm[v][q] = 0.f; }
+    auto count = [&](int st, const floatx16 (&acc)[kVg]) {
+      const int tok = c0 + st * kSub + n;
+      const bool counted = (tok >= o0 && tok < o1) || (last && tok >= P && tok < Lb);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const bool ok = counted && (!a.causal || tok <= P + hi * 4 + (q & 3));
+#pragma unroll
+        for (int v = 0; v < kVg; ++v) {
+          const float zz = ok ? acc[v][q] * a.scale_log2e : kNegBig;
+          const float d = zz - mx[v][q];
+          const float e = fast_exp2(-fabsf(d));
+          sm[v][q] = d > 0.f ? sm[v][q] * e + 1.f : sm[v][q] + (ok ? e : 0.f);
+          mx[v][q] = fmaxf(mx[v][q], zz);
+        }
+      }
+    };
+    if (n_re > 0) issue(0, first_t{});
+    else issue(0, rest_t{});
+#pragma unroll 1
+    for (int st = 0; st < n_re; ++st) {
+      floatx16 acc[kVg];
+      logits(acc);
+      if (st + 1 < n_re) issue(st + 1, first_t{});
+      else issue(st + 1, rest_t{});
+      count(st, acc);
+    }
+#pragma unroll
+    for (int t = 0; t < kKeep; ++t)
+      if (t < n_keep) {
+        logits(z[t]);
+        if (t + 1 < n_keep) issue(n_re + t + 1, rest_t{});
+        else if (n_re > 0) issue(0, rest_t{});  // the first tile of phase 3
+        count(n_re + t, z[t]);
+      }
+#pragma unroll
+    for (int v = 0; v < kVg; ++v) {
+      float mloc[16];
+      fold_and_post(f, mx[v], sm[v], mloc, g + v, lane, poisoned);
+    }
+  }
+  // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
+  // (fkv_clear_error) every launch only marks its scores invalid.
+  if (!has_group) flag_arrived(poisoned);
+  if (poisoned != 0u) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    poison_scores(a, col0, o0, o1);
+    return;
+  }
+
+  // ---- phase 2
+  bool wave_ok = owner_duty(a, f, xch, wave, lane);
+  if (has_group) {
+#pragma unroll
+    for (int v = 0; v < kVg; ++v) wave_ok = wave_ok && collect_lse(f, g + v, lane, cst_lds[g + v]);
+  }
+
+  // ---- phase 3
+  if (has_group && wave_ok) {
+    wave_lds_sync();
+    float cst[kVg][16];
+#pragma unroll
+    for (int v = 0; v < kVg; ++v)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) cst[v][q] = cst_lds[g + v][(q >> 2) * 8 + hi * 4 + (q & 3)];
+    auto finish = [&](int st, const floatx16 (&acc)[kVg]) {
+      const int tok = c0 + st * kSub + n;
+      const bool inb = tok >= 0 && tok < min(P, c1);  // only prefix tokens are scored; slots past c1 were never loaded
+#pragma unroll
+      for (int v = 0; v < kVg; ++v)
+#pragma unroll
+        for (int hl = 0; hl < 4; ++hl) {
+          float sum = 0.f;
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) {
+            const float e = fast_exp2(acc[v][hl * 4 + rr] * a.scale_log2e - cst[v][hl * 4 + rr]);
+            sum += (hi * 4 + rr < a.W) ? e : 0.f;
+          }
+          sum = add_across_halves(sum);  // other half of the window rows
+          if (hi == 0 && hl < vg_heads(a, g + v)) s_head[(g + v) * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
+        }
+    };
+    auto again = [&](int st) {
+      floatx16 acc[kVg];
+      logits(acc);
+      if (st + 1 < n_re) issue(st + 1, rest_t{});
+      finish(st, acc);
+    };
+#pragma unroll
+    for (int t = 0; t < kKeep; ++t) {  // a kept tile's probabilities while the next tile is on its way
+      if (t < n_re) again(t);
+      if (t < n_keep) finish(n_re + t, z[t]);
+    }
+#pragma unroll 1
+    for (int st = kKeep; st < n_re; ++st) again(st);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing may land in LDS after this point
+  if (lane == 0) late_lds[wave] = wave_ok ? 0u : 1u;
+  lds_barrier();
+  bool grid_ok = true;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) grid_ok = grid_ok && late_lds[w] == 0u;
+
+  // ---- phase 4
+  if (grid_ok) {
+    pool_and_write<kSlots>(a, s_head, g_sum, c0, o0, o1, col0);
+  } else {
+    poison_scores(a, col0, o0, o1);
+    if (threadIdx.x == 0) __hip_atomic_store(f.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+hipError_t launch_score_keep(const ScoreArgs &a, const FusedArgs &f, hipStream_t s) {
+  if (a.V > kMaxKvHeads)
+    hipLaunchKernelGGL((k_score_keep<2, 2, kKeepSubWide>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+  else
+    hipLaunchKernelGGL((k_score_keep<1, 8, kKeepSub>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+  return hipGetLastError();
+}
+
+}  // namespace fkv
