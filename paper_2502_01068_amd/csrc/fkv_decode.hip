@@ -20,12 +20,14 @@
 // tokens (16 KiB of K and V) in flight while it works on the one before it; one block of 4 waves per CU is
 // enough for that (more resident waves were slower: 256 / 512 / 1024 blocks took 57 / 61 / 68 us for 304 MB).
 //
-// The tiles of all rows (row = KV head of a sequence) form one line that is cut into equal shares, one per
-// block, so ragged batches leave no CU idle.  Rows cut by a share's end are folded by the last block
-// that finishes a piece of them, in piece order (reproducible): one launch per call, nothing waits.
+// A row (KV head of a sequence) takes one block each where that loads the CUs evenly.  Else the tiles of all
+// rows form one line that is cut into equal shares, one per block, so no CU idles; rows cut by a share's end
+// are folded by the last block that finishes a piece of them, in piece order (reproducible).  One launch per
+// call, nothing waits.  The fold (4 us for 32 pieces) is bound by what one CU reads past its caches: wider loads, more
+// of them in flight and folding after all pieces of a block were each no faster.
 //
-// Measured (device time per call, before -> after): 2048 tokens, 1 sequence 11.0 -> 8.0 us; 32768 tokens 35.5 ->
-// 26.9 us (5.0 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 56.3 us (5.4 TB/s).
+// Measured (device time per call, before -> after): 2048 tokens, 1 sequence 11.0 -> 7.9 us; 32768 tokens 35.5 ->
+// 26.9 us (5.0 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 50.5 us (6.0 TB/s).
 #include <algorithm>
 #include <type_traits>
 
@@ -103,7 +105,8 @@ __device__ __forceinline__ int dec_block_of(int64_t tile, int64_t tiles, int64_t
   return (int)(((tile + 1) * n_blocks - 1) / tiles);
 }
 
-template <bool kPaged, int kWaves>
+// kWhole: one block per row instead of equal shares.
+template <bool kPaged, bool kWhole, int kWaves>
 __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   constexpr int kThr = kWaves * 64;
   constexpr int kTileBytes = kDecTile * kHeadDim * 2;
@@ -118,8 +121,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   const int c = lane & 15, q = lane >> 4;
   const int G = a.G;
   const int64_t n_blocks = gridDim.x;
-  int64_t at = dec_first_tile(blockIdx.x, a.tiles, n_blocks);
-  const int64_t at_end = dec_first_tile((int64_t)blockIdx.x + 1, a.tiles, n_blocks);
+  int64_t at, at_end;
+  if (kWhole) {
+    const int row_seq = (int)blockIdx.x / a.Hkv, len = a.tile0[row_seq + 1] - a.tile0[row_seq];
+    at = (int64_t)a.tile0[row_seq] * a.Hkv + (int64_t)((int)blockIdx.x - row_seq * a.Hkv) * len;
+    at_end = at + len;
+  } else {
+    at = dec_first_tile(blockIdx.x, a.tiles, n_blocks);
+    at_end = dec_first_tile((int64_t)blockIdx.x + 1, a.tiles, n_blocks);
+  }
   uint8_t *stage = k_lds[wave];
   // Row c of the first contraction's A operand is token 4 (c % 4) + c / 4 of a half tile, so that row 4 q + r of
   // its result is token 4 r + q: the tokens whose V rows one load instruction brings to lane group q in turn.
@@ -280,7 +290,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       if (q == 0) { m_lds[wave][c] = m; l_lds[wave][c] = l; }
     }
     __syncthreads();
-    const bool whole = tile0 == 0 && tile1 == row_tiles;  // this block has the entire row
+    const bool whole = kWhole || (tile0 == 0 && tile1 == row_tiles);  // this block has the entire row
     float *part = a.part + (2 * (size_t)blockIdx.x + (tile0 == 0 ? 1 : 0)) * kDecodeSlotFloats;
     float *out = a.out + ((size_t)b * a.Hq + (size_t)kvh * G) * kHeadDim;
     for (int e = tid; e < G * (kHeadDim / 2); e += kThr) {
@@ -304,6 +314,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         if (d == 0) agent_store2(part + kMaxReal * kHeadDim + 2 * h, M, L);
       }
     }
+    if constexpr (kWhole) return;
     at = row_at + tile1;
     if (whole) {
       __syncthreads();  // the next piece reuses the tables
@@ -368,19 +379,30 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
     a.tile0[b + 1] = (int)tiles;
   }
   a.tiles = tiles * a.Hkv;
-  // One block per CU, with a tile for each of its waves.  Two per CU where a block goes through several short
-  // rows: each row begins with the latency of its first loads, which the other block then covers
-  // (512 rows of 10 tiles: 24.7 instead of 27 us; of 23 tiles: no difference; of 56 tiles: 88 instead of 80 us).
   const int rows = a.n_seq * a.Hkv;
-  const int per_cu = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
-  int64_t blocks = std::min<int64_t>(std::min(per_cu * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
+  const dim3 block(kWaves * 64);
+  // One block per row where that loads the CUs evenly: rows close to a multiple of the CUs, none much longer than
+  // the mean.  A cut row costs a restart of the loads and the fold: 256 rows of 2048-2560 tokens 50.8 instead of 56 us,
+  // of 1280-2560 45.6 instead of 48; but 320 rows 54 instead of 47.7.
+  const int per_cu = (rows + n_cu - 1) / n_cu;
+  if (10 * rows >= 9 * per_cu * n_cu && 2 * longest * a.n_seq <= 3 * tiles) {
+    if (a.block_table)
+      hipLaunchKernelGGL((k_decode<true, true, kWaves>), dim3((unsigned)rows), block, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_decode<false, true, kWaves>), dim3((unsigned)rows), block, 0, s, a);
+    return hipGetLastError();
+  }
+  // Else equal shares: one block per CU, with a tile for each of its waves.  Two per CU where a block goes through
+  // several short rows: each row begins with the latency of its first loads, which the other block then covers.
+  const int share = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
+  int64_t blocks = std::min<int64_t>(std::min(share * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
   // a row is cut into at most kDecodeMaxSplits pieces: the fold keeps a weight for each
   blocks = std::max<int64_t>(1, std::min(blocks, a.tiles * (kDecodeMaxSplits - 2) / longest));
   const dim3 grid((unsigned)blocks);
   if (a.block_table)
-    hipLaunchKernelGGL((k_decode<true, kWaves>), grid, dim3(kWaves * 64), 0, s, a);
+    hipLaunchKernelGGL((k_decode<true, false, kWaves>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((k_decode<false, kWaves>), grid, dim3(kWaves * 64), 0, s, a);
+    hipLaunchKernelGGL((k_decode<false, false, kWaves>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
