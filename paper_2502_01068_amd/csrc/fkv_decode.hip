@@ -20,14 +20,14 @@
 // tokens (16 KiB of K and V) in flight while it works on the one before it; one block of 4 waves per CU is
 // enough for that (more resident waves were slower: 256 / 512 / 1024 blocks took 57 / 61 / 68 us for 304 MB).
 //
-// A row (KV head of a sequence) takes one block each where that loads the CUs evenly.  Else the tiles of all
-// rows form one line that is cut into equal shares, one per block, so no CU idles; rows cut by a share's end
-// are folded by the last block that finishes a piece of them, in piece order (reproducible).  One launch per
-// call, nothing waits.  The fold (4 us for 32 pieces) is bound by what one CU reads past its caches: wider loads, more
-// of them in flight and folding after all pieces of a block were each no faster.
+// A row (KV head of a sequence) is one block's work, or is cut into equal pieces, one per block; or the tiles of
+// all rows form one line that is cut into equal shares (see launch_decode).  Rows in pieces are folded by the last
+// block that finishes one, in piece order (reproducible).  One launch per call, nothing waits.  The fold (4 us for 32
+// pieces) is bound by what one CU reads past its caches: wider loads, more of them in flight and folding after all
+// pieces of a block were each no faster.
 //
-// Measured (device time per call, before -> after): 2048 tokens, 1 sequence 11.0 -> 7.9 us; 32768 tokens 35.5 ->
-// 26.9 us (5.0 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 50.5 us (6.0 TB/s).
+// Measured (device time per call, before -> after): 218 tokens, 1 sequence 10.2 -> 5.2 us; 2048 tokens 11.0 -> 7.8;
+// 32768 tokens 35.5 -> 26.0 (5.2 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 50.5 us (6.0 TB/s).
 #include <algorithm>
 #include <type_traits>
 
@@ -105,8 +105,9 @@ __device__ __forceinline__ int dec_block_of(int64_t tile, int64_t tiles, int64_t
   return (int)(((tile + 1) * n_blocks - 1) / tiles);
 }
 
-// kWhole: one block per row instead of equal shares.
-template <bool kPaged, bool kWhole, int kWaves>
+// kAligned: every row of sequence b is cut into a.piece0[b + 1] - a.piece0[b] equal pieces, one per block (KV heads
+// fastest), instead of equal shares of the line of tiles.
+template <bool kPaged, bool kAligned, int kWaves>
 __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   constexpr int kThr = kWaves * 64;
   constexpr int kTileBytes = kDecTile * kHeadDim * 2;
@@ -121,11 +122,18 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   const int c = lane & 15, q = lane >> 4;
   const int G = a.G;
   const int64_t n_blocks = gridDim.x;
+  int b = 0;
   int64_t at, at_end;
-  if (kWhole) {
-    const int row_seq = (int)blockIdx.x / a.Hkv, len = a.tile0[row_seq + 1] - a.tile0[row_seq];
-    at = (int64_t)a.tile0[row_seq] * a.Hkv + (int64_t)((int)blockIdx.x - row_seq * a.Hkv) * len;
-    at_end = at + len;
+  int n_piece = 1, piece_blk0 = 0;  // kAligned: pieces of the row and the block of its first one
+  if (kAligned) {
+    while ((int)blockIdx.x >= a.piece0[b + 1] * a.Hkv) ++b;
+    n_piece = a.piece0[b + 1] - a.piece0[b];
+    const int rel = (int)blockIdx.x - a.piece0[b] * a.Hkv, p = rel / a.Hkv, kvh = rel - p * a.Hkv;
+    piece_blk0 = (int)blockIdx.x - p * a.Hkv;
+    const int len = a.tile0[b + 1] - a.tile0[b];
+    const int64_t row_at = (int64_t)a.tile0[b] * a.Hkv + (int64_t)kvh * len;
+    at = row_at + (int64_t)len * p / n_piece;
+    at_end = row_at + (int64_t)len * (p + 1) / n_piece;
   } else {
     at = dec_first_tile(blockIdx.x, a.tiles, n_blocks);
     at_end = dec_first_tile((int64_t)blockIdx.x + 1, a.tiles, n_blocks);
@@ -137,7 +145,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   uint32_t k_addr[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) k_addr[s] = (uint32_t)(uintptr_t)(lptr_t)stage + kt * 256 + (((4 * s + q) ^ kt) << 4);
-  int b = 0;
 
   while (at < at_end) {
     // ---- the piece [tile0, tile1) of row (b, kvh)
@@ -290,8 +297,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       if (q == 0) { m_lds[wave][c] = m; l_lds[wave][c] = l; }
     }
     __syncthreads();
-    const bool whole = kWhole || (tile0 == 0 && tile1 == row_tiles);  // this block has the entire row
-    float *part = a.part + (2 * (size_t)blockIdx.x + (tile0 == 0 ? 1 : 0)) * kDecodeSlotFloats;
+    const bool whole = tile0 == 0 && tile1 == row_tiles;  // this block has the entire row
+    float *part = a.part + (2 * (size_t)blockIdx.x + (!kAligned && tile0 == 0 ? 1 : 0)) * kDecodeSlotFloats;
     float *out = a.out + ((size_t)b * a.Hq + (size_t)kvh * G) * kHeadDim;
     for (int e = tid; e < G * (kHeadDim / 2); e += kThr) {
       const int h = e >> 6, d = (e & 63) * 2;
@@ -314,9 +321,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         if (d == 0) agent_store2(part + kMaxReal * kHeadDim + 2 * h, M, L);
       }
     }
-    if constexpr (kWhole) return;
     at = row_at + tile1;
     if (whole) {
+      if (kAligned) return;
       __syncthreads();  // the next piece reuses the tables
       continue;
     }
@@ -324,8 +331,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     // ---- count this piece; the last one of the row folds them
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    const int blk0 = dec_block_of(row_at, a.tiles, n_blocks);
-    const int n_split = dec_block_of(row_at + row_tiles - 1, a.tiles, n_blocks) - blk0 + 1;
+    const int blk0 = kAligned ? piece_blk0 : dec_block_of(row_at, a.tiles, n_blocks);
+    const int n_split = kAligned ? n_piece : dec_block_of(row_at + row_tiles - 1, a.tiles, n_blocks) - blk0 + 1;
     unsigned *count = a.count + b * kMaxKvHeads + kvh;
     if (tid == 0) {
       const unsigned old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -334,9 +341,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     __syncthreads();
     if (last_lds != 0u) {
       if (tid == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
-      // piece p of the row lies in block blk0 + p; only the first one begins the row
+      // equal shares: piece p of the row lies in block blk0 + p; only the first one begins the row
       const float *src = a.part + 2 * (size_t)blk0 * kDecodeSlotFloats;
-      auto piece = [&](int p) { return src + (size_t)(p == 0 ? 1 : 2 * p) * kDecodeSlotFloats; };
+      auto piece = [&](int p) { return src + (size_t)(kAligned ? 2 * p * a.Hkv : p == 0 ? 1 : 2 * p) * kDecodeSlotFloats; };
       for (int hw = wave; hw < G; hw += kWaves) {  // one wave per head, lane = piece: the pieces' weights
         const float2 ml = agent_load2(piece(min(lane, n_split - 1)) + kMaxReal * kHeadDim + 2 * hw);
         const float mp = lane < n_split ? ml.x : kDecNegBig;
@@ -363,6 +370,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x, y);
       }
     }
+    if (kAligned) return;
     __syncthreads();
   }
 }
@@ -370,6 +378,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 // Tiles of every sequence (a.tile0, a.tiles), the blocks to spread them over, and the launch.
 hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   constexpr int kWaves = 4;
+  const dim3 block(kWaves * 64);
   int64_t tiles = 0, longest = 1;
   a.tile0[0] = 0;
   for (int b = 0; b < a.n_seq; ++b) {
@@ -379,23 +388,36 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
     a.tile0[b + 1] = (int)tiles;
   }
   a.tiles = tiles * a.Hkv;
+  // Each row cut into pieces of about a CU's share, or left whole, unless that loads the CUs unevenly for long: a share
+  // of the line that straddles rows costs a restart of the loads and one more fold, about 5 us.
+  //   Whole: rows close to a multiple of the CUs and none much longer than the mean (256 rows of 2048-2560 tokens 50.8
+  //   against 56 us, of 1280-2560 45.6 against 48; but 320 rows 54 against 47.7); rows of up to 12 tiles, where a fold
+  //   costs more than it saves (160 rows of 250 tokens 7.4 against 13.9).
+  //   Pieces: few rows, or few tiles per CU (128 rows of 1000 tokens 14.2 against 17 us; of 5000, 63 against 55.7).
+  constexpr int kWholeTiles = 12;
   const int rows = a.n_seq * a.Hkv;
-  const dim3 block(kWaves * 64);
-  // One block per row where that loads the CUs evenly: rows close to a multiple of the CUs, none much longer than
-  // the mean.  A cut row costs a restart of the loads and the fold: 256 rows of 2048-2560 tokens 50.8 instead of 56 us,
-  // of 1280-2560 45.6 instead of 48; but 320 rows 54 instead of 47.7.
   const int per_cu = (rows + n_cu - 1) / n_cu;
-  if (10 * rows >= 9 * per_cu * n_cu && 2 * longest * a.n_seq <= 3 * tiles) {
+  const bool even = 10 * rows >= 9 * per_cu * n_cu && 2 * longest * a.n_seq <= 3 * tiles;
+  const bool pieces = 4 * rows <= n_cu || (rows <= n_cu && a.tiles <= (int64_t)48 * n_cu);  // <= 1.5 n_cu of them
+  if (even || pieces || longest <= kWholeTiles) {
+    const int64_t share = std::max<int64_t>(kWaves, (a.tiles + n_cu - 1) / n_cu);
+    a.piece0[0] = 0;
+    for (int b = 0; b < a.n_seq; ++b) {
+      const int64_t t = a.tile0[b + 1] - a.tile0[b];
+      int64_t n = even || t <= kWholeTiles ? 1 : std::min<int64_t>((2 * t + share) / (2 * share), kDecodeMaxSplits);
+      a.piece0[b + 1] = a.piece0[b] + (int)std::max<int64_t>(n, 1);
+    }
+    const dim3 grid((unsigned)(a.piece0[a.n_seq] * a.Hkv));
     if (a.block_table)
-      hipLaunchKernelGGL((k_decode<true, true, kWaves>), dim3((unsigned)rows), block, 0, s, a);
+      hipLaunchKernelGGL((k_decode<true, true, kWaves>), grid, block, 0, s, a);
     else
-      hipLaunchKernelGGL((k_decode<false, true, kWaves>), dim3((unsigned)rows), block, 0, s, a);
+      hipLaunchKernelGGL((k_decode<false, true, kWaves>), grid, block, 0, s, a);
     return hipGetLastError();
   }
-  // Else equal shares: one block per CU, with a tile for each of its waves.  Two per CU where a block goes through
-  // several short rows: each row begins with the latency of its first loads, which the other block then covers.
-  const int share = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
-  int64_t blocks = std::min<int64_t>(std::min(share * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
+  // Equal shares: one block per CU; two where a block goes through several short rows, as each starts with the latency
+  // of its first loads, which the other block then covers.
+  const int shares = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
+  int64_t blocks = std::min<int64_t>(std::min(shares * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
   // a row is cut into at most kDecodeMaxSplits pieces: the fold keeps a weight for each
   blocks = std::max<int64_t>(1, std::min(blocks, a.tiles * (kDecodeMaxSplits - 2) / longest));
   const dim3 grid((unsigned)blocks);

@@ -22,6 +22,7 @@ def ctx():
 @pytest.mark.parametrize("ns,Hq,Hkv", [
     ([31], 32, 8), ([33], 32, 8), ([1, 32, 1], 7, 1), ([4097], 32, 8), ([9000], 4, 1), ([20000], 8, 1),
     ([30000, 1, 65], 32, 8), ([37] * 64, 32, 8), ([5 * i + 1 for i in range(64)], 64, 8), ([640] * 33, 32, 8),
+    ([390 + 3 * i for i in range(40)], 32, 8), ([2100 - i for i in range(41)], 32, 8), ([384, 385] * 4, 32, 8),
 ])
 def test_decode_cut_rows(ctx, ns, Hq, Hkv):
     print("case: decode split n=%s.. (%d) Hq=%d Hkv=%d" % (ns[:4], len(ns), Hq, Hkv), flush=True)
