@@ -1,17 +1,17 @@
 // Window-attention scores (Sec. 4.2 Eq. 1-2, App. B.1) of inputs whose logits do not all fit on the chip: the grid is
-// resident like that of fkv_score_fused.hip, but a block keeps only the logits of its last tiles in registers while the
+// resident like that of fkv_score_fused.hip, but a block keeps only the logits of its last tiles, in registers and LDS, while the
 // grid agrees on the softmax normalisers, and streams its first tiles of K a second time afterwards.
 //
 //   phase 1  stream the block's tiles (owned tokens plus pooling halo): running (max, sum) of the owned tokens per
-//            softmax row; raw logits of the last kKeep tiles stay in registers
+//            softmax row; raw logits of the last kLds + kKeep tiles stay on the chip
 //   phase 2  grid exchange of the row statistics (fkv_score_exchange.h); the first tile of phase 3 is on its way
 //   phase 3  probabilities of the tiles streamed again and, between their loads, of the kept ones; window sums to LDS
 //   phase 4  pooling, head means, scores
 //
 // Against the two-pass kernels (fkv_score.hip), which read K twice and need three launches, K's second read shrinks
 // by the kept part and a launch boundary (the statistics' way through memory and back) becomes the exchange:
-// 131072 tokens (17 tiles per block, 8 kept) 102 -> 80 us, 8 sequences of 8192-16384 tokens 87 -> 61 us.  With more than
-// 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and keeps 2 tiles of each:
+// 131072 tokens (17 tiles per block, 10 kept) 102 -> 76 us, 8 sequences of 8192-16384 tokens 87 -> 58 us.  With more than
+// 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and keeps 3 tiles of each:
 // 64 / 8 heads at 20001 tokens 39 -> 25 us.
 // A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not.
 #include <type_traits>
@@ -20,11 +20,14 @@
 
 namespace fkv {
 
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 constexpr int kKeepSub = 17, kKeepSubWide = 9;  // tiles per block: the window sums of all heads wait for the pooling in LDS
 
 int keep_sub_max(int v_groups) { return v_groups > kMaxKvHeads ? kKeepSubWide : kKeepSub; }
 
-template <int kVg, int kKeep, int kMaxSub>
+// kKeep tiles of logits stay in registers; the kLds tiles before those in the part of the window sums' array that
+// the wave fills itself, which is idle until phase 3 (8 kept -> 10: 131072 tokens 3.5 us less, 100000 tokens 2.8).
+template <int kVg, int kKeep, int kLds, int kMaxSub>
 __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs f) {
   constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
@@ -32,8 +35,10 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   __shared__ float g_sum[kGroups][kSlots];
   __shared__ float cst_lds[kGroups][kRowsPerGroup];
   __shared__ unsigned late_lds[kWaves];
-  static_assert(sizeof(ExchangeLds) <= sizeof(s_head), "the exchange's tables lie where the window sums go later");
-  ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(s_head);
+  static_assert(sizeof(ExchangeLds) <= sizeof(g_sum), "the exchange's tables lie where the group sums go later");
+  ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(g_sum);
+  constexpr int kWaveSums = kVg * kMaxGroup * kSlots;  // floats of s_head that one wave fills
+  static_assert(kLds * kVg * kRowsPerGroup * kSub <= kWaveSums && kWaveSums % 4 == 0, "logits kept in LDS");
   typedef __attribute__((address_space(1))) const void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
 
@@ -49,11 +54,12 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   const bool last = local == a.map.blk[b + 1] - a.map.blk[b] - 1;         // also owns the window columns
   const int c0 = o0 - r, c1 = last ? max(Lb, o1 + r) : o1 + r;            // computed tokens
   const int n_sub = (c1 - c0 + kSub - 1) / kSub;                          // <= kMaxSub (host guarantees)
-  const int n_keep = min(n_sub, kKeep), n_re = n_sub - n_keep;
+  const int n_keep = min(n_sub, kKeep), n_lds = min(n_sub - n_keep, kLds), n_re = n_sub - n_keep - n_lds;
   const int col0 = tok_base - b * a.W;
   const int g = wave * kVg;
   const bool has_group = g < a.V;
   uint8_t *stage = stage_all + wave * kStageBytes;
+  floatx4 *kept = reinterpret_cast<floatx4 *>(&s_head[0][0] + wave * kWaveSums) + lane;  // [tile][group][4][lane]
   unsigned poisoned = request_flag(f.err);
 
   bf16x8 qa[kVg][8];
@@ -130,13 +136,26 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
       else issue(st + 1, rest_t{});
       count(st, acc);
     }
+#pragma unroll 1
+    for (int t = 0; t < n_lds; ++t) {
+      floatx16 acc[kVg];
+      logits(acc);
+      issue(n_re + t + 1, rest_t{});  // there are kept tiles behind these
+#pragma unroll
+      for (int v = 0; v < kVg; ++v)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          kept[((t * kVg + v) * 4 + q) * 64] = floatx4{acc[v][4 * q], acc[v][4 * q + 1], acc[v][4 * q + 2], acc[v][4 * q + 3]};
+      count(n_re + t, acc);
+    }
+    const int st0 = n_re + n_lds;
 #pragma unroll
     for (int t = 0; t < kKeep; ++t)
       if (t < n_keep) {
         logits(z[t]);
-        if (t + 1 < n_keep) issue(n_re + t + 1, rest_t{});
+        if (t + 1 < n_keep) issue(st0 + t + 1, rest_t{});
         else if (n_re > 0) issue(0, rest_t{});  // the first tile of phase 3
-        count(n_re + t, z[t]);
+        count(st0 + t, z[t]);
       }
 #pragma unroll
     for (int v = 0; v < kVg; ++v) {
@@ -191,10 +210,26 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
       if (st + 1 < n_re) issue(st + 1, rest_t{});
       finish(st, acc);
     };
+    floatx16 zl[kLds][kVg];
+#pragma unroll
+    for (int t = 0; t < kLds; ++t)
+      if (t < n_lds)
+#pragma unroll
+        for (int v = 0; v < kVg; ++v)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const floatx4 x = kept[((t * kVg + v) * 4 + q) * 64];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) zl[t][v][4 * q + i] = x[i];
+          }
+    wave_lds_sync();  // the sums may overwrite them
+#pragma unroll
+    for (int t = 0; t < kLds; ++t)
+      if (t < n_lds) finish(n_re + t, zl[t]);
 #pragma unroll
     for (int t = 0; t < kKeep; ++t) {  // a kept tile's probabilities while the next tile is on its way
       if (t < n_re) again(t);
-      if (t < n_keep) finish(n_re + t, z[t]);
+      if (t < n_keep) finish(n_re + n_lds + t, z[t]);
     }
 #pragma unroll 1
     for (int st = kKeep; st < n_re; ++st) again(st);
@@ -217,9 +252,9 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
 
 hipError_t launch_score_keep(const ScoreArgs &a, const FusedArgs &f, hipStream_t s) {
   if (a.V > kMaxKvHeads)
-    hipLaunchKernelGGL((k_score_keep<2, 2, kKeepSubWide>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+    hipLaunchKernelGGL((k_score_keep<2, 2, 1, kKeepSubWide>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   else
-    hipLaunchKernelGGL((k_score_keep<1, 8, kKeepSub>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+    hipLaunchKernelGGL((k_score_keep<1, 8, 2, kKeepSub>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   return hipGetLastError();
 }
 

@@ -22,7 +22,7 @@ def _inputs(lengths, Hq, Hkv):
 @pytest.mark.parametrize("lengths,Hq,Hkv,pool_mode,pool_kernel", [
     ([64001], 32, 8, "max", 7), ([137000], 32, 8, "avg", 7), ([20000, 31000, 9, 40000], 32, 8, "avg", 15), ([131072], 28, 4, "max", 1),
     ([9], 64, 8, "avg", 7), ([2056], 64, 8, "max", 7), ([16001, 8], 64, 8, "avg", 7), ([40000], 56, 8, "max", 31), ([72000], 64, 8, "avg", 7),
-    ([700] * 60, 64, 8, "avg", 7),
+    ([700] * 60, 64, 8, "avg", 7), ([72000], 32, 8, "avg", 7), ([80000, 8000], 32, 8, "max", 5), ([22000], 64, 8, "avg", 7),
 ])
 def test_matches_two_pass(lengths, Hq, Hkv, pool_mode, pool_kernel):
     print("case: score keep lengths=%s Hq=%d Hkv=%d %s %d" % (lengths[:4], Hq, Hkv, pool_mode, pool_kernel), flush=True)
