@@ -32,19 +32,18 @@ __device__ __forceinline__ void poison_scores(const ScoreArgs &a, int col0, int 
   }
 }
 
-// The error flag, on its way while K is streamed (flag_arrived before it is looked at).  Written out: for a load of a
-// uniform value the compiler waits on the spot (0.7 us before the first K load).
+// The error flag, on its way while K is streamed: waited for where it is first looked at.  The address is made to look
+// different per lane, since the compiler waits on the spot for a load of a uniform value (0.7 us before the first K load).
 __device__ __forceinline__ unsigned request_flag(const unsigned *err) {
-  unsigned v;
-  asm volatile("global_load_dword %0, %1, %2 sc1" : "=v"(v) : "v"(0), "s"(err) : "memory");
-  return v;
+  unsigned zero = 0;
+  asm("" : "+v"(zero));
+  return __hip_atomic_load(err + zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void flag_arrived(unsigned &v) { asm volatile("s_waitcnt vmcnt(0)" : "+v"(v)); }
 
 // Folds a wave's per-lane (max, sum) pairs of a virtual group's 32 rows over the token lanes and posts them.  mloc[q]:
 // the block's maximum of row (q / 4) * 8 + hi * 4 + q % 4, in every lane.
 __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
-                                              int g, int lane, unsigned &poisoned) {
+                                              int g, int lane, unsigned poisoned) {
 #pragma unroll
   for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
   float srow[16];
@@ -52,7 +51,6 @@ __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&
   for (int q = 0; q < 16; ++q) srow[q] = sm[q] * fast_exp2(mx[q] - mloc[q]);
   // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
   const float ps = half_sum_scatter(srow, lane), pm = pick16(mloc, lane);
-  flag_arrived(poisoned);
   // lanes 0-15 post the 16 rows of the low half, lanes 32-47 those of the high half
   if ((lane & 31) < 16 && poisoned == 0u) {
     const int q = lane & 15;

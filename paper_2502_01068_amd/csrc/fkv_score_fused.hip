@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   const int g = wave;
   const bool has_group = g < a.V;  // the host takes this kernel only for V <= 8 (one wave per virtual group)
 
-  unsigned poisoned = request_flag(f.err);
+  const unsigned poisoned = request_flag(f.err);
   if (threadIdx.x == 0) flag_lds[0] = 1u;
 
   FKV_TICK(32);
@@ -112,7 +112,6 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   }
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
   // (fkv_clear_error) every launch only marks its scores invalid.
-  if (!has_group) flag_arrived(poisoned);
   if (poisoned != 0u) {
     poison_scores(a, col0, o0, o1);
     return;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   const bool has_group = g < a.V;
   uint8_t *stage = stage_all + wave * kStageBytes;
   floatx4 *kept = reinterpret_cast<floatx4 *>(&s_head[0][0] + wave * kWaveSums) + lane;  // [tile][group][4][lane]
-  unsigned poisoned = request_flag(f.err);
+  const unsigned poisoned = request_flag(f.err);
 
   bf16x8 qa[kVg][8];
   const int c = lane & 15, tq = lane >> 4;
@@ -165,7 +165,6 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   }
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
   // (fkv_clear_error) every launch only marks its scores invalid.
-  if (!has_group) flag_arrived(poisoned);
   if (poisoned != 0u) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
     poison_scores(a, col0, o0, o1);
