@@ -249,15 +249,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       const float alpha = dec_exp2(m - m_new);
       m = m_new;
       float psum = 0.f;
-      bf16x8 p0, p1, p2;  // p = p0 + p1 + p2, 8 bits each
+      // p = p0 + p1 + p2, 8 bits each, cut off and not rounded; the lower two are kept above 0, which adds less than
+      // 2^-125 of V: an infinite V stays infinite in the sum (0 times it, or a negative piece, would make it NaN).
+      constexpr float kTiny = 0x1p-126f;
+      u32x4 p0, p1, p2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float p = dec_exp2(z[i] - m_new);
-        psum += p;
-        p0[i] = (__bf16)p;
-        const float r1 = p - (float)p0[i];
-        p1[i] = (__bf16)r1;
-        p2[i] = (__bf16)(r1 - (float)p1[i]);
+      for (int i = 0; i < 8; i += 2) {
+        uint32_t w0[2], w1[2], w2[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float p = dec_exp2(z[i + e] - m_new);
+          psum += p;
+          w0[e] = __float_as_uint(p);
+          const float r1 = fmaxf(p - __uint_as_float(w0[e] & 0xffff0000u), kTiny);
+          w1[e] = __float_as_uint(r1);
+          w2[e] = __float_as_uint(fmaxf(r1 - __uint_as_float(w1[e] & 0xffff0000u), kTiny));
+        }
+        p0[i / 2] = __builtin_amdgcn_perm(w0[1], w0[0], 0x07060302u);
+        p1[i / 2] = __builtin_amdgcn_perm(w1[1], w1[0], 0x07060302u);
+        p2[i / 2] = __builtin_amdgcn_perm(w2[1], w2[0], 0x07060302u);
       }
       l = l * alpha + psum;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
@@ -277,9 +287,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const bf16x8 vj = __builtin_bit_cast(bf16x8, va[j]);
-        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p2, o[j], 0, 0, 0);
-        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p1, o[j], 0, 0, 0);
-        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, p0, o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, __builtin_bit_cast(bf16x8, p2), o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, __builtin_bit_cast(bf16x8, p1), o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vj, __builtin_bit_cast(bf16x8, p0), o[j], 0, 0, 0);
       }
     };
     for (; tile + kWaves < tile1; tile += kWaves) step(std::true_type{});  // uniform per wave
@@ -361,10 +371,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 #pragma unroll
           for (int i = 0; i < kBatch; ++i) v[i] = agent_load2(piece(min(s0 + i, n_split - 1)) + h * kHeadDim + d);
 #pragma unroll
-          for (int i = 0; i < kBatch; ++i) {  // past the last piece the weight is 0
+          for (int i = 0; i < kBatch; ++i) {  // past the last piece nothing is added: 0 times an infinite sum would be NaN
             const float f = w_lds[h][s0 + i];
-            x += v[i].x * f;
-            y += v[i].y * f;
+            x += s0 + i < n_split ? v[i].x * f : 0.f;
+            y += s0 + i < n_split ? v[i].y * f : 0.f;
           }
         }
         *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x, y);

@@ -41,3 +41,28 @@ def test_decode_cut_rows(ctx, ns, Hq, Hkv):
             err = np.abs(out[b] - ref) / np.abs(ref).max(axis=-1, keepdims=True)
             assert err.max() <= 1e-5, "seq %d: %.3g" % (b, err.max())
         o += n
+
+
+@pytest.mark.parametrize("ns,Hkv,paged", [([64], 8, False), ([4096], 8, False), ([9000], 1, False), ([2048] * 32, 8, True)])
+def test_decode_infinite_v(ctx, ns, Hkv, paged):
+    """An infinite V of a token with weight > 0 gives that infinity in its column, not NaN, and nothing elsewhere."""
+    print("case: decode with infinite V n=%s.. (%d) Hkv=%d paged=%s" % (ns[:4], len(ns), Hkv, paged), flush=True)
+    B, d, tot, page = len(ns), 128, sum(ns), 16
+    q = dev_bf16(wl.normal_bf16(71, 0, "q_win", (B, Hkv * 4, d)))
+    k, v = (dev_bf16(wl.normal_bf16(71, 0, n, (tot, Hkv, d))) for n in ("k", "v"))
+    shape = fk.make_shape(ns, n_q_heads=Hkv * 4, n_kv_heads=Hkv)
+
+    def run():
+        if not paged:
+            return ctx.fkv_decode_attention(shape, q, k, v, ns, "token_major")
+        table = torch.arange(tot // page, dtype=torch.int32, device="cuda").reshape(B, -1)
+        dims = (tot // page, page, Hkv, d)
+        return ctx.fkv_decode_attention_paged(shape, q, k.view(dims), v.view(dims), table, ns)
+
+    plain = run().clone()
+    vf = v.view(torch.bfloat16)
+    vf[3, 0, 5], vf[ns[0] - 40, Hkv - 1, 77] = float("inf"), float("-inf")
+    out = run()
+    want = plain.clone().view(B, Hkv, 4, d)
+    want[0, 0, :, 5], want[0, Hkv - 1, :, 77] = float("inf"), float("-inf")
+    assert torch.equal(out.view(B, Hkv, 4, d), want)
