@@ -335,7 +335,7 @@ def run_decode(args):
         "unit": "us", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": us_c * 1e-3,
         "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "bf16 inputs, fp32 accumulate and output",
         "data": "synthetic N(0,1) bf16", "config": {"workload": "decode: 1 sequence, 32 q / 8 kv heads, d=128, cache 2048 vs 32768 tokens"},
-        "roofline": {"bound": "hbm", "kernel": "k_decode_partial+combine", "achieved": bytes_f / (us_f * 1e-6) / 1e9, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "k_decode", "achieved": bytes_f / (us_f * 1e-6) / 1e9, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": bytes_f / (us_f * 1e-6) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                      "note": "bandwidth figure is for the 32768-token cache (134 MB); the 2048-token cache (8.4 MB) is latency-bound"},
         "path": {"compacted_us": us_c, "full_cache_us": us_f, "speedup_of_this_layer": us_f / us_c,
