@@ -303,7 +303,7 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
  * order.  What is said here about single-pass launches holds for both resident kernels. */
 int fkv_set_score_path(fkv_ctx *ctx, int mode);
 
-/* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 24576 keys
+/* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 24573 keys
  * are cut into at most 8 slices (8192, 16384 or 32768 keys each, by row length), one block per slice,
  * and the blocks of a row agree on the threshold through device memory inside one launch, when every
  * block of the call can be resident at once (rows x slices x sequences <= compute units, rows up to

@@ -161,7 +161,7 @@ constexpr int kCoopHistRounds = 4;    // histogram exchanges a search can need (
 constexpr int kCoopWords = (kCoopHistRounds + 1) * 1024 + 64;  // mailbox words per block: one region per round, the list, the key range
 constexpr int kCoopMaxSlices = 8;     // slices (blocks) per row; 8192, 16384 or 32768 keys each
 constexpr int kCoopMaxBlocks = 256;   // blocks per launch the mailboxes hold
-constexpr int kCoopMinKeys = 24576;   // rows up to here stay on the one-block kernel (24500 keys: 13 against 14.9 us; 28000: equal)
+constexpr int kCoopMinKeys = 24576;   // rows of up to 3 keys fewer stay on the one-block kernel (24500 keys: 13 against 14.9 us; 28000: equal)
 constexpr size_t kCoopBoxBytes = (size_t)kCoopMaxBlocks * kCoopWords * sizeof(unsigned long long);
 constexpr int kCtrSelEpoch = 1;       // context counters: epoch of the next launch (never 0),
 constexpr int kCtrSelDone = 2;        // finish count of the running launch
