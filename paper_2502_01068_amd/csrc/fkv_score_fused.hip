@@ -163,7 +163,12 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
         for (int hl = 0; hl < 4; ++hl) {
           float sum = 0.f;
 #pragma unroll
-          for (int rr = 0; rr < 4; ++rr) sum += z[st][hl * 4 + rr] * fac[hl * 4 + rr];
+          for (int rr = 0; rr < 4; ++rr) {
+            // Each probability is rounded before it is added: as one multiply-add the scores move by an ulp, and with
+            // them which of two nearly equal tokens is kept.
+#pragma clang fp contract(off)
+            sum += z[st][hl * 4 + rr] * fac[hl * 4 + rr];
+          }
           sum = add_across_halves(sum);  // other half of the window rows
           if (hi == 0 && hl < vg_heads(a, g)) s_head[g * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
         }
