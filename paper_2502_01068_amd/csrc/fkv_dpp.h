@@ -10,7 +10,6 @@
 
 namespace fkv {
 
-constexpr int kDppRowShl = 0x100;   // + n: lane i reads lane i + n of its row
 constexpr int kDppRowShr = 0x110;   // + n: lane i reads lane i - n of its row
 constexpr int kDppRowRor = 0x120;   // + n: lane i reads lane (i - n) mod 16 of its row
 constexpr int kDppQuadXor1 = 0xB1;  // lane i of a quad reads lane i ^ 1,
@@ -67,10 +66,8 @@ __device__ __forceinline__ float dpp_f32(float old, float src) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), kCtrl, kRowMask, 0xF, false));
 }
 
-// Maximum / sum over the 32 lanes of each wave half (lanes 0-31 and 32-63 separately), in every lane.
-// Rotations inside the 16-lane DPP rows, then one swap of the odd and even rows.  The summation order
-// depends on the lane, so two lanes of a half may differ in the last bit: callers that need one
-// value take it from a fixed lane.
+// Maximum over the 32 lanes of each wave half (lanes 0-31 and 32-63 separately), in every lane: rotations inside the
+// 16-lane DPP rows, then one swap of the odd and even rows.
 __device__ __forceinline__ float half_max(float x) {
   x = fmaxf(x, dpp_f32<kDppRowRor + 8>(x, x));
   x = fmaxf(x, dpp_f32<kDppRowRor + 4>(x, x));
@@ -80,41 +77,7 @@ __device__ __forceinline__ float half_max(float x) {
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float half_sum(float x) {
-  x += dpp_f32<kDppRowRor + 8>(0.f, x);
-  x += dpp_f32<kDppRowRor + 4>(0.f, x);
-  x += dpp_f32<kDppRowRor + 2>(0.f, x);
-  x += dpp_f32<kDppRowRor + 1>(0.f, x);
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
-// half_sum of 16 values at once, scattered: lane q of each 16-lane row returns the sum of x[q] over its wave half.  At
-// every level a lane keeps the half of the values its lane bit names and adds its partner's, so 15 exchanges
-// do the work of 64; the pairs added are those of half_sum (addition commutes), so the sums have the same bits.
-__device__ __forceinline__ float half_sum_scatter(const float (&x)[16], int lane) {
-  float a[8], b[4], c[2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float lo = x[k] + dpp_f32<kDppRowShl + 8>(0.f, x[k]), hi = x[k + 8] + dpp_f32<kDppRowShr + 8>(0.f, x[k + 8]);
-    a[k] = (lane & 8) ? hi : lo;
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float lo = a[k] + dpp_f32<kDppRowShl + 4>(0.f, a[k]), hi = a[k + 4] + dpp_f32<kDppRowShr + 4>(0.f, a[k + 4]);
-    b[k] = (lane & 4) ? hi : lo;
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float lo = b[k] + dpp_f32<kDppQuadXor2>(0.f, b[k]), hi = b[k + 2] + dpp_f32<kDppQuadXor2>(0.f, b[k + 2]);
-    c[k] = (lane & 2) ? hi : lo;
-  }
-  const float lo = c[0] + dpp_f32<kDppQuadXor1>(0.f, c[0]), hi = c[1] + dpp_f32<kDppQuadXor1>(0.f, c[1]);
-  const unsigned u = __float_as_uint((lane & 1) ? hi : lo);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 // One of two registers by a lane bit.  (Written as a choice between two elements of an array the compiler makes it a
 // lane-dependent index and moves the array to LDS.)
 __device__ __forceinline__ float lane_pick(bool second, float x, float y) {
@@ -129,6 +92,29 @@ __device__ __forceinline__ float pick16(const float (&x)[16], int lane) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) b[k] = lane_pick((lane & 4) != 0, a[k], a[k + 4]);
   return lane_pick((lane & 1) != 0, lane_pick((lane & 2) != 0, b[0], b[2]), lane_pick((lane & 2) != 0, b[1], b[3]));
+}
+
+// Sums of 16 products x[q] * y[q] over each wave half: lane q of each 16-lane row returns the q-th.  The tree of a sum is that
+// of rotations by 8, 4, 2 and 1 lanes read at lane q, and a product is rounded only on its way to the lane 8 further on,
+// which adds it to its own one in a multiply-add; the sums' last bits depend on both.  After the rotation by 4 the tree
+// of lane q needs lanes q - 3 .. q of its row: four sums 4 lanes apart share a register from there on.
+__device__ __forceinline__ float half_sums_of_products(const float (&x)[16], const float (&y)[16], int lane) {
+  float s[16], c[4];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    s[q] = __builtin_fmaf(x[q], y[q], dpp_f32<kDppRowRor + 8>(0.f, x[q] * y[q]));
+    s[q] += dpp_f32<kDppRowRor + 4>(0.f, s[q]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int at = lane + 3 - k;  // bits 2 and 3: which of sums k, k + 4, k + 8, k + 12 this lane belongs to
+    c[k] = lane_pick((at & 8) != 0, lane_pick((at & 4) != 0, s[k], s[k + 4]), lane_pick((at & 4) != 0, s[k + 8], s[k + 12]));
+    c[k] += dpp_f32<kDppRowRor + 2>(0.f, c[k]);
+    c[k] += dpp_f32<kDppRowRor + 1>(0.f, c[k]);
+  }
+  const unsigned u = __float_as_uint(lane_pick((lane & 2) != 0, lane_pick((lane & 1) != 0, c[0], c[1]), lane_pick((lane & 1) != 0, c[2], c[3])));
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Maximum / sum over the 64 lanes as a wave-uniform value (fixed order: reproducible).

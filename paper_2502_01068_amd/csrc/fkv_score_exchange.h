@@ -46,11 +46,11 @@ __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&
                                               int g, int lane, unsigned poisoned) {
 #pragma unroll
   for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
-  float srow[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) srow[q] = sm[q] * fast_exp2(mx[q] - mloc[q]);
   // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
-  const float ps = half_sum_scatter(srow, lane), pm = pick16(mloc, lane);
+  float shrink[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) shrink[q] = fast_exp2(mx[q] - mloc[q]);
+  const float ps = half_sums_of_products(sm, shrink, lane), pm = pick16(mloc, lane);
   // lanes 0-15 post the 16 rows of the low half, lanes 32-47 those of the high half
   if ((lane & 31) < 16 && poisoned == 0u) {
     const int q = lane & 15;
