@@ -133,6 +133,13 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 #pragma unroll
         for (int q = 0; q < 16; ++q) z[st][q] = fast_exp2(z[st][q] - mloc[q]);
       }
+    if (a.W < kMaxWindow) {  // rows the window does not have: their logits may be NaN (0 times an infinite K)
+#pragma unroll
+      for (int st = 0; st < kFusedSub; ++st)
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          if (hi * 4 + (q & 3) >= a.W) z[st][q] = 0.f;
+    }
   }
   FKV_TICK(36);
 
@@ -148,12 +155,9 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 
   // ---- phase 3: probabilities from the kept logits, window sums into LDS
   if (has_group && wave_ok) {
-    float fac[16];  // 2^(block reference - global log-sum-exp) per row, 0 for rows the window does not have
+    float fac[16];  // 2^(block reference - global log-sum-exp) per row
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      fac[q] = fast_exp2(mloc[q] - cst_lds[wave][(q >> 2) * 8 + hi * 4 + (q & 3)]);
-      if (hi * 4 + (q & 3) >= a.W) fac[q] = 0.f;
-    }
+    for (int q = 0; q < 16; ++q) fac[q] = fast_exp2(mloc[q] - cst_lds[wave][(q >> 2) * 8 + hi * 4 + (q & 3)]);
 #pragma unroll
     for (int st = 0; st < kFusedSub; ++st) {
       if (st < n_sub) {

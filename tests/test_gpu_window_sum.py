@@ -43,3 +43,25 @@ def test_window_sum_is_the_sum_of_rounded_probabilities(lengths, Hq, Hkv, path):
     assert (want > 0).all() and torch.equal(full.cpu(), want)
     assert ctx.fkv_query_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("window,lengths,Hq,Hkv,path", [
+    (1, [300], 32, 8, 2), (3, [2049], 32, 8, 2), (7, [12289], 28, 4, 2), (5, [40000], 32, 8, 2), (3, [700, 40], 32, 8, 1), (3, [5000], 64, 8, 0),
+])
+def test_infinite_key_with_a_short_window(window, lengths, Hq, Hkv, path):
+    """A key whose logits are -inf in every row of the window scores 0; the matrix tile's rows past the window, whose
+    queries are 0 and whose logits of that key are NaN, do not count."""
+    print("case: infinite key window=%d lengths=%s Hq=%d Hkv=%d path=%d" % (window, lengths, Hq, Hkv, path), flush=True)
+    ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=len(lengths))
+    ctx.fkv_set_score_path(path)
+    shape = fk.make_shape(lengths, n_q_heads=Hq, n_kv_heads=Hkv, pool_kernel=1, window=window)
+    q, k = _inputs(lengths, Hq, Hkv)
+    q = q[:, :window].contiguous()
+    q[..., 0] = -1.0
+    at = lengths[0] // 3
+    k[at, :, 0] = float("inf")
+    heads = ctx.fkv_score_heads(shape, q, k)
+    assert torch.isfinite(heads).all()
+    assert (heads[:, at] == 0).all() and (heads[:, at + 1] > 0).all()
+    assert ctx.fkv_query_error() == 0
+    ctx.close()
