@@ -192,6 +192,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       }
     };
     auto load_v = [&](int tile, int slot) {
+      keep_access_order();  // read_k_tile waits for all but the 8 youngest loads: these
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + (size_t)token_of(i, tile, slot) * a.tok_stride));

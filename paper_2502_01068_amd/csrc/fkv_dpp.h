@@ -66,6 +66,10 @@ __device__ __forceinline__ float dpp_f32(float old, float src) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), kCtrl, kRowMask, 0xF, false));
 }
 
+// Neither the compiler nor its scheduler moves a memory access across this.  A wait that leaves the n youngest loads in
+// flight needs it where the order of those loads matters and they do not depend on each other.
+__device__ __forceinline__ void keep_access_order() { asm volatile("" ::: "memory"); }
+
 // Maximum over the 32 lanes of each wave half (lanes 0-31 and 32-63 separately), in every lane: rotations inside the
 // 16-lane DPP rows, then one swap of the odd and even rows.
 __device__ __forceinline__ float half_max(float x) {

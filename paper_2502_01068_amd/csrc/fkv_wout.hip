@@ -21,6 +21,7 @@
 // Tokens are split over blocks (8 waves each); a block merges its waves' running states through
 // LDS and leaves one partial (max, sum, 32 x 128 accumulator) per (sequence, group, split); a second
 // launch folds the splits in a fixed order.
+#include "fkv_dpp.h"
 #include "fkv_score_common.h"
 
 namespace fkv {
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
     }
   };
   auto issue_v = [&](int tile) {
+    keep_access_order();  // the wait for a K tile leaves the 8 youngest loads in flight: these
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int t = min(tile * kSub + i * 4 + tq, Lb - 1);
