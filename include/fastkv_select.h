@@ -337,8 +337,10 @@ int fkv_query_error(fkv_ctx *ctx, int32_t *flag_out);
 /* fkv_set_wait_limit: bound of every wait of the single-pass kernel's grid exchange in microseconds
  * (0 restores the 2 s default, at most 60 s).  A wave that gives up still leaves the kernel
  * normally; a tiny limit is how the failure path is exercised.  fkv_clear_error synchronises the
- * device, empties the exchange's mailboxes (a failed exchange may leave values in them) and resets
- * the flag; the next call works again. */
+ * device, empties the exchange's mailboxes (a failed exchange may leave values in them), zeroes the
+ * decode kernel's counts of finished pieces (a launch that was cut short, or overlapped another one of
+ * the context, may leave them off: later results of rows in pieces would be wrong without an error) and
+ * resets the flag; the next call works again. */
 int fkv_set_wait_limit(fkv_ctx *ctx, int64_t microseconds);
 int fkv_clear_error(fkv_ctx *ctx);
 

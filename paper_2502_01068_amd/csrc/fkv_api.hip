@@ -549,6 +549,11 @@ hipError_t reset_select_exchange(fkv_ctx *c) {
     e = hipMemcpy(c->ws + c->lay.counters + kCtrSelEpoch * sizeof(unsigned), init, sizeof init, hipMemcpyHostToDevice);
   return e;
 }
+
+// Pieces that have finished, per row: zero between launches, unless one was cut short or overlapped another.
+hipError_t reset_decode_counts(fkv_ctx *c) {
+  return hipMemset(c->ws + c->lay.dec_count, 0, (size_t)c->max_seqs * kMaxKvHeads * sizeof(unsigned));
+}
 }  // namespace
 
 int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_seqs) {
@@ -601,7 +606,7 @@ int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_
   }
   const bool counted = e == hipSuccess;
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.counters, 0, kNumCounters * sizeof(unsigned));
-  if (e == hipSuccess) e = hipMemset(c->ws + c->lay.dec_count, 0, (size_t)max_seqs * kMaxKvHeads * sizeof(unsigned));
+  if (e == hipSuccess) e = reset_decode_counts(c);
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.fused_part, 0xFF, kFusedPartBytes);  // every mailbox empty
   if (e == hipSuccess) e = hipMemset(c->ws + c->lay.fused_lse, 0xFF, kFusedLseBytes);
   if (e == hipSuccess) e = reset_select_exchange(c);
@@ -1247,6 +1252,7 @@ int fkv_clear_error(fkv_ctx *ctx) {
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.fused_part, 0xFF, kFusedPartBytes);
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.fused_lse, 0xFF, kFusedLseBytes);
   if (e == hipSuccess) e = reset_select_exchange(ctx);
+  if (e == hipSuccess) e = reset_decode_counts(ctx);
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.counters + kCtrError * sizeof(unsigned), 0, sizeof(unsigned));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   return e == hipSuccess ? FKV_OK : hip_fail(e);

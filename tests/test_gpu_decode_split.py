@@ -1,5 +1,7 @@
 """Decode attention where its work is cut: rows that end inside a block's share, rows of one tile, tiles
 with one token, more rows than blocks, and one long row next to short ones."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -66,3 +68,34 @@ def test_decode_infinite_v(ctx, ns, Hkv, paged):
     want = plain.clone().view(B, Hkv, 4, d)
     want[0, 0, :, 5], want[0, Hkv - 1, :, 77] = float("inf"), float("-inf")
     assert torch.equal(out.view(B, Hkv, 4, d), want)
+
+
+class _Layout(ctypes.Structure):  # WsLayout of csrc/fkv_api.hip
+    _fields_ = [(n, ctypes.c_size_t) for n in ("partial", "rowstat", "scores_group", "scores_tsp", "counters", "fused_part", "fused_lse",
+                                               "sel_long", "sel_coop", "dec_part", "dec_count", "wout_o", "wout_ms", "total")] + [("max_stat_blocks", ctypes.c_int)]
+
+
+class _Ctx(ctypes.Structure):  # the first members of fkv_ctx
+    _fields_ = [("device", ctypes.c_int), ("max_tokens", ctypes.c_int64), ("max_seqs", ctypes.c_int32), ("lay", _Layout), ("ws", ctypes.c_void_p)]
+
+
+def test_clear_error_resets_piece_counts():
+    """Counts as a cut launch leaves them (written from the host): after fkv_clear_error rows in pieces are right again."""
+    print("case: decode piece counts after fkv_clear_error", flush=True)
+    c = fk.Context(max_total_tokens=4096, max_seqs=2)
+    q, k, v = (dev_bf16(wl.normal_bf16(72, 0, n, dims)) for n, dims in (("q_win", (2, 32, 128)), ("k", (8192, 8, 128)), ("v", (8192, 8, 128))))
+    shape = fk.make_shape([8, 8])
+    want = c.fkv_decode_attention(shape, q, k, v, [4096, 4096], "token_major")
+    raw = _Ctx.from_address(c.handle.value)
+    assert (raw.device, raw.max_tokens, raw.max_seqs) == (c.device, 4096, 2)
+    assert raw.lay.dec_count + 2 * 8 * 4 <= raw.lay.wout_o < raw.lay.total
+    off = (ctypes.c_uint32 * 16)(*range(1, 17))
+    torch.cuda.synchronize()
+    copy = fk.load().hipMemcpy  # of the runtime that the library itself uses
+    copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+    assert copy(raw.ws + raw.lay.dec_count, ctypes.addressof(off), ctypes.sizeof(off), 1) == 0
+    c.fkv_clear_error()
+    for _ in range(2):
+        out = torch.full_like(want, float("nan"))
+        assert torch.equal(c.fkv_decode_attention(shape, q, k, v, [4096, 4096], "token_major", out=out), want)
+    c.close()
