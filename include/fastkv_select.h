@@ -326,9 +326,10 @@ int fkv_set_select_path(fkv_ctx *ctx, int mode);
 int fkv_score_plan(const fkv_shape *shape, int32_t max_blocks, int32_t *first_block, int32_t *own, int32_t *n_sub_max);
 
 /* Synchronises the device (hipDeviceSynchronize) and reports the context's sticky error flag: 0, or
- * 1 if a wave of the single-pass score kernel gave up waiting for the rest of its grid (2 s bound).
- * Cannot happen while the library's launches are the only work competing for the device's compute
- * units for that long.  The failure is visible on the device without this call: the blocks that
+ * 1 if a wave of a resident kernel (fkv_set_score_path, fkv_set_select_path) gave up waiting for the rest
+ * of its grid (2 s bound).  Cannot happen while the library's launches are the only work competing for the
+ * device's compute units for that long; a program whose own kernels may hold them, or their LDS, takes the
+ * kernels that need no resident grid (mode 1 of both).  The failure is visible on the device without this call: the blocks that
  * gave up write NaN scores, and while the flag is set every single-pass score launch of the context
  * writes only NaN scores, fkv_compress_kv / fkv_compress_kv_paged write -1 into every index and the
  * gathers copy nothing for those.  The flag stays set until fkv_clear_error. */

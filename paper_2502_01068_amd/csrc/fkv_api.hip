@@ -93,6 +93,7 @@ struct ScoreWs {
   float *fused_lse;
   unsigned *err;
   int n_cu;             // resident blocks the single-pass kernel may use; also the block-count target of the two-pass launches
+  int n_cu_keep;        // the same of the kernel that keeps part of the logits (0: not available)
   int score_path;       // 0 auto, 1 two-pass, 2 single-pass or fail
   unsigned long long wait_ticks;
   int device;
@@ -110,6 +111,7 @@ struct fkv_ctx {
   WsLayout lay;
   uint8_t *ws;
   int n_cu;            // compute units x resident blocks per CU of the single-pass score kernel
+  int n_cu_keep;       // the same of the score kernel that keeps part of the logits (0: not available)
   int score_path;      // 0 auto, 1 two-pass kernels, 2 single-pass resident grid
   int n_cu_select;     // resident blocks of the several-blocks-per-row select kernel (0: not available)
   int select_path;     // 0 auto, 1 never several blocks per row, 2 several blocks per row whenever the launch fits
@@ -297,6 +299,7 @@ ScoreWs ws_of(fkv_ctx *ctx) {
   w.fused_lse = reinterpret_cast<float *>(ctx->ws + ctx->lay.fused_lse);
   w.err = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters) + kCtrError;
   w.n_cu = ctx->n_cu;
+  w.n_cu_keep = ctx->n_cu_keep;
   w.score_path = ctx->score_path;
   w.wait_ticks = ctx->wait_ticks;
   w.device = ctx->device;
@@ -383,7 +386,7 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
     if (!fits && w.score_path == 0 && !several_contexts(w.device)) {
       // Longer inputs and wide groups: part of the logits kept, the rest of K read again.  Not while several contexts
       // exist on the device: resident launches of different contexts are chained, the two-pass kernels overlap.
-      keep = fits = plan_fused(r, a.pool_r, keep_sub_max(r.V) * 32, max_blocks, a.map.blk, f.own, &f.n_sub_max);
+      keep = fits = plan_fused(r, a.pool_r, keep_sub_max(r.V) * 32, std::min(w.n_cu_keep, kMaxFusedBlocks), a.map.blk, f.own, &f.n_sub_max);
     }
     if (fits) total = a.map.blk[r.n_seq];
     if (w.score_path == 2 && !(fits && total > 0)) return FKV_EUNSUPPORTED;
@@ -586,6 +589,7 @@ int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_
     if (e != hipSuccess) { delete c; return hip_fail(e); }
     const int per_cu = score_fused_max_blocks_per_cu();
     c->n_cu = prop.multiProcessorCount * (per_cu > 0 ? 1 : 0);  // one resident block per CU
+    c->n_cu_keep = prop.multiProcessorCount * (score_keep_max_blocks_per_cu() > 0 ? 1 : 0);
     c->n_cu_select = prop.multiProcessorCount * (select_coop_max_blocks_per_cu() > 0 ? 1 : 0);
   }
   c->select_path = 0;

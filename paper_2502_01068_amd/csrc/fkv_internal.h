@@ -121,6 +121,7 @@ int fused_preferred_blocks(int n_sub);
 int score_fused_max_blocks_per_cu(void);
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
 int keep_sub_max(int v_groups);
+int score_keep_max_blocks_per_cu(void);
 hipError_t launch_score_keep(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
 
 int stats_chunk_tokens(void);

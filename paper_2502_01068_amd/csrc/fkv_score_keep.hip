@@ -257,4 +257,11 @@ hipError_t launch_score_keep(const ScoreArgs &a, const FusedArgs &f, hipStream_t
   return hipGetLastError();
 }
 
+int score_keep_max_blocks_per_cu(void) {  // they take nearly all of a CU's LDS, twice what k_score_fused does
+  int n = 0, wide = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_score_keep<1, 8, 2, kKeepSub>, kThreads, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&wide, k_score_keep<2, 2, 1, kKeepSubWide>, kThreads, 0) != hipSuccess) return 0;
+  return n < wide ? n : wide;
+}
+
 }  // namespace fkv
