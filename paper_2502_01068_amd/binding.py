@@ -117,7 +117,7 @@ def load():
     lib.fkv_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_float), pi32, i32]
     for name in EXPORTS:
         getattr(lib, name)  # raises AttributeError if a declared symbol is missing
-    _native.bind(FkvShape, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
+    _native.bind(FkvShape, FkvError, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
     _lib = lib
     return lib
 

@@ -6,8 +6,9 @@
 // checks, argument conversion and torch.empty.  Here a decode call is issued in 4.1 us and a compress call in 12.7, launches included.
 //
 // Every function returns None for anything it does not recognise as a correct call (wrong type, size, device, count,
-// an error status of the library): the Python wrapper then makes the call itself, whose checks name the
-// mistake.  Nothing has been enqueued in that case, since the library validates before its first launch.
+// a call the library refuses): the Python wrapper then makes the call itself, whose checks name the
+// mistake.  Nothing has been enqueued in that case, since the library validates before its first launch.  A failed
+// HIP call is raised from here: launches before it may have been enqueued, so the call is not made again.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -35,6 +36,7 @@ struct Api {
 } api;
 
 PyTypeObject *shape_type = nullptr;
+PyObject *error_type = nullptr;
 PyObject *key_k_out, *key_v_out, *key_idx_kv, *key_x_out, *key_idx_tsp;
 
 // The fixed head of every call: context handle and device, descriptor, and the sizes that follow from it.
@@ -127,13 +129,21 @@ struct Counts {
   }
 };
 
+struct HipFailure { const char *where; };
+
+// False if the library refuses the call.
 template <typename F>
-bool call(F &&f) {
-  struct NoGil {
-    PyThreadState *state = PyEval_SaveThread();
-    ~NoGil() { PyEval_RestoreThread(state); }
-  } no_gil;
-  return f() == FKV_OK;
+bool call(const char *where, F &&f) {
+  int status;
+  {
+    struct NoGil {
+      PyThreadState *state = PyEval_SaveThread();
+      ~NoGil() { PyEval_RestoreThread(state); }
+    } no_gil;
+    status = f();
+  }
+  if (status == FKV_EHIP) throw HipFailure{where};
+  return status == FKV_OK;
 }
 
 PyObject *none() { Py_RETURN_NONE; }
@@ -149,6 +159,12 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t n) {
   if (n != kArgs) return none();
   try {
     return F(args);
+  } catch (const HipFailure &e) {
+    if (PyObject *error = PyObject_CallFunction(error_type, "is", (int)FKV_EHIP, e.where)) {
+      PyErr_SetObject(error_type, error);
+      Py_DECREF(error);
+    }
+    return nullptr;
   } catch (...) {
     PyErr_Clear();
     return none();
@@ -163,7 +179,10 @@ PyObject *score_window(PyObject *const *a) {
   at::Tensor sg, st;
   if (!q || !k || !output(c, a[5], kF32, c.hkv * c.sum_p, {c.hkv, c.sum_p}, at::kFloat, sg)) return none();
   if ((a[6] != Py_None || a[7] == Py_True) && !output(c, a[6], kF32, c.sum_p, {c.sum_p}, at::kFloat, st)) return none();
-  if (!call([&] { return api.score_window(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), f32(sg), f32(st), c.stream); })) return none();
+  if (!call("fkv_score_window", [&] {
+        return api.score_window(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), f32(sg), f32(st), c.stream);
+      }))
+    return none();
   return Py_BuildValue("(NN)", wrap(sg), wrap_or_none(st));
 }
 
@@ -174,7 +193,10 @@ PyObject *score_heads(PyObject *const *a) {
   const at::Tensor *q = tensor(c, a[3], kBf16, c.q_win), *k = tensor(c, a[4], kBf16, c.kv);
   at::Tensor sh;
   if (!q || !k || !output(c, a[5], kF32, c.hq * c.sum_p, {c.hq, c.sum_p}, at::kFloat, sh)) return none();
-  if (!call([&] { return api.score_heads(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), f32(sh), c.stream); })) return none();
+  if (!call("fkv_score_heads", [&] {
+        return api.score_heads(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), f32(sh), c.stream);
+      }))
+    return none();
   return wrap(sh);
 }
 
@@ -188,7 +210,10 @@ PyObject *select_topk(PyObject *const *a) {
   const int64_t rows = s->dim() == 1 ? 1 : s->size(0);
   at::Tensor idx;
   if (rows > INT32_MAX || !output(c, a[5], kI32, rows * n.sum, {rows, n.sum}, at::kInt, idx)) return none();
-  if (!call([&] { return api.select_topk(c.ctx, c.shape, f32(*s), (int32_t)rows, n.v, i32(idx), c.stream); })) return none();
+  if (!call("fkv_select_topk", [&] {
+        return api.select_topk(c.ctx, c.shape, f32(*s), (int32_t)rows, n.v, i32(idx), c.stream);
+      }))
+    return none();
   return wrap(idx);
 }
 
@@ -204,7 +229,10 @@ PyObject *gather_rows(PyObject *const *a) {
   c10::DimVector sizes(x->sizes().begin(), x->sizes().end());
   sizes[0] = n.sum;
   if (!output(c, a[6], kAny, 0, sizes, x->scalar_type(), out) || out.nbytes() < n.sum * row_bytes) return none();
-  if (!call([&] { return api.gather_rows(c.ctx, c.shape, x->data_ptr(), row_bytes, i32(*idx), n.v, out.data_ptr(), c.stream); })) return none();
+  if (!call("fkv_gather_rows", [&] {
+        return api.gather_rows(c.ctx, c.shape, x->data_ptr(), row_bytes, i32(*idx), n.v, out.data_ptr(), c.stream);
+      }))
+    return none();
   return wrap(out);
 }
 
@@ -224,7 +252,7 @@ PyObject *gather_kv(PyObject *const *a) {
   if (!output(c, a[7], kBf16, heads * n.sum * c.d, sizes, k->scalar_type(), ko)) return none();
   if (has_v && !output(c, a[8], kBf16, heads * n.sum * c.d, sizes, v->scalar_type(), vo)) return none();
   const auto fn = kPerHead ? api.gather_kv_per_head : api.gather_kv;
-  if (!call([&] {
+  if (!call(kPerHead ? "fkv_gather_kv_per_head" : "fkv_gather_kv", [&] {
         return fn(c.ctx, c.shape, k->data_ptr(), has_v ? v->data_ptr() : nullptr, i32(*idx), n.v, ko.data_ptr(),
                   has_v ? vo.data_ptr() : nullptr, c.stream);
       }))
@@ -259,7 +287,7 @@ PyObject *compress_kv(PyObject *const *a) {
     if (!output(c, item(key_x_out), kAny, 0, sizes, x->scalar_type(), xo) || xo.nbytes() < nt.sum * row_bytes) return none();
     if (!output(c, item(key_idx_tsp), kI32, nt.sum, {nt.sum}, at::kInt, it)) return none();
   }
-  if (!call([&] {
+  if (!call("fkv_compress_kv", [&] {
         return api.compress_kv(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), nb.v, ko.data_ptr(), vo.data_ptr(), i32(ik),
                                tsp ? x->data_ptr() : nullptr, row_bytes, tsp ? nt.v : nullptr, tsp ? xo.data_ptr() : nullptr,
                                tsp ? i32(it) : nullptr, c.stream);
@@ -305,7 +333,7 @@ PyObject *compress_kv_paged(PyObject *const *a) {
   const at::Tensor *q = tensor(c, a[3], kBf16, c.q_win), *k = tensor(c, a[4], kBf16, c.kv), *v = tensor(c, a[5], kBf16, c.kv);
   at::Tensor idx;
   if (!q || !k || !v || !output(c, a[10], kI32, c.hkv * n.sum, {c.hkv, n.sum}, at::kInt, idx)) return none();
-  if (!call([&] {
+  if (!call("fkv_compress_kv_paged", [&] {
         return api.compress_kv_paged(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), n.v, i32(*p.table), (int32_t)p.table->size(1),
                                      (int32_t)p.k->size(1), p.k->size(0), p.k->data_ptr(), p.v->data_ptr(), i32(idx), c.stream);
       }))
@@ -326,7 +354,9 @@ PyObject *decode_attention(PyObject *const *a) {
   const at::Tensor *q = tensor(c, a[3], kBf16, c.q_dec), *k = tensor(c, a[4], kBf16, n_cache), *v = tensor(c, a[5], kBf16, n_cache);
   at::Tensor out;
   if (!q || !k || !v || !output(c, a[8], kF32, c.q_dec, {c.n_seq, c.hq, c.d}, at::kFloat, out)) return none();
-  if (!call([&] { return api.decode_attention(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), layout, n.v, f32(out), c.stream); }))
+  if (!call("fkv_decode_attention", [&] {
+        return api.decode_attention(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), layout, n.v, f32(out), c.stream);
+      }))
     return none();
   return wrap(out);
 }
@@ -340,7 +370,7 @@ PyObject *decode_attention_paged(PyObject *const *a) {
   const at::Tensor *q = tensor(c, a[3], kBf16, c.q_dec);
   at::Tensor out;
   if (!q || !output(c, a[8], kF32, c.q_dec, {c.n_seq, c.hq, c.d}, at::kFloat, out)) return none();
-  if (!call([&] {
+  if (!call("fkv_decode_attention_paged", [&] {
         return api.decode_attention_paged(c.ctx, c.shape, q->data_ptr(), p.k->data_ptr(), p.v->data_ptr(), i32(*p.table), (int32_t)p.table->size(1),
                                           (int32_t)p.k->size(1), p.k->size(0), n.v, f32(out), c.stream);
       }))
@@ -355,7 +385,10 @@ PyObject *window_output(PyObject *const *a) {
   const at::Tensor *q = tensor(c, a[3], kBf16, c.q_win), *k = tensor(c, a[4], kBf16, c.kv), *v = tensor(c, a[5], kBf16, c.kv);
   at::Tensor out;
   if (!q || !k || !v || !output(c, a[6], kF32, c.q_win, {c.n_seq, c.shape->window, c.hq, c.d}, at::kFloat, out)) return none();
-  if (!call([&] { return api.window_output(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), f32(out), c.stream); })) return none();
+  if (!call("fkv_window_output", [&] {
+        return api.window_output(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), f32(out), c.stream);
+      }))
+    return none();
   return wrap(out);
 }
 
@@ -368,17 +401,17 @@ PyObject *score_window_output(PyObject *const *a) {
   if (!q || !k || !v || !output(c, a[6], kF32, c.hkv * c.sum_p, {c.hkv, c.sum_p}, at::kFloat, sg)) return none();
   if ((a[7] != Py_None || a[9] == Py_True) && !output(c, a[7], kF32, c.sum_p, {c.sum_p}, at::kFloat, st)) return none();
   if (!output(c, a[8], kF32, c.q_win, {c.n_seq, c.shape->window, c.hq, c.d}, at::kFloat, out)) return none();
-  if (!call([&] {
+  if (!call("fkv_score_window_output", [&] {
         return api.score_window_output(c.ctx, c.shape, q->data_ptr(), k->data_ptr(), v->data_ptr(), f32(sg), f32(st), f32(out), c.stream);
       }))
     return none();
   return Py_BuildValue("(NNN)", wrap(sg), wrap_or_none(st), wrap(out));
 }
 
-// bind(shape type, {name: address}): the library the calls go to.
+// bind(shape type, error type, {name: address}): the library the calls go to.
 PyObject *bind(PyObject *, PyObject *args) {
-  PyObject *type, *addresses;
-  if (!PyArg_ParseTuple(args, "O!O!", &PyType_Type, &type, &PyDict_Type, &addresses)) return nullptr;
+  PyObject *type, *error, *addresses;
+  if (!PyArg_ParseTuple(args, "O!O!O!", &PyType_Type, &type, &PyType_Type, &error, &PyDict_Type, &addresses)) return nullptr;
   bool ok = true;
   auto get = [&](auto &slot, const char *name) {
     PyObject *o = PyDict_GetItemString(addresses, name);
@@ -404,6 +437,8 @@ PyObject *bind(PyObject *, PyObject *args) {
     return nullptr;
   }
   Py_INCREF(type);
+  Py_INCREF(error);
+  error_type = error;
   shape_type = reinterpret_cast<PyTypeObject *>(type);
   Py_RETURN_NONE;
 }

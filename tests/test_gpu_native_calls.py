@@ -1,6 +1,8 @@
 """The wrappers' native call path against the ctypes one: numpy counts are not recognised by the native
 path, so the same call goes both ways; results must be the same, on any stream, with and without
 preallocated outputs."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -68,3 +70,28 @@ def test_native_and_ctypes_calls_agree():
     ctx.close()
     with pytest.raises(fk.FkvError):
         ctx.fkv_select_topk(shape, heads, 40)
+
+
+def test_failed_hip_call_is_raised_once():
+    """A library call that reports a failed HIP call (a stand-in here) is not made again: part of it may be enqueued."""
+    print("case: native call path, failed HIP call", flush=True)
+    ctx = fk.Context(max_total_tokens=300, max_seqs=1)
+    shape, scores = fk.make_shape(300), torch.rand((8, 292), device="cuda")
+    want = ctx.fkv_select_topk(shape, scores, 40)
+    calls, lib = [], fk.load()
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p)
+    def failing(*_):
+        calls.append(1)
+        return fk.FKV_EHIP
+
+    addresses = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in fk.EXPORTS}
+    try:
+        fk._native.bind(fk.FkvShape, fk.FkvError, dict(addresses, fkv_select_topk=ctypes.cast(failing, ctypes.c_void_p).value))
+        with pytest.raises(fk.FkvError, match="fkv_select_topk") as e:
+            ctx.fkv_select_topk(shape, scores, 40)
+        assert e.value.status == fk.FKV_EHIP and len(calls) == 1
+    finally:
+        fk._native.bind(fk.FkvShape, fk.FkvError, addresses)
+    assert torch.equal(ctx.fkv_select_topk(shape, scores, 40), want)
+    ctx.close()
