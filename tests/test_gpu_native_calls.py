@@ -1,6 +1,6 @@
-"""The wrappers' native call path against the ctypes one: numpy counts are not recognised by the native
-path, so the same call goes both ways; results must be the same, on any stream, with and without
-preallocated outputs."""
+"""The wrappers' native call path against the ctypes one: results must be the same, on any stream, with and without
+preallocated outputs, and a valid call must have gone the way it is meant to go.  Numpy counts are not recognised by
+the native path; calls without counts are refused on its behalf."""
 import ctypes
 
 import numpy as np
@@ -18,8 +18,25 @@ def _flat(o):
     return [t for t in (o if isinstance(o, tuple) else (o,)) if t is not None]
 
 
-def test_native_and_ctypes_calls_agree():
+class _Watched:
+    """The native part, with a note of what each call came back with; refuse: it recognises nothing."""
+
+    def __init__(self, native):
+        self.native, self.refuse, self.taken = native, False, []
+
+    def __getattr__(self, name):
+        def fn(*args):
+            out = None if self.refuse else getattr(self.native, name)(*args)
+            self.taken.append((name, out is not None))
+            return out
+        return fn
+
+
+def test_native_and_ctypes_calls_agree(monkeypatch):
     print("case: native call path", flush=True)
+    fk.load()
+    watch = _Watched(fk._native)
+    monkeypatch.setattr(fk, "_native", watch)
     lengths, n64 = [900, 333], lambda n: [np.int64(n)] * 2
     ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=2)
     shape = fk.make_shape(lengths)
@@ -51,9 +68,28 @@ def test_native_and_ctypes_calls_agree():
     for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
         with torch.cuda.stream(stream):
             for i, call in enumerate(calls):
-                a, b = _flat(call(40)), _flat(call(n64(40)))
+                watch.taken.clear()
+                a = _flat(call(40))
+                assert watch.taken and all(ok for _, ok in watch.taken), watch.taken
+                names = [name for name, _ in watch.taken]
+                watch.taken.clear()
+                b = _flat(call(n64(40)))
+                # the outputs that a call reuses come from a native one
+                assert [name for name, _ in watch.taken] == names and not watch.taken[-1][1], watch.taken
                 torch.cuda.synchronize()
                 assert len(a) == len(b) and all(s.dtype == t.dtype and torch.equal(s, t) for s, t in zip(a, b)), i
+    for i, call in enumerate((lambda: ctx.fkv_score_window(shape, q, k), lambda: ctx.fkv_score_window(shape, q, k, want_tsp=False),
+                              lambda: ctx.fkv_score_heads(shape, q, k), lambda: ctx.fkv_window_output(shape, q, k, v),
+                              lambda: ctx.fkv_score_window_output(shape, q, k, v),
+                              lambda: ctx.fkv_score_window_output(shape, q, k, v, want_tsp=False),
+                              lambda: ctx.fkv_score_window(shape, q, k, *(torch.empty_like(t) for t in ctx.fkv_score_window(shape, q, k))))):
+        watch.taken.clear()
+        a = _flat(call())
+        assert watch.taken and all(ok for _, ok in watch.taken), watch.taken
+        watch.refuse = True
+        b = _flat(call())
+        watch.refuse = False
+        assert len(a) == len(b) and all(s.dtype == t.dtype and torch.equal(s, t) for s, t in zip(a, b)), i
     sg, none = ctx.fkv_score_window(shape, q, k, want_tsp=False)
     sg2, st2 = ctx.fkv_score_window(shape, q, k)
     assert none is None and torch.equal(sg, sg2) and st2.shape == (1233 - 16,)
