@@ -383,7 +383,11 @@ __device__ __forceinline__ SelectRow locate_row(const SelectArgs &a) {
   return r;
 }
 
-// Rows of at most 1024 kKpt - 3 keys; longer ones of the call are left to another launch.
+// Rows of at most 1024 kKpt - 3 keys; longer ones of the call are left to another launch.  kKpt follows the longest row:
+// rows much shorter than that take fewer keys per thread, since empty slots cost what full ones do and a batch of many
+// short rows is several rounds of blocks (24000 and 62 times 1500 keys, 9 rows each: 27.0 -> 16.1 us per call).
+constexpr int kShortKpt = 8;
+
 template <int kKpt>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   __shared__ __attribute__((aligned(16))) SelectLds<kKpt> lds;
@@ -394,7 +398,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
     return;
   }
   if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;  // window tokens are always kept
-  if (r.kp > 0) select_resident<kKpt>(r.sc, r.P, r.kp, r.out, lds);
+  if (r.kp <= 0) return;
+  if constexpr (kKpt > kShortKpt) {
+    static_assert(sizeof(SelectLds<kShortKpt>) <= sizeof lds, "the short row's tables lie where the long one's would");
+    if (r.P + 3 <= kSelThreads * kShortKpt) {
+      select_resident<kShortKpt>(r.sc, r.P, r.kp, r.out, reinterpret_cast<SelectLds<kShortKpt> &>(lds));
+      return;
+    }
+  }
+  select_resident<kKpt>(r.sc, r.P, r.kp, r.out, lds);
 }
 
 // Longer rows on one block each, re-read from the caches pass by pass: only for calls with more such rows than the

@@ -28,3 +28,25 @@ def test_select_row_edges(P, path):
             np.testing.assert_array_equal(idx[r], oracle.select_topk(rows[r], W, k), err_msg="row %d k %d" % (r, k))
     assert ctx.fkv_query_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("lengths", [[24000, 1500, 8189, 8190, 9, 40], [16000] + [700, 4093, 4094] * 4, [30000, 300, 12000, 8, 5000], [8189, 8190, 1]])
+def test_select_mixed_lengths(lengths):
+    """Rows that take fewer keys per thread than the longest one of their launch."""
+    print("case: select mixed lengths %s.. (%d)" % (lengths[:4], len(lengths)), flush=True)
+    total = sum(lengths) + W * len(lengths)
+    ctx = fk.Context(max_total_tokens=total, max_seqs=len(lengths))
+    ctx.fkv_set_select_path(1)
+    shape = fk.make_shape([P + W for P in lengths])
+    rows = wl.random_scores(91, 3, sum(lengths))
+    rows[1] = np.round(rows[1] * 64) / 64
+    for counts in ([W + P // 9 for P in lengths], [W + P for P in lengths]):
+        idx = ctx.fkv_select_topk(shape, torch.from_numpy(rows).cuda(), counts).cpu().numpy()
+        for r in range(3):
+            at = out = 0
+            for P, k in zip(lengths, counts):
+                np.testing.assert_array_equal(idx[r, out:out + k], oracle.select_topk(rows[r, at:at + P], W, k), err_msg="row %d P %d" % (r, P))
+                at += P
+                out += k
+    assert ctx.fkv_query_error() == 0
+    ctx.close()
