@@ -83,6 +83,10 @@ __device__ __forceinline__ void read_k_tile(u32x4 (&r)[8], const uint32_t (&addr
       : "memory");
 }
 
+// The sum a row is divided by.  Zero: no token has a finite logit and the softmax no value; NaN then, and not what the
+// kept-up pieces of the probabilities (see k_decode) divided by zero would give.
+__device__ __forceinline__ float row_sum(float l) { return l > 0.f ? l : __uint_as_float(0x7FC00000u); }
+
 __device__ __forceinline__ void agent_store2(float *p, float x, float y) {
   const float2 v = make_float2(x, y);
   unsigned long long bits;
@@ -242,7 +246,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         z[i] = acc[i >> 2][i & 3] * a.scale_log2e;
-        if (edge && tile * kDecTile + 4 * i + q >= n) z[i] = kDecNegBig;
+        if (edge && tile * kDecTile + 4 * i + q >= n) z[i] = -INFINITY;  // weight 0 below whatever the maximum: it is at least kDecNegBig
         tmax = fmaxf(tmax, z[i]);
       }
       tmax = quad_max(tmax);
@@ -326,7 +330,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         y += f * ov.y;
       }
       if (whole) {
-        *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x / L, y / L);
+        const float sum = row_sum(L);
+        *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x / sum, y / sum);
       } else {
         agent_store2(part + h * kHeadDim + d, x, y);
         if (d == 0) agent_store2(part + kMaxReal * kHeadDim + 2 * h, M, L);
@@ -359,7 +364,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         const float2 ml = agent_load2(piece(min(lane, n_split - 1)) + kMaxReal * kHeadDim + 2 * hw);
         const float mp = lane < n_split ? ml.x : kDecNegBig;
         const float f = dec_exp2(mp - wave_fmax(mp));
-        const float L = wave_fsum(lane < n_split ? ml.y * f : 0.f);
+        const float L = row_sum(wave_fsum(lane < n_split ? ml.y * f : 0.f));
         w_lds[hw][lane] = lane < n_split ? f / L : 0.f;
       }
       __syncthreads();

@@ -70,6 +70,23 @@ def test_decode_infinite_v(ctx, ns, Hkv, paged):
     assert torch.equal(out.view(B, Hkv, 4, d), want)
 
 
+@pytest.mark.parametrize("ns,Hkv", [([64], 8), ([4096], 8), ([9000], 1), ([2048] * 32, 8)])
+def test_decode_without_a_finite_logit(ctx, ns, Hkv):
+    """Heads whose logits are all -inf have no softmax: NaN, as 0 / 0 gives, and nothing else changes."""
+    print("case: decode without a finite logit n=%s.. (%d) Hkv=%d" % (ns[:4], len(ns), Hkv), flush=True)
+    B, d, tot = len(ns), 128, sum(ns)
+    q = dev_bf16(wl.normal_bf16(73, 0, "q_win", (B, Hkv * 4, d))).view(torch.bfloat16)
+    k, v = (dev_bf16(wl.normal_bf16(73, 0, n, (tot, Hkv, d))).view(torch.bfloat16) for n in ("k", "v"))
+    shape = fk.make_shape(ns, n_q_heads=Hkv * 4, n_kv_heads=Hkv)
+    q[..., 0] = -1
+    want = ctx.fkv_decode_attention(shape, q, k, v, ns, "token_major").view(B, Hkv, 4, d).clone()
+    k[:ns[0], 0, 0] = float("inf")
+    out = ctx.fkv_decode_attention(shape, q, k, v, ns, "token_major").view(B, Hkv, 4, d)
+    assert torch.isnan(out[0, 0]).all()
+    want[0, 0] = out[0, 0] = 0
+    assert torch.equal(out, want)
+
+
 class _Layout(ctypes.Structure):  # WsLayout of csrc/fkv_api.hip
     _fields_ = [(n, ctypes.c_size_t) for n in ("partial", "rowstat", "scores_group", "scores_tsp", "counters", "fused_part", "fused_lse",
                                                "sel_long", "sel_coop", "dec_part", "dec_count", "wout_o", "wout_ms", "total")] + [("max_stat_blocks", ctypes.c_int)]
