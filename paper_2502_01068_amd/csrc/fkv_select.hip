@@ -201,6 +201,7 @@ struct SelectLds {
   uint32_t list[kListCap];                 // keys of the threshold's interval, relative to its smallest,
   uint32_t list_wave[kListCap];            // and the waves that hold them
   uint32_t tot[kSelWaves], cnt[kSelWaves]; // wave totals: histogram scan, keys kept for sure
+  uint32_t low[kSelWaves];                 // smallest keys of an interval (the largest ones go to tot)
   uint32_t kmax, not_kmin, n_list, pick[3];
   int32_t stage[kSelWaves][64 * kKpt + 64];  // kept indices of each wave, then a word per lane for dropped ones
 };
@@ -358,6 +359,28 @@ __device__ __forceinline__ void select_resident(const float *sc, int P, int kp, 
     span = min((1u << shift) - 1u, span - 1u - at);
     remaining = uniform(s.pick[1]);
     n_in = uniform(s.pick[2]);
+    if (n_in > (uint32_t)kListCap && n_in != remaining) {
+      // Too many for the list: ties, as a rule.  The interval shrinks to the keys it holds, so equal ones are seen as
+      // such and do not queue up at one bin in another pass (9 rows of 20000 keys, two values: 36 -> 19 us).
+      uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+#pragma unroll
+      for (int e = 0; e < kKpt; ++e) {
+        const bool in = key[e] - base <= span;
+        kmax = max(kmax, in ? key[e] : 0u);
+        kmin = min(kmin, in ? key[e] : 0xFFFFFFFFu);
+      }
+      kmax = wave_max_to_last(kmax);
+      kmin = wave_min_to_last(kmin);
+      if (lane == 63) {
+        s.tot[wave] = kmax;
+        s.low[wave] = kmin;
+      }
+      __syncthreads();
+      kmax = wave_max_to_last(s.tot[lane & (kSelWaves - 1)]);
+      kmin = wave_min_to_last(s.low[lane & (kSelWaves - 1)]);
+      base = wave_last(kmin);
+      span = wave_last(kmax) - base;
+    }
   }
 
   compact_wave<kKpt>(key, T, need_eq, before_gt, before_eq, wave, -mis, out, s.stage[wave]);

@@ -30,6 +30,25 @@ def test_select_row_edges(P, path):
     ctx.close()
 
 
+@pytest.mark.parametrize("P", [300, 4093, 16381, 24573, 32765])
+@pytest.mark.parametrize("values", [2, 3, 20])
+def test_select_few_distinct_values(P, values):
+    """More equal keys in the threshold's bin than the list holds: the interval shrinks to the values it holds."""
+    print("case: select P=%d, %d distinct values" % (P, values), flush=True)
+    ctx = fk.Context(max_total_tokens=P + W, max_seqs=1)
+    ctx.fkv_set_select_path(1)
+    gen = np.random.default_rng(P + values)
+    rows = np.stack([gen.uniform(-1, 1, values).astype(np.float32)[gen.integers(0, values, P)],
+                     (1 + gen.integers(0, values, P) * 2.0 ** -23).astype(np.float32)])  # neighbouring floats
+    rows[0, P // 2] = 1e30  # one key far away: the others share a bin of the first pass
+    for k in sorted({W + 1, W + P // 10, W + P // 2, W + P - P // 10, W + P - 1}):
+        idx = ctx.fkv_select_topk(fk.make_shape(P + W), torch.from_numpy(rows).cuda(), k).cpu().numpy()
+        for r in range(len(rows)):
+            np.testing.assert_array_equal(idx[r], oracle.select_topk(rows[r], W, k), err_msg="row %d k %d" % (r, k))
+    assert ctx.fkv_query_error() == 0
+    ctx.close()
+
+
 @pytest.mark.parametrize("lengths", [[24000, 1500, 8189, 8190, 9, 40], [16000] + [700, 4093, 4094] * 4, [30000, 300, 12000, 8, 5000], [8189, 8190, 1]])
 def test_select_mixed_lengths(lengths):
     """Rows that take fewer keys per thread than the longest one of their launch."""
