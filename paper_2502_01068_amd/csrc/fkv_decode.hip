@@ -16,9 +16,10 @@
 //                column chunk c (8 values) of those same 8 tokens into registers, whole rows per
 //                instruction; the 8x8 block is transposed inside the lane (32 byte permutes), so operand j
 //                holds d = 8 c + j.
-// Probabilities enter as three bf16 pieces that add up to the fp32 value.  A wave keeps one tile of 32
-// tokens (16 KiB of K and V) in flight while it works on the one before it; one block of 4 waves per CU is
-// enough for that (more resident waves were slower: 256 / 512 / 1024 blocks took 57 / 61 / 68 us for 304 MB).
+// Probabilities enter as three bf16 pieces that add up to the fp32 value.  A wave requests its next tile of 32
+// tokens (16 KiB of K and V) while it works on the present one, as registers and LDS become free (what is waited for
+// when: see step); one block of 4 waves per CU is enough (more resident waves were slower: 256 / 512 / 1024 blocks
+// took 57 / 61 / 68 us for 304 MB).
 //
 // A row (KV head of a sequence) is one block's work, or is cut into equal pieces, one per block; or the tiles of
 // all rows form one line that is cut into equal shares (see launch_decode).  Rows in pieces are folded by the last
@@ -27,7 +28,7 @@
 // pieces of a block were each no faster.
 //
 // Measured (device time per call, before -> after): 218 tokens, 1 sequence 10.2 -> 5.2 us; 2048 tokens 11.0 -> 7.8;
-// 32768 tokens 35.5 -> 26.0 (5.2 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 50.5 us (6.0 TB/s).
+// 32768 tokens 35.5 -> 26.0 (5.2 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 51.6 us (5.9 TB/s).
 #include <algorithm>
 #include <type_traits>
 
@@ -65,7 +66,7 @@ __device__ __forceinline__ float quad_sum(float x) {
 
 // The K tile's operands: waits until at most the 8 youngest loads (the V tile's) are outstanding, reads and waits for
 // the reads, so that the tile may be overwritten.  One asm block: for an ordinary LDS read the compiler would
-// wait for every outstanding load, the V tile's too.
+// wait for every outstanding load, the V tile's too (paged, it does so already, see step).
 __device__ __forceinline__ void read_k_tile(u32x4 (&r)[8], const uint32_t (&addr)[4]) {
   asm volatile(
       "s_waitcnt vmcnt(8)\n\t"
@@ -220,7 +221,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       load_v(t, slot);
     }
     // One tile; kMore: the loads of the wave's next one go out as their registers and LDS become free (a
-    // compile-time flag, so that the waits count exactly what is in flight).
+    // compile-time flag: no branch around loads).  The compiler's own waits are longer than need be.  Ordinary loads
+    // behind LDS-direct ones are waited for together with everything requested: the V tile with the next K tile,
+    // requested a contraction earlier; a paged cache's page entry, before the K tile is read, with the V tile; the first tile
+    // of a piece, unpaged, sends half of its K loads and all of V after q has come.  Exact waits inside the loop (V through
+    // LDS-direct loads, read in asm blocks like K) were no faster: 2048 tokens 7.77 against 7.65 us, 32 paged sequences 52.5
+    // against 51.6.
     auto step = [&](auto more_t) {
       constexpr bool kMore = decltype(more_t)::value;
       u32x4 kr[8];

@@ -19,10 +19,11 @@
 //   phase 3  probabilities from the kept logits, window sum, LDS pooling, head means, write
 //
 // Per launch, before -> after the grouped exchange, the scattered row sums and the barriers that leave stores
-// in flight: 2048 tokens 15.0 -> 13.4 us, 6554 18.0 -> 16.4, 12289 20.5 -> 17.9, 32768 28.4 -> 25.0.
+// in flight: 2048 tokens 15.0 -> 13.4 us, 6554 18.0 -> 16.4, 12289 20.5 -> 17.9, 32768 28.4 -> 25.0 (the row sums' former
+// order, put back since, costs 0.1 us; in the kernel trace they are 14.6, 17.4, 18.0 and 25.4 us).
 //
-// Used when the batch fits the resident grid (about 64K tokens on 256 CUs); longer inputs take
-// the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
+// Used when the batch fits the resident grid (about 61K tokens on 256 CUs); longer inputs take
+// the kernel of fkv_score_keep.hip or the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
 // for within the time limit raises the context's error flag, and its block writes NaN scores.
 #include "fkv_score_exchange.h"
 
@@ -35,8 +36,9 @@ constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 int fused_slots(void) { return kFusedSlotsMax; }
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more
 // sub-tile per block (fewer, longer blocks): the exchange gets slower with the number of blocks.
-// Swept over 2048 .. 49152 tokens (e.g. 6554 tokens: 64 blocks 21.1 us, 113 blocks 18.0, 160 blocks
-// 18.6, 256 blocks 18.4; 32768 tokens: 213 blocks 28.3, 256 blocks 28.7).
+// Swept over 2048 .. 49152 tokens with the former exchange of one owner wave per row (e.g. 6554 tokens: 64 blocks 21.1
+// us, 113 blocks 18.0, 160 blocks 18.6, 256 blocks 18.4; 32768 tokens: 213 blocks 28.3, 256 blocks 28.7).  The kernel of
+// fkv_score_keep.hip follows it too and takes every block for more sub-tiles than this one holds.
 int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : n_sub * kSub <= kFusedSlotsMax ? 224 : kMaxFusedBlocks; }
 
 template <int kFusedSub>

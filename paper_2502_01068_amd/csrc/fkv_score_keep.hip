@@ -10,10 +10,11 @@
 //
 // Against the two-pass kernels (fkv_score.hip), which read K twice and need three launches, K's second read shrinks
 // by the kept part and a launch boundary (the statistics' way through memory and back) becomes the exchange:
-// 131072 tokens (17 tiles per block, 10 kept) 102 -> 76 us, 8 sequences of 8192-16384 tokens 87 -> 58 us.  With more than
-// 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and keeps 3 tiles of each:
-// 64 / 8 heads at 20001 tokens 39 -> 25 us.
-// A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not.
+// 131072 tokens (17 tiles per block, 10 kept) 97.6 -> 68.6 us in the kernel trace, 8 sequences of 8192-16384 tokens 82.4 ->
+// 55.6 us.  With more than 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and
+// keeps 3 tiles of each: 64 / 8 heads at 20001 tokens 40.0 -> 28.2 us.
+// A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not; the
+// normaliser is added up over other block shares in another order, so the scores are theirs up to its last bits.
 #include <type_traits>
 
 #include "fkv_score_exchange.h"
