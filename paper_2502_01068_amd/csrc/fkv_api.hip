@@ -366,6 +366,9 @@ void fill_score_args(ScoreArgs &a, const ScoreWs &w, const fkv_shape *sh, const 
   a.causal = sh->causal;
   a.pool_r = sh->pool_kernel / 2;
   a.pool_mode = sh->pool_mode;
+  a.inv_k = 1.0f / (float)(2 * a.pool_r + 1);
+  a.inv_g = 1.0f / (float)r.G;
+  a.inv_h = 1.0f / (float)r.Hq;
   a.sum_p = r.sum_p;
   fill_map(r, &a.map);
 }

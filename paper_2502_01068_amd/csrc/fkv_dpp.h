@@ -70,16 +70,42 @@ __device__ __forceinline__ float dpp_f32(float old, float src) {
 // flight needs it where the order of those loads matters and they do not depend on each other.
 __device__ __forceinline__ void keep_access_order() { asm volatile("" ::: "memory"); }
 
-// Maximum over the 32 lanes of each wave half (lanes 0-31 and 32-63 separately), in every lane: rotations inside the
-// 16-lane DPP rows, then one swap of the odd and even rows.
-__device__ __forceinline__ float half_max(float x) {
-  x = fmaxf(x, dpp_f32<kDppRowRor + 8>(x, x));
-  x = fmaxf(x, dpp_f32<kDppRowRor + 4>(x, x));
-  x = fmaxf(x, dpp_f32<kDppRowRor + 2>(x, x));
-  x = fmaxf(x, dpp_f32<kDppRowRor + 1>(x, x));
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// Lane i reads lane (i - kN) mod 16 of its row.  Every lane has a source, so the routing can become part of the
+// instruction that uses it.
+template <int kN>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kDppRowRor + kN, 0xF, 0xF, true));
+}
+
+// out[q]: maximum of x[q] over the 32 lanes of each wave half (lanes 0-31 and 32-63 separately), in every lane.  A swap of
+// odd and even rows lets two registers share one from the first step on; then rotations inside the rows, 8 registers side
+// by side.  In asm: in front of a maximum the compiler quietens each operand anew (16 maxima in 100 instructions, not 450).
+// The leading and trailing waits are what lane routing needs next to other vector instructions.
+__device__ __forceinline__ void half_max16(const float (&x)[16], float (&out)[16]) {
+  float m[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[2 * k]), __float_as_uint(x[2 * k + 1]), false, false);
+    asm("v_max_f32 %0, %1, %2" : "=v"(m[k]) : "v"(r[0]), "v"(r[1]));
+  }
+#define FKV_ROW_MAX(n)                                                    \
+  "v_max_f32_dpp %0, %0, %0 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %1, %1, %1 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %2, %2, %2 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %3, %3, %3 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %4, %4, %4 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %5, %5, %5 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %6, %6, %6 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_max_f32_dpp %7, %7, %7 row_ror:" n " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" FKV_ROW_MAX("8") FKV_ROW_MAX("4") FKV_ROW_MAX("2") FKV_ROW_MAX("1") "s_nop 1"
+      : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "+v"(m[4]), "+v"(m[5]), "+v"(m[6]), "+v"(m[7]));
+#undef FKV_ROW_MAX
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m[k]), __float_as_uint(m[k]), false, false);
+    out[2 * k] = __uint_as_float(r[0]);
+    out[2 * k + 1] = __uint_as_float(r[1]);
+  }
 }
 
 // One of two registers by a lane bit.  (Written as a choice between two elements of an array the compiler makes it a
@@ -106,15 +132,15 @@ __device__ __forceinline__ float half_sums_of_products(const float (&x)[16], con
   float s[16], c[4];
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
-    s[q] = __builtin_fmaf(x[q], y[q], dpp_f32<kDppRowRor + 8>(0.f, x[q] * y[q]));
-    s[q] += dpp_f32<kDppRowRor + 4>(0.f, s[q]);
+    s[q] = __builtin_fmaf(x[q], y[q], row_ror<8>(x[q] * y[q]));
+    s[q] += row_ror<4>(s[q]);
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int at = lane + 3 - k;  // bits 2 and 3: which of sums k, k + 4, k + 8, k + 12 this lane belongs to
     c[k] = lane_pick((at & 8) != 0, lane_pick((at & 4) != 0, s[k], s[k + 4]), lane_pick((at & 4) != 0, s[k + 8], s[k + 12]));
-    c[k] += dpp_f32<kDppRowRor + 2>(0.f, c[k]);
-    c[k] += dpp_f32<kDppRowRor + 1>(0.f, c[k]);
+    c[k] += row_ror<2>(c[k]);
+    c[k] += row_ror<1>(c[k]);
   }
   const unsigned u = __float_as_uint(lane_pick((lane & 2) != 0, lane_pick((lane & 1) != 0, c[0], c[1]), lane_pick((lane & 1) != 0, c[2], c[3])));
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);

@@ -84,6 +84,7 @@ struct ScoreArgs {
   int causal;
   int pool_r;             // pooling radius (kernel = 2r+1)
   int pool_mode;          // FKV_POOL_AVG / FKV_POOL_MAX
+  float inv_k, inv_g, inv_h;  // 1 / pooling kernel, 1 / heads per group, 1 / heads
   int chunk;              // tokens per block in the stats launch
   int tile_own;           // tokens each block of the scores launch owns
   int tile_sub;           // 32-token sub-tiles that hold them and the pooling halo

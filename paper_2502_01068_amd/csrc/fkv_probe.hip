@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void k_probe_logits(ScoreArgs a, uint32_t
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ __attribute__((aligned(16))) uint16_t q_lds[kMfma ? 1 : kWaves][kMfma ? 8 : kRowsPerGroup * kHeadDim];
   __shared__ uint32_t keys_lds[kWaves][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int Lb = a.map.cu[1];
   const int t0 = blockIdx.x * tokens_per_block, t1 = min(Lb, t0 + tokens_per_block);

@@ -29,7 +29,7 @@ int scores_sub_wide(void) { return kScoresSubWide; }
 template <int kVg>
 __global__ __launch_bounds__(kThreads) void k_stats(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
   const int tok_base = a.map.cu[b];
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a) {
   __shared__ float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
   __shared__ float g_sum[kGroups][kSlots];               // per virtual group sums of pooled head scores
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
   const int tok_base = a.map.cu[b];

@@ -1,6 +1,7 @@
 // Device helpers shared by the score kernels: MFMA operand loads and the K streaming loop.
 #pragma once
 
+#include "fkv_dpp.h"
 #include "fkv_internal.h"
 
 namespace fkv {
@@ -32,22 +33,26 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// `bytes` bytes from p on as a raw buffer: a lane's access past them reads zeros and touches no memory, so ranges need
+// neither clamps nor branches, and addresses are 32-bit offsets.  p is the same in every lane.
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t buffer_of(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+
 // MFMA A operand for virtual group g: lane (m = lane%32, hi = lane/32) holds, for step s, the 8
-// values d = hi*64 + s*8 .. +7 of query row m (head vg_head0(g) + m/8, window row m%8).  The
-// contraction index may be permuted freely as long as K uses the same permutation.
+// values d = hi*64 + s*8 .. +7 of query row m (head vg_head0(g) + m/8, window row m%8), zeros for rows that the shape
+// does not have.  The contraction index may be permuted freely as long as K uses the same permutation.  g is uniform.
 template <typename A>
 __device__ __forceinline__ void load_q(const A &a, int b, int g, int lane, bf16x8 (&qa)[8]) {
   const int m = lane & 31, hi = lane >> 5;
   const int hl = m >> 3, w = m & 7;
+  const uint32_t seq_bytes = (uint32_t)(a.W * a.Hq) * (kHeadDim * 2);
+  const buffer_t q = buffer_of(a.q_win + (size_t)b * a.W * a.Hq * kHeadDim, seq_bytes);
   const bool ok = hl < vg_heads(a, g) && w < a.W;
-  const u32x4 *src = reinterpret_cast<const u32x4 *>(
-      a.q_win + (((size_t)b * a.W + (ok ? w : 0)) * a.Hq + (size_t)vg_head0(a, g) + (ok ? hl : 0)) * kHeadDim + hi * 64);
+  const uint32_t at = ok ? (uint32_t)((w * a.Hq + vg_head0(a, g) + hl) * (kHeadDim * 2) + hi * 128) : seq_bytes;
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    u32x4 v = src[s];
-    if (!ok) v = (u32x4){0u, 0u, 0u, 0u};
-    qa[s] = __builtin_bit_cast(bf16x8, v);
-  }
+  for (int s = 0; s < 8; ++s) qa[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(q, (int)at, s * 16, 0));
 }
 
 // Streams the K rows of virtual group g's KV head for `n_slots` consecutive tokens, in 32-token sub-tiles, starting at
@@ -106,54 +111,87 @@ __device__ __forceinline__ void stream_head(const ScoreArgs &a, const bf16x8 (&q
   }
 }
 
-// The same stream with the sub-tiles loaded straight from global memory into the wave's LDS tile
-// (gfx950's 128-bit LDS-direct loads: lane l of a load instruction lands at tile offset 16 l), so no
-// registers hold a tile while the previous one is being consumed.  The XOR swizzle moves to the global
-// side: the lane that owns LDS column c' of token slot t fetches the row's column c' ^ (t & 15).
-// Per sub-tile: wait for its loads, run the MFMAs off the tile, start the next sub-tile's loads into
-// the same (now free) tile, run fn while they are in flight.
-// Only the first n_slots token slots (counted from `first`) are loaded: the rest of the last sub-tile
-// keeps whatever the LDS tile held, and the caller ignores those tokens' logits (they may be anything,
-// NaN included; a token is one MFMA column, so nothing spreads to other tokens).
-template <typename F>
-__device__ __forceinline__ void stream_head_direct(const ScoreArgs &a, const bf16x8 (&qa)[8], int tok_base, int Lb,
-                                                   int g, int first, int n_slots, uint8_t *stage, int lane, F fn) {
-  const int n_sub = (n_slots + kSub - 1) / kSub;
-  const int c = lane & 15;        // LDS column of this lane within a token slot
-  const int tq = lane >> 4;       // token within the quad of 4 tokens one load instruction covers
-  const int n = lane & 31, hi = lane >> 5;
-  const uint16_t *kbase = a.k + (size_t)vg_kv_head(a, g) * kHeadDim;
-  const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
-  typedef __attribute__((address_space(1))) const void *gptr_t;
-  typedef __attribute__((address_space(3))) void *lptr_t;
+// K rows of a wave's KV head, tokens `first` to `end` of a sequence, as 32-token tiles that go straight from global memory
+// into the wave's LDS tile (gfx950's 128-bit LDS-direct loads: lane l of a load lands at tile offset 16 l, i.e. 4 tokens
+// per load, 16 lanes a row), so no registers hold a tile in flight.  The XOR swizzle lies on the global side: the lane
+// that owns LDS column c of token slot t fetches the row's column c ^ (t & 15).  Slots whose token lies outside [0, end)
+// are not loaded; the caller ignores their logits.  What used to bound the resident score kernels at short inputs were the
+// instructions around these loads (64-bit address products, clamps and a branch per load): the first tile's requests left
+// 2.3 us after a wave's start and the next tile's 0.8 us after its operands were read.
+struct KTiles {
+  buffer_t rows;
+  uint32_t at[4];       // byte offsets of this lane's part of token slots tq, 4 + tq, 8 + tq and 12 + tq of tile 0
+  uint32_t half_bytes;  // 16 tokens
+  uint8_t *stage;
 
-  auto issue = [&](int st) {
+  template <typename A>
+  __device__ __forceinline__ KTiles(const A &a, int tok_base, int kv_head, int first, int end, uint8_t *stage_, int lane)
+      : stage(stage_) {
+    const uint32_t row = (uint32_t)a.Hkv * (kHeadDim * 2);  // the host bounds a sequence by 2^31 bytes of K on these paths
+    rows = buffer_of(a.k + ((size_t)tok_base * a.Hkv + kv_head) * kHeadDim, (uint32_t)(end - 1) * row + kHeadDim * 2);
+    half_bytes = 16 * row;
+    const int c = lane & 15, tq = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (st * kSub + i * 4 >= n_slots) break;  // wave-uniform: this instruction's 4 tokens are all beyond the range
+    for (int i = 0; i < 4; ++i) {
       const int slot = i * 4 + tq;
-      int t = first + st * kSub + slot;
-      t = min(max(t, 0), Lb - 1);
-      const uint16_t *src = kbase + (size_t)(tok_base + t) * tok_stride + ((c ^ (slot & 15)) << 3);
-      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stage + i * 1024), 16, 0, 0);
+      at[i] = (uint32_t)(first + slot) * row + ((c ^ slot) << 4);  // a token before the sequence wraps past the buffer's end
     }
-  };
-  issue(0);
-#pragma unroll 1
-  for (int st = 0; st < n_sub; ++st) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed in LDS
-    wave_lds_sync();
-    floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const u32x4 kb = *reinterpret_cast<const u32x4 *>(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s], __builtin_bit_cast(bf16x8, kb), acc, 0, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): every lane's operands have left the tile
-    wave_lds_sync();
-    if (st + 1 < n_sub) issue(st + 1);   // in flight while fn runs
-    fn(st, acc);
   }
+  template <int kAux>
+  __device__ __forceinline__ void issue(int st) const {
+    typedef __attribute__((address_space(3))) void *lptr_t;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lptr_t)(stage + i * 1024), 16, (int)(at[i & 3] + (2 * st + (i >> 2)) * half_bytes), 0, 0, kAux);
+  }
+};
+
+// LDS addresses of the 8 operands that lane (token n, half hi) reads of such a tile.
+__device__ __forceinline__ void operand_addresses(const uint8_t *stage, int lane, uint32_t (&addr)[8]) {
+  typedef __attribute__((address_space(3))) const void *lptr_t;
+  const int n = lane & 31, hi = lane >> 5;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) addr[s] = (uint32_t)(uintptr_t)(lptr_t)(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
+}
+
+// The operands of a tile whose loads have been waited for; they have left the tile when this returns, so it can be
+// requested anew before the contraction.  An asm block: ahead of an ordinary LDS read the compiler waits for every outstanding
+// LDS-direct load (window output, 32768 tokens 33.0 -> 31.8 us per call, 22 sequences of 1600 104 -> 101).
+template <int kN>
+__device__ __forceinline__ void read_operands(u32x4 (&r)[kN], const uint32_t *addr) {
+  static_assert(kN == 8 || kN == 4, "");
+  if constexpr (kN == 8)
+    asm volatile(
+        "ds_read_b128 %0, %8\n\t"
+        "ds_read_b128 %1, %9\n\t"
+        "ds_read_b128 %2, %10\n\t"
+        "ds_read_b128 %3, %11\n\t"
+        "ds_read_b128 %4, %12\n\t"
+        "ds_read_b128 %5, %13\n\t"
+        "ds_read_b128 %6, %14\n\t"
+        "ds_read_b128 %7, %15\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+        : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]), "v"(addr[5]), "v"(addr[6]), "v"(addr[7])
+        : "memory");
+  else
+    asm volatile(
+        "ds_read_b128 %0, %4\n\t"
+        "ds_read_b128 %1, %5\n\t"
+        "ds_read_b128 %2, %6\n\t"
+        "ds_read_b128 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+        : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
+        : "memory");
+}
+
+// One element of the running (max, sum) of a softmax row: `one` is 1 if the logit is counted, else 0.  One exponential.
+__device__ __forceinline__ void count_logit(float z, float one, float &mx, float &sm) {
+  const float d = z - mx;
+  const float e = fast_exp2(-fabsf(d));
+  sm = d > 0.f ? __builtin_fmaf(sm, e, one) : __builtin_fmaf(one, e, sm);
+  mx = d > 0.f ? z : mx;
 }
 
 // Block barrier that orders LDS accesses only.  __syncthreads also waits for the acknowledgement of every
@@ -203,10 +241,68 @@ __device__ __forceinline__ float add_across_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Merges two (max, sum) pairs of the same softmax row (log2 domain).
-__device__ __forceinline__ float2 merge_stats(float2 x, float2 y) {
-  const float mn = fmaxf(x.x, y.x);
-  return make_float2(mn, x.y * fast_exp2(x.x - mn) + y.y * fast_exp2(y.x - mn));
+// The window sums of a token for the 4 heads of virtual group g, which both wave halves hold, into s_head[4 g + i][slot]: each
+// half stores two of them.  A token that is not scored counts as 0 (see pool_and_write).
+template <int kStride>
+__device__ __forceinline__ void store_sums(const ScoreArgs &a, float (*s_head)[kStride], int g, int slot, int hi, bool scored,
+                                           const float (&sum)[4]) {
+  const int heads = vg_heads(a, g);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const float x = lane_pick(hi != 0, sum[2 * j], sum[2 * j + 1]);
+    if (2 * j + hi < heads) s_head[g * kMaxGroup + 2 * j + hi][slot] = scored ? x : 0.f;
+  }
+}
+
+// max(x, y, z) without the quietening of every operand that fmaxf on values from memory costs.
+__device__ __forceinline__ float max3(float x, float y, float z) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+  return r;
+}
+
+// Pooling kernel 7 (the paper's) for the owned tokens of one virtual group, two neighbouring tokens per lane, whose 8 taps
+// are four 8-byte LDS reads per head (the first tap of owned token jj is slot jj).  See pool_and_write.
+template <int kStride, bool kMax>
+__device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*s_head)[kStride], float (*g_sum)[kStride], int g,
+                                            int own, size_t col, int lane) {
+#pragma clang fp contract(off)  // a pooled value is rounded before it enters a mean
+  typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+  const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
+#pragma unroll 1
+  for (int jj = 2 * lane; jj < own; jj += 128) {
+    float p[kMaxGroup][2];
+#pragma unroll
+    for (int hl = 0; hl < kMaxGroup; ++hl) {
+      const float2 *row = reinterpret_cast<const float2 *>(s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + jj);
+      const float2 v01 = row[0], v23 = row[1], v45 = row[2], v67 = row[3];
+      const float v[8] = {v01.x, v01.y, v23.x, v23.y, v45.x, v45.y, v67.x, v67.y};
+      if constexpr (kMax) {
+        const float mid = max3(v[1], v[2], max3(v[3], v[4], max3(v[5], v[6], v[6])));  // the taps both tokens have
+        p[hl][0] = max3(mid, v[0], v[0]);
+        p[hl][1] = max3(mid, v[7], v[7]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          p[hl][i] = ((((((v[i] + v[i + 1]) + v[i + 2]) + v[i + 3]) + v[i + 4]) + v[i + 5]) + v[i + 6]) * a.inv_k;
+      }
+    }
+    const bool both = jj + 1 < own;
+    auto put = [&](float *dst, float x, float y) {
+      if (both) *reinterpret_cast<f32x2u *>(dst) = f32x2u{x, y};
+      else *dst = x;
+    };
+    float gs[2] = {0.f, 0.f};
+#pragma unroll
+    for (int hl = 0; hl < kMaxGroup; ++hl)
+      if (hl < n_h) {
+        if (a.scores_head) put(a.scores_head + (size_t)(h0 + hl) * a.sum_p + col + jj, p[hl][0], p[hl][1]);
+        gs[0] += p[hl][0];
+        gs[1] += p[hl][1];
+      }
+    *reinterpret_cast<float2 *>(&g_sum[g][jj]) = make_float2(gs[0], gs[1]);  // past the last owned token: not read
+    if (a.scores_group && a.vsh == 0) put(a.scores_group + (size_t)g * a.sum_p + col + jj, gs[0] * a.inv_g, gs[1] * a.inv_g);
+  }
 }
 
 // Pools the per-head window sums along tokens (Eq. 1), averages the heads of each KV group
@@ -217,50 +313,19 @@ __device__ __forceinline__ float2 merge_stats(float2 x, float2 y) {
 template <int kStride>
 __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (*s_head)[kStride],
                                                float (*g_sum)[kStride], int j0, int o0, int o1, int col0) {
+#pragma clang fp contract(off)
   const int r = a.pool_r;
   const int own = o1 - o0;
-  const float inv_k = 1.0f / (float)(2 * r + 1), inv_g = 1.0f / (float)a.G, inv_h = 1.0f / (float)a.Hq;
   const bool is_max = a.pool_mode == FKV_POOL_MAX;
   const int lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
   const bool split = a.vsh != 0;  // a KV group spans two virtual groups: its mean is formed after the barrier
-  for (int g = threadIdx.x >> 6; g < a.V; g += n_waves) {  // one wave per virtual group
-    const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
+  for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g < a.V; g += n_waves) {  // one wave per virtual group
     if (r == 3) {
-      // kernel 7 (the paper's): two neighbouring tokens per lane, whose 8 taps are four 8-byte LDS reads per head (o0 - j0 is
-      // r: the first tap of owned token jj is slot jj)
-      typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
-#pragma unroll 1
-      for (int jj = 2 * lane; jj < own; jj += 128) {
-        float p[kMaxGroup][2];
-#pragma unroll
-        for (int hl = 0; hl < kMaxGroup; ++hl) {
-          const float2 *row = reinterpret_cast<const float2 *>(s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + jj);
-          const float2 v01 = row[0], v23 = row[1], v45 = row[2], v67 = row[3];
-          const float v[8] = {v01.x, v01.y, v23.x, v23.y, v45.x, v45.y, v67.x, v67.y};
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            p[hl][i] = is_max ? fmaxf(fmaxf(fmaxf(v[i], v[i + 1]), fmaxf(v[i + 2], v[i + 3])), fmaxf(fmaxf(v[i + 4], v[i + 5]), v[i + 6]))
-                              : ((((((v[i] + v[i + 1]) + v[i + 2]) + v[i + 3]) + v[i + 4]) + v[i + 5]) + v[i + 6]) * inv_k;
-        }
-        const bool both = jj + 1 < own;
-        auto put = [&](float *dst, float x, float y) {
-          if (both) *reinterpret_cast<f32x2u *>(dst) = f32x2u{x, y};
-          else *dst = x;
-        };
-        float gs[2] = {0.f, 0.f};
-#pragma unroll
-        for (int hl = 0; hl < kMaxGroup; ++hl)
-          if (hl < n_h) {
-            if (a.scores_head) put(a.scores_head + (size_t)(h0 + hl) * a.sum_p + col0 + o0 + jj, p[hl][0], p[hl][1]);
-            gs[0] += p[hl][0];
-            gs[1] += p[hl][1];
-          }
-        g_sum[g][jj] = gs[0];
-        if (both) g_sum[g][jj + 1] = gs[1];
-        if (a.scores_group && !split) put(a.scores_group + (size_t)g * a.sum_p + col0 + o0 + jj, gs[0] * inv_g, gs[1] * inv_g);
-      }
+      if (is_max) pool7_group<kStride, true>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
+      else pool7_group<kStride, false>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
       continue;
     }
+    const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
 #pragma unroll 1
     for (int jj = lane; jj < own; jj += 64) {
       const int c = o0 + jj - j0;  // slot of the pooled token
@@ -275,13 +340,13 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
         } else {
           p = 0.f;
           for (int t = -r; t <= r; ++t) p += row[t];
-          p *= inv_k;
+          p *= a.inv_k;
         }
         if (a.scores_head) a.scores_head[(size_t)(h0 + hl) * a.sum_p + col0 + o0 + jj] = p;
         gs += p;
       }
       g_sum[g][jj] = gs;
-      if (a.scores_group && !split) a.scores_group[(size_t)g * a.sum_p + col0 + o0 + jj] = gs * inv_g;
+      if (a.scores_group && !split) a.scores_group[(size_t)g * a.sum_p + col0 + o0 + jj] = gs * a.inv_g;
     }
   }
   if (a.scores_tsp == nullptr && !(split && a.scores_group)) return;
@@ -289,14 +354,14 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   if (split && a.scores_group) {
     for (int i = threadIdx.x; i < own * a.Hkv; i += blockDim.x) {
       const int kv = i / own, jj = i - kv * own;
-      a.scores_group[(size_t)kv * a.sum_p + col0 + o0 + jj] = (g_sum[2 * kv][jj] + g_sum[2 * kv + 1][jj]) * inv_g;
+      a.scores_group[(size_t)kv * a.sum_p + col0 + o0 + jj] = (g_sum[2 * kv][jj] + g_sum[2 * kv + 1][jj]) * a.inv_g;
     }
   }
   if (a.scores_tsp == nullptr) return;
   for (int jj = threadIdx.x; jj < own; jj += blockDim.x) {
     float tot = 0.f;
     for (int g = 0; g < a.V; ++g) tot += g_sum[g][jj];
-    a.scores_tsp[col0 + o0 + jj] = tot * inv_h;
+    a.scores_tsp[col0 + o0 + jj] = tot * a.inv_h;
   }
 }
 

@@ -44,8 +44,7 @@ __device__ __forceinline__ unsigned request_flag(const unsigned *err) {
 // the block's maximum of row (q / 4) * 8 + hi * 4 + q % 4, in every lane.
 __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
                                               int g, int lane, unsigned poisoned) {
-#pragma unroll
-  for (int q = 0; q < 16; ++q) mloc[q] = half_max(mx[q]);
+  half_max16(mx, mloc);
   // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
   float shrink[16];
 #pragma unroll

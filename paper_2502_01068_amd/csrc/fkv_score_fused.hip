@@ -18,9 +18,12 @@
 //            wave) were 1.2 us slower, of 4 or 2 rows no faster.
 //   phase 3  probabilities from the kept logits, window sum, LDS pooling, head means, write
 //
-// Per launch, before -> after the grouped exchange, the scattered row sums and the barriers that leave stores
-// in flight: 2048 tokens 15.0 -> 13.4 us, 6554 18.0 -> 16.4, 12289 20.5 -> 17.9, 32768 28.4 -> 25.0 (the row sums' former
-// order, put back since, costs 0.1 us; in the kernel trace they are 14.6, 17.4, 18.0 and 25.4 us).
+// What bounds it at short inputs is instruction issue (two waves share a SIMD's vector issue, 4 cycles an instruction) and the
+// two trips of the exchange; from about 30000 tokens on the K stream.  So a tile's requests are one addition each (KTiles),
+// a tile is requested anew before its contraction, the row maxima take 100 instructions instead of 450, a kept tile goes to its
+// registers by a branch, and the flag is looked at before the posts, whose acknowledgement it was waited for with.
+// Kernel trace, before -> after: 2048 tokens 14.5 -> 12.2 us, 6554 17.6 -> 14.2, 12289 18.1 -> 15.1, 16384 (head-wise) 20.2 ->
+// 16.5, 32768 25.4 -> 21.3.
 //
 // Used when the batch fits the resident grid (about 61K tokens on 256 CUs); longer inputs take
 // the kernel of fkv_score_keep.hip or the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
@@ -29,7 +32,10 @@
 
 namespace fkv {
 
-constexpr int kFusedSubShort = 5;  // sub-tiles (of 32 tokens) a block keeps in registers: the variant for inputs
+// Sub-tiles (of 32 tokens) a block keeps in registers.  The variants for inputs with fewer per block carry less code and
+// registers for them.
+constexpr int kFusedSubFew = 2;
+constexpr int kFusedSubShort = 5;
 constexpr int kFusedSubLong = 8;   // that fit 5 per block carries less register-select work per logit
 constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 
@@ -53,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
       reinterpret_cast<float(*)[kFusedSlots]>(lds_all + kMaxKvHeads * kMaxGroup * kFusedSlots * 4);
   static_assert((kMaxKvHeads * kMaxGroup + kMaxKvHeads) * kFusedSlots * 4 <= kWaves * kStageBytes, "LDS reuse");
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
   const int tok_base = a.map.cu[b];
@@ -72,46 +78,74 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   const int g = wave;
   const bool has_group = g < a.V;  // the host takes this kernel only for V <= 8 (one wave per virtual group)
 
-  const unsigned poisoned = request_flag(f.err);
+  const unsigned flag = request_flag(f.err);
   if (threadIdx.x == 0) flag_lds[0] = 1u;
 
   FKV_TICK(32);
   FKV_BTICK(0);
   // ---- phase 1: logits into registers, running statistics of the owned tokens
-  float z[kFusedSub][16], mloc[16];
+  float z[kFusedSub][16], mloc[16], mx[16], sm[16];
   if (has_group) {
+    const KTiles tiles(a, tok_base, vg_kv_head(a, g), c0, min(Lb, c1), stage, lane);
+    tiles.issue<0>(0);
+    FKV_WTICK(0);
     bf16x8 qa[8];
     load_q(a, b, g, lane, qa);
-    float mx[16], sm[16];
+    uint32_t addr[8];
+    operand_addresses(stage, lane, addr);
 #pragma unroll
     for (int q = 0; q < 16; ++q) { mx[q] = kNegBig; sm[q] = 0.f; }
-    stream_head_direct(a, qa, tok_base, Lb, g, c0, c1 - c0, stage, lane, [&](int st, const floatx16 &acc) {
-      const int tok = c0 + st * kSub + n;
-      const bool counted = (tok >= o0 && tok < o1) || (last && tok >= P && tok < Lb);
-      const bool scored = tok >= 0 && tok < min(P, c1);  // a prefix token (owned or halo): its probability is formed in phase 3
+#pragma unroll 1
+    for (int st = 0; st < n_sub; ++st) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed in LDS
+      if (st == 0) FKV_WTICK(1);
+      constexpr int kHalf = kFusedSub > 5 ? 4 : 8;  // operands in registers at a time
+      u32x4 kb[kHalf];
+      read_operands<kHalf>(kb, addr);
+      if (kHalf == 8 && st + 1 < n_sub) tiles.issue<0>(st + 1);
+      floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int w = hi * 4 + (q & 3);
-        const bool ok = counted && (!a.causal || tok <= P + w);
-        const float zz = acc[q] * a.scale_log2e;
+      for (int s = 0; s < kHalf; ++s)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s], __builtin_bit_cast(bf16x8, kb[s]), acc, 0, 0, 0);
+      if constexpr (kHalf == 4) {
+        read_operands<4>(kb, addr + 4);
+        if (st + 1 < n_sub) tiles.issue<0>(st + 1);
 #pragma unroll
-        for (int t = 0; t < kFusedSub; ++t)
-          if (t == st) z[t][q] = zz;
-        // running reference = max over every logit that is counted or later scored, so that
-        // 2^(z - reference) <= 1 for all of them; only counted keys enter the sum.  Masked window
-        // keys and clamped slots outside the sequence are neither: they must not move the reference.
-        const float zr = (ok || scored) ? zz : kNegBig;
-        const float d = zr - mx[q];
-        const float e = fast_exp2(-fabsf(d));
-        const float one = ok ? 1.f : 0.f;
-        sm[q] = d > 0.f ? sm[q] * e + one : sm[q] + one * e;
-        mx[q] = fmaxf(mx[q], zr);
+        for (int s = 0; s < 4; ++s)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[4 + s], __builtin_bit_cast(bf16x8, kb[s]), acc, 0, 0, 0);
       }
-    });
+      const int tok = c0 + st * kSub + n;
+      const bool counted = ((tok >= o0) & (tok < o1)) | (last & (tok >= P) & (tok < Lb));
+      const bool scored = (tok >= 0) & (tok < min(P, c1));  // a prefix token (owned or halo): its probability is formed in phase 3
+      bool take[4];
+      float one[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool ok = counted & ((a.causal == 0) | (tok <= P + hi * 4 + i));
+        take[i] = ok | scored;
+        one[i] = ok ? 1.f : 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[q] *= a.scale_log2e;
+#pragma unroll
+      for (int t = 0; t < kFusedSub; ++t)
+        if (t == st) {
+          asm volatile("");  // a branch, not 16 choices for every t
+#pragma unroll
+          for (int q = 0; q < 16; ++q) z[t][q] = acc[q];
+        }
+      // running reference = max over every logit that is counted or later scored, so that
+      // 2^(z - reference) <= 1 for all of them; only counted keys enter the sum.  Masked window
+      // keys and slots outside the sequence are neither: they must not move the reference.
+#pragma unroll
+      for (int q = 0; q < 16; ++q) count_logit(take[q & 3] ? acc[q] : kNegBig, one[q & 3], mx[q], sm[q]);
+      if (st == 0) FKV_WTICK(2);
+    }
     FKV_TICK(33);
-    FKV_WTICK(0);
-    fold_and_post(f, mx, sm, mloc, g, lane, poisoned);
   }
+  // Looked at before the mailbox posts go out: a load is waited for together with them otherwise.
+  const unsigned poisoned = __builtin_amdgcn_readfirstlane(flag);
+  if (has_group) fold_and_post(f, mx, sm, mloc, g, lane, poisoned);
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
   // (fkv_clear_error) every launch only marks its scores invalid.
   if (poisoned != 0u) {
@@ -120,11 +154,10 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   }
   FKV_TICK(34);
   FKV_BTICK(1);
-  FKV_WTICK(1);
+  FKV_WTICK(3);
 
   bool wave_ok = owner_duty(a, f, xch, wave, lane);
   FKV_TICK(35);
-  FKV_WTICK(2);
 
   // While the exchange is in flight: turn the kept logits into 2^(z - block reference).  The
   // global normaliser then costs one multiply per value instead of an exponential.
@@ -150,7 +183,6 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
     wave_ok = collect_lse(f, g, lane, cst_lds[wave]);
   }
   FKV_BTICK(2);
-  FKV_WTICK(3);
   lds_barrier();  // every wave has left its staging tile (phase 3 reuses them); flag_lds is initialised
   if (!wave_ok && lane == 0) flag_lds[0] = 0u;
   FKV_TICK(37);
@@ -165,19 +197,20 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
       if (st < n_sub) {
         const int tok = c0 + st * kSub + n;
         const bool inb = tok >= 0 && tok < min(P, c1);  // only prefix tokens are scored; slots past c1 were never loaded
+        float sum[4];
 #pragma unroll
         for (int hl = 0; hl < 4; ++hl) {
-          float sum = 0.f;
+          sum[hl] = 0.f;
 #pragma unroll
           for (int rr = 0; rr < 4; ++rr) {
             // Each probability is rounded before it is added: as one multiply-add the scores move by an ulp, and with
             // them which of two nearly equal tokens is kept.
 #pragma clang fp contract(off)
-            sum += z[st][hl * 4 + rr] * fac[hl * 4 + rr];
+            sum[hl] += z[st][hl * 4 + rr] * fac[hl * 4 + rr];
           }
-          sum = add_across_halves(sum);  // other half of the window rows
-          if (hi == 0 && hl < vg_heads(a, g)) s_head[g * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
+          sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
+        store_sums<kFusedSlots>(a, s_head, g, st * kSub + n, hi, inb, sum);
       }
     }
   }
@@ -195,7 +228,9 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 }
 
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s) {
-  if (f.n_sub_max <= kFusedSubShort)
+  if (f.n_sub_max <= kFusedSubFew)
+    hipLaunchKernelGGL(k_score_fused<kFusedSubFew>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+  else if (f.n_sub_max <= kFusedSubShort)
     hipLaunchKernelGGL(k_score_fused<kFusedSubShort>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   else
     hipLaunchKernelGGL(k_score_fused<kFusedSubLong>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   typedef __attribute__((address_space(1))) const void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
   const int tok_base = a.map.cu[b];

@@ -21,7 +21,6 @@
 // Tokens are split over blocks (8 waves each); a block merges its waves' running states through
 // LDS and leaves one partial (max, sum, 32 x 128 accumulator) per (sequence, group, split); a second
 // launch folds the splits in a fixed order.
-#include "fkv_dpp.h"
 #include "fkv_score_common.h"
 
 namespace fkv {
@@ -41,24 +40,6 @@ __device__ __forceinline__ float max_across_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// The operands of a tile whose loads have been waited for; they have left the tile when this returns.  Asm blocks: for an
-// ordinary LDS read the compiler waits for every outstanding LDS-direct load, so each tile's loads were waited for
-// right after they were issued (32768 tokens 33.0 -> 31.8 us per call, 22 sequences of 1600 104 -> 101).
-__device__ __forceinline__ void read_k_tile(u32x4 (&r)[8], const uint32_t (&addr)[8]) {
-  asm volatile(
-      "ds_read_b128 %0, %8\n\t"
-      "ds_read_b128 %1, %9\n\t"
-      "ds_read_b128 %2, %10\n\t"
-      "ds_read_b128 %3, %11\n\t"
-      "ds_read_b128 %4, %12\n\t"
-      "ds_read_b128 %5, %13\n\t"
-      "ds_read_b128 %6, %14\n\t"
-      "ds_read_b128 %7, %15\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-      : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]), "v"(addr[5]), "v"(addr[6]), "v"(addr[7])
-      : "memory");
-}
 __device__ __forceinline__ void read_v_half(u32x2 (&r)[8], uint32_t addr) {  // tokens (i & 3) + 8 (i / 4) from addr on
   asm volatile(
       "ds_read_b64 %0, %8\n\t"
@@ -135,8 +116,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   const int vis_last = a.causal ? P + (n & 7) : Lb - 1;  // last key softmax row n may see
 
   uint32_t kaddr[8];
-#pragma unroll
-  for (int s8 = 0; s8 < 8; ++s8) kaddr[s8] = (uint32_t)(uintptr_t)(lptr_t)(ktile + n * 256 + (((hi * 8 + s8) ^ (n & 15)) << 4));
+  operand_addresses(ktile, lane, kaddr);
   const uint32_t vaddr = (uint32_t)(uintptr_t)(lptr_t)(vtile + hi * 1024 + n * 8);
   int tile = t0 + wave;
   if (tile < t1) {
@@ -148,7 +128,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
     const bool more = tile + kWoWaves < t1;
     __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8): the K tile has landed (V may still be on its way)
     u32x4 kb[8];
-    read_k_tile(kb, kaddr);
+    read_operands<8>(kb, kaddr);
     if (more) issue_k(tile + kWoWaves);
     floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
