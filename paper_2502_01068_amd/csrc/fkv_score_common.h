@@ -20,9 +20,13 @@ constexpr float kNegBig = -1.0e30f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The sequence a block works on.  Eight entries a step: one by one each costs a trip through the scalar cache (0.15 us).
 __device__ __forceinline__ int find_seq(const SeqMap &map, int block) {
   int b = 0;
-  while (b + 1 < map.n_seq && block >= map.blk[b + 1]) ++b;
+  for (int i = 1; i < map.n_seq && b == i - 1; i += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b += (i + j < map.n_seq) & (block >= map.blk[i + j]);
+  }
   return b;
 }
 
@@ -140,9 +144,11 @@ struct KTiles {
   template <int kAux>
   __device__ __forceinline__ void issue(int st) const {
     typedef __attribute__((address_space(3))) void *lptr_t;
+    uint32_t lo = 2 * st * half_bytes, hi = lo + half_bytes;
+    asm("" : "+s"(lo), "+s"(hi));  // else every load of a loop gets an induction variable of its own, in a register per lane
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lptr_t)(stage + i * 1024), 16, (int)(at[i & 3] + (2 * st + (i >> 2)) * half_bytes), 0, 0, kAux);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lptr_t)(stage + i * 1024), 16, (int)(at[i & 3] + (i < 4 ? lo : hi)), 0, 0, kAux);
   }
 };
 
@@ -360,7 +366,13 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   if (a.scores_tsp == nullptr) return;
   for (int jj = threadIdx.x; jj < own; jj += blockDim.x) {
     float tot = 0.f;
-    for (int g = 0; g < a.V; ++g) tot += g_sum[g][jj];
+    for (int g0 = 0; g0 < a.V; g0 += kMaxKvHeads) {  // the reads of 8 groups at a time (there are rows for as many), added in order
+      float x[kMaxKvHeads];
+#pragma unroll
+      for (int i = 0; i < kMaxKvHeads; ++i) x[i] = g_sum[g0 + i][jj];
+#pragma unroll
+      for (int i = 0; i < kMaxKvHeads; ++i) tot = g0 + i < a.V ? tot + x[i] : tot;
+    }
     a.scores_tsp[col0 + o0 + jj] = tot * a.inv_h;
   }
 }

@@ -40,6 +40,13 @@ __device__ __forceinline__ unsigned request_flag(const unsigned *err) {
   return __hip_atomic_load(err + zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The arguments a block needs before its first load of K, requested together: left to itself the compiler loads each where
+// it is first used, four trips one after the other.
+__device__ __forceinline__ void request_args(const ScoreArgs &a, const FusedArgs &f) {
+  asm volatile("" ::"s"(a.k), "s"(a.q_win), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.W), "s"(a.V), "s"(a.vsh), "s"(a.pool_r), "s"(f.err),
+               "s"(a.map.n_seq), "s"(a.scale_log2e), "s"(a.causal), "s"(f.part));
+}
+
 // Folds a wave's per-lane (max, sum) pairs of a virtual group's 32 rows over the token lanes and posts them.  mloc[q]:
 // the block's maximum of row (q / 4) * 8 + hi * 4 + q % 4, in every lane.
 __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
@@ -127,18 +134,20 @@ __device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &
   return wave_ok;
 }
 
-// The log-sum-exps of a virtual group's 32 rows from the block's result boxes, into dst (LDS, 32 floats).  Wave-uniform
-// result: false if the wait ran out.
+// The log-sum-exps of the 32 rows of virtual groups g .. g + kVg - 1 from the block's result boxes, a lane each, into dst
+// (LDS, 32 kVg floats).  Wave-uniform result: false if the wait ran out.
+template <int kVg>
 __device__ __forceinline__ bool collect_lse(const FusedArgs &f, int g, int lane, float *dst) {
-  float *box = f.lse + (size_t)blockIdx.x * kLseRowsPerBlock + g * kRowsPerGroup + (lane & 31);
+  const bool mine = lane < kVg * kRowsPerGroup;
+  float *box = f.lse + (size_t)blockIdx.x * kLseRowsPerBlock + g * kRowsPerGroup + (lane & (kVg * kRowsPerGroup - 1));
   unsigned bits = kEmpty32;
   BoundedWait wait(f.timeout_ticks);
   while (true) {
-    if (lane < 32 && bits == kEmpty32) bits = box_peek(box);
-    if (!__any(lane < 32 && bits == kEmpty32)) break;
+    if (mine && bits == kEmpty32) bits = box_peek(box);
+    if (!__any(mine && bits == kEmpty32)) break;
     if (wait.expired()) return false;
   }
-  if (lane < 32) {
+  if (mine) {
     box_clear(box);
     dst[lane] = __uint_as_float(bits);
   }

@@ -22,8 +22,8 @@
 // two trips of the exchange; from about 30000 tokens on the K stream.  So a tile's requests are one addition each (KTiles),
 // a tile is requested anew before its contraction, the row maxima take 100 instructions instead of 450, a kept tile goes to its
 // registers by a branch, and the flag is looked at before the posts, whose acknowledgement it was waited for with.
-// Kernel trace, before -> after: 2048 tokens 14.5 -> 12.2 us, 6554 17.6 -> 14.2, 12289 18.1 -> 15.1, 16384 (head-wise) 20.2 ->
-// 16.5, 32768 25.4 -> 21.3.
+// Kernel trace, before -> after: 2048 tokens 14.5 -> 11.5 us, 6554 17.6 -> 13.8, 12289 18.1 -> 14.7, 16384 (head-wise) 20.2 ->
+// 16.5, 32768 25.4 -> 21.1.
 //
 // Used when the batch fits the resident grid (about 61K tokens on 256 CUs); longer inputs take
 // the kernel of fkv_score_keep.hip or the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
@@ -36,7 +36,7 @@ namespace fkv {
 // registers for them.
 constexpr int kFusedSubFew = 2;
 constexpr int kFusedSubShort = 5;
-constexpr int kFusedSubLong = 8;   // that fit 5 per block carries less register-select work per logit
+constexpr int kFusedSubLong = 8;
 constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 
 int fused_slots(void) { return kFusedSlotsMax; }
@@ -59,6 +59,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
       reinterpret_cast<float(*)[kFusedSlots]>(lds_all + kMaxKvHeads * kMaxGroup * kFusedSlots * 4);
   static_assert((kMaxKvHeads * kMaxGroup + kMaxKvHeads) * kFusedSlots * 4 <= kWaves * kStageBytes, "LDS reuse");
 
+  request_args(a, f);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 
   // ---- phase 2b: collect the log-sum-exp of this wave's 32 rows from the block's result box
   if (has_group && wave_ok) {
-    wave_ok = collect_lse(f, g, lane, cst_lds[wave]);
+    wave_ok = collect_lse<1>(f, g, lane, cst_lds[wave]);
   }
   FKV_BTICK(2);
   lds_barrier();  // every wave has left its staging tile (phase 3 reuses them); flag_lds is initialised

@@ -10,13 +10,13 @@
 //
 // Against the two-pass kernels (fkv_score.hip), which read K twice and need three launches, K's second read shrinks
 // by the kept part and a launch boundary (the statistics' way through memory and back) becomes the exchange:
-// 131072 tokens (17 tiles per block, 10 kept) 97.6 -> 68.6 us in the kernel trace, 8 sequences of 8192-16384 tokens 82.4 ->
+// 131072 tokens (17 tiles per block, 10 kept) 97.6 -> 66.4 us in the kernel trace, 8 sequences of 8192-16384 tokens 82.4 ->
 // 55.6 us.  With more than 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and
-// keeps 3 tiles of each: 64 / 8 heads at 20001 tokens 40.0 -> 28.2 us.
+// keeps 3 tiles of each: 64 / 8 heads at 20001 tokens 40.0 -> 24.8 us.  The tiles go through loops whose code is 20 KB; written
+// out tile by tile it was 60 KB (42 KB for wide groups), fetched once each, with 64-bit addresses per load: 131072 tokens 68.5,
+// 20001 tokens 28.0 us.
 // A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not; the
 // normaliser is added up over other block shares in another order, so the scores are theirs up to its last bits.
-#include <type_traits>
-
 #include "fkv_score_exchange.h"
 
 namespace fkv {
@@ -40,9 +40,9 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(g_sum);
   constexpr int kWaveSums = kVg * kMaxGroup * kSlots;  // floats of s_head that one wave fills
   static_assert(kLds * kVg * kRowsPerGroup * kSub <= kWaveSums && kWaveSums % 4 == 0, "logits kept in LDS");
-  typedef __attribute__((address_space(1))) const void *gptr_t;
-  typedef __attribute__((address_space(3))) void *lptr_t;
+  constexpr int kPlain = 0, kOnce = 2;  // cache policies of a tile's loads
 
+  request_args(a, f);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
   const int b = find_seq(a.map, blockIdx.x);
@@ -61,103 +61,99 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   const bool has_group = g < a.V;
   uint8_t *stage = stage_all + wave * kStageBytes;
   floatx4 *kept = reinterpret_cast<floatx4 *>(&s_head[0][0] + wave * kWaveSums) + lane;  // [tile][group][4][lane]
-  const unsigned poisoned = request_flag(f.err);
+  const unsigned flag = request_flag(f.err);
 
+  const KTiles tiles(a, tok_base, vg_kv_head(a, has_group ? g : 0), c0, min(Lb, c1), stage, lane);
+  uint32_t addr[8];
+  operand_addresses(stage, lane, addr);
   bf16x8 qa[kVg][8];
-  const int c = lane & 15, tq = lane >> 4;
-  const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
-  const uint16_t *kbase = a.k + (size_t)tok_base * tok_stride + (size_t)vg_kv_head(a, has_group ? g : 0) * kHeadDim;
-  // Tile st of the block into the wave's LDS tile (see stream_head_direct); token slots past the range are not loaded.
-  // Tiles that will be read again are loaded plainly, all others non-temporal: 131072 tokens 2 us less than with every
-  // load non-temporal, 4 us less than with none.
-  typedef std::integral_constant<int, 0> first_t;
-  typedef std::integral_constant<int, 2> rest_t;
-  auto issue = [&](int st, auto aux_t) {
-    constexpr int kAux = decltype(aux_t)::value;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (st * kSub + i * 4 >= c1 - c0) break;  // wave-uniform
-      const int slot = i * 4 + tq;
-      const int t = min(max(c0 + st * kSub + slot, 0), Lb - 1);
-      __builtin_amdgcn_global_load_lds((gptr_t)(kbase + (size_t)t * tok_stride + ((c ^ (slot & 15)) << 3)),
-                                       (lptr_t)(stage + i * 1024), 16, 0, kAux);
-    }
-  };
-  // Logits of the tile that was requested last; the LDS tile is free afterwards.
-  auto logits = [&](floatx16 (&acc)[kVg]) {
+  // Logits of the tile that was requested last; `next` requests another one as soon as the operands have left the LDS tile.
+  auto logits = [&](floatx16 (&acc)[kVg], auto next) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
-    wave_lds_sync();
 #pragma unroll
     for (int v = 0; v < kVg; ++v)
       acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const u32x4 kb = *reinterpret_cast<const u32x4 *>(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
+    for (int half = 0; half < 2; ++half) {
+      u32x4 kb[4];
+      read_operands<4>(kb, addr + 4 * half);
+      if (half == 1) next();
 #pragma unroll
-      for (int v = 0; v < kVg; ++v)
-        acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][s], __builtin_bit_cast(bf16x8, kb), acc[v], 0, 0, 0);
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int v = 0; v < kVg; ++v)
+          acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][4 * half + s], __builtin_bit_cast(bf16x8, kb[s]), acc[v], 0, 0, 0);
     }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): every lane's operands have left the tile
-    wave_lds_sync();
   };
 
   // ---- phase 1
-  floatx16 z[kKeep][kVg];
+  float z[kKeep][kVg][16];
+  float mx[kVg][16], sm[kVg][16];
   if (has_group) {
+    // Tiles that will be read again are loaded plainly, all others non-temporal: 131072 tokens 2 us less than with every
+    // load non-temporal, 4 us less than with none.
+    if (n_re > 0) tiles.issue<kPlain>(0);
+    else tiles.issue<kOnce>(0);
 #pragma unroll
-    for (int v = 0; v < kVg; ++v) load_q(a, b, g + v, lane, qa[v]);
-    float mx[kVg][16], sm[kVg][16];
-#pragma unroll
-    for (int v = 0; v < kVg; ++v)
+    for (int v = 0; v < kVg; ++v) {
+      load_q(a, b, g + v, lane, qa[v]);
 #pragma unroll
       for (int q = 0; q < 16; ++q) { mx[v][q] = kNegBig; sm[v][q] = 0.f; }
+    }
     auto count = [&](int st, const floatx16 (&acc)[kVg]) {
       const int tok = c0 + st * kSub + n;
-      const bool counted = (tok >= o0 && tok < o1) || (last && tok >= P && tok < Lb);
+      const bool counted = ((tok >= o0) & (tok < o1)) | (last & (tok >= P) & (tok < Lb));
+      bool ok[4];
+      float one[4];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const bool ok = counted && (!a.causal || tok <= P + hi * 4 + (q & 3));
-#pragma unroll
-        for (int v = 0; v < kVg; ++v) {
-          const float zz = ok ? acc[v][q] * a.scale_log2e : kNegBig;
-          const float d = zz - mx[v][q];
-          const float e = fast_exp2(-fabsf(d));
-          sm[v][q] = d > 0.f ? sm[v][q] * e + 1.f : sm[v][q] + (ok ? e : 0.f);
-          mx[v][q] = fmaxf(mx[v][q], zz);
-        }
+      for (int i = 0; i < 4; ++i) {
+        ok[i] = counted & ((a.causal == 0) | (tok <= P + hi * 4 + i));
+        one[i] = ok[i] ? 1.f : 0.f;
       }
-    };
-    if (n_re > 0) issue(0, first_t{});
-    else issue(0, rest_t{});
-#pragma unroll 1
-    for (int st = 0; st < n_re; ++st) {
-      floatx16 acc[kVg];
-      logits(acc);
-      if (st + 1 < n_re) issue(st + 1, first_t{});
-      else issue(st + 1, rest_t{});
-      count(st, acc);
-    }
-#pragma unroll 1
-    for (int t = 0; t < n_lds; ++t) {
-      floatx16 acc[kVg];
-      logits(acc);
-      issue(n_re + t + 1, rest_t{});  // there are kept tiles behind these
 #pragma unroll
       for (int v = 0; v < kVg; ++v)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          kept[((t * kVg + v) * 4 + q) * 64] = floatx4{acc[v][4 * q], acc[v][4 * q + 1], acc[v][4 * q + 2], acc[v][4 * q + 3]};
-      count(n_re + t, acc);
+        for (int q = 0; q < 16; ++q)
+          count_logit(ok[q & 3] ? acc[v][q] * a.scale_log2e : kNegBig, one[q & 3], mx[v][q], sm[v][q]);
+    };
+#pragma unroll 1
+    for (int st = 0; st < n_re + n_lds; ++st) {  // there are kept tiles behind these
+      floatx16 acc[kVg];
+      logits(acc, [&] {
+        if (st + 1 < n_re) tiles.issue<kPlain>(st + 1);
+        else tiles.issue<kOnce>(st + 1);
+      });
+      if (st >= n_re) {
+#pragma unroll
+        for (int v = 0; v < kVg; ++v)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            kept[(((st - n_re) * kVg + v) * 4 + q) * 64] = floatx4{acc[v][4 * q], acc[v][4 * q + 1], acc[v][4 * q + 2], acc[v][4 * q + 3]};
+      }
+      count(st, acc);
     }
     const int st0 = n_re + n_lds;
+#pragma unroll 1
+    for (int k = 0; k < n_keep; ++k) {
+      floatx16 acc[kVg];
+      logits(acc, [&] {
+        const bool more = k + 1 < n_keep;
+        if (more || n_re > 0) tiles.issue<kOnce>(more ? st0 + k + 1 : 0);  // 0: the first tile of phase 3
+      });
 #pragma unroll
-    for (int t = 0; t < kKeep; ++t)
-      if (t < n_keep) {
-        logits(z[t]);
-        if (t + 1 < n_keep) issue(st0 + t + 1, rest_t{});
-        else if (n_re > 0) issue(0, rest_t{});  // the first tile of phase 3
-        count(st0 + t, z[t]);
-      }
+      for (int t = 0; t < kKeep; ++t)
+        if (t == k) {
+          asm volatile("");  // a branch, not a choice per register for every t
+#pragma unroll
+          for (int v = 0; v < kVg; ++v)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) z[t][v][q] = acc[v][q];
+        }
+      count(st0 + k, acc);
+    }
+  }
+  const unsigned poisoned = __builtin_amdgcn_readfirstlane(flag);  // ahead of the posts, see k_score_fused
+  if (has_group) {
 #pragma unroll
     for (int v = 0; v < kVg; ++v) {
       float mloc[16];
@@ -174,10 +170,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
 
   // ---- phase 2
   bool wave_ok = owner_duty(a, f, xch, wave, lane);
-  if (has_group) {
-#pragma unroll
-    for (int v = 0; v < kVg; ++v) wave_ok = wave_ok && collect_lse(f, g + v, lane, cst_lds[g + v]);
-  }
+  if (has_group) wave_ok = wave_ok && collect_lse<kVg>(f, g, lane, cst_lds[g]);
 
   // ---- phase 3
   if (has_group && wave_ok) {
@@ -187,52 +180,73 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
     for (int v = 0; v < kVg; ++v)
 #pragma unroll
       for (int q = 0; q < 16; ++q) cst[v][q] = cst_lds[g + v][(q >> 2) * 8 + hi * 4 + (q & 3)];
-    auto finish = [&](int st, const floatx16 (&acc)[kVg]) {
+    auto finish = [&](int st, const auto &acc) {
       const int tok = c0 + st * kSub + n;
-      const bool inb = tok >= 0 && tok < min(P, c1);  // only prefix tokens are scored; slots past c1 were never loaded
+      const bool inb = (tok >= 0) & (tok < min(P, c1));  // only prefix tokens are scored; slots past c1 were never loaded
 #pragma unroll
-      for (int v = 0; v < kVg; ++v)
+      for (int v = 0; v < kVg; ++v) {
+        float sum[4];
 #pragma unroll
         for (int hl = 0; hl < 4; ++hl) {
-          float sum = 0.f;
+          sum[hl] = 0.f;
 #pragma unroll
           for (int rr = 0; rr < 4; ++rr) {
-            const float e = fast_exp2(acc[v][hl * 4 + rr] * a.scale_log2e - cst[v][hl * 4 + rr]);
-            sum += (hi * 4 + rr < a.W) ? e : 0.f;
+            const float e = fast_exp2(__builtin_fmaf(acc[v][hl * 4 + rr], a.scale_log2e, -cst[v][hl * 4 + rr]));
+            sum[hl] += (hi * 4 + rr < a.W) ? e : 0.f;
           }
-          sum = add_across_halves(sum);  // other half of the window rows
-          if (hi == 0 && hl < vg_heads(a, g + v)) s_head[(g + v) * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
+          sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
+        store_sums<kSlots>(a, s_head, g + v, st * kSub + n, hi, inb, sum);
+      }
     };
-    auto again = [&](int st) {
-      floatx16 acc[kVg];
-      logits(acc);
-      if (st + 1 < n_re) issue(st + 1, rest_t{});
-      finish(st, acc);
-    };
-    floatx16 zl[kLds][kVg];
+    {
+      float zl[kLds][kVg][16];
 #pragma unroll
-    for (int t = 0; t < kLds; ++t)
-      if (t < n_lds)
+      for (int t = 0; t < kLds; ++t)
+        if (t < n_lds)
+#pragma unroll
+          for (int v = 0; v < kVg; ++v)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const floatx4 x = kept[((t * kVg + v) * 4 + q) * 64];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) zl[t][v][4 * q + i] = x[i];
+            }
+      wave_lds_sync();  // the sums may overwrite them
+#pragma unroll
+      for (int t = 0; t < kLds; ++t)
+        if (t < n_lds) finish(n_re + t, zl[t]);
+    }
+    // A tile streamed again and one kept in registers in turn, whose probabilities are formed while the next tile is on its
+    // way.  A loop, so that its code is fetched once.
+    int re = 0, kp = 0;
+#pragma unroll 1
+    while (re < n_re || kp < n_keep) {
+      float x[kVg][16];
+      int st;
+      if (re < n_re && (re <= kp || kp == n_keep)) {
+        st = re++;
+        floatx16 acc[kVg];
+        logits(acc, [&] { if (re < n_re) tiles.issue<kOnce>(re); });
 #pragma unroll
         for (int v = 0; v < kVg; ++v)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const floatx4 x = kept[((t * kVg + v) * 4 + q) * 64];
+          for (int q = 0; q < 16; ++q) x[v][q] = acc[v][q];
+      } else {
+        st = n_re + n_lds + kp;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) zl[t][v][4 * q + i] = x[i];
+        for (int t = 0; t < kKeep; ++t)
+          if (t == kp) {
+            asm volatile("");
+#pragma unroll
+            for (int v = 0; v < kVg; ++v)
+#pragma unroll
+              for (int q = 0; q < 16; ++q) x[v][q] = z[t][v][q];
           }
-    wave_lds_sync();  // the sums may overwrite them
-#pragma unroll
-    for (int t = 0; t < kLds; ++t)
-      if (t < n_lds) finish(n_re + t, zl[t]);
-#pragma unroll
-    for (int t = 0; t < kKeep; ++t) {  // a kept tile's probabilities while the next tile is on its way
-      if (t < n_re) again(t);
-      if (t < n_keep) finish(n_re + n_lds + t, z[t]);
+        ++kp;
+      }
+      finish(st, x);
     }
-#pragma unroll 1
-    for (int st = kKeep; st < n_re; ++st) again(st);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing may land in LDS after this point
   if (lane == 0) late_lds[wave] = wave_ok ? 0u : 1u;
