@@ -327,11 +327,17 @@ int even_share(const Resolved &r, int skip, int halo, int n_cu, int lo, int hi) 
   return sub * 32 - halo;
 }
 
-// Second pass of the two-pass score kernels: probabilities from the per-row normalisers in
-// a.rowstat, window sum, pooling, head means.  Tiles overlap by the pooling halo.
-int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, hipStream_t st) {
+// Second pass of the two-pass score kernels: probabilities from the per-row normalisers, window sum, pooling, head
+// means.  Tiles overlap by the pooling halo.  The normalisers are a.rowstat's, or (wo) those of the window output's splits, whose
+// merge then goes into the same launch, on CUs that the scores leave idle, at most four units a block; with many sequences it
+// is more than they can take beside the scores and a launch of its own.
+int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, const WoutArgs *wo, hipStream_t st) {
+  constexpr int kMergeUnits = 4;
   const int sub_max = r.V > kMaxKvHeads ? scores_sub_wide() : scores_sub_long();
-  const int own = even_share(r, r.W, 2 * a.pool_r, w.n_cu, scores_sub_short(), sub_max);
+  const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
+  const int units = wo ? wout_merge_units(*wo) : 0, beside = (units + kMergeUnits - 1) / kMergeUnits;
+  const bool merge = units > 0 && 8 * beside <= n_cu;
+  const int own = even_share(r, r.W, 2 * a.pool_r, merge ? n_cu - beside : n_cu, scores_sub_short(), sub_max);
   a.tile_own = own;
   a.tile_sub = (own + 2 * a.pool_r + 31) / 32;
   int nb = 0;
@@ -341,9 +347,16 @@ int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, hipS
     nb += (P + own - 1) / own;
   }
   a.map.blk[r.n_seq] = nb;
+  hipError_t e = hipSuccess;
+  if (units > 0 && (!merge || nb == 0)) {
+    Timed t(w.prof, st, KID_WOUT);
+    e = launch_wout_merge(*wo, st);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   if (nb > 0) {
     Timed t(w.prof, st, KID_SCORES);
-    const hipError_t e = launch_scores(a, nb, st);
+    const int idle = std::max(beside, (n_cu - nb % n_cu) % n_cu);
+    e = wo ? launch_wout_scores(a, *wo, nb, merge ? std::min(idle, units) : 0, st) : launch_scores(a, nb, st);
     if (e != hipSuccess) return hip_fail(e);
   }
   return FKV_OK;
@@ -427,7 +440,7 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
   { Timed t(w.prof, st, KID_COMBINE); e = launch_combine(a, st); }
   if (e != hipSuccess) return hip_fail(e);
 
-  return enqueue_scores_pass2(w, a, r, st);
+  return enqueue_scores_pass2(w, a, r, nullptr, st);
 }
 
 // The select launch(es) of a call.  Rows long enough take the several-blocks-per-row kernel, whose
@@ -867,19 +880,17 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
 }  // namespace
 
 namespace {
-// Launches the window rows' attention output; rowstat != nullptr also stores every softmax row's
-// log-sum-exp there and keeps K in the caches for the score pass that follows.
+// Launches the partials of the window rows' attention output and fills `a` for their merge; keep_k: K stays in the caches for
+// the score pass that follows.
 int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const void *q_win, const void *k, const void *v,
-                 float *out, float *rowstat, hipStream_t st) {
-  WoutArgs a{};
+                 float *out, bool keep_k, WoutArgs &a, hipStream_t st) {
   a.q_win = static_cast<const uint16_t *>(q_win);
   a.k = static_cast<const uint16_t *>(k);
   a.v = static_cast<const uint16_t *>(v);
   a.part_o = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
   a.part_ms = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.wout_ms);
   a.out = out;
-  a.rowstat = rowstat;
-  a.keep_k = rowstat != nullptr;
+  a.keep_k = keep_k;
   int tiles_max = 1;
   for (int b = 0; b <= r.n_seq; ++b) a.cu[b] = r.cu[b];
   for (int b = 0; b < r.n_seq; ++b) tiles_max = std::max(tiles_max, (r.cu[b + 1] - r.cu[b] + 31) / 32);
@@ -896,6 +907,12 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   const hipError_t e = launch_wout(a, st);
   return e == hipSuccess ? FKV_OK : hip_fail(e);
 }
+
+int enqueue_wout_merge(fkv_ctx *ctx, const WoutArgs &a, hipStream_t st) {
+  Timed t(ctx, st, KID_WOUT);
+  const hipError_t e = launch_wout_merge(a, st);
+  return e == hipSuccess ? FKV_OK : hip_fail(e);
+}
 }  // namespace
 
 int fkv_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, const void *k, const void *v,
@@ -907,7 +924,10 @@ int fkv_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, c
   if (misaligned(q_win) || misaligned(k) || misaligned(v) || misaligned(out)) return FKV_EALIGN;
   rc = check_ctx(ctx, r);
   if (rc != FKV_OK) return rc;
-  return enqueue_wout(ctx, shape, r, q_win, k, v, out, nullptr, static_cast<hipStream_t>(stream));
+  WoutArgs wo{};
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  rc = enqueue_wout(ctx, shape, r, q_win, k, v, out, false, wo, st);
+  return rc == FKV_OK ? enqueue_wout_merge(ctx, wo, st) : rc;
 }
 
 int fkv_score_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, const void *k, const void *v,
@@ -923,14 +943,15 @@ int fkv_score_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_
   if (rc != FKV_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const ScoreWs w = ws_of(ctx);
-  // one pass over K and V: the window rows' output and, as a by-product, every softmax row's normaliser
-  rc = enqueue_wout(ctx, shape, r, q_win, k, v, out, w.rowstat, st);
-  if (rc != FKV_OK || r.sum_p == 0) return rc;
-  // second pass over K (what the first pass left in the caches is reused): the scores
+  // one pass over K and V: the partials of the window rows' output, which hold every softmax row's normaliser
+  WoutArgs wo{};
+  rc = enqueue_wout(ctx, shape, r, q_win, k, v, out, r.sum_p > 0, wo, st);
+  if (rc != FKV_OK) return rc;
+  if (r.sum_p == 0) return enqueue_wout_merge(ctx, wo, st);
+  // second pass over K (what the first pass left in the caches is reused): the scores, and the merge of the output
   ScoreArgs a{};
   fill_score_args(a, w, shape, r, q_win, k, scores_group, scores_tsp, nullptr);
-  a.k_cached = r.V <= kMaxKvHeads ? 1 : 0;
-  return enqueue_scores_pass2(w, a, r, st);
+  return enqueue_scores_pass2(w, a, r, &wo, st);
 }
 
 int fkv_decode_attention(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const void *k, const void *v,

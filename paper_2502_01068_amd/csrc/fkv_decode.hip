@@ -46,24 +46,6 @@ constexpr float kDecNegBig = -1.0e30f;
 
 __device__ __forceinline__ float dec_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Maximum / sum over the 4 lanes that hold the same head (16 lanes apart), in every lane.
-__device__ __forceinline__ float quad_max(float x) {
-  unsigned u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  u = __float_as_uint(x);
-  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float quad_sum(float x) {
-  unsigned u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  u = __float_as_uint(x);
-  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // The K tile's operands: waits until at most the 8 youngest loads (the V tile's) are outstanding, reads and waits for
 // the reads, so that the tile may be overwritten.  One asm block: for an ordinary LDS read the compiler would
 // wait for every outstanding load, the V tile's too (paged, it does so already, see step).
@@ -255,7 +237,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         if (edge && tile * kDecTile + 4 * i + q >= n) z[i] = -INFINITY;  // weight 0 below whatever the maximum: it is at least kDecNegBig
         tmax = fmaxf(tmax, z[i]);
       }
-      tmax = quad_max(tmax);
+      tmax = quarters_max(tmax);
       const float m_new = fmaxf(m, tmax);
       const float alpha = dec_exp2(m - m_new);
       m = m_new;
@@ -307,7 +289,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     if (tile < tile1) step(std::false_type{});
 
     // ---- the waves' states into LDS: lane (head c, q) holds d = 32 q + 8 r + j in o[j][r]
-    l = quad_sum(l);
+    l = quarters_sum(l);
     if (c < G) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)

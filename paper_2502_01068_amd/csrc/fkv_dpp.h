@@ -147,6 +147,24 @@ __device__ __forceinline__ float half_sums_of_products(const float (&x)[16], con
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Maximum / sum over the 4 lanes that are 16 apart, in every lane; the sum as (0 + 1) + (2 + 3).
+__device__ __forceinline__ float quarters_max(float x) {
+  unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  u = __float_as_uint(x);
+  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quarters_sum(float x) {
+  unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  u = __float_as_uint(x);
+  r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Maximum / sum over the 64 lanes as a wave-uniform value (fixed order: reproducible).
 __device__ __forceinline__ float wave_fmax(float x) {
   x = fmaxf(x, dpp_f32<kDppRowRor + 8>(x, x));

@@ -88,7 +88,6 @@ struct ScoreArgs {
   int chunk;              // tokens per block in the stats launch
   int tile_own;           // tokens each block of the scores launch owns
   int tile_sub;           // 32-token sub-tiles that hold them and the pooling halo
-  int k_cached;           // scores launch: K was streamed by the launch just before (read it with plain loads)
   int64_t sum_p;          // row stride of scores_group
 };
 
@@ -228,12 +227,15 @@ struct WoutArgs {
   int n_split;            // blocks per (sequence, virtual group)
   int causal;
   float scale_log2e;
-  float *rowstat;         // [n_seq][V*32] or nullptr: receives each softmax row's log-sum-exp (log2 units), the
-                          // normaliser the second pass of the two-pass score kernels reads
   int keep_k;             // K is read with plain loads (it will be read again soon) instead of non-temporal ones
 };
 int wout_tiles_per_block_min(void);
-hipError_t launch_wout(const WoutArgs &a, hipStream_t s);
+hipError_t launch_wout(const WoutArgs &a, hipStream_t s);        // the splits' partials
+hipError_t launch_wout_merge(const WoutArgs &a, hipStream_t s);  // the output from them
+int wout_merge_units(const WoutArgs &a);
+// The scores from those partials, whose normalisers every block folds for itself, in one launch; its first n_merge blocks
+// (may be none) write the output instead, wout_merge_units(a) units of work in all.
+hipError_t launch_wout_scores(const ScoreArgs &a, const WoutArgs &o, int n_blocks, int n_merge, hipStream_t s);
 
 // ---- diagnostics ------------------------------------------------------------------------
 struct DiagOverlapArgs {

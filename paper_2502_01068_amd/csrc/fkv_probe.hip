@@ -80,14 +80,16 @@ __global__ __launch_bounds__(kThreads) void k_probe_logits(ScoreArgs a, uint32_t
   uint8_t *stage = stage_all + wave * kStageBytes;
   for (int g = wave; g < a.V; g += kWaves) {
     if (kMfma) {
+      const KTiles tiles(a, 0, vg_kv_head(a, g), t0, min(Lb, t0 + n_sub * kSub), stage, lane);
+      tiles.issue<kPlain>(0);
       bf16x8 qa[1][8];
       load_q(a, 0, g, lane, qa[0]);
       float mx[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx[r] = kNegBig;
-      stream_head(a, qa, 0, Lb, g, t0, n_sub * kSub, stage, lane, [&](int, const floatx16 (&acc)[1]) {
+      stream_tiles<kPlain>(tiles, qa, n_sub, lane, [&](int st, const floatx16 (&acc)[1]) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], acc[0][r]);
+        for (int r = 0; r < 16; ++r) mx[r] = t0 + st * kSub + n < Lb ? fmaxf(mx[r], acc[0][r]) : mx[r];
       });
       probe_fold_rows(mx, [&](int r) { return (r >> 2) * 8 + hi * 4 + (r & 3); }, rowkeys, g, keys_lds[wave], lane);
     } else {

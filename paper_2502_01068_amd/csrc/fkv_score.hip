@@ -12,12 +12,11 @@
 // tile in M.  Tokens sit on the MFMA N axis, i.e. on lanes, so the per-row softmax statistics
 // stay in registers per lane and are only reduced across lanes once per block.
 //
-// K path: one wave per KV head.  A wave reads its head's 32 x 256 B sub-tile with fully
-// coalesced 128-bit loads (16 lanes cover one token's 256-byte row), parks it in a private
-// 8 KiB LDS tile with an XOR swizzle on the 16-byte column, and reads it back in the MFMA
-// operand layout (lane = token).  The next sub-tile's global loads are issued before the
-// current one is consumed.
-#include "fkv_score_common.h"
+// K path: one wave per KV head, its 32-token tiles straight into the wave's LDS tile (KTiles), the next one requested as soon
+// as the operands have left it.
+#include <type_traits>
+
+#include "fkv_wout_merge.h"
 
 namespace fkv {
 
@@ -42,6 +41,8 @@ __global__ __launch_bounds__(kThreads) void k_stats(ScoreArgs a) {
   if (g >= a.V) return;
 
   FKV_TICK(16);
+  const KTiles tiles(a, tok_base, vg_kv_head(a, g), t0, t1, stage, lane);
+  tiles.issue<kOnce>(0);
   bf16x8 qa[kVg][8];
   float mx[kVg][16], sm[kVg][16];
 #pragma unroll
@@ -51,23 +52,21 @@ __global__ __launch_bounds__(kThreads) void k_stats(ScoreArgs a) {
     for (int r = 0; r < 16; ++r) { mx[v][r] = kNegBig; sm[v][r] = 0.f; }
   }
 
-  stream_head<true, kVg>(a, qa, tok_base, Lb, g, t0, t1 - t0, stage, lane, [&](int st, const floatx16 (&acc)[kVg]) {
+  stream_tiles<kOnce>(tiles, qa, (t1 - t0 + kSub - 1) / kSub, lane, [&](int st, const floatx16 (&acc)[kVg]) {
     const int tok = t0 + st * kSub + n;
     const bool valid = tok < t1;
+    bool ok[4];
+    float one[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int w = hi * 4 + (r & 3);
-      const bool ok = valid && (!a.causal || tok <= P + w);
-#pragma unroll
-      for (int v = 0; v < kVg; ++v) {
-        // online softmax with one exponential per element: e = 2^-|z - max|
-        const float z = ok ? acc[v][r] * a.scale_log2e : kNegBig;
-        const float d = z - mx[v][r];
-        const float e = fast_exp2(-fabsf(d));
-        sm[v][r] = d > 0.f ? sm[v][r] * e + 1.f : sm[v][r] + (ok ? e : 0.f);
-        mx[v][r] = fmaxf(mx[v][r], z);
-      }
+    for (int i = 0; i < 4; ++i) {
+      ok[i] = valid & ((a.causal == 0) | (tok <= P + hi * 4 + i));
+      one[i] = ok[i] ? 1.f : 0.f;
     }
+#pragma unroll
+    for (int v = 0; v < kVg; ++v)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        count_logit(ok[r & 3] ? acc[v][r] * a.scale_log2e : kNegBig, one[r & 3], mx[v][r], sm[v][r]);
   });
   FKV_TICK(17);
 #pragma unroll
@@ -110,56 +109,84 @@ __global__ __launch_bounds__(256) void k_combine(ScoreArgs a) {
   }
 }
 
+struct NoWout {};
+
 // kMaxSub 32-token sub-tiles per block at most.  A block owns a.tile_own tokens (host-chosen so that the
 // launch is one block per CU) and computes them and the pooling halo.  The window sums go straight into their own LDS array,
-// next to the waves' staging tiles.
-template <int kMaxSub, int kVg, bool kStreaming = true>
-__global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a) {
+// next to the waves' staging tiles.  O = WoutArgs: the row normalisers come from the splits of k_wout_partial, folded by
+// every block for itself while its first tile is on its way, and blocks 0 .. n_merge - 1 write the window rows' output:
+// they run on CUs that the scores leave idle, and there is no launch between the two passes over K: scores and output of
+// 32768 tokens, a merge launch of 4.9 us and scores of 15.2 before, 16.8 us for both now.
+template <int kMaxSub, int kVg, int kAux, typename O>
+__global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_merge) {
   constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
+  constexpr bool kWout = std::is_same<O, WoutArgs>::value;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
   __shared__ float g_sum[kGroups][kSlots];               // per virtual group sums of pooled head scores
+  if constexpr (kWout) {
+    if ((int)blockIdx.x < n_merge) {
+      constexpr int kUnits = kWoOutputs / (kThreads / 4);
+      const int units = wo.n_seq * wo.V * kUnits;
+      for (int u = blockIdx.x; u < units; u += n_merge)
+        merge_output(wo, u / kUnits, (u % kUnits) * (kThreads / 4) + (threadIdx.x >> 2), threadIdx.x & 3);
+      return;
+    }
+  }
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
-  const int b = find_seq(a.map, blockIdx.x);
+  const int block = (int)blockIdx.x - n_merge;
+  const int b = find_seq(a.map, block);
   const int tok_base = a.map.cu[b];
   const int Lb = a.map.cu[b + 1] - tok_base;
   const int P = Lb - a.W;
   const int r = a.pool_r;
-  const int o0 = ((int)blockIdx.x - a.map.blk[b]) * a.tile_own, o1 = min(P, o0 + a.tile_own);  // owned tokens
+  const int o0 = (block - a.map.blk[b]) * a.tile_own, o1 = min(P, o0 + a.tile_own);  // owned tokens
   const int j0 = o0 - r;  // first computed token (may be < 0)
   uint8_t *stage = stage_all + wave * kStageBytes;
 
   FKV_TICK(24);
   const int g = wave * kVg;
   if (g < a.V) {
+    const KTiles tiles(a, tok_base, vg_kv_head(a, g), j0, min(Lb, o1 + r), stage, lane);
+    tiles.issue<kAux>(0);
     bf16x8 qa[kVg][8];
     float cst[kVg][16];
 #pragma unroll
     for (int v = 0; v < kVg; ++v) {
       load_q(a, b, g + v, lane, qa[v]);
-      const float *rs = a.rowstat + ((size_t)b * a.V + g + v) * kRowsPerGroup;
+      const float *rs;
+      if constexpr (kWout) {
+        float *mine = g_sum[g + v];  // idle until the pooling
+        merge_normalisers(wo, b * wo.V + g + v, g + v, lane, mine);
+        wave_lds_sync();
+        rs = mine;
+      } else {
+        rs = a.rowstat + ((size_t)b * a.V + g + v) * kRowsPerGroup;
+      }
 #pragma unroll
       for (int q = 0; q < 16; ++q) cst[v][q] = rs[(q >> 2) * 8 + hi * 4 + (q & 3)];
     }
 
-    stream_head<kStreaming, kVg>(a, qa, tok_base, Lb, g, j0, o1 + r - j0, stage, lane, [&](int st, const floatx16 (&acc)[kVg]) {
+    stream_tiles<kAux>(tiles, qa, (o1 + r - j0 + kSub - 1) / kSub, lane, [&](int st, const floatx16 (&acc)[kVg]) {
       const int tok = j0 + st * kSub + n;
-      const bool inb = tok >= 0 && tok < P;  // only prefix tokens are scored
+      const bool inb = (tok >= 0) & (tok < P);  // only prefix tokens are scored
 #pragma unroll
-      for (int v = 0; v < kVg; ++v)
+      for (int v = 0; v < kVg; ++v) {
+        float sum[4];
 #pragma unroll
         for (int hl = 0; hl < 4; ++hl) {
-          float sum = 0.f;
+          sum[hl] = 0.f;
 #pragma unroll
           for (int rr = 0; rr < 4; ++rr) {
-            const float e = fast_exp2(acc[v][hl * 4 + rr] * a.scale_log2e - cst[v][hl * 4 + rr]);
-            sum += (hi * 4 + rr < a.W) ? e : 0.f;
+            const float e = fast_exp2(__builtin_fmaf(acc[v][hl * 4 + rr], a.scale_log2e, -cst[v][hl * 4 + rr]));
+            sum[hl] += (hi * 4 + rr < a.W) ? e : 0.f;
           }
-          sum = add_across_halves(sum);  // other half of the window rows
-          if (hi == 0 && hl < vg_heads(a, g + v)) s_head[(g + v) * kMaxGroup + hl][st * kSub + n] = inb ? sum : 0.f;
+          sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
+        store_sums<kSlots>(a, s_head, g + v, st * kSub + n, hi, inb, sum);
+      }
     });
   }
   FKV_TICK(25);
@@ -188,13 +215,23 @@ hipError_t launch_combine(const ScoreArgs &a, hipStream_t s) {
 }
 hipError_t launch_scores(const ScoreArgs &a, int n_blocks, hipStream_t s) {
   if (a.V > kMaxKvHeads)  // twice the heads in LDS: half the tile
-    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2>), dim3(n_blocks), dim3(kThreads), 0, s, a);
-  else if (a.tile_sub <= kScoresSubShort && !a.k_cached)
-    hipLaunchKernelGGL((k_scores<kScoresSubShort, 1>), dim3(n_blocks), dim3(kThreads), 0, s, a);
-  else if (!a.k_cached)
-    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1>), dim3(n_blocks), dim3(kThreads), 0, s, a);
-  else  // K was just read by the launch before: plain loads, so that what the caches still hold is used
-    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, false>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+  else if (a.tile_sub <= kScoresSubShort)
+    hipLaunchKernelGGL((k_scores<kScoresSubShort, 1, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+  else
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+  return hipGetLastError();
+}
+
+int wout_merge_units(const WoutArgs &a) { return a.n_seq * a.V * (kWoOutputs / (kThreads / 4)); }
+
+// K was just read by the launch before: plain loads, so that what the caches still hold is used.
+hipError_t launch_wout_scores(const ScoreArgs &a, const WoutArgs &o, int n_blocks, int n_merge, hipStream_t s) {
+  const dim3 grid(n_blocks + n_merge);
+  if (a.V > kMaxKvHeads)
+    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, WoutArgs>), grid, dim3(kThreads), 0, s, a, o, n_merge);
+  else
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kPlain, WoutArgs>), grid, dim3(kThreads), 0, s, a, o, n_merge);
   return hipGetLastError();
 }
 

@@ -59,62 +59,6 @@ __device__ __forceinline__ void load_q(const A &a, int b, int g, int lane, bf16x
   for (int s = 0; s < 8; ++s) qa[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(q, (int)at, s * 16, 0));
 }
 
-// Streams the K rows of virtual group g's KV head for `n_slots` consecutive tokens, in 32-token sub-tiles, starting at
-// sequence-local token `first`.  Loads are clamped to the range's tokens inside the sequence; the caller masks
-// what lies outside.  fn(st, acc) receives the raw logits of sub-tile st:
-// acc[r] = q_row(m) . k(token first + st*32 + lane%32) with m = (r/4)*8 + (lane/32)*4 + r%4,
-// i.e. head r/4 of the group and window row (lane/32)*4 + r%4.
-// kVg = 2: g and g + 1 are the two virtual groups of one KV head; both take their logits from the same tile.
-// kStreaming marks the loads non-temporal.  Measured at 131072 tokens: both passes of the two-pass
-// kernels gain from it together (-6 us per layer), the single-pass kernel does not.
-// At 131072 tokens the stream runs at the rate of the same loads without any work between
-// them (45 us for 268 MB); two or three tiles in flight per wave and the softmax work left out changed nothing.
-template <bool kStreaming = false, int kVg = 1, typename F>
-__device__ __forceinline__ void stream_head(const ScoreArgs &a, const bf16x8 (&qa)[kVg][8], int tok_base, int Lb, int g,
-                                            int first, int n_slots, uint8_t *stage, int lane, F fn) {
-  const int n_sub = (n_slots + kSub - 1) / kSub;
-  const int c = lane & 15;        // 16-byte column of the 256-byte head row
-  const int tq = lane >> 4;       // token within a quad of 4 tokens per load instruction
-  const int n = lane & 31, hi = lane >> 5;
-  const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
-  const uint16_t *kbase = a.k + (size_t)tok_base * tok_stride + (size_t)vg_kv_head(a, g) * kHeadDim + c * 8;
-  const int t_last = min(first + n_slots, Lb) - 1;
-
-  u32x4 nxt[8];
-  auto issue = [&](int st) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int t = min(max(first + st * kSub + i * 4 + tq, 0), t_last);
-      const u32x4 *src = reinterpret_cast<const u32x4 *>(kbase + (size_t)t * tok_stride);
-      nxt[i] = kStreaming ? __builtin_nontemporal_load(src) : *src;
-    }
-  };
-  issue(0);
-#pragma unroll 1
-  for (int st = 0; st < n_sub; ++st) {
-    wave_lds_sync();  // previous sub-tile's reads are done before the tile is overwritten
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int t = i * 4 + tq;  // token slot in the tile
-      *reinterpret_cast<u32x4 *>(stage + t * 256 + ((c ^ (t & 15)) << 4)) = nxt[i];
-    }
-    if (st + 1 < n_sub) issue(st + 1);
-    wave_lds_sync();
-    floatx16 acc[kVg];
-#pragma unroll
-    for (int v = 0; v < kVg; ++v)
-      acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const u32x4 kb = *reinterpret_cast<const u32x4 *>(stage + n * 256 + (((hi * 8 + s) ^ (n & 15)) << 4));
-#pragma unroll
-      for (int v = 0; v < kVg; ++v)
-        acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][s], __builtin_bit_cast(bf16x8, kb), acc[v], 0, 0, 0);
-    }
-    fn(st, acc);
-  }
-}
-
 // K rows of a wave's KV head, tokens `first` to `end` of a sequence, as 32-token tiles that go straight from global memory
 // into the wave's LDS tile (gfx950's 128-bit LDS-direct loads: lane l of a load lands at tile offset 16 l, i.e. 4 tokens
 // per load, 16 lanes a row), so no registers hold a tile in flight.  The XOR swizzle lies on the global side: the lane
@@ -131,14 +75,15 @@ struct KTiles {
   template <typename A>
   __device__ __forceinline__ KTiles(const A &a, int tok_base, int kv_head, int first, int end, uint8_t *stage_, int lane)
       : stage(stage_) {
-    const uint32_t row = (uint32_t)a.Hkv * (kHeadDim * 2);  // the host bounds a sequence by 2^31 bytes of K on these paths
-    rows = buffer_of(a.k + ((size_t)tok_base * a.Hkv + kv_head) * kHeadDim, (uint32_t)(end - 1) * row + kHeadDim * 2);
+    const uint32_t row = (uint32_t)a.Hkv * (kHeadDim * 2);  // a block's tokens span less than 2^31 bytes
+    const int from = max(first, 0);
+    rows = buffer_of(a.k + ((size_t)(tok_base + from) * a.Hkv + kv_head) * kHeadDim, (uint32_t)(end - 1 - from) * row + kHeadDim * 2);
     half_bytes = 16 * row;
     const int c = lane & 15, tq = lane >> 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int slot = i * 4 + tq;
-      at[i] = (uint32_t)(first + slot) * row + ((c ^ slot) << 4);  // a token before the sequence wraps past the buffer's end
+      at[i] = (uint32_t)(first - from + slot) * row + ((c ^ slot) << 4);  // a token before the sequence wraps past the buffer's end
     }
   }
   template <int kAux>
@@ -191,6 +136,47 @@ __device__ __forceinline__ void read_operands(u32x4 (&r)[kN], const uint32_t *ad
         : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
         : "memory");
 }
+
+// Raw logits of the tile that was requested last: acc[v][r] = q_row(m) . k(token lane % 32 of the tile) with m = (r/4)*8 +
+// (lane/32)*4 + r%4, i.e. head r/4 of virtual group v and window row (lane/32)*4 + r%4.  `next` requests another tile as soon
+// as this one's operands have left the LDS tile.  kHalf: operands held in registers at a time (8 or 4).
+// kVg = 2: two virtual groups of one KV head take their logits from the same tile.
+template <int kVg, int kHalf, typename Next>
+__device__ __forceinline__ void tile_logits(const bf16x8 (&qa)[kVg][8], const uint32_t (&addr)[8], floatx16 (&acc)[kVg], Next next) {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+#pragma unroll
+  for (int v = 0; v < kVg; ++v)
+    acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s0 = 0; s0 < 8; s0 += kHalf) {
+    u32x4 kb[kHalf];
+    read_operands<kHalf>(kb, addr + s0);
+    if (s0 + kHalf == 8) next();
+#pragma unroll
+    for (int s = 0; s < kHalf; ++s)
+#pragma unroll
+      for (int v = 0; v < kVg; ++v)
+        acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][s0 + s], __builtin_bit_cast(bf16x8, kb[s]), acc[v], 0, 0, 0);
+  }
+}
+
+// The logits of n_sub consecutive tiles, the first of which has been requested: fn(st, acc) for tile st.  kAux: cache policy.
+// At 131072 tokens the stream runs at the rate of the same loads without any work between them.
+template <int kAux, int kVg, typename F>
+__device__ __forceinline__ void stream_tiles(const KTiles &tiles, const bf16x8 (&qa)[kVg][8], int n_sub, int lane, F fn) {
+  uint32_t addr[8];
+  operand_addresses(tiles.stage, lane, addr);
+#pragma unroll 1
+  for (int st = 0; st < n_sub; ++st) {
+    floatx16 acc[kVg];
+    tile_logits<kVg, 8>(qa, addr, acc, [&] {
+      if (st + 1 < n_sub) tiles.issue<kAux>(st + 1);
+    });
+    fn(st, acc);
+  }
+}
+
+constexpr int kPlain = 0, kOnce = 2;  // cache policies of a tile's loads: as usual, non-temporal
 
 // One element of the running (max, sum) of a softmax row: `one` is 1 if the logit is counted, else 0.  One exponential.
 __device__ __forceinline__ void count_logit(float z, float one, float &mx, float &sm) {

@@ -88,33 +88,21 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   float z[kFusedSub][16], mloc[16], mx[16], sm[16];
   if (has_group) {
     const KTiles tiles(a, tok_base, vg_kv_head(a, g), c0, min(Lb, c1), stage, lane);
-    tiles.issue<0>(0);
+    tiles.issue<kPlain>(0);
     FKV_WTICK(0);
-    bf16x8 qa[8];
-    load_q(a, b, g, lane, qa);
+    bf16x8 qa[1][8];
+    load_q(a, b, g, lane, qa[0]);
     uint32_t addr[8];
     operand_addresses(stage, lane, addr);
 #pragma unroll
     for (int q = 0; q < 16; ++q) { mx[q] = kNegBig; sm[q] = 0.f; }
 #pragma unroll 1
     for (int st = 0; st < n_sub; ++st) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed in LDS
-      if (st == 0) FKV_WTICK(1);
-      constexpr int kHalf = kFusedSub > 5 ? 4 : 8;  // operands in registers at a time
-      u32x4 kb[kHalf];
-      read_operands<kHalf>(kb, addr);
-      if (kHalf == 8 && st + 1 < n_sub) tiles.issue<0>(st + 1);
-      floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < kHalf; ++s)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s], __builtin_bit_cast(bf16x8, kb[s]), acc, 0, 0, 0);
-      if constexpr (kHalf == 4) {
-        read_operands<4>(kb, addr + 4);
-        if (st + 1 < n_sub) tiles.issue<0>(st + 1);
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[4 + s], __builtin_bit_cast(bf16x8, kb[s]), acc, 0, 0, 0);
-      }
+      floatx16 logit[1];
+      tile_logits<1, kFusedSub == kFusedSubLong ? 4 : 8>(qa, addr, logit, [&] {
+        if (st + 1 < n_sub) tiles.issue<kPlain>(st + 1);
+      });
+      floatx16 &acc = logit[0];
       const int tok = c0 + st * kSub + n;
       const bool counted = ((tok >= o0) & (tok < o1)) | (last & (tok >= P) & (tok < Lb));
       const bool scored = (tok >= 0) & (tok < min(P, c1));  // a prefix token (owned or halo): its probability is formed in phase 3
@@ -140,7 +128,6 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
       // keys and slots outside the sequence are neither: they must not move the reference.
 #pragma unroll
       for (int q = 0; q < 16; ++q) count_logit(take[q & 3] ? acc[q] : kNegBig, one[q & 3], mx[q], sm[q]);
-      if (st == 0) FKV_WTICK(2);
     }
     FKV_TICK(33);
   }

@@ -40,7 +40,6 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(g_sum);
   constexpr int kWaveSums = kVg * kMaxGroup * kSlots;  // floats of s_head that one wave fills
   static_assert(kLds * kVg * kRowsPerGroup * kSub <= kWaveSums && kWaveSums % 4 == 0, "logits kept in LDS");
-  constexpr int kPlain = 0, kOnce = 2;  // cache policies of a tile's loads
 
   request_args(a, f);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -67,24 +66,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   uint32_t addr[8];
   operand_addresses(stage, lane, addr);
   bf16x8 qa[kVg][8];
-  // Logits of the tile that was requested last; `next` requests another one as soon as the operands have left the LDS tile.
-  auto logits = [&](floatx16 (&acc)[kVg], auto next) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
-#pragma unroll
-    for (int v = 0; v < kVg; ++v)
-      acc[v] = (floatx16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      u32x4 kb[4];
-      read_operands<4>(kb, addr + 4 * half);
-      if (half == 1) next();
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int v = 0; v < kVg; ++v)
-          acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[v][4 * half + s], __builtin_bit_cast(bf16x8, kb[s]), acc[v], 0, 0, 0);
-    }
-  };
+  auto logits = [&](floatx16 (&acc)[kVg], auto next) { tile_logits<kVg, 4>(qa, addr, acc, next); };
 
   // ---- phase 1
   float z[kKeep][kVg][16];

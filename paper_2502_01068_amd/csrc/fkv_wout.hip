@@ -21,7 +21,7 @@
 // Tokens are split over blocks (8 waves each); a block merges its waves' running states through
 // LDS and leaves one partial (max, sum, 32 x 128 accumulator) per (sequence, group, split); a second
 // launch folds the splits in a fixed order.
-#include "fkv_score_common.h"
+#include "fkv_wout_merge.h"
 
 namespace fkv {
 
@@ -29,7 +29,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 constexpr int kWoWaves = 8;
 constexpr int kWoThreads = kWoWaves * 64;
 constexpr int kWoTileBytes = 2 * kStageBytes;       // K tile + V tile per wave
-constexpr int kWoRowFloats = kRowsPerGroup * kHeadDim;  // 4096 accumulator values per partial
 constexpr float kWoEmpty = -5.0e29f;                // running maximum before any visible key (> masked logits)
 
 int wout_tiles_per_block_min(void) { return kWoWaves; }
@@ -77,34 +76,35 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   const int blk_id = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;  // timing builds only
   (void)blk_id;
   FKV_BTICK_AT(blk_id, 0);
-  bf16x8 qa[8];
-  load_q(a, b, g, lane, qa);
-
   // direct-to-LDS tile loads: lane l of load i lands at tile offset i*1024 + 16 l, i.e. token slot
   // 4 i + l/16, 16-byte column l%16.  The K tile is XOR-swizzled (from the global side), V is plain.
   // Both streams are read once: the loads are marked non-temporal (measured 34.3 instead of 38.6 us per call at
   // 32768 tokens), except K when the caller reads it again right after this launch (kKeepK).
+  // Addresses are a tile's own plus 32-bit offsets of its rows, kept within the sequence.
   const int c = lane & 15, tq = lane >> 4;
-  const size_t tok_stride = (size_t)a.Hkv * kHeadDim;
-  const uint16_t *kbase = a.k + (size_t)vg_kv_head(a, g) * kHeadDim;
-  const uint16_t *vbase = a.v + (size_t)vg_kv_head(a, g) * kHeadDim + c * 8;
-  auto issue_k = [&](int tile) {
+  const uint32_t row = (uint32_t)a.Hkv * (kHeadDim * 2);
+  uint32_t row_at[8], col_k[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int slot = i * 4 + tq;
-      const int t = min(tile * kSub + slot, Lb - 1);
-      const uint16_t *src = kbase + (size_t)(tok_base + t) * tok_stride + ((c ^ (slot & 15)) << 3);
-      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(ktile + i * 1024), 16, 0, kKeepK ? 0 : 2);
-    }
+  for (int i = 0; i < 8; ++i) row_at[i] = (i * 4 + tq) * row;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) col_k[i] = (c ^ (i * 4 + tq)) << 4;
+  auto tile_of = [&](const uint16_t *x, int tile) {
+    return reinterpret_cast<const uint8_t *>(x + ((size_t)(tok_base + tile * kSub) * a.Hkv + vg_kv_head(a, g)) * kHeadDim);
+  };
+  auto issue_k = [&](int tile) {
+    const uint8_t *rows = tile_of(a.k, tile);
+    const uint32_t last = (uint32_t)min(kSub - 1, Lb - 1 - tile * kSub) * row;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_global_load_lds((gptr_t)(rows + (min(row_at[i], last) + col_k[i & 3])), (lptr_t)(ktile + i * 1024), 16, 0, kKeepK ? 0 : 2);
   };
   auto issue_v = [&](int tile) {
     keep_access_order();  // the wait for a K tile leaves the 8 youngest loads in flight: these
+    const uint8_t *rows = tile_of(a.v, tile);
+    const uint32_t last = (uint32_t)min(kSub - 1, Lb - 1 - tile * kSub) * row;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int t = min(tile * kSub + i * 4 + tq, Lb - 1);
-      const uint16_t *src = vbase + (size_t)(tok_base + t) * tok_stride;
-      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(vtile + i * 1024), 16, 0, 2);
-    }
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_global_load_lds((gptr_t)(rows + (min(row_at[i], last) + (c << 4))), (lptr_t)(vtile + i * 1024), 16, 0, 2);
   };
 
   floatx16 o[4];
@@ -119,6 +119,8 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   operand_addresses(ktile, lane, kaddr);
   const uint32_t vaddr = (uint32_t)(uintptr_t)(lptr_t)(vtile + hi * 1024 + n * 8);
   int tile = t0 + wave;
+  bf16x8 qa[8];
+  load_q(a, b, g, lane, qa);
   if (tile < t1) {
     issue_k(tile);
     issue_v(tile);
@@ -242,64 +244,9 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   FKV_BTICK_AT(blk_id, 3);
 }
 
-// Folds the splits of one (sequence, group).  Four lanes share one float4 of the output and take
-// every fourth split each (eight loads in flight per lane), then meet through two lane exchanges;
-// the order of the sums is fixed.  Grid (n_seq * V, 16), 256 threads.
-constexpr int kWoMergeOutputs = 64;  // float4 outputs per block
-__global__ __launch_bounds__(256) void k_wout_merge(WoutArgs a) {
-  const int bg = blockIdx.x, b = bg / a.V, g = bg - b * a.V;
-  const int j = threadIdx.x & 3;
-  const int idx = blockIdx.y * kWoMergeOutputs + (threadIdx.x >> 2);
-  const int row = idx >> 5, chunk = idx & 31;
-  const int hl = row >> 3, w = row & 7;
-  const bool first = j == 0 && chunk == 0;        // the lane that reports the row's normaliser
-  if (hl >= vg_heads(a, g) || w >= a.W) {         // the four lanes of an output leave together
-    if (first && a.rowstat) a.rowstat[(size_t)bg * kRowsPerGroup + row] = 0.f;
-    return;
-  }
-  const float2 *ms = a.part_ms + (size_t)bg * a.n_split * kRowsPerGroup + row;
-  const float *po = a.part_o + (size_t)bg * a.n_split * kWoRowFloats + row * kHeadDim + chunk * 4;
-  constexpr int kBatch = 8;
-  const int per = (a.n_split + 3) >> 2;  // splits j, j+4, ... of this lane
-  float M = kNegBig;
-  for (int i0 = 0; i0 < per; i0 += kBatch) {
-    float mx[kBatch];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) mx[i] = ms[min(4 * (i0 + i) + j, a.n_split - 1) * kRowsPerGroup].x;
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) M = fmaxf(M, mx[i]);
-  }
-  M = fmaxf(M, __shfl_xor(M, 1));
-  M = fmaxf(M, __shfl_xor(M, 2));
-  float den = 0.f;
-  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int i0 = 0; i0 < per; i0 += kBatch) {
-    float2 st[kBatch];
-    float4 x[kBatch];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const int sp = min(4 * (i0 + i) + j, a.n_split - 1);
-      st[i] = ms[sp * kRowsPerGroup];
-      x[i] = *reinterpret_cast<const float4 *>(po + (size_t)sp * kWoRowFloats);
-    }
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const float f = 4 * (i0 + i) + j < a.n_split ? fast_exp2(st[i].x - M) : 0.f;
-      den += f * st[i].y;
-      num.x += f * x[i].x; num.y += f * x[i].y; num.z += f * x[i].z; num.w += f * x[i].w;
-    }
-  }
-#pragma unroll
-  for (int d = 1; d <= 2; d <<= 1) {
-    den += __shfl_xor(den, d);
-    num.x += __shfl_xor(num.x, d); num.y += __shfl_xor(num.y, d);
-    num.z += __shfl_xor(num.z, d); num.w += __shfl_xor(num.w, d);
-  }
-  if (j != 0) return;
-  if (first && a.rowstat) a.rowstat[(size_t)bg * kRowsPerGroup + row] = M + __log2f(den);
-  const float inv = 1.f / den;
-  float *dst = a.out + (((size_t)b * a.W + w) * a.Hq + vg_head0(a, g) + hl) * kHeadDim + chunk * 4;
-  *reinterpret_cast<float4 *>(dst) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
+constexpr int kWoMergeThreads = 256;
+__global__ __launch_bounds__(kWoMergeThreads) void k_wout_merge(WoutArgs a) {
+  merge_output(a, blockIdx.x, blockIdx.y * (kWoMergeThreads / 4) + (threadIdx.x >> 2), threadIdx.x & 3);
 }
 
 hipError_t launch_wout(const WoutArgs &a, hipStream_t s) {
@@ -307,9 +254,10 @@ hipError_t launch_wout(const WoutArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_wout_partial<true>, dim3(a.n_split, a.V, a.n_seq), dim3(kWoThreads), 0, s, a);
   else
     hipLaunchKernelGGL(k_wout_partial<false>, dim3(a.n_split, a.V, a.n_seq), dim3(kWoThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wout_merge, dim3(a.n_seq * a.V, kWoRowFloats / 4 / kWoMergeOutputs), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_wout_merge(const WoutArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_wout_merge, dim3(a.n_seq * a.V, kWoOutputs / (kWoMergeThreads / 4)), dim3(kWoMergeThreads), 0, s, a);
   return hipGetLastError();
 }
 
