@@ -66,6 +66,23 @@ __device__ __forceinline__ void read_k_tile(u32x4 (&r)[8], const uint32_t (&addr
       : "memory");
 }
 
+// A lane's four operands from the queries in LDS, whose loads lie ahead of a tile of K and one of V (16 loads).
+__device__ __forceinline__ void read_queries(bf16x8 (&qb)[4], uint32_t addr, bool live) {
+  u32x4 r[4];
+  asm volatile(
+      "s_waitcnt vmcnt(16)\n\t"
+      "ds_read_b128 %0, %4\n\t"
+      "ds_read_b128 %1, %4 offset:64\n\t"
+      "ds_read_b128 %2, %4 offset:128\n\t"
+      "ds_read_b128 %3, %4 offset:192\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+      : "v"(addr)
+      : "memory");
+#pragma unroll
+  for (int s = 0; s < 4; ++s) qb[s] = __builtin_bit_cast(bf16x8, live ? r[s] : u32x4{0u, 0u, 0u, 0u});
+}
+
 // The sum a row is divided by.  Zero: no token has a finite logit and the softmax no value; NaN then, and not what the
 // kept-up pieces of the probabilities (see k_decode) divided by zero would give.
 __device__ __forceinline__ float row_sum(float l) { return l > 0.f ? l : __uint_as_float(0x7FC00000u); }
@@ -87,8 +104,12 @@ __device__ __forceinline__ float2 agent_load2(const float *p) {
 // The work of a launch is a line of 32-token tiles, row after row (a row = one KV head of one sequence); block i
 // of N takes tiles [i T / N, (i + 1) T / N).  A row that lies inside one block is finished there; the pieces of a row
 // that is cut go to partial slots, at most two per block (2 i: a piece that does not begin its row, 2 i + 1: one that does).
-__device__ __forceinline__ int64_t dec_first_tile(int64_t block, int64_t tiles, int64_t n_blocks) { return block * tiles / n_blocks; }
-__device__ __forceinline__ int dec_block_of(int64_t tile, int64_t tiles, int64_t n_blocks) {
+// T < 2^30; the products of these bounds are not, so they are formed from quotient and remainder.
+__device__ __forceinline__ uint32_t share_at(uint32_t len, uint32_t part, uint32_t parts) {  // len * part / parts
+  const uint32_t per = len / parts, rem = len - per * parts;
+  return part * per + part * rem / parts;
+}
+__device__ __forceinline__ int dec_block_of(uint64_t tile, uint64_t tiles, uint64_t n_blocks) {
   return (int)(((tile + 1) * n_blocks - 1) / tiles);
 }
 
@@ -101,29 +122,35 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t k_lds[kWaves][kTileBytes];
   __shared__ __attribute__((aligned(16))) float o_lds[kWaves][kMaxReal][kHeadDim];
   __shared__ float m_lds[kWaves][16], l_lds[kWaves][16];
-  __shared__ float w_lds[kMaxReal][kDecodeMaxSplits];
   __shared__ unsigned last_lds;
   typedef __attribute__((address_space(1))) const void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, q = lane >> 4;
   const int G = a.G;
-  const int64_t n_blocks = gridDim.x;
-  int b = 0;
-  int64_t at, at_end;
-  int n_piece = 1, piece_blk0 = 0;  // kAligned: pieces of the row and the block of its first one
+  // 64-bit divisions in front of the first load took 400 instructions, and a search of the sequence entry by entry 0.15 us a step.
+  int b = 0, at, at_end;
+  int n_piece = 1, piece_blk0 = 0, kvh0 = 0;  // kAligned: pieces of the row, the block of its first one, its KV head
   if (kAligned) {
-    while ((int)blockIdx.x >= a.piece0[b + 1] * a.Hkv) ++b;
+    const int unit = (int)((uint32_t)blockIdx.x / (uint32_t)a.Hkv);  // pieces before this one, KV heads left aside
+    for (int i = 1; i < a.n_seq && b == i - 1; i += 8) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) b += (i + j < a.n_seq) & (unit >= a.piece0[i + j]);
+    }
     n_piece = a.piece0[b + 1] - a.piece0[b];
-    const int rel = (int)blockIdx.x - a.piece0[b] * a.Hkv, p = rel / a.Hkv, kvh = rel - p * a.Hkv;
+    const int p = unit - a.piece0[b];
+    kvh0 = (int)blockIdx.x - unit * a.Hkv;
     piece_blk0 = (int)blockIdx.x - p * a.Hkv;
     const int len = a.tile0[b + 1] - a.tile0[b];
-    const int64_t row_at = (int64_t)a.tile0[b] * a.Hkv + (int64_t)kvh * len;
-    at = row_at + (int64_t)len * p / n_piece;
-    at_end = row_at + (int64_t)len * (p + 1) / n_piece;
+    at = 0;
+    at_end = len;
+    if (n_piece > 1) {
+      at = (int)share_at(len, p, n_piece);
+      at_end = (int)share_at(len, p + 1, n_piece);
+    }
   } else {
-    at = dec_first_tile(blockIdx.x, a.tiles, n_blocks);
-    at_end = dec_first_tile((int64_t)blockIdx.x + 1, a.tiles, n_blocks);
+    at = (int)share_at(a.tiles, blockIdx.x, gridDim.x);
+    at_end = (int)share_at(a.tiles, blockIdx.x + 1, gridDim.x);
   }
   uint8_t *stage = k_lds[wave];
   // Row c of the first contraction's A operand is token 4 (c % 4) + c / 4 of a half tile, so that row 4 q + r of
@@ -135,28 +162,35 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 
   while (at < at_end) {
     // ---- the piece [tile0, tile1) of row (b, kvh)
-    while (at >= (int64_t)a.tile0[b + 1] * a.Hkv) ++b;
+    int row_at = 0, kvh = kvh0;  // kAligned: `at` counts from the row's first tile
+    if (!kAligned) {
+      while (at >= a.tile0[b + 1] * a.Hkv) ++b;
+    }
     const int row_tiles = a.tile0[b + 1] - a.tile0[b];
-    const int64_t seq_at = (int64_t)a.tile0[b] * a.Hkv;
-    const int kvh = (int)((at - seq_at) / row_tiles);
-    const int64_t row_at = seq_at + (int64_t)kvh * row_tiles;
-    const int tile0 = (int)(at - row_at), tile1 = (int)min((int64_t)row_tiles, at_end - row_at);
+    if (!kAligned) {
+      const int seq_at = a.tile0[b] * a.Hkv;
+      kvh = (int)((uint32_t)(at - seq_at) / (uint32_t)row_tiles);
+      row_at = seq_at + kvh * row_tiles;
+    }
+    const int tile0 = at - row_at, tile1 = min(row_tiles, at_end - row_at);
     const int n = a.off[b + 1] - a.off[b];
 
-    // B operand of the first contraction: head n = c, columns 8 (4 s + q) .. + 7 in step s
-    bf16x8 qb[4];
+    // The row's queries (8 rows of 256 B, those the group does not have are not read) go to the wave's part of o_lds, idle until
+    // the end, ahead of the loads of K and V and in the same order: loaded into registers, the compiler would wait for them
+    // together with everything requested.
+    uint8_t *q_lds = reinterpret_cast<uint8_t *>(&o_lds[wave][0][0]);
     {
-      const u32x4 *src = reinterpret_cast<const u32x4 *>(a.q + ((size_t)b * a.Hq + (size_t)kvh * G + (c < G ? c : 0)) * kHeadDim) + q;
+      const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.q + ((size_t)b * a.Hq + (size_t)kvh * G) * kHeadDim), 0,
+                                                          G * kHeadDim * 2, 0x00027000);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        u32x4 w = src[4 * s];
-        if (c >= G) w = (u32x4){0u, 0u, 0u, 0u};
-        qb[s] = __builtin_bit_cast(bf16x8, w);
-      }
+      for (int i = 0; i < 2; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lptr_t)(q_lds + i * 1024), 16, i * 1024 + lane * 16, 0, 0, 0);
+      keep_access_order();  // read_queries waits for all but the 16 youngest loads: a tile of K and one of V
     }
     const size_t first = kPaged ? 0 : (size_t)a.off[b];  // a paged sequence is addressed through its block table
-    const uint16_t *kb = a.k + (size_t)kvh * a.head_stride + first * a.tok_stride;
-    const uint16_t *vb = a.v + (size_t)kvh * a.head_stride + first * a.tok_stride + c * 8;
+    typedef __attribute__((address_space(1))) const uint8_t *rows_t;
+    const rows_t kb = (rows_t)(a.k + (size_t)kvh * a.head_stride + first * a.tok_stride);
+    const rows_t vb = (rows_t)(a.v + (size_t)kvh * a.head_stride + first * a.tok_stride);
+    const uint32_t row = (uint32_t)a.tok_stride * 2;  // bytes of a token's row, at most 2 KiB
     const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
 
     // Page of this lane's token (lane % 32) of a tile; an entry outside the pool is clamped into it.
@@ -166,24 +200,40 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       return (min(max(page, 0), a.n_pages - 1) << a.page_shift) + (t & ((1 << a.page_shift) - 1));
     };
     u32x4 vr[8];
-    // Load i of a tile covers its tokens 4 i .. 4 i + 3, one per 16 lanes.  `slot`: page slots of the tile's
-    // tokens, one per lane (paged cache only).
-    auto token_of = [&](int i, int tile, int slot) {
-      return kPaged ? __shfl(slot, 4 * i + q) : min(tile * kDecTile + 4 * i + q, n - 1);
+    uint32_t slots[8];  // paged: page slots of the rows that this lane's loads touch
+    // Load i of a tile covers its tokens 4 i .. 4 i + 3, one per 16 lanes.  `slot`: page slots of the tile's tokens, one per lane
+    // (paged cache only).  Unpaged, an address is the tile's own plus a 32-bit offset within the row's end.
+    auto row_of = [&](rows_t base, int i, int tile, uint32_t column) {
+      if constexpr (kPaged) return base + (uint64_t)slots[i] * row + column;
+      const uint32_t last = (uint32_t)min(kDecTile - 1, n - 1 - tile * kDecTile) * row;
+      return base + (min((4 * i + q) * row, last) + column);
+    };
+    auto rows_of = [&](rows_t base, int tile) {
+      if constexpr (!kPaged) {
+        base += (size_t)tile * kDecTile * row;
+        asm("" : "+s"(base));  // else every load of the loop gets an address of its own, in two registers per lane
+      }
+      return base;
     };
     auto load_k = [&](int tile, int slot) {
+      const rows_t rows = rows_of(kb, tile);
+      if constexpr (kPaged) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint16_t *src = kb + (size_t)token_of(i, tile, slot) * a.tok_stride + ((c ^ ((4 * i + q) & 15)) << 3);
-        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stage + i * 1024), 16, 0, 2);
+        for (int i = 0; i < 8; ++i) slots[i] = (uint32_t)__shfl(slot, 4 * i + q);
       }
-    };
-    auto load_v = [&](int tile, int slot) {
-      keep_access_order();  // read_k_tile waits for all but the 8 youngest loads: these
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + (size_t)token_of(i, tile, slot) * a.tok_stride));
+        __builtin_amdgcn_global_load_lds((gptr_t)row_of(rows, i, tile, (c ^ ((4 * i + q) & 15)) << 4), (lptr_t)(stage + i * 1024), 16, 0, 2);
     };
+    auto load_v = [&](int tile) {  // of the tile that load_k was called for last
+      keep_access_order();  // read_k_tile waits for all but the 8 youngest loads: these
+      const rows_t rows = rows_of(vb, tile);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) vr[i] = __builtin_nontemporal_load((__attribute__((address_space(1))) const u32x4 *)row_of(rows, i, tile, c << 4));
+    };
+
+    // B operand of the first contraction: head n = c, columns 8 (4 s + q) .. + 7 in step s; zeros past the last head
+    bf16x8 qb[4];
 
     floatx4 o[8];
 #pragma unroll
@@ -200,7 +250,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         slot = slot_of(t, page);
       }
       load_k(t, slot);
-      load_v(t, slot);
+      load_v(t);
+      read_queries(qb, (uint32_t)(uintptr_t)(lptr_t)(q_lds + (c & 7) * 256 + q * 16), c < G);
     }
     // One tile; kMore: the loads of the wave's next one go out as their registers and LDS become free (a
     // compile-time flag: no branch around loads).  The compiler's own waits are longer than need be.  Ordinary loads
@@ -276,7 +327,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
           va[2 * w][i] = __builtin_amdgcn_perm(vr[2 * i + 1][w], vr[2 * i][w], 0x05040100u);
           va[2 * w + 1][i] = __builtin_amdgcn_perm(vr[2 * i + 1][w], vr[2 * i][w], 0x07060302u);
         }
-      if constexpr (kMore) load_v(tile + kWaves, slot);
+      if constexpr (kMore) load_v(tile + kWaves);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const bf16x8 vj = __builtin_bit_cast(bf16x8, va[j]);
@@ -335,8 +386,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     // ---- count this piece; the last one of the row folds them
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    const int blk0 = kAligned ? piece_blk0 : dec_block_of(row_at, a.tiles, n_blocks);
-    const int n_split = kAligned ? n_piece : dec_block_of(row_at + row_tiles - 1, a.tiles, n_blocks) - blk0 + 1;
+    const int blk0 = kAligned ? piece_blk0 : dec_block_of(row_at, a.tiles, gridDim.x);
+    const int n_split = kAligned ? n_piece : dec_block_of(row_at + row_tiles - 1, a.tiles, gridDim.x) - blk0 + 1;
     unsigned *count = a.count + b * kMaxKvHeads + kvh;
     if (tid == 0) {
       const unsigned old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -348,30 +399,31 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       // equal shares: piece p of the row lies in block blk0 + p; only the first one begins the row
       const float *src = a.part + 2 * (size_t)blk0 * kDecodeSlotFloats;
       auto piece = [&](int p) { return src + (size_t)(kAligned ? 2 * p * a.Hkv : p == 0 ? 1 : 2 * p) * kDecodeSlotFloats; };
-      for (int hw = wave; hw < G; hw += kWaves) {  // one wave per head, lane = piece: the pieces' weights
-        const float2 ml = agent_load2(piece(min(lane, n_split - 1)) + kMaxReal * kHeadDim + 2 * hw);
+      constexpr int kBatch = 16;  // partial rows in flight per lane
+      for (int h = wave; h < G; h += kWaves) {  // one wave per head, two columns per lane
+        const float2 ml = agent_load2(piece(min(lane, n_split - 1)) + kMaxReal * kHeadDim + 2 * h);
+        float2 v[kBatch];
+        auto request = [&](int s0) {
+#pragma unroll
+          for (int i = 0; i < kBatch; ++i) v[i] = agent_load2(piece(min(s0 + i, n_split - 1)) + h * kHeadDim + 2 * lane);
+        };
+        request(0);
+        // the pieces' weights, a lane each
         const float mp = lane < n_split ? ml.x : kDecNegBig;
         const float f = dec_exp2(mp - wave_fmax(mp));
         const float L = row_sum(wave_fsum(lane < n_split ? ml.y * f : 0.f));
-        w_lds[hw][lane] = lane < n_split ? f / L : 0.f;
-      }
-      __syncthreads();
-      constexpr int kBatch = 16;  // partial rows in flight per thread
-      for (int e = tid; e < G * (kHeadDim / 2); e += kThr) {
-        const int h = e >> 6, d = (e & 63) * 2;
+        const int weight = __float_as_int(lane < n_split ? f / L : 0.f);
         float x = 0.f, y = 0.f;
         for (int s0 = 0; s0 < n_split; s0 += kBatch) {
-          float2 v[kBatch];
-#pragma unroll
-          for (int i = 0; i < kBatch; ++i) v[i] = agent_load2(piece(min(s0 + i, n_split - 1)) + h * kHeadDim + d);
+          if (s0 > 0) request(s0);
 #pragma unroll
           for (int i = 0; i < kBatch; ++i) {  // past the last piece nothing is added: 0 times an infinite sum would be NaN
-            const float f = w_lds[h][s0 + i];
-            x += s0 + i < n_split ? v[i].x * f : 0.f;
-            y += s0 + i < n_split ? v[i].y * f : 0.f;
+            const float w = __int_as_float(__builtin_amdgcn_readlane(weight, s0 + i));
+            x += s0 + i < n_split ? v[i].x * w : 0.f;
+            y += s0 + i < n_split ? v[i].y * w : 0.f;
           }
         }
-        *reinterpret_cast<float2 *>(out + h * kHeadDim + d) = make_float2(x, y);
+        *reinterpret_cast<float2 *>(out + h * kHeadDim + 2 * lane) = make_float2(x, y);
       }
     }
     if (kAligned) return;
@@ -391,7 +443,7 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
     longest = std::max(longest, t);
     a.tile0[b + 1] = (int)tiles;
   }
-  a.tiles = tiles * a.Hkv;
+  a.tiles = (int)(tiles * a.Hkv);  // < 2^30: there are less than 2^31 tokens, and 8 KV heads at most
   // Each row cut into pieces of about a CU's share, or left whole, unless that loads the CUs unevenly for long: a share
   // of the line that straddles rows costs a restart of the loads and one more fold, about 5 us.
   //   Whole: rows close to a multiple of the CUs and none much longer than the mean (256 rows of 2048-2560 tokens 50.8
@@ -404,7 +456,7 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   const bool even = 10 * rows >= 9 * per_cu * n_cu && 2 * longest * a.n_seq <= 3 * tiles;
   const bool pieces = 4 * rows <= n_cu || (rows <= n_cu && a.tiles <= (int64_t)48 * n_cu);  // <= 1.5 n_cu of them
   if (even || pieces || longest <= kWholeTiles) {
-    const int64_t share = std::max<int64_t>(kWaves, (a.tiles + n_cu - 1) / n_cu);
+    const int64_t share = std::max<int64_t>(kWaves, ((int64_t)a.tiles + n_cu - 1) / n_cu);
     a.piece0[0] = 0;
     for (int b = 0; b < a.n_seq; ++b) {
       const int64_t t = a.tile0[b + 1] - a.tile0[b];
@@ -421,9 +473,9 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   // Equal shares: one block per CU; two where a block goes through several short rows, as each starts with the latency
   // of its first loads, which the other block then covers.
   const int shares = rows > n_cu && a.tiles <= (int64_t)rows * 16 ? 2 : 1;
-  int64_t blocks = std::min<int64_t>(std::min(shares * n_cu, kDecodeMaxBlocks), (a.tiles + kWaves - 1) / kWaves);
+  int64_t blocks = std::min<int64_t>(std::min(shares * n_cu, kDecodeMaxBlocks), ((int64_t)a.tiles + kWaves - 1) / kWaves);
   // a row is cut into at most kDecodeMaxSplits pieces: the fold keeps a weight for each
-  blocks = std::max<int64_t>(1, std::min(blocks, a.tiles * (kDecodeMaxSplits - 2) / longest));
+  blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)a.tiles * (kDecodeMaxSplits - 2) / longest));
   const dim3 grid((unsigned)blocks);
   if (a.block_table)
     hipLaunchKernelGGL((k_decode<true, false, kWaves>), grid, block, 0, s, a);

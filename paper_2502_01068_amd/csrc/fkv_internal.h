@@ -205,7 +205,7 @@ struct DecodeArgs {
   int off[FKV_MAX_SEQS + 1];     // token prefix sums
   int tile0[FKV_MAX_SEQS + 1];   // prefix sums of the sequences' 32-token tiles
   int piece0[FKV_MAX_SEQS + 1];  // rows cut one by one: prefix sums of the pieces per row
-  int64_t tiles;                 // tiles of the launch: those of every (sequence, KV head)
+  int tiles;                     // tiles of the launch: those of every (sequence, KV head)
   // paged cache (block_table != nullptr): k, v are page pools [n_pages][page_size][Hkv][d]; logical
   // token t of sequence b lives in page block_table[b*max_pages + t/page_size], slot t % page_size
   const int32_t *block_table;
