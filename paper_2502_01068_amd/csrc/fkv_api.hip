@@ -469,6 +469,7 @@ void fill_rowset(SelectRowSet *rs, const float *scores, int64_t stride, int n_ro
   rs->row_stride = stride;
   rs->n_rows = n_rows;
   rs->idx_out = out;
+  rs->total = off[n_seq];
   for (int b = 0; b <= n_seq; ++b) rs->cnt_off[b] = off[b];
 }
 

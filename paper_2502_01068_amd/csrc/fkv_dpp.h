@@ -38,13 +38,13 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
 __device__ __forceinline__ uint32_t wave_last(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 
 // Maximum / minimum over the 64 lanes; the result is valid in lane 63 only (use wave_last to spread it).
-__device__ __forceinline__ uint32_t wave_max_to_last(uint32_t x) {
-  x = max(x, dpp_u32<kDppRowRor + 8>(x, x));
-  x = max(x, dpp_u32<kDppRowRor + 4>(x, x));
-  x = max(x, dpp_u32<kDppRowRor + 2>(x, x));
-  x = max(x, dpp_u32<kDppRowRor + 1>(x, x));
-  x = max(x, dpp_u32<kDppBcast15, 0xA>(x, x));
-  x = max(x, dpp_u32<kDppBcast31, 0xC>(x, x));
+__device__ __forceinline__ uint32_t wave_max_to_last(uint32_t x) {  // `old` is the maximum's identity: one instruction a step
+  x = max(x, dpp_u32<kDppRowRor + 8>(0u, x));
+  x = max(x, dpp_u32<kDppRowRor + 4>(0u, x));
+  x = max(x, dpp_u32<kDppRowRor + 2>(0u, x));
+  x = max(x, dpp_u32<kDppRowRor + 1>(0u, x));
+  x = max(x, dpp_u32<kDppBcast15, 0xA>(0u, x));
+  x = max(x, dpp_u32<kDppBcast31, 0xC>(0u, x));
   return x;
 }
 __device__ __forceinline__ uint32_t wave_min_to_last(uint32_t x) { return ~wave_max_to_last(~x); }

@@ -138,6 +138,7 @@ struct SelectRowSet {
   int64_t row_stride;   // floats between rows
   int n_rows;
   int32_t *idx_out;     // [n_rows][cnt_off[n_seq]]
+  int total;            // kept indices per row: cnt_off[n_seq]
   int cnt_off[FKV_MAX_SEQS + 1];  // prefix sums of the per-sequence keep counts
 };
 // Rows longer than 32768 keys are selected by a chain of launches that keeps per-row state here.

@@ -178,6 +178,48 @@ __device__ __forceinline__ void select_row(const float *sc, int P, int kp, int32
   FKV_BTICK(3);
 }
 
+struct SelectRow {
+  const float *sc;
+  int32_t *out;
+  int P, k, kp;
+  unsigned failed;  // the context's error flag, in flight: waited for where it is looked at
+};
+__device__ __forceinline__ SelectRow locate_row(const SelectArgs &a) {
+  // All arguments that the row can need, requested together (left to itself the compiler loads each where it is first used, four
+  // trips one after the other), both sets' among them.
+  const int b = blockIdx.y;
+  const int at0 = a.cu[b], at1 = a.cu[b + 1], n_rows0 = a.set[0].n_rows;
+  const float *scores[2] = {a.set[0].scores, a.set[1].scores};
+  int32_t *idx[2] = {a.set[0].idx_out, a.set[1].idx_out};
+  const int64_t stride[2] = {a.set[0].row_stride, a.set[1].row_stride};
+  const int total[2] = {a.set[0].total, a.set[1].total};
+  const int c0[2] = {a.set[0].cnt_off[b], a.set[1].cnt_off[b]}, c1[2] = {a.set[0].cnt_off[b + 1], a.set[1].cnt_off[b + 1]};
+  asm volatile("" ::"s"(at0), "s"(at1), "s"(n_rows0), "s"(a.n_sets), "s"(a.W), "s"(a.err), "s"(scores[0]), "s"(scores[1]), "s"(idx[0]),
+               "s"(idx[1]), "s"(stride[0]), "s"(stride[1]), "s"(total[0]), "s"(total[1]), "s"(c0[0]), "s"(c0[1]), "s"(c1[0]), "s"(c1[1]));
+  int zero = 0;
+  asm("" : "+v"(zero));  // else the flag, a uniform value, is waited for on the spot
+  SelectRow r;
+  r.failed = a.err != nullptr ? a.err[zero] : 0u;
+  const bool second = a.n_sets > 1 && (int)blockIdx.x >= n_rows0;
+  const int row = (int)blockIdx.x - (second ? n_rows0 : 0);
+  r.P = at1 - at0 - a.W;
+  r.k = second ? c1[1] - c0[1] : c1[0] - c0[0];
+  r.kp = r.k - a.W;  // prefix tokens to keep
+  r.sc = (second ? scores[1] : scores[0]) + (size_t)row * (second ? stride[1] : stride[0]) + (at0 - b * a.W);
+  r.out = (second ? idx[1] : idx[0]) + (size_t)row * (second ? total[1] : total[0]) + (second ? c0[1] : c0[0]);
+  return r;
+}
+// The window's indices, which are always kept; while the flag is up, -1 in every index (the scores are invalid, none may look
+// usable) and false.  Block-uniform.
+__device__ __forceinline__ bool window_or_failed(const SelectArgs &a, const SelectRow &r) {
+  if (uniform(r.failed) != 0u) {
+    for (int i = threadIdx.x; i < r.k; i += kSelThreads) r.out[i] = -1;
+    return false;
+  }
+  if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;
+  return true;
+}
+
 // ---- rows of up to 32768 keys: everything in registers -----------------------------------------
 // One 1024-thread block per row, kKpt keys per thread.  Bound by instruction issue and by the latency of the
 // steps between block barriers (one block per row leaves most of the chip idle whatever is done), so per key
@@ -207,7 +249,10 @@ struct SelectLds {
 };
 
 template <int kKpt>
-__device__ __forceinline__ void select_resident(const float *sc, int P, int kp, int32_t *out, SelectLds<kKpt> &s) {
+__device__ __forceinline__ void select_resident(const SelectArgs &a, const SelectRow &r, SelectLds<kKpt> &s) {
+  const float *sc = r.sc;
+  const int P = r.P, kp = r.kp;
+  int32_t *out = r.out;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
@@ -216,6 +261,7 @@ __device__ __forceinline__ void select_resident(const float *sc, int P, int kp, 
   for (int i = tid; i < kBins / 4; i += kSelThreads) *reinterpret_cast<u32x4 *>(&s.hist[4 * i]) = u32x4{0u, 0u, 0u, 0u};
   if (tid < kListCap / 4) *reinterpret_cast<u32x4 *>(&s.list[4 * tid]) = u32x4{0u, 0u, 0u, 0u};
   if (tid < 3) (&s.kmax)[tid] = 0u;  // kmax, not_kmin, n_list
+  if (!window_or_failed(a, r)) return;
   __syncthreads();
 
   {
@@ -386,26 +432,6 @@ __device__ __forceinline__ void select_resident(const float *sc, int P, int kp, 
   compact_wave<kKpt>(key, T, need_eq, before_gt, before_eq, wave, -mis, out, s.stage[wave]);
 }
 
-struct SelectRow {
-  const float *sc;
-  int32_t *out;
-  int P, k, kp;
-};
-__device__ __forceinline__ SelectRow locate_row(const SelectArgs &a) {
-  int row = blockIdx.x;
-  const int set_id = (a.n_sets > 1 && row >= a.set[0].n_rows) ? 1 : 0;
-  if (set_id) row -= a.set[0].n_rows;
-  const SelectRowSet &rs = a.set[set_id];
-  const int b = blockIdx.y;
-  SelectRow r;
-  r.P = a.cu[b + 1] - a.cu[b] - a.W;
-  r.k = rs.cnt_off[b + 1] - rs.cnt_off[b];
-  r.kp = r.k - a.W;  // prefix tokens to keep
-  r.sc = rs.scores + (size_t)row * rs.row_stride + (a.cu[b] - b * a.W);
-  r.out = rs.idx_out + (size_t)row * rs.cnt_off[a.n_seq] + rs.cnt_off[b];
-  return r;
-}
-
 // Rows of at most 1024 kKpt - 3 keys; longer ones of the call are left to another launch.  kKpt follows the longest row:
 // rows much shorter than that take fewer keys per thread, since empty slots cost what full ones do and a batch of many
 // short rows is several rounds of blocks (24000 and 62 times 1500 keys, 9 rows each: 27.0 -> 16.1 us per call).
@@ -416,20 +442,18 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   __shared__ __attribute__((aligned(16))) SelectLds<kKpt> lds;
   const SelectRow r = locate_row(a);
   if (r.P + 3 > kSelThreads * kKpt) return;
-  if (a.err != nullptr && *a.err != 0u) {  // the scores are invalid: no index may look usable
-    for (int i = threadIdx.x; i < r.k; i += kSelThreads) r.out[i] = -1;
+  if (r.kp <= 0) {
+    window_or_failed(a, r);
     return;
   }
-  if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;  // window tokens are always kept
-  if (r.kp <= 0) return;
   if constexpr (kKpt > kShortKpt) {
     static_assert(sizeof(SelectLds<kShortKpt>) <= sizeof lds, "the short row's tables lie where the long one's would");
     if (r.P + 3 <= kSelThreads * kShortKpt) {
-      select_resident<kShortKpt>(r.sc, r.P, r.kp, r.out, reinterpret_cast<SelectLds<kShortKpt> &>(lds));
+      select_resident<kShortKpt>(a, r, reinterpret_cast<SelectLds<kShortKpt> &>(lds));
       return;
     }
   }
-  select_resident<kKpt>(r.sc, r.P, r.kp, r.out, lds);
+  select_resident<kKpt>(a, r, lds);
 }
 
 // Longer rows on one block each, re-read from the caches pass by pass: only for calls with more such rows than the
@@ -442,11 +466,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_chunks(SelectArgs a) {
   __shared__ uint32_t bcast[8 + 64];  // broadcast slots, then one sink word per lane
   const SelectRow r = locate_row(a);
   if (r.P + 3 <= kSelThreads * kMaxKpt) return;
-  if (a.err != nullptr && *a.err != 0u) {
-    for (int i = threadIdx.x; i < r.k; i += kSelThreads) r.out[i] = -1;
-    return;
-  }
-  if ((int)threadIdx.x < a.W) r.out[r.kp + threadIdx.x] = r.P + threadIdx.x;
+  if (!window_or_failed(a, r)) return;
   if (r.kp > 0) select_row(r.sc, r.P, r.kp, r.out, hist, wsum, bcast, scan_tbl);
 }
 

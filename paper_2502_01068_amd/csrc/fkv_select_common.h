@@ -42,22 +42,23 @@ __device__ __forceinline__ void load_keys(const float *base, int mis, int P, int
     }
     return;
   }
+  // A row begins or ends in the wave's range: word by word, all loads on their way together, past the row's end without an access.
+  // (Four words a load with a branch for the last ones took a trip to memory per load, and every row has such a wave,
+  // which the others wait for: 2 us at 12281 keys.)
+  const int n = min(mis + P - v_wave, 64 * kKpt);
+  if (n <= 0) {
 #pragma unroll
-  for (int q = 0; q < kKpt / 4; ++q) {
-    const int v = v_chunk + slot_pos<kKpt>(wave, lane, q);
-    if (v >= mis && v + 3 < mis + P) {
-      const f32x4 f = *reinterpret_cast<const f32x4 *>(base + v);
-      key[4 * q + 0] = order_key(f[0]);
-      key[4 * q + 1] = order_key(f[1]);
-      key[4 * q + 2] = order_key(f[2]);
-      key[4 * q + 3] = order_key(f[3]);
-    } else {
+    for (int e = 0; e < kKpt; ++e) key[e] = 0u;
+    return;
+  }
+  const auto row = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base + v_wave), 0, n * 4, 0x00027000);
+  const int first = max(mis - v_wave, 0);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int vv = v + e;
-        key[4 * q + e] = (vv >= mis && vv < mis + P) ? order_key(base[vv]) : 0u;
-      }
-    }
+  for (int e = 0; e < kKpt; ++e) key[e] = __builtin_amdgcn_raw_buffer_load_b32(row, lane * 16 + (e >> 2) * 1024 + (e & 3) * 4, 0, 0);
+#pragma unroll
+  for (int e = 0; e < kKpt; ++e) {
+    const int at = lane * 4 + (e >> 2) * 256 + (e & 3);
+    key[e] = (uint32_t)(at - first) < (uint32_t)(n - first) ? order_key(__uint_as_float(key[e])) : 0u;
   }
 }
 
@@ -231,35 +232,38 @@ __device__ __forceinline__ void compact_wave(const uint32_t (&key)[kKpt], uint32
   const int lane = threadIdx.x & 63;
   const uint32_t first = before_gt + min(before_eq, need_eq);  // this wave's first output
   uint32_t n_out = 0, eq_seen = before_eq;
+  const int i_lane = slot_pos<kKpt>(wave, lane, 0) + i_base;
 #pragma unroll
   for (int q = 0; q < kKpt / 4; ++q) {
-    bool kept[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) kept[e] = key[4 * q + e] > T;
-    if (need_eq != 0u) {
-      uint32_t rank = eq_seen;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) rank = lanes_before(__builtin_amdgcn_ballot_w64(key[4 * q + e] == T), rank);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool eq = key[4 * q + e] == T;
-        eq_seen += __popcll(__builtin_amdgcn_ballot_w64(eq));
-        kept[e] = kept[e] || (eq && rank < need_eq);
-        rank += eq ? 1u : 0u;
-      }
-    }
     uint64_t m[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = __builtin_amdgcn_ballot_w64(kept[e]);
+    for (int e = 0; e < 4; ++e) m[e] = __builtin_amdgcn_ballot_w64(key[4 * q + e] > T);
+    if (need_eq != 0u) {
+      uint64_t eq[4];
+      uint32_t rank = eq_seen;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        eq[e] = __builtin_amdgcn_ballot_w64(key[4 * q + e] == T);
+        rank = lanes_before(eq[e], rank);
+        eq_seen += __popcll(eq[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        m[e] |= eq[e] & __builtin_amdgcn_ballot_w64(rank < need_eq);
+        rank += __builtin_amdgcn_inverse_ballot_w64(eq[e]) ? 1u : 0u;
+      }
+    }
     uint32_t at = n_out;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) at = lanes_before(m[e], at);
-    const int i0 = slot_pos<kKpt>(wave, lane, q) + i_base;
+    for (int e = 0; e < 4; ++e) {
+      at = lanes_before(m[e], at);
+      n_out += __popcll(m[e]);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      stage[kept[e] ? at : 64u * kKpt + lane] = i0 + e;  // a dropped key goes to the lane's spare word
-      at += kept[e] ? 1u : 0u;
-      n_out += __popcll(m[e]);
+      const bool kept = __builtin_amdgcn_inverse_ballot_w64(m[e]);
+      stage[kept ? at : 64u * kKpt + lane] = i_lane + q * 256 + e;  // a dropped key goes to the lane's spare word
+      at += kept ? 1u : 0u;
     }
   }
   wave_sync_lds();

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
   const int k = rs.cnt_off[b + 1] - rs.cnt_off[b];
   const int kp = k - a.W;  // prefix tokens to keep
   const float *sc = rs.scores + (size_t)row * rs.row_stride + (a.cu[b] - b * a.W);
-  int32_t *out = rs.idx_out + (size_t)row * rs.cnt_off[a.n_seq] + rs.cnt_off[b];
+  int32_t *out = rs.idx_out + (size_t)row * rs.total + rs.cnt_off[b];
   const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
   const int v0 = s * kChunk;
   // the keys, the epoch and the flag are on their way while the tables are cleared
