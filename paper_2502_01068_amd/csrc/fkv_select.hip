@@ -232,9 +232,9 @@ __device__ __forceinline__ bool window_or_failed(const SelectArgs &a, const Sele
 //   2. the threshold's bin; while it holds more than kListCap keys (ties, very long tails) it is binned again
 //   3. its keys are listed in LDS, a thread each ranks them by a sweep over the list
 //   4. ordered compaction, staged per wave in LDS.
-// Per launch inside a compress call, before -> after: 2040 keys 7.5 -> 5.6 us, 6546 8.7 -> 7.8, 12281 (max pooling)
-// 12.2 -> 10.8, 32 rows of 16376 10.5 -> 9.0.  At 16376 keys: loading 1.8 us, range 0.7, histogram 1.1, bin 0.4,
-// list 1.5, rank 0.7, compaction 1.5 (2.4 GHz clock).
+// Per launch (kernel trace), before -> after the wave that a row ends in requests all its words at once, the arguments come in one
+// batch and the flag travels beside the keys: 2040 keys 5.2 -> 4.8 us, 6546 7.3 -> 6.5, 12281 (max pooling) 10.6 -> 8.6, 20000
+// 12.1 -> 10.1, 32 rows of 16376 9.3 -> 7.9, 72 rows of 8184-16376 10.5 -> 9.0.
 constexpr int kListCap = 256;
 
 template <int kKpt>
