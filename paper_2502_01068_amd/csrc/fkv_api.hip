@@ -330,8 +330,9 @@ int even_share(const Resolved &r, int skip, int halo, int n_cu, int lo, int hi) 
 // Second pass of the two-pass score kernels: probabilities from the per-row normalisers, window sum, pooling, head
 // means.  Tiles overlap by the pooling halo.  The normalisers are a.rowstat's, or (wo) those of the window output's splits, whose
 // merge then goes into the same launch, on CUs that the scores leave idle, at most four units a block; with many sequences it
-// is more than they can take beside the scores and a launch of its own.
-int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, const WoutArgs *wo, hipStream_t st) {
+// is more than they can take beside the scores and a launch of its own, which leaves the normalisers (3 sequences of 5000
+// tokens: folding them in every block of the scores as well would be 1 us more).
+int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, WoutArgs *wo, hipStream_t st) {
   constexpr int kMergeUnits = 4;
   const int sub_max = r.V > kMaxKvHeads ? scores_sub_wide() : scores_sub_long();
   const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
@@ -348,15 +349,16 @@ int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, cons
   }
   a.map.blk[r.n_seq] = nb;
   hipError_t e = hipSuccess;
-  if (units > 0 && (!merge || nb == 0)) {
+  if (units > 0 && !merge) {
     Timed t(w.prof, st, KID_WOUT);
+    wo->rowstat = a.rowstat;
     e = launch_wout_merge(*wo, st);
     if (e != hipSuccess) return hip_fail(e);
   }
   if (nb > 0) {
     Timed t(w.prof, st, KID_SCORES);
     const int idle = std::max(beside, (n_cu - nb % n_cu) % n_cu);
-    e = wo ? launch_wout_scores(a, *wo, nb, merge ? std::min(idle, units) : 0, st) : launch_scores(a, nb, st);
+    e = merge ? launch_wout_scores(a, *wo, nb, std::min(idle, units), st) : launch_scores(a, nb, wo != nullptr, st);
     if (e != hipSuccess) return hip_fail(e);
   }
   return FKV_OK;

@@ -130,7 +130,7 @@ int scores_sub_long(void);
 int scores_sub_wide(void);
 hipError_t launch_stats(const ScoreArgs &a, int n_blocks, hipStream_t s);
 hipError_t launch_combine(const ScoreArgs &a, hipStream_t s);
-hipError_t launch_scores(const ScoreArgs &a, int n_blocks, hipStream_t s);
+hipError_t launch_scores(const ScoreArgs &a, int n_blocks, bool k_cached, hipStream_t s);
 
 // ---- select -----------------------------------------------------------------------------
 struct SelectRowSet {
@@ -228,6 +228,7 @@ struct WoutArgs {
   int n_split;            // blocks per (sequence, virtual group)
   int causal;
   float scale_log2e;
+  float *rowstat;         // [n_seq][V*32] or nullptr: the merge leaves each softmax row's log-sum-exp (log2 units) here
   int keep_k;             // K is read with plain loads (it will be read again soon) instead of non-temporal ones
 };
 int wout_tiles_per_block_min(void);
@@ -235,7 +236,7 @@ hipError_t launch_wout(const WoutArgs &a, hipStream_t s);        // the splits' 
 hipError_t launch_wout_merge(const WoutArgs &a, hipStream_t s);  // the output from them
 int wout_merge_units(const WoutArgs &a);
 // The scores from those partials, whose normalisers every block folds for itself, in one launch; its first n_merge blocks
-// (may be none) write the output instead, wout_merge_units(a) units of work in all.
+// write the output instead, wout_merge_units(a) units of work in all.
 hipError_t launch_wout_scores(const ScoreArgs &a, const WoutArgs &o, int n_blocks, int n_merge, hipStream_t s);
 
 // ---- diagnostics ------------------------------------------------------------------------

@@ -213,19 +213,22 @@ hipError_t launch_combine(const ScoreArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_combine, dim3((rows + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_scores(const ScoreArgs &a, int n_blocks, hipStream_t s) {
+// k_cached: K was just read by the launch before; plain loads then, so that what the caches still hold is used.
+hipError_t launch_scores(const ScoreArgs &a, int n_blocks, bool k_cached, hipStream_t s) {
+  const dim3 grid(n_blocks), block(kThreads);
   if (a.V > kMaxKvHeads)  // twice the heads in LDS: half the tile
-    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+    hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, NoWout>), grid, block, 0, s, a, NoWout{}, 0);
+  else if (k_cached)
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kPlain, NoWout>), grid, block, 0, s, a, NoWout{}, 0);
   else if (a.tile_sub <= kScoresSubShort)
-    hipLaunchKernelGGL((k_scores<kScoresSubShort, 1, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+    hipLaunchKernelGGL((k_scores<kScoresSubShort, 1, kOnce, NoWout>), grid, block, 0, s, a, NoWout{}, 0);
   else
-    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kOnce, NoWout>), dim3(n_blocks), dim3(kThreads), 0, s, a, NoWout{}, 0);
+    hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kOnce, NoWout>), grid, block, 0, s, a, NoWout{}, 0);
   return hipGetLastError();
 }
 
 int wout_merge_units(const WoutArgs &a) { return a.n_seq * a.V * (kWoOutputs / (kThreads / 4)); }
 
-// K was just read by the launch before: plain loads, so that what the caches still hold is used.
 hipError_t launch_wout_scores(const ScoreArgs &a, const WoutArgs &o, int n_blocks, int n_merge, hipStream_t s) {
   const dim3 grid(n_blocks + n_merge);
   if (a.V > kMaxKvHeads)

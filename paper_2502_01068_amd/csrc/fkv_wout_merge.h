@@ -15,7 +15,11 @@ __device__ __forceinline__ void merge_output(const WoutArgs &a, int bg, int idx,
   const int b = bg / a.V, g = bg - b * a.V;
   const int row = idx >> 5, chunk = idx & 31;
   const int hl = row >> 3, w = row & 7;
-  if (hl >= vg_heads(a, g) || w >= a.W) return;  // the four lanes of an output leave together
+  const bool first = j == 0 && chunk == 0;  // the lane that reports the row's normaliser
+  if (hl >= vg_heads(a, g) || w >= a.W) {   // the four lanes of an output leave together
+    if (first && a.rowstat) a.rowstat[(size_t)bg * kRowsPerGroup + row] = 0.f;
+    return;
+  }
   const float2 *ms = a.part_ms + (size_t)bg * a.n_split * kRowsPerGroup + row;
   const float *po = a.part_o + (size_t)bg * a.n_split * kWoRowFloats + row * kHeadDim + chunk * 4;
   constexpr int kBatch = 8;
@@ -55,6 +59,7 @@ __device__ __forceinline__ void merge_output(const WoutArgs &a, int bg, int idx,
     num.z += __shfl_xor(num.z, d); num.w += __shfl_xor(num.w, d);
   }
   if (j != 0) return;
+  if (first && a.rowstat) a.rowstat[(size_t)bg * kRowsPerGroup + row] = M + __log2f(den);
   const float inv = 1.f / den;
   float *dst = a.out + (((size_t)b * a.W + w) * a.Hq + vg_head0(a, g) + hl) * kHeadDim + chunk * 4;
   *reinterpret_cast<float4 *>(dst) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
