@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
   constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
   constexpr bool kWout = std::is_same<O, WoutArgs>::value;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
-  __shared__ float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
+  __shared__ __attribute__((aligned(16))) float s_head_all[kGroups * kMaxGroup * kSlots + kPoolPad];  // window-summed probabilities per head
+  float(*s_head)[kSlots] = reinterpret_cast<float(*)[kSlots]>(s_head_all);
   __shared__ float g_sum[kGroups][kSlots];               // per virtual group sums of pooled head scores
   if constexpr (kWout) {
     if ((int)blockIdx.x < n_merge) {

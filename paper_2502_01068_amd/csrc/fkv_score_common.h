@@ -1,6 +1,8 @@
 // Device helpers shared by the score kernels: MFMA operand loads and the K streaming loop.
 #pragma once
 
+#include <type_traits>
+
 #include "fkv_dpp.h"
 #include "fkv_internal.h"
 
@@ -253,47 +255,63 @@ __device__ __forceinline__ float max3(float x, float y, float z) {
   return r;
 }
 
-// Pooling kernel 7 (the paper's) for the owned tokens of one virtual group, two neighbouring tokens per lane, whose 8 taps
-// are four 8-byte LDS reads per head (the first tap of owned token jj is slot jj).  See pool_and_write.
-template <int kStride, bool kMax>
+// Pooling kernel 7 (the paper's) for the owned tokens of one virtual group, kPer neighbouring tokens per lane, whose kPer + 6
+// taps are 8-byte LDS reads per head (the first tap of owned token jj is slot jj).  See pool_and_write.  Reads up to kPer - 1 slots past
+// the last tap of an owned token (kPoolPad floats behind the last row); what they give is not used.
+constexpr int kPoolPad = 4;
+template <int kStride, bool kMax, int kPer>
 __device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*s_head)[kStride], float (*g_sum)[kStride], int g,
                                             int own, size_t col, int lane) {
 #pragma clang fp contract(off)  // a pooled value is rounded before it enters a mean
   typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
   const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
 #pragma unroll 1
-  for (int jj = 2 * lane; jj < own; jj += 128) {
-    float p[kMaxGroup][2];
+  for (int jj = kPer * lane; jj < own; jj += 64 * kPer) {
+    float p[kMaxGroup][kPer];
 #pragma unroll
     for (int hl = 0; hl < kMaxGroup; ++hl) {
       const float2 *row = reinterpret_cast<const float2 *>(s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + jj);
-      const float2 v01 = row[0], v23 = row[1], v45 = row[2], v67 = row[3];
-      const float v[8] = {v01.x, v01.y, v23.x, v23.y, v45.x, v45.y, v67.x, v67.y};
-      if constexpr (kMax) {
-        const float mid = max3(v[1], v[2], max3(v[3], v[4], max3(v[5], v[6], v[6])));  // the taps both tokens have
-        p[hl][0] = max3(mid, v[0], v[0]);
-        p[hl][1] = max3(mid, v[7], v[7]);
-      } else {
+      float v[kPer + 6];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          p[hl][i] = ((((((v[i] + v[i + 1]) + v[i + 2]) + v[i + 3]) + v[i + 4]) + v[i + 5]) + v[i + 6]) * a.inv_k;
+      for (int i = 0; i < kPer + 6; i += 2) {
+        const float2 x = row[i / 2];
+        v[i] = x.x;
+        v[i + 1] = x.y;
+      }
+#pragma unroll
+      for (int i = 0; i < kPer; i += 2) {
+        if constexpr (kMax) {
+          const float mid = max3(v[i + 1], v[i + 2], max3(v[i + 3], v[i + 4], max3(v[i + 5], v[i + 6], v[i + 6])));  // the taps both tokens have
+          p[hl][i] = max3(mid, v[i], v[i]);
+          p[hl][i + 1] = max3(mid, v[i + 7], v[i + 7]);
+        } else {
+#pragma unroll
+          for (int e = i; e < i + 2; ++e)
+            p[hl][e] = ((((((v[e] + v[e + 1]) + v[e + 2]) + v[e + 3]) + v[e + 4]) + v[e + 5]) + v[e + 6]) * a.inv_k;
+        }
       }
     }
-    const bool both = jj + 1 < own;
-    auto put = [&](float *dst, float x, float y) {
-      if (both) *reinterpret_cast<f32x2u *>(dst) = f32x2u{x, y};
-      else *dst = x;
+    auto put = [&](float *dst, const float (&x)[kPer], float f) {
+#pragma unroll
+      for (int i = 0; i < kPer; i += 2) {
+        if (jj + i + 1 < own) *reinterpret_cast<f32x2u *>(dst + i) = f32x2u{x[i] * f, x[i + 1] * f};
+        else if (jj + i < own) dst[i] = x[i] * f;
+      }
     };
-    float gs[2] = {0.f, 0.f};
+    float gs[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) gs[i] = 0.f;
 #pragma unroll
     for (int hl = 0; hl < kMaxGroup; ++hl)
       if (hl < n_h) {
-        if (a.scores_head) put(a.scores_head + (size_t)(h0 + hl) * a.sum_p + col + jj, p[hl][0], p[hl][1]);
-        gs[0] += p[hl][0];
-        gs[1] += p[hl][1];
+        if (a.scores_head) put(a.scores_head + (size_t)(h0 + hl) * a.sum_p + col + jj, p[hl], 1.f);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) gs[i] += p[hl][i];
       }
-    *reinterpret_cast<float2 *>(&g_sum[g][jj]) = make_float2(gs[0], gs[1]);  // past the last owned token: not read
-    if (a.scores_group && a.vsh == 0) put(a.scores_group + (size_t)g * a.sum_p + col + jj, gs[0] * a.inv_g, gs[1] * a.inv_g);
+#pragma unroll
+    for (int i = 0; i < kPer; i += 2)
+      *reinterpret_cast<float2 *>(&g_sum[g][jj + i]) = make_float2(gs[i], gs[i + 1]);  // past the last owned token: not read
+    if (a.scores_group && a.vsh == 0) put(a.scores_group + (size_t)g * a.sum_p + col + jj, gs, a.inv_g);
   }
 }
 
@@ -313,8 +331,14 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   const bool split = a.vsh != 0;  // a KV group spans two virtual groups: its mean is formed after the barrier
   for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g < a.V; g += n_waves) {  // one wave per virtual group
     if (r == 3) {
-      if (is_max) pool7_group<kStride, true>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
-      else pool7_group<kStride, false>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
+      // two tokens per lane as long as that is one step of the loop; four then, for half the steps
+      auto pool = [&](auto max_t, auto per) {
+        pool7_group<kStride, decltype(max_t)::value, decltype(per)::value>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
+      };
+      typedef std::integral_constant<int, 2> two_t;
+      typedef std::integral_constant<int, 4> four_t;
+      if (own <= 128) { is_max ? pool(std::true_type{}, two_t{}) : pool(std::false_type{}, two_t{}); }
+      else { is_max ? pool(std::true_type{}, four_t{}) : pool(std::false_type{}, four_t{}); }
       continue;
     }
     const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);

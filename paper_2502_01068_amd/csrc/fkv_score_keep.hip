@@ -32,7 +32,8 @@ template <int kVg, int kKeep, int kLds, int kMaxSub>
 __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs f) {
   constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
-  __shared__ __attribute__((aligned(16))) float s_head[kGroups * kMaxGroup][kSlots];  // window-summed probabilities per head
+  __shared__ __attribute__((aligned(16))) float s_head_all[kGroups * kMaxGroup * kSlots + kPoolPad];  // window-summed probabilities per head
+  float(*s_head)[kSlots] = reinterpret_cast<float(*)[kSlots]>(s_head_all);
   __shared__ float g_sum[kGroups][kSlots];
   __shared__ float cst_lds[kGroups][kRowsPerGroup];
   __shared__ unsigned late_lds[kWaves];
