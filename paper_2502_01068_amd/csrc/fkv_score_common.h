@@ -331,7 +331,8 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   const bool split = a.vsh != 0;  // a KV group spans two virtual groups: its mean is formed after the barrier
   for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g < a.V; g += n_waves) {  // one wave per virtual group
     if (r == 3) {
-      // two tokens per lane as long as that is one step of the loop; four then, for half the steps
+      // two tokens per lane as long as that is one step of the loop; four then, for half the steps: each exposes its LDS reads
+      // (32768 tokens: compress with 154 per block 56.2 -> 55.7 us per call, scores and window output 41.7 -> 41.4)
       auto pool = [&](auto max_t, auto per) {
         pool7_group<kStride, decltype(max_t)::value, decltype(per)::value>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
       };
