@@ -124,7 +124,8 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ __attribute__((aligned(16))) float s_head_all[kGroups * kMaxGroup * kSlots + kPoolPad];  // window-summed probabilities per head
   float(*s_head)[kSlots] = reinterpret_cast<float(*)[kSlots]>(s_head_all);
-  __shared__ float g_sum[kGroups][kSlots];               // per virtual group sums of pooled head scores
+  __shared__ __attribute__((aligned(16))) float g_sum[kGroups][kSlots];  // per virtual group sums of pooled head scores
+  static_assert(__alignof__(g_sum) >= alignof(float2), "the pooling writes pairs of sums");
   if constexpr (kWout) {
     if ((int)blockIdx.x < n_merge) {
       constexpr int kUnits = kWoOutputs / (kThreads / 4);

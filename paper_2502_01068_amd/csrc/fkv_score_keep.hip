@@ -34,10 +34,11 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ __attribute__((aligned(16))) float s_head_all[kGroups * kMaxGroup * kSlots + kPoolPad];  // window-summed probabilities per head
   float(*s_head)[kSlots] = reinterpret_cast<float(*)[kSlots]>(s_head_all);
-  __shared__ float g_sum[kGroups][kSlots];
+  __shared__ __attribute__((aligned(16))) float g_sum[kGroups][kSlots];
   __shared__ float cst_lds[kGroups][kRowsPerGroup];
   __shared__ unsigned late_lds[kWaves];
   static_assert(sizeof(ExchangeLds) <= sizeof(g_sum), "the exchange's tables lie where the group sums go later");
+  static_assert(__alignof__(g_sum) >= alignof(float2) && __alignof__(g_sum) >= alignof(ExchangeLds), "the pooling writes pairs of sums");
   ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(g_sum);
   constexpr int kWaveSums = kVg * kMaxGroup * kSlots;  // floats of s_head that one wave fills
   static_assert(kLds * kVg * kRowsPerGroup * kSub <= kWaveSums && kWaveSums % 4 == 0, "logits kept in LDS");
