@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
   constexpr int kChunk = kSelThreads * kKpt;  // keys per block
   __shared__ uint32_t hist[kBins + 32];  // + one spare word per bank for key slots that are not counted
   __shared__ __attribute__((aligned(16))) uint32_t scan_tbl[kSelWaves * (64 * kMaxKpt + 64)];  // 132 KiB: the list's tables, then output staging
+  static_assert(8 * kSelThreads <= sizeof(scan_tbl) / sizeof(scan_tbl[0]), "the list's 8192 bins lie in it");
   __shared__ uint32_t wsum[2 * kSelWaves];
   __shared__ uint32_t bcast[8 + 64];
   __shared__ uint32_t slice_cnt[kCoopMaxSlices];  // keys of each slice inside the current interval
@@ -170,9 +171,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
         }
       }
     };
-    // With every slice's histogram word of this thread's bin pair in w[] (own slice included): stages them,
-    // picks the bin of the `remaining`-th largest key of the row and updates remaining, n_in, own_in,
-    // in_before, gt_before.  `failed`: this wave's fetch ran out.  False if any wave's did.
+    // With every slice's histogram word of this thread's bin pair in w[] (own slice included): picks the bin of the
+    // `remaining`-th largest key of the row and updates remaining, n_in, own_in, in_before, gt_before.
+    // `failed`: this wave's fetch ran out.  False if any wave's did.
     auto pick = [&](const uint32_t (&w)[kSl], bool failed, uint32_t &digit) -> bool {
       uint32_t tot0 = 0, tot1 = 0, bef0 = 0, bef1 = 0;
 #pragma unroll
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
       whole = false;
       if (n_in <= 128u) {
         // few keys: 8 threads rank each of them by a sweep over the list (unused entries are 0)
-        uint32_t *list = scan_tbl + kCoopMaxSlices * kSelThreads;
+        uint32_t *list = scan_tbl;
         __syncthreads();
         if (tid < 128) list[tid] = (uint32_t)tid < n_in ? cand : 0u;
         __syncthreads();
@@ -248,9 +249,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
         return;
       }
       if (span > 0u) {
-        // first pass over 8192 bins (behind the staged histogram words): with a few hundred keys in the interval
-        // the threshold's bin then holds one key, or only ties, and the search is over
-        uint32_t *wide = scan_tbl + kCoopMaxSlices * kSelThreads;
+        // first pass over 8192 bins: with a few hundred keys in the interval the threshold's bin then holds one key, or
+        // only ties, and the search is over
+        uint32_t *wide = scan_tbl;
         const int shift = max(32 - __clz(span) - 13, 0);
         const int grp = kSelThreads - 1 - tid;  // bins 8*grp .. 8*grp+7: thread order runs from the top bin down
         __syncthreads();
