@@ -332,14 +332,20 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
   for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g < a.V; g += n_waves) {  // one wave per virtual group
     if (r == 3) {
       // two tokens per lane as long as that is one step of the loop; four then, for half the steps: each exposes its LDS reads
-      // (32768 tokens: compress with 154 per block 56.2 -> 55.7 us per call, scores and window output 41.7 -> 41.4)
-      auto pool = [&](auto max_t, auto per) {
-        pool7_group<kStride, decltype(max_t)::value, decltype(per)::value>(a, s_head, g_sum, g, own, (size_t)col0 + o0, lane);
+      // (32768 tokens: compress with 154 per block 56.2 -> 55.7 us per call, scores and window output 41.7 -> 41.4).  Kernels
+      // whose rows cannot hold more, with six slots of halo, have no code for four (4 KB of 20).
+      auto pool = [&](auto max_t, auto per, int n) {
+        pool7_group<kStride, decltype(max_t)::value, decltype(per)::value>(a, s_head, g_sum, g, n, (size_t)col0 + o0, lane);
       };
       typedef std::integral_constant<int, 2> two_t;
       typedef std::integral_constant<int, 4> four_t;
-      if (own <= 128) { is_max ? pool(std::true_type{}, two_t{}) : pool(std::false_type{}, two_t{}); }
-      else { is_max ? pool(std::true_type{}, four_t{}) : pool(std::false_type{}, four_t{}); }
+      constexpr int kOneStep = 128;
+      if (kStride - 6 <= kOneStep || own <= kOneStep) {
+        const int n = min(own, kOneStep);  // says that it is one step: as a loop, 2048 tokens take 0.15 us more
+        is_max ? pool(std::true_type{}, two_t{}, n) : pool(std::false_type{}, two_t{}, n);
+      } else if constexpr (kStride - 6 > kOneStep) {
+        is_max ? pool(std::true_type{}, four_t{}, own) : pool(std::false_type{}, four_t{}, own);
+      }
       continue;
     }
     const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
