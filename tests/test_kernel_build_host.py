@@ -25,3 +25,14 @@ def test_pooling_forms_can_be_reached(source, tmp_path):
     forms = {(int(stride), int(per)) for stride, per in re.findall(r"^define .*pool7_groupILi(\d+)ELb[01]ELi(\d)E", ir, re.M)}
     assert {per for _, per in forms} == {2, 4}, forms
     assert all(stride - 6 > 128 for stride, per in forms if per == 4), forms
+
+
+@pytest.mark.parametrize("source", ["fkv_score.hip", "fkv_score_fused.hip", "fkv_score_keep.hip", "fkv_decode.hip", "fkv_wout.hip"])
+def test_no_register_goes_to_scratch(source, tmp_path):
+    """The kernels whose loops fill the vector registers keep all of them there: a spill is a trip to memory between the loads."""
+    said = _device_code(source, tmp_path, "-c", "-Rpass-analysis=kernel-resource-usage")[1]
+    kernels = re.findall(r"Function Name: (\S+)", said)
+    scratch = [int(n) for n in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", said)]
+    spilled = [int(n) for n in re.findall(r" VGPRs Spill: (\d+)", said)]
+    assert kernels and len(kernels) == len(scratch) == len(spilled)
+    assert not any(scratch) and not any(spilled), list(zip(kernels, scratch, spilled))
