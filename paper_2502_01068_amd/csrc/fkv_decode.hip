@@ -192,6 +192,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     const rows_t vb = (rows_t)(a.v + (size_t)kvh * a.head_stride + first * a.tok_stride);
     const uint32_t row = (uint32_t)a.tok_stride * 2;  // bytes of a token's row, at most 2 KiB
     const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
+    // Long pieces of a token-major cache: the K requests of a tile go out in pairs with pauses between them.  The heads' blocks read
+    // 256 bytes each of the same 2 KiB; all 8 requests at once (one addition each; a 64-bit product each used to space them)
+    // disturb that.  With pauses, without, with the products: 32 rows of 3600-4000 tokens 79.1, 80.3, 79.2 us, 32 of 2048 43.6,
+    // 44.5, 43.9, 12 of 7000-8000 65.7, 66.5, 66.2, one of 120000 79.2, 80.3, 80.1.  Short pieces and a compact cache are faster
+    // without: one row of 32768 (32 tiles a piece) 25.9, 25.6, 26.7; 48 of 500-1000 31.8, 31.3, 33.6; compact 32 of
+    // 3600-4000 76.5, 76.0, 77.1.
+    constexpr int kPacedTiles = 40;
+    const bool paced = !kPaged && a.tok_stride > kHeadDim && tile1 - tile0 >= kPacedTiles;
 
     // Page of this lane's token (lane % 32) of a tile; an entry outside the pool is clamped into it.
     auto page_of = [&](int tile) { return table[min(tile * kDecTile + (lane & 31), n - 1) >> a.page_shift]; };
@@ -215,15 +223,17 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       }
       return base;
     };
-    auto load_k = [&](int tile, int slot) {
+    auto load_k = [&](int tile, int slot, bool pauses) {
       const rows_t rows = rows_of(kb, tile);
       if constexpr (kPaged) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) slots[i] = (uint32_t)__shfl(slot, 4 * i + q);
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 8; ++i) {
         __builtin_amdgcn_global_load_lds((gptr_t)row_of(rows, i, tile, (c ^ ((4 * i + q) & 15)) << 4), (lptr_t)(stage + i * 1024), 16, 0, 2);
+        if ((i & 1) != 0 && pauses) __builtin_amdgcn_s_sleep(2);  // 128 cycles
+      }
     };
     auto load_v = [&](int tile) {  // of the tile that load_k was called for last
       keep_access_order();  // read_k_tile waits for all but the 8 youngest loads: these
@@ -249,17 +259,16 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         page_next = page_of(t + kWaves);
         slot = slot_of(t, page);
       }
-      load_k(t, slot);
+      load_k(t, slot, false);
       load_v(t);
       read_queries(qb, (uint32_t)(uintptr_t)(lptr_t)(q_lds + (c & 7) * 256 + q * 16), c < G);
     }
     // One tile; kMore: the loads of the wave's next one go out as their registers and LDS become free (a
     // compile-time flag: no branch around loads).  The compiler's own waits are longer than need be.  Ordinary loads
     // behind LDS-direct ones are waited for together with everything requested: the V tile with the next K tile,
-    // requested a contraction earlier; a paged cache's page entry, before the K tile is read, with the V tile; the first tile
-    // of a piece, unpaged, sends half of its K loads and all of V after q has come.  Exact waits inside the loop (V through
-    // LDS-direct loads, read in asm blocks like K) were no faster: 2048 tokens 7.77 against 7.65 us, 32 paged sequences 52.5
-    // against 51.6.
+    // requested a contraction earlier; a paged cache's page entry, before the K tile is read, with the V tile.  Exact waits inside
+    // the loop (V through LDS-direct loads, read in asm blocks like K) were no faster: 2048 tokens 7.77 against 7.65 us, 32
+    // paged sequences 52.5 against 51.6 (with q in registers, see read_queries).
     auto step = [&](auto more_t) {
       constexpr bool kMore = decltype(more_t)::value;
       u32x4 kr[8];
@@ -268,7 +277,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         slot = slot_of(tile + kWaves, page_next);
         page_next = page_of(tile + 2 * kWaves);
       }
-      if constexpr (kMore) load_k(tile + kWaves, slot);
+      if constexpr (kMore) load_k(tile + kWaves, slot, paced);
       floatx4 acc[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {

@@ -116,3 +116,22 @@ def test_clear_error_resets_piece_counts():
         out = torch.full_like(want, float("nan"))
         assert torch.equal(c.fkv_decode_attention(shape, q, k, v, [4096, 4096], "token_major", out=out), want)
     c.close()
+
+
+@pytest.mark.parametrize("ns,Hkv", [([1216 + 11 * i for i in range(32)], 8), ([1248, 1249] * 32, 4), ([9000] * 9, 8), ([11000], 8)])
+def test_decode_layouts_agree(ctx, ns, Hkv):
+    """Pieces on both sides of 40 tiles, from which on a token-major cache is requested in another rhythm than a compact one:
+    the same bits from both."""
+    print("case: decode layouts n=%s.. (%d) Hkv=%d" % (ns[:4], len(ns), Hkv), flush=True)
+    B, d, tot = len(ns), 128, sum(ns)
+    gen = torch.Generator(device="cuda").manual_seed(72)
+    q, k, v = (torch.randn(s, device="cuda", generator=gen).to(torch.bfloat16) for s in ((B, Hkv * 4, d), (tot, Hkv, d), (tot, Hkv, d)))
+    shape = fk.make_shape(ns, n_q_heads=Hkv * 4, n_kv_heads=Hkv)
+    rows = ctx.fkv_decode_attention(shape, q, k, v, ns, "token_major")
+    heads = ctx.fkv_decode_attention(shape, q, k.transpose(0, 1).contiguous(), v.transpose(0, 1).contiguous(), ns, "compact")
+    assert torch.equal(rows, heads)
+    kf, vf = k[:ns[0]].float().double(), v[:ns[0]].float().double()
+    for h in (0, Hkv * 4 - 1):
+        p = torch.softmax(kf[:, h // 4] @ q[0, h].double() / d ** 0.5, 0)
+        ref = p @ vf[:, h // 4]
+        assert ((rows[0, h].double() - ref).abs().max() / ref.abs().max()).item() <= 1e-5
