@@ -114,8 +114,8 @@ __device__ __forceinline__ int dec_block_of(uint64_t tile, uint64_t tiles, uint6
 }
 
 // kAligned: every row of sequence b is cut into a.piece0[b + 1] - a.piece0[b] equal pieces, one per block (KV heads
-// fastest), instead of equal shares of the line of tiles.
-template <bool kPaged, bool kAligned, int kWaves>
+// fastest), instead of equal shares of the line of tiles.  kPauses: the K requests of a tile go out in pairs, see launch_decode.
+template <bool kPaged, bool kAligned, bool kPauses, int kWaves>
 __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
   constexpr int kThr = kWaves * 64;
   constexpr int kTileBytes = kDecTile * kHeadDim * 2;
@@ -192,15 +192,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     const rows_t vb = (rows_t)(a.v + (size_t)kvh * a.head_stride + first * a.tok_stride);
     const uint32_t row = (uint32_t)a.tok_stride * 2;  // bytes of a token's row, at most 2 KiB
     const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
-    // Long pieces of a token-major cache: the K requests of a tile go out in pairs with pauses between them.  The heads' blocks read
-    // 256 bytes each of the same 2 KiB; all 8 requests at once (one addition each; a 64-bit product each used to space them)
-    // disturb that.  With pauses, without, with the products: 32 rows of 3600-4000 tokens 79.1, 80.3, 79.2 us, 32 of 2048 43.6,
-    // 44.5, 43.9, 12 of 7000-8000 65.7, 66.5, 66.2, one of 120000 79.2, 80.3, 80.1.  Short pieces and a compact cache are faster
-    // without: one row of 32768 (32 tiles a piece) 25.9, 25.6, 26.7; 48 of 500-1000 31.8, 31.3, 33.6; compact 32 of
-    // 3600-4000 76.5, 76.0, 77.1.
-    constexpr int kPacedTiles = 40;
-    const bool paced = !kPaged && a.tok_stride > kHeadDim && tile1 - tile0 >= kPacedTiles;
-
     // Page of this lane's token (lane % 32) of a tile; an entry outside the pool is clamped into it.
     auto page_of = [&](int tile) { return table[min(tile * kDecTile + (lane & 31), n - 1) >> a.page_shift]; };
     auto slot_of = [&](int tile, int page) {
@@ -223,7 +214,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
       }
       return base;
     };
-    auto load_k = [&](int tile, int slot, bool pauses) {
+    auto load_k = [&](int tile, int slot, auto pauses_t) {
       const rows_t rows = rows_of(kb, tile);
       if constexpr (kPaged) {
 #pragma unroll
@@ -232,7 +223,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         __builtin_amdgcn_global_load_lds((gptr_t)row_of(rows, i, tile, (c ^ ((4 * i + q) & 15)) << 4), (lptr_t)(stage + i * 1024), 16, 0, 2);
-        if ((i & 1) != 0 && pauses) __builtin_amdgcn_s_sleep(2);  // 128 cycles
+        if constexpr (decltype(pauses_t)::value) {
+          if (i & 1) __builtin_amdgcn_s_sleep(2);  // 128 cycles
+        }
       }
     };
     auto load_v = [&](int tile) {  // of the tile that load_k was called for last
@@ -259,7 +252,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         page_next = page_of(t + kWaves);
         slot = slot_of(t, page);
       }
-      load_k(t, slot, false);
+      load_k(t, slot, std::false_type{});
       load_v(t);
       read_queries(qb, (uint32_t)(uintptr_t)(lptr_t)(q_lds + (c & 7) * 256 + q * 16), c < G);
     }
@@ -277,7 +270,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
         slot = slot_of(tile + kWaves, page_next);
         page_next = page_of(tile + 2 * kWaves);
       }
-      if constexpr (kMore) load_k(tile + kWaves, slot, paced);
+      if constexpr (kMore) load_k(tile + kWaves, slot, std::bool_constant<kPauses>{});
       floatx4 acc[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -460,6 +453,13 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   //   costs more than it saves (160 rows of 250 tokens 7.4 against 13.9).
   //   Pieces: few rows, or few tiles per CU (128 rows of 1000 tokens 14.2 against 17 us; of 5000, 63 against 55.7).
   constexpr int kWholeTiles = 12;
+  // Pauses between K requests, for a token-major cache and 40 tiles per block or more.  The heads' blocks read 256 bytes each of the
+  // same 2 KiB; all 8 requests of a tile at once (one addition each; a 64-bit product each used to space them) disturb that.
+  // With pauses, without, with the products: 32 rows of 3600-4000 tokens 79.1, 80.3, 79.2 us, 32 of 2048 43.6, 44.5, 43.9, 12 of
+  // 7000-8000 65.7, 66.5, 66.2, one of 120000 79.2, 80.3, 80.1.  Fewer tiles and a compact cache are faster without: one row of
+  // 32768 (32 tiles per block) 25.9, 25.6, 26.7; 48 of 500-1000 31.8, 31.3, 33.6; compact 32 of 3600-4000 76.5, 76.0, 77.1.
+  constexpr int kPausesTiles = 40;
+  auto pauses = [&](dim3 grid) { return a.tok_stride > kHeadDim && a.tiles >= (int64_t)kPausesTiles * grid.x; };
   const int rows = a.n_seq * a.Hkv;
   const int per_cu = (rows + n_cu - 1) / n_cu;
   const bool even = 10 * rows >= 9 * per_cu * n_cu && 2 * longest * a.n_seq <= 3 * tiles;
@@ -474,9 +474,11 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
     }
     const dim3 grid((unsigned)(a.piece0[a.n_seq] * a.Hkv));
     if (a.block_table)
-      hipLaunchKernelGGL((k_decode<true, true, kWaves>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_decode<true, true, false, kWaves>), grid, block, 0, s, a);
+    else if (pauses(grid))
+      hipLaunchKernelGGL((k_decode<false, true, true, kWaves>), grid, block, 0, s, a);
     else
-      hipLaunchKernelGGL((k_decode<false, true, kWaves>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_decode<false, true, false, kWaves>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   // Equal shares: one block per CU; two where a block goes through several short rows, as each starts with the latency
@@ -487,9 +489,11 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)a.tiles * (kDecodeMaxSplits - 2) / longest));
   const dim3 grid((unsigned)blocks);
   if (a.block_table)
-    hipLaunchKernelGGL((k_decode<true, false, kWaves>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_decode<true, false, false, kWaves>), grid, block, 0, s, a);
+  else if (pauses(grid))
+    hipLaunchKernelGGL((k_decode<false, false, true, kWaves>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((k_decode<false, false, kWaves>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_decode<false, false, false, kWaves>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -120,7 +120,7 @@ def test_clear_error_resets_piece_counts():
 
 @pytest.mark.parametrize("ns,Hkv", [([1216 + 11 * i for i in range(32)], 8), ([1248, 1249] * 32, 4), ([9000] * 9, 8), ([11000], 8)])
 def test_decode_layouts_agree(ctx, ns, Hkv):
-    """Pieces on both sides of 40 tiles, from which on a token-major cache is requested in another rhythm than a compact one:
+    """Both sides of 40 tiles per block, from which on a token-major cache is requested in another rhythm than a compact one:
     the same bits from both."""
     print("case: decode layouts n=%s.. (%d) Hkv=%d" % (ns[:4], len(ns), Hkv), flush=True)
     B, d, tot = len(ns), 128, sum(ns)
