@@ -27,8 +27,10 @@
 // pieces) is bound by what one CU reads past its caches: wider loads, more of them in flight and folding after all
 // pieces of a block were each no faster.
 //
-// Measured (device time per call, before -> after): 218 tokens, 1 sequence 10.2 -> 5.2 us; 2048 tokens 11.0 -> 7.8;
-// 32768 tokens 35.5 -> 26.0 (5.2 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 51.6 us (5.9 TB/s).
+// Measured (us per call, with vector dot products -> now): 218 tokens, 1 sequence 10.2 -> 4.9; 2048 tokens 11.0 -> 7.1;
+// 32768 tokens 35.5 -> 25.6 (5.2 TB/s); 32 sequences of 2048-2560 tokens, paged, 119 -> 51.0 (5.9 TB/s).  Equal shares (34 to 46
+// scalars kept in vector lanes, for the walk through the rows): 10 sequences of 12000-12800 tokens 87.7, 40 of 2400-3000, paged,
+// 79.6, 48 of 500-1000 31.1, no slower than with 64-bit bounds in registers (87.9, 79.9, 33.3).
 #include <algorithm>
 #include <type_traits>
 

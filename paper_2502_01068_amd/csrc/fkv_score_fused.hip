@@ -41,10 +41,17 @@ constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 
 int fused_slots(void) { return kFusedSlotsMax; }
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more
-// sub-tile per block (fewer, longer blocks): the exchange gets slower with the number of blocks.
-// Swept over 2048 .. 49152 tokens with the former exchange of one owner wave per row (e.g. 6554 tokens: 64 blocks 21.1
-// us, 113 blocks 18.0, 160 blocks 18.6, 256 blocks 18.4; 32768 tokens: 213 blocks 28.3, 256 blocks 28.7).  The kernel of
-// fkv_score_keep.hip follows it too and takes every block for more sub-tiles than this one holds.
+// sub-tile per block (fewer, longer blocks): the exchange gets slower with the number of blocks, a sub-tile costs a trip to memory.
+// Launches in a row, us (blocks: sub-tiles per block):
+//    3000 tokens  79: 2 11.9, 116: 1 10.5, 158: 1 10.8, 250: 1 11.4     4096  71: 2 11.8, 128: 2 12.3, 158: 1 11.0, 256: 1 11.6
+//    6554  80: 3 13.7, 113: 2 12.2, 160: 2 12.7, 252: 1 12.1             9001  112: 3 15.0, 156: 2 13.3, 205: 2 13.6, 250: 2 14.1
+//   12289  160: 3 15.6, 212: 2 14.3, 224: 2 14.4, 256: 2 14.8           24000  160: 5 20.3, 197: 4 19.0, 223: 4 19.4, 256: 4 19.8
+//   32768  192: 6 24.0, 213: 5 22.5, 256: 5 22.7                        49152  197: 8 29.7, 208: 8 29.4, 240: 7 28.7, 256: 7 30.0
+// 224 fits these.  128 for one sub-tile comes from a sweep with the former exchange of one owner wave per row and is
+// too low by now: 4096 tokens would be 0.8 us shorter on 158 blocks.  The shares decide the order of a row's sum and with it the
+// last bits of the scores.  The kernel of fkv_score_keep.hip follows the rule too and takes every block for more
+// sub-tiles than this one holds (64 / 8 heads: 3000 tokens 111: 2 18.7, 125: 1 15.6, 250: 1 16.3; 8000 127: 3 22.1, 160: 2 19.4,
+// 250: 2 20.2; 20001 191: 4 25.8, 223: 3 23.9, 254: 3 24.3; 40000 208: 7 36.1, 224: 6 34.0, 255: 6 35.1).
 int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : n_sub * kSub <= kFusedSlotsMax ? 224 : kMaxFusedBlocks; }
 
 template <int kFusedSub>

@@ -12,9 +12,9 @@
 // by the kept part and a launch boundary (the statistics' way through memory and back) becomes the exchange:
 // 131072 tokens (17 tiles per block, 10 kept) 97.6 -> 66.4 us in the kernel trace, 8 sequences of 8192-16384 tokens 82.4 ->
 // 55.6 us.  With more than 4 query heads per KV head a wave takes both virtual groups of its KV head from one tile and
-// keeps 3 tiles of each: 64 / 8 heads at 20001 tokens 40.0 -> 24.8 us.  The tiles go through loops whose code is 20 KB; written
-// out tile by tile it was 60 KB (42 KB for wide groups), fetched once each, with 64-bit addresses per load: 131072 tokens 68.5,
-// 20001 tokens 28.0 us.
+// keeps 3 tiles of each: 64 / 8 heads at 20001 tokens 40.0 -> 24.6 us.  The tiles go through loops whose code is 23.6 KB (27.7 KB for
+// wide groups); written out tile by tile it was 63 KB (46 KB), fetched once each, with 64-bit addresses per load: 131072 tokens
+// 68.5, 20001 tokens 28.0 us.
 // A probability is 2^(logit * scale - log-sum-exp), the two-pass kernels' formula, whether its logit was kept or not; the
 // normaliser is added up over other block shares in another order, so the scores are theirs up to its last bits.
 #include "fkv_score_exchange.h"

@@ -232,9 +232,10 @@ __device__ __forceinline__ bool window_or_failed(const SelectArgs &a, const Sele
 //   2. the threshold's bin; while it holds more than kListCap keys (ties, very long tails) it is binned again
 //   3. its keys are listed in LDS, a thread each ranks them by a sweep over the list
 //   4. ordered compaction, staged per wave in LDS.
-// Per launch (kernel trace), before -> after the wave that a row ends in requests all its words at once, the arguments come in one
-// batch and the flag travels beside the keys: 2040 keys 5.2 -> 4.8 us, 6546 7.3 -> 6.5, 12281 (max pooling) 10.6 -> 8.6, 20000
-// 12.1 -> 10.1, 32 rows of 16376 9.3 -> 7.9, 72 rows of 8184-16376 10.5 -> 9.0.
+// Per launch (kernel trace; another run gives up to 0.3 us more or less), before -> after the wave that a row ends in requests all
+// its words at once, the arguments come in one batch and the flag travels beside the keys: 2040 keys 5.2 -> 4.7 us, 6546 7.3 ->
+// 6.7, 12281 (max pooling) 10.6 -> 8.7, 20000 12.1 -> 10.2, 32 rows of 16376 9.3 -> 8.1, 72 rows of 8184-16376 10.5 -> 8.9.
+// 24 and 32 keys per thread keep 7 and 31 scalars in vector lanes: 32 rows of 22000 keys 10.5 -> 9.6 us per call, of 30000 12.6 -> 11.4.
 constexpr int kListCap = 256;
 
 template <int kKpt>
