@@ -194,6 +194,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_decode(DecodeArgs a) {
     const rows_t vb = (rows_t)(a.v + (size_t)kvh * a.head_stride + first * a.tok_stride);
     const uint32_t row = (uint32_t)a.tok_stride * 2;  // bytes of a token's row, at most 2 KiB
     const int32_t *table = kPaged ? a.block_table + (size_t)b * a.max_pages : nullptr;
+
     // Page of this lane's token (lane % 32) of a tile; an entry outside the pool is clamped into it.
     auto page_of = [&](int tile) { return table[min(tile * kDecTile + (lane & 31), n - 1) >> a.page_shift]; };
     auto slot_of = [&](int tile, int page) {
@@ -457,8 +458,8 @@ hipError_t launch_decode(DecodeArgs &a, int n_cu, hipStream_t s) {
   constexpr int kWholeTiles = 12;
   // Pauses between K requests, for a token-major cache and 40 tiles per block or more.  The heads' blocks read 256 bytes each of the
   // same 2 KiB; all 8 requests of a tile at once (one addition each; a 64-bit product each used to space them) disturb that.
-  // With pauses, without, with the products: 32 rows of 3600-4000 tokens 79.1, 80.3, 79.2 us, 32 of 2048 43.6, 44.5, 43.9, 12 of
-  // 7000-8000 65.7, 66.5, 66.2, one of 120000 79.2, 80.3, 80.1.  Fewer tiles and a compact cache are faster without: one row of
+  // With pauses, without, with the products: 32 sequences of 3600-4000 tokens 79.1, 80.3, 79.2 us, 32 of 2048 43.6, 44.5, 43.9, 12 of
+  // 7000-8000 65.7, 66.5, 66.2, one of 120000 79.2, 80.3, 80.1.  Fewer tiles and a compact cache are faster without: one sequence of
   // 32768 (32 tiles per block) 25.9, 25.6, 26.7; 48 of 500-1000 31.8, 31.3, 33.6; compact 32 of 3600-4000 76.5, 76.0, 77.1.
   constexpr int kPausesTiles = 40;
   auto pauses = [&](dim3 grid) { return a.tok_stride > kHeadDim && a.tiles >= (int64_t)kPausesTiles * grid.x; };
