@@ -351,7 +351,9 @@ int fkv_clear_error(fkv_ctx *ctx);
  * 2 us on MI355X, which a caller can estimate as the excess of the summed figures over the
  * un-profiled time of the same call).  fkv_profile_read synchronises those events, writes
  * the accumulated milliseconds and launch counts of kernel ids 0 .. n-1 (n =
- * fkv_profile_kernels()) and clears the accumulators.  Not for use under graph capture. */
+ * fkv_profile_kernels()) and clears the accumulators.  Calls that otherwise select and gather in one launch
+ * (the compress calls on short rows) make two while timing is on, so that each has its own figure; their
+ * results are the same.  Not for use under graph capture. */
 int fkv_profile_kernels(void);
 const char *fkv_profile_kernel_name(int id);
 int fkv_profile_enable(fkv_ctx *ctx, int on);

@@ -8,7 +8,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfastkv_select.so")
 NATIVE = os.path.join(PKG, "_native.so")
-SOURCES = ["fkv_api.hip", "fkv_score.hip", "fkv_score_fused.hip", "fkv_score_keep.hip", "fkv_select.hip", "fkv_select_long.hip", "fkv_select_coop.hip", "fkv_gather.hip", "fkv_decode.hip", "fkv_diag.hip", "fkv_probe.hip", "fkv_wout.hip"]
+SOURCES = ["fkv_api.hip", "fkv_score.hip", "fkv_score_fused.hip", "fkv_score_keep.hip", "fkv_select.hip", "fkv_select_gather.hip", "fkv_select_long.hip", "fkv_select_coop.hip", "fkv_gather.hip", "fkv_decode.hip", "fkv_diag.hip", "fkv_probe.hip", "fkv_wout.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -100,6 +100,13 @@ struct ScoreWs {
   fkv_ctx *prof;        // context whose timing facility brackets the launches, may be nullptr
 };
 
+int log2_exact(int x) {  // log2 of a power of two, else -1
+  if (x < 1 || (x & (x - 1)) != 0) return -1;
+  int sh = 0;
+  while ((1 << sh) < x) ++sh;
+  return sh;
+}
+
 struct EventPair { hipEvent_t a, b, start; int kid; };  // start = own `a` or the previous launch's `b`
 
 }  // namespace
@@ -465,6 +472,50 @@ hipError_t enqueue_select(fkv_ctx *ctx, const SelectArgs &a, hipStream_t st) {
   return gated_launch(ctx->device, st, [&] { return launch_select(a, long_state, &coop, st); });
 }
 
+// Select and gather of a compress call in one launch, where every row is one block's work in the select (fkv_select.hip); `done` says
+// whether it was taken.  While launches are timed they stay apart, so that each has a figure of its own.
+int enqueue_select_gather(fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r, hipStream_t st, bool *done) {
+  *done = false;
+  if (ctx->prof_on || ctx->select_path == 2) return FKV_OK;
+  const SelectArgs &a = g.sel;
+  int longest = 0;
+  int64_t bytes = 0;
+  for (int b = 0; b < r.n_seq; ++b) {
+    longest = std::max(longest, r.cu[b + 1] - r.cu[b] - r.W + 3);
+    bytes += (int64_t)(a.set[0].cnt_off[b + 1] - a.set[0].cnt_off[b]) * r.Hkv * (2 * kHeadDim * 2);
+    if (a.n_sets > 1) bytes += (int64_t)(a.set[1].cnt_off[b + 1] - a.set[1].cnt_off[b]) * g.x_row_bytes;
+  }
+  const int n_cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
+  if (longest > kSelGatherMaxKeys || bytes > (int64_t)kSelGatherMaxShare * n_cu) return FKV_OK;
+  // The smallest share of the bytes (in steps of an eighth) whose blocks fit the CUs once, at least one for every row.
+  int rows = 0;
+  for (int i = 0; i < a.n_sets; ++i) rows += a.set[i].n_rows * r.n_seq;
+  uint32_t share = rows >= n_cu ? (uint32_t)bytes : std::max((uint32_t)bytes / (uint32_t)n_cu, 1u), heaviest;
+  int nb;
+  while (true) {
+    nb = 0;
+    heaviest = 0;
+    for (int b = 0; b < r.n_seq; ++b) {
+      g.blk[b] = nb;
+      for (int i = 0; i < a.n_sets; ++i) {
+        const uint32_t kept = a.set[i].cnt_off[b + 1] - a.set[i].cnt_off[b];
+        const uint32_t row = kept * (uint32_t)(i == 0 ? 2 * kHeadDim * 2 : g.x_row_bytes);
+        const uint32_t parts = std::min((row + share - 1) / share, kept);
+        g.parts[i][b] = (int)parts;
+        heaviest = std::max(heaviest, (kept + parts - 1) / parts * (row / kept));
+        nb += (int)parts * a.set[i].n_rows;
+      }
+    }
+    if (nb <= n_cu || nb == rows) break;
+    share += share / 8 + 1;
+  }
+  if (heaviest > kSelGatherMaxShare) return FKV_OK;
+  g.blk[r.n_seq] = nb;
+  const hipError_t e = launch_select_gather(g, longest, st);
+  *done = true;
+  return e == hipSuccess ? FKV_OK : hip_fail(e);
+}
+
 void fill_rowset(SelectRowSet *rs, const float *scores, int64_t stride, int n_rows, int32_t *out,
                  const int *off, int n_seq) {
   rs->scores = scores;
@@ -495,10 +546,7 @@ int enqueue_gather(fkv_ctx *ctx, GatherArgs &g, const Resolved &r, hipStream_t s
   for (int i = 0; i < g.n_jobs; ++i) {
     GatherJob &j = g.job[i];
     if ((int64_t)j.total_rows * (j.row_bytes / 16) >= (int64_t)1 << 31) return FKV_EUNSUPPORTED;
-    const int cpr = j.row_bytes / 16;
-    j.cpr_shift = -1;
-    for (int sft = 0; sft < 31; ++sft)
-      if ((1 << sft) == cpr) j.cpr_shift = sft;
+    j.cpr_shift = log2_exact(j.row_bytes / 16);
     j.blk0 = nb;
     j.blocks_per_head = gather_blocks_per_head(j);
     nb += j.blocks_per_head * j.n_heads;
@@ -818,15 +866,9 @@ struct Paging {  // block-table addressing of a paged cache; table == nullptr: n
   int max_pages, page_size;
   int64_t n_pages;
 };
-int page_shift_of(int page_size) {  // log2 of a power of two, else -1
-  if (page_size < 1 || (page_size & (page_size - 1)) != 0) return -1;
-  int sh = 0;
-  while ((1 << sh) < page_size) ++sh;
-  return sh;
-}
 int check_paging(const Paging &pg, int Hkv) {
   if (!pg.table) return FKV_ENULL;
-  if (page_shift_of(pg.page_size) < 0 || pg.max_pages < 1 || pg.n_pages < 1) return FKV_EINVAL;
+  if (log2_exact(pg.page_size) < 0 || pg.max_pages < 1 || pg.n_pages < 1) return FKV_EINVAL;
   if (pg.n_pages * pg.page_size > INT32_MAX / Hkv) return FKV_EINVAL;  // slot * Hkv stays below 2^31
   return FKV_OK;
 }
@@ -869,7 +911,7 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
   if (pg) {
     a.block_table = pg->table;
     a.max_pages = pg->max_pages;
-    a.page_shift = page_shift_of(pg->page_size);
+    a.page_shift = log2_exact(pg->page_size);
     a.n_pages = (int)pg->n_pages;
   }
   a.Hq = r.Hq; a.Hkv = r.Hkv; a.G = r.G; a.n_seq = r.n_seq;
@@ -990,7 +1032,7 @@ int enqueue_gather_paged(fkv_ctx *ctx, const Resolved &r, PagedGatherArgs &g, co
   g.idx = idx_kv;
   g.block_table = pg.table;
   g.max_pages = pg.max_pages;
-  g.page_shift = page_shift_of(pg.page_size);
+  g.page_shift = log2_exact(pg.page_size);
   g.n_pages = (int)pg.n_pages;
   g.Hkv = r.Hkv;
   g.total_rows = g.cnt_off[r.n_seq];
@@ -1048,6 +1090,20 @@ int fkv_compress_kv_paged(fkv_ctx *ctx, const fkv_shape *shape, const void *q_wi
   a.err = ws_of(ctx).err;
   fill_rowset(&a.set[a.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, g.cnt_off, r.n_seq);
   {
+    SelectGatherArgs c{};
+    c.sel = a;
+    c.k = static_cast<const uint8_t *>(k);
+    c.v = static_cast<const uint8_t *>(v);
+    c.k_out = static_cast<uint8_t *>(k_pages);
+    c.v_out = static_cast<uint8_t *>(v_pages);
+    c.Hkv = r.Hkv;
+    c.block_table = pg.table;
+    c.max_pages = pg.max_pages;
+    c.page_shift = log2_exact(pg.page_size);
+    c.n_pages = (int)pg.n_pages;
+    bool done = false;
+    rc = enqueue_select_gather(ctx, c, r, st, &done);
+    if (rc != FKV_OK || done) return rc;
     const hipError_t e = enqueue_select(ctx, a, st);
     if (e != hipSuccess) return hip_fail(e);
   }
@@ -1157,6 +1213,20 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
   fill_rowset(&a.set[a.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, off_kv, r.n_seq);
   if (tsp) fill_rowset(&a.set[a.n_sets++], stp, r.sum_p, 1, idx_tsp, off_tsp, r.n_seq);
   {
+    SelectGatherArgs sg{};
+    sg.sel = a;
+    sg.k = static_cast<const uint8_t *>(k);
+    sg.v = static_cast<const uint8_t *>(v);
+    sg.k_out = static_cast<uint8_t *>(k_out);
+    sg.v_out = static_cast<uint8_t *>(v_out);
+    sg.x = static_cast<const uint8_t *>(x);
+    sg.x_out = static_cast<uint8_t *>(x_out);
+    sg.x_row_bytes = (int)x_row_bytes;
+    sg.x_cpr_shift = log2_exact((int)(x_row_bytes / 16));
+    sg.Hkv = r.Hkv;
+    bool done = false;
+    rc = enqueue_select_gather(ctx, sg, r, st, &done);
+    if (rc != FKV_OK || done) return rc;
     const hipError_t e = enqueue_select(ctx, a, st);
     if (e != hipSuccess) return hip_fail(e);
   }

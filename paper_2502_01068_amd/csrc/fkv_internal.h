@@ -299,4 +299,27 @@ hipError_t launch_gather_paged(const PagedGatherArgs &a, hipStream_t s);
 int gather_blocks_per_head(const GatherJob &j);
 hipError_t launch_gather(const GatherArgs &a, int n_blocks, hipStream_t s);
 
+
+// ---- select and gather in one launch ------------------------------------------------------
+struct SelectGatherArgs {
+  SelectArgs sel;               // set[0]: KV heads' rows, set[1] (if any): the TSP row; long_state is not used
+  const uint8_t *k, *v;         // [sum L][Hkv][d] bf16
+  uint8_t *k_out, *v_out;       // [Hkv][kept][d], or page pools (block_table)
+  const uint8_t *x;             // hidden rows, with set[1]
+  uint8_t *x_out;
+  int x_row_bytes, x_cpr_shift; // as in GatherJob
+  int Hkv;
+  const int32_t *block_table;   // as in PagedGatherArgs, or nullptr
+  int max_pages, page_shift, n_pages;
+  int parts[2][FKV_MAX_SEQS];   // blocks that share a row of each set
+  int blk[FKV_MAX_SEQS + 1];    // first block of sequence b: its KV heads' rows, then its TSP row, a row's parts side by side
+};
+// Rows that the one-block select of fkv_select.hip takes too, and the most bytes a block may copy: with more, two launches are
+// faster, whose gather has many short blocks.  us, two launches -> one (bytes of a block): 2048 tokens with hidden rows 19.4 -> 18.1
+// (22 K), 8192 29.9 -> 27.7 (91 K), 16384 38.2 -> 37.6 (146 K), 24000 46.9 -> 46.1 (191 K), 52.9 -> 54.1 (270 K); 8 sequences of
+// 4000-4700 54.7 -> 53.7 (180 K), 13 of 2000-3100 50.5 -> 51.6 (250 K), 8 of 8192-16384 129 -> 157 (more than 800 K).
+constexpr int kSelGatherMaxKeys = 24 * 1024;
+constexpr uint32_t kSelGatherMaxShare = 192 << 10;
+hipError_t launch_select_gather(const SelectGatherArgs &a, int longest, hipStream_t s);
+
 }  // namespace fkv

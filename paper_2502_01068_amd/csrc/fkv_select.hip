@@ -16,7 +16,7 @@
 //      difference between the interval's key count and the histogram's total;
 //   2. a scan of the per-item keep counts gives every kept key its output offset in index order: all
 //      keys > T and the first `need_eq` keys == T by index.
-#include "fkv_select_common.h"
+#include "fkv_select_search.h"
 
 namespace fkv {
 
@@ -236,208 +236,29 @@ __device__ __forceinline__ bool window_or_failed(const SelectArgs &a, const Sele
 // its words at once, the arguments come in one batch and the flag travels beside the keys: 2040 keys 5.2 -> 4.7 us, 6546 7.3 ->
 // 6.7, 12281 (max pooling) 10.6 -> 8.7, 20000 12.1 -> 10.2, 32 rows of 16376 9.3 -> 8.1, 72 rows of 8184-16376 10.5 -> 8.9.
 // 24 and 32 keys per thread keep 7 and 31 scalars in vector lanes: 32 rows of 22000 keys 10.5 -> 9.6 us per call, of 30000 12.6 -> 11.4.
-constexpr int kListCap = 256;
-
 template <int kKpt>
 struct SelectLds {
-  uint32_t hist[kBins + 64];               // first: 16-byte aligned; + one spare word per lane for slots that are not counted
-  uint32_t list[kListCap];                 // keys of the threshold's interval, relative to its smallest,
-  uint32_t list_wave[kListCap];            // and the waves that hold them
-  uint32_t tot[kSelWaves], cnt[kSelWaves]; // wave totals: histogram scan, keys kept for sure
-  uint32_t low[kSelWaves];                 // smallest keys of an interval (the largest ones go to tot)
-  uint32_t kmax, not_kmin, n_list, pick[3];
+  SearchLds search;  // first: 16-byte aligned
   int32_t stage[kSelWaves][64 * kKpt + 64];  // kept indices of each wave, then a word per lane for dropped ones
 };
 
 template <int kKpt>
 __device__ __forceinline__ void select_resident(const SelectArgs &a, const SelectRow &r, SelectLds<kKpt> &s) {
-  const float *sc = r.sc;
-  const int P = r.P, kp = r.kp;
-  int32_t *out = r.out;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
+  const int mis = (int)((reinterpret_cast<uintptr_t>(r.sc) >> 2) & 3);
   uint32_t key[kKpt];
-  load_keys<kKpt>(sc - mis, mis, P, 0, wave, lane, key);
-  for (int i = tid; i < kBins / 4; i += kSelThreads) *reinterpret_cast<u32x4 *>(&s.hist[4 * i]) = u32x4{0u, 0u, 0u, 0u};
-  if (tid < kListCap / 4) *reinterpret_cast<u32x4 *>(&s.list[4 * tid]) = u32x4{0u, 0u, 0u, 0u};
-  if (tid < 3) (&s.kmax)[tid] = 0u;  // kmax, not_kmin, n_list
+  load_keys<kKpt>(r.sc - mis, mis, r.P, 0, wave, lane, key);
+  clear_search(s.search, tid);
   if (!window_or_failed(a, r)) return;
   __syncthreads();
-
-  {
-    uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
-    const int v_wave = wave * (64 * kKpt);
-    if (v_wave >= mis && v_wave + 64 * kKpt <= mis + P) {
-#pragma unroll
-      for (int e = 0; e < kKpt; ++e) {
-        kmax = max(kmax, key[e]);
-        kmin = min(kmin, key[e]);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < kKpt; ++e) {
-        kmax = max(kmax, key[e]);
-        kmin = min(kmin, key[e] != 0u ? key[e] : 0xFFFFFFFFu);  // 0: no element
-      }
-    }
-    kmax = wave_max_to_last(kmax);
-    kmin = wave_min_to_last(kmin);
-    if (lane == 63) {
-      atomicMax(&s.kmax, kmax);
-      atomicMax(&s.not_kmin, ~kmin);
-    }
-  }
-  __syncthreads();
-  // the interval [base, base + span] holds n_in keys, among them the `remaining`-th largest one of it: the threshold
-  uint32_t base = uniform(~s.not_kmin), span = uniform(s.kmax) - base;
-  uint32_t n_in = (uint32_t)P, remaining = (uint32_t)kp;
-  uint32_t T, need_eq = 0;      // kept: keys > T and the first need_eq keys == T
-  uint32_t before_gt, before_eq = 0;  // keys > T and == T in the waves before this one
-
-  // What the other waves hold of a key class: one word per wave through LDS.
-  auto exchange = [&](uint32_t mine) {
-    if (lane == 0) s.cnt[wave] = mine;
-    __syncthreads();
-    return wave_prefix(s.cnt, lane, wave).before;
-  };
-  auto settle = [&](uint32_t t, uint32_t eq) {  // the threshold is known without the list
-    T = t;
-    need_eq = eq;
-    uint32_t mine = count_keys<kKpt>(key, [&](uint32_t k) { return k > t; });
-    if (eq != 0u) mine |= count_keys<kKpt>(key, [&](uint32_t k) { return k == t; }) << 16;
-    const uint32_t b = exchange(mine);
-    before_gt = b & 0xFFFFu;
-    before_eq = b >> 16;
-  };
-
-  while (true) {
-    if (n_in == remaining) { settle(base - 1u, 0u); break; }  // the whole interval
-    if (span == 0u) { settle(base, remaining); break; }
-    if (n_in <= (uint32_t)kListCap) {
-      uint64_t in[kKpt];
-      uint32_t mine = 0, above = 0;
-#pragma unroll
-      for (int e = 0; e < kKpt; ++e) {
-        in[e] = __builtin_amdgcn_ballot_w64(key[e] - base <= span);
-        mine += __popcll(in[e]);
-        above += key[e] > base + span ? 1u : 0u;
-      }
-      if (mine != 0u) {
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&s.n_list, mine);
-        at = uniform(at);
-#pragma unroll
-        for (int q = 0; q < kKpt / 4; ++q)
-          if ((in[4 * q] | in[4 * q + 1] | in[4 * q + 2] | in[4 * q + 3]) != 0ull) {
-#pragma unroll
-            for (int e = 4 * q; e < 4 * q + 4; ++e) {
-              if (key[e] - base <= span) {
-                const uint32_t to = lanes_before(in[e], at);
-                s.list[to] = key[e] - base + 1u;
-                s.list_wave[to] = wave;
-              }
-              at += __popcll(in[e]);
-            }
-          }
-      }
-      before_gt = exchange(wave_last(wave_sum_to_last(above)));
-      // one list key per thread: its rank from a sweep over the list, four keys per read (unused entries are 0)
-      if ((uint32_t)tid < n_in) {
-        const uint32_t x = s.list[tid];
-        uint32_t gt = 0, ge = 0;
-        for (uint32_t j = 0; j < n_in; j += 4) {
-          const u32x4 y = *reinterpret_cast<const u32x4 *>(&s.list[j]);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            gt += y[i] > x ? 1u : 0u;
-            ge += y[i] >= x ? 1u : 0u;
-          }
-        }
-        if (gt < remaining && remaining <= ge) {  // x is the threshold (equal keys write the same words)
-          s.pick[0] = ge == remaining ? x - 1u : x;
-          s.pick[1] = ge == remaining ? 0u : remaining - gt;
-        }
-      }
-      __syncthreads();
-      const uint32_t t = uniform(s.pick[0]);
-      need_eq = uniform(s.pick[1]);
-      T = base + t - 1u;
-      for (uint32_t j = 0; j < n_in; j += 64) {  // kept and tied list keys of the waves before this one
-        const bool live = j + lane < n_in && s.list_wave[j + lane] < (uint32_t)wave;
-        const uint32_t x = live ? s.list[j + lane] : 0u;
-        before_gt += __popcll(__builtin_amdgcn_ballot_w64(live && x > t));
-        if (need_eq != 0u) before_eq += __popcll(__builtin_amdgcn_ballot_w64(live && x == t));
-      }
-      break;
-    }
-    const int shift = max(21 - __clz((span - 1u) | 1u), 0);  // 2048 bins for keys base + 1 .. base + span
-    const uint32_t spare = (uint32_t)kBins + lane;
-#pragma unroll
-    for (int e = 0; e < kKpt; ++e) {
-      // empty slots and what lies below the interval or on its smallest key wrap above span
-      const uint32_t rel = key[e] - (base + 1u);
-      atomicAdd(&s.hist[rel < span ? rel >> shift : spare], 1u);
-    }
-    __syncthreads();
-    // thread t owns bins 2 (1023 - t), + 1: thread order runs from the top bin down
-    const int pair = kSelThreads - 1 - tid;
-    const uint2 h = *reinterpret_cast<const uint2 *>(&s.hist[2 * pair]);
-    *reinterpret_cast<uint2 *>(&s.hist[2 * pair]) = make_uint2(0u, 0u);
-    const uint32_t mine = h.x + h.y;
-    const uint32_t run = wave_scan_add(mine);
-    if (lane == 63) s.tot[wave] = run;
-    __syncthreads();
-    const WavePrefix wp = wave_prefix(s.tot, lane, wave);
-    if (remaining > wp.total) {  // the threshold is the interval's smallest key
-      settle(base, remaining - wp.total);
-      break;
-    }
-    const uint32_t above = wp.before + run - mine;
-    if (above < remaining && remaining <= above + mine) {
-      const bool top = remaining <= above + h.y;
-      s.pick[0] = 2 * pair + (top ? 1 : 0);
-      s.pick[1] = remaining - above - (top ? 0u : h.y);
-      s.pick[2] = top ? h.y : h.x;
-    }
-    __syncthreads();
-    const uint32_t at = uniform(s.pick[0]) << shift;
-    base += 1u + at;
-    span = min((1u << shift) - 1u, span - 1u - at);
-    remaining = uniform(s.pick[1]);
-    n_in = uniform(s.pick[2]);
-    if (n_in > (uint32_t)kListCap && n_in != remaining) {
-      // Too many for the list: ties, as a rule.  The interval shrinks to the keys it holds, so equal ones are seen as
-      // such and do not queue up at one bin in another pass (9 rows of 20000 keys, two values: 36 -> 19 us).
-      uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
-#pragma unroll
-      for (int e = 0; e < kKpt; ++e) {
-        const bool in = key[e] - base <= span;
-        kmax = max(kmax, in ? key[e] : 0u);
-        kmin = min(kmin, in ? key[e] : 0xFFFFFFFFu);
-      }
-      kmax = wave_max_to_last(kmax);
-      kmin = wave_min_to_last(kmin);
-      if (lane == 63) {
-        s.tot[wave] = kmax;
-        s.low[wave] = kmin;
-      }
-      __syncthreads();
-      kmax = wave_max_to_last(s.tot[lane & (kSelWaves - 1)]);
-      kmin = wave_min_to_last(s.low[lane & (kSelWaves - 1)]);
-      base = wave_last(kmin);
-      span = wave_last(kmax) - base;
-    }
-  }
-
-  compact_wave<kKpt>(key, T, need_eq, before_gt, before_eq, wave, -mis, out, s.stage[wave]);
+  const RowCut cut = find_cut<kKpt>(key, r.P, r.kp, mis, wave, lane, s.search);
+  compact_wave<kKpt>(key, cut.T, cut.need_eq, cut.before_gt, cut.before_eq, wave, -mis, r.out, s.stage[wave]);
 }
 
 // Rows of at most 1024 kKpt - 3 keys; longer ones of the call are left to another launch.  kKpt follows the longest row:
 // rows much shorter than that take fewer keys per thread, since empty slots cost what full ones do and a batch of many
 // short rows is several rounds of blocks (24000 and 62 times 1500 keys, 9 rows each: 27.0 -> 16.1 us per call).
-constexpr int kShortKpt = 8;
-
 template <int kKpt>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   __shared__ __attribute__((aligned(16))) SelectLds<kKpt> lds;

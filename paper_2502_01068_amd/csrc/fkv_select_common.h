@@ -220,17 +220,14 @@ __device__ __forceinline__ uint32_t lanes_before(uint64_t mask, uint32_t add) {
 }
 
 
-// Ordered compaction of one wave's keys: appends to `out` the indices (+ i_base) of all keys > T and of keys == T
-// while fewer than need_eq equal keys came before, in index order ((q, lane, e) for key 4 q + e).  before_gt /
-// before_eq: keys > T / == T of the row before this wave.  stage: 64 kKpt + 64 words of LDS of this wave's own.  The
-// masks of kept keys stay scalar; a key's place is a lane prefix over them (v_mbcnt).
-// kCoherentOut: the indices leave as agent-scope atomic stores (straight to device memory instead of
-// resting in the writing CU's L2), for kernels whose blocks order their output among themselves.
-template <int kKpt, bool kCoherentOut = false>
-__device__ __forceinline__ void compact_wave(const uint32_t (&key)[kKpt], uint32_t T, uint32_t need_eq, uint32_t before_gt,
-                                             uint32_t before_eq, int wave, int i_base, int32_t *out, int32_t *stage) {
+// Ordered compaction of one wave's keys into LDS: the indices (+ i_base) of all keys > T and of keys == T while fewer than
+// need_eq equal keys came before, in index order ((q, lane, e) for key 4 q + e), to dst[0 .. n); returns n.  before_eq: keys
+// == T of the row before this wave.  A dropped key goes to the lane's spare word dst[spare + lane].  The masks of kept keys
+// stay scalar; a key's place is a lane prefix over them (v_mbcnt).
+template <int kKpt>
+__device__ __forceinline__ uint32_t place_wave(const uint32_t (&key)[kKpt], uint32_t T, uint32_t need_eq, uint32_t before_eq, int wave,
+                                               int i_base, int32_t *dst, uint32_t spare) {
   const int lane = threadIdx.x & 63;
-  const uint32_t first = before_gt + min(before_eq, need_eq);  // this wave's first output
   uint32_t n_out = 0, eq_seen = before_eq;
   const int i_lane = slot_pos<kKpt>(wave, lane, 0) + i_base;
 #pragma unroll
@@ -262,10 +259,23 @@ __device__ __forceinline__ void compact_wave(const uint32_t (&key)[kKpt], uint32
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool kept = __builtin_amdgcn_inverse_ballot_w64(m[e]);
-      stage[kept ? at : 64u * kKpt + lane] = i_lane + q * 256 + e;  // a dropped key goes to the lane's spare word
+      dst[kept ? at : spare + lane] = i_lane + q * 256 + e;
       at += kept ? 1u : 0u;
     }
   }
+  return n_out;
+}
+
+// The same through a part of LDS of the wave's own (64 kKpt + 64 words) to its place in `out`.  before_gt: keys > T of the row
+// before this wave.
+// kCoherentOut: the indices leave as agent-scope atomic stores (straight to device memory instead of
+// resting in the writing CU's L2), for kernels whose blocks order their output among themselves.
+template <int kKpt, bool kCoherentOut = false>
+__device__ __forceinline__ void compact_wave(const uint32_t (&key)[kKpt], uint32_t T, uint32_t need_eq, uint32_t before_gt,
+                                             uint32_t before_eq, int wave, int i_base, int32_t *out, int32_t *stage) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t first = before_gt + min(before_eq, need_eq);  // this wave's first output
+  const uint32_t n_out = place_wave<kKpt>(key, T, need_eq, before_eq, wave, i_base, stage, 64u * kKpt);
   wave_sync_lds();
   for (uint32_t o = lane; o < n_out; o += 64) {
     if (kCoherentOut)
