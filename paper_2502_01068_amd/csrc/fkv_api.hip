@@ -334,6 +334,8 @@ int even_share(const Resolved &r, int skip, int halo, int n_cu, int lo, int hi) 
   return sub * 32 - halo;
 }
 
+int64_t sums_stride(const Resolved &r) { return (r.sum_p + 3) & ~(int64_t)3; }
+
 // Second pass of the two-pass score kernels: probabilities from the per-row normalisers, window sum, pooling, head
 // means.  Tiles overlap by the pooling halo.  The normalisers are a.rowstat's, or (wo) those of the window output's splits, whose
 // merge then goes into the same launch, on CUs that the scores leave idle, at most four units a block; with many sequences it
@@ -395,8 +397,10 @@ void fill_score_args(ScoreArgs &a, const ScoreWs &w, const fkv_shape *sh, const 
   fill_map(r, &a.map);
 }
 
+// group_sums: room for the groups' sums, if the caller takes those instead of scores_tsp; *summed says that it has to.
 int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, const void *q_win, const void *k,
-                  float *scores_group, float *scores_tsp, float *scores_head, hipStream_t st) {
+                  float *scores_group, float *scores_tsp, float *scores_head, hipStream_t st, float *group_sums = nullptr,
+                  bool *summed = nullptr) {
   ScoreArgs a{};
   fill_score_args(a, w, sh, r, q_win, k, scores_group, scores_tsp, scores_head);
 
@@ -419,7 +423,18 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
       f.part = w.fused_part;
       f.lse = w.fused_lse;
       f.err = w.err;
-      f.n_wg = total;
+      f.split = keep ? -1 : fused_split(r.V, total, f.n_sub_max, max_blocks);
+      if (f.split > 0 && scores_tsp) {  // no block sees every head
+        if (group_sums) {
+          a.scores_tsp = nullptr;
+          a.group_sums = group_sums;
+          a.sums_stride = sums_stride(r);
+          *summed = true;
+        } else {
+          f.split = -1;
+        }
+      }
+      f.n_wg = f.split > 0 ? total << f.split : total;
       f.timeout_ticks = w.wait_ticks;
       const hipError_t e = gated_launch(w.device, st, [&] {
         Timed t(w.prof, st, KID_SCORE_FUSED);  // both resident score kernels
@@ -472,11 +487,18 @@ hipError_t enqueue_select(fkv_ctx *ctx, const SelectArgs &a, hipStream_t st) {
   return gated_launch(ctx->device, st, [&] { return launch_select(a, long_state, &coop, st); });
 }
 
-// Select and gather of a compress call in one launch, where every row is one block's work in the select (fkv_select.hip); `done` says
-// whether it was taken.  While launches are timed they stay apart, so that each has a figure of its own.
-int enqueue_select_gather(fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r, hipStream_t st, bool *done) {
-  *done = false;
-  if (ctx->prof_on || ctx->select_path == 2) return FKV_OK;
+void fill_select(SelectArgs &a, fkv_ctx *ctx, const Resolved &r) {  // the row sets aside
+  a.W = r.W;
+  a.n_seq = r.n_seq;
+  for (int b = 0; b <= r.n_seq; ++b) a.cu[b] = r.cu[b];
+  a.n_sets = 0;
+  a.err = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters) + kCtrError;
+}
+
+// Whether select and gather of a compress call go in one launch, and its blocks: where every row is one block's work in the
+// select (fkv_select.hip).  While launches are timed they stay apart, so that each has a figure of its own.
+bool plan_select_gather(const fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r) {
+  if (ctx->prof_on || ctx->select_path == 2) return false;
   const SelectArgs &a = g.sel;
   int longest = 0;
   int64_t bytes = 0;
@@ -486,7 +508,7 @@ int enqueue_select_gather(fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r, 
     if (a.n_sets > 1) bytes += (int64_t)(a.set[1].cnt_off[b + 1] - a.set[1].cnt_off[b]) * g.x_row_bytes;
   }
   const int n_cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
-  if (longest > kSelGatherMaxKeys || bytes > (int64_t)kSelGatherMaxShare * n_cu) return FKV_OK;
+  if (longest > kSelGatherMaxKeys || bytes > (int64_t)kSelGatherMaxShare * n_cu) return false;
   // The smallest share of the bytes (in steps of an eighth) whose blocks fit the CUs once, at least one for every row.
   int rows = 0;
   for (int i = 0; i < a.n_sets; ++i) rows += a.set[i].n_rows * r.n_seq;
@@ -509,11 +531,9 @@ int enqueue_select_gather(fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r, 
     if (nb <= n_cu || nb == rows) break;
     share += share / 8 + 1;
   }
-  if (heaviest > kSelGatherMaxShare) return FKV_OK;
   g.blk[r.n_seq] = nb;
-  const hipError_t e = launch_select_gather(g, longest, st);
-  *done = true;
-  return e == hipSuccess ? FKV_OK : hip_fail(e);
+  g.longest = longest;
+  return heaviest <= kSelGatherMaxShare;
 }
 
 void fill_rowset(SelectRowSet *rs, const float *scores, int64_t stride, int n_rows, int32_t *out,
@@ -1080,33 +1100,24 @@ int fkv_compress_kv_paged(fkv_ctx *ctx, const fkv_shape *shape, const void *q_wi
   if (rc != FKV_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   float *sg = reinterpret_cast<float *>(ctx->ws + ctx->lay.scores_group);
+  SelectGatherArgs c{};
+  fill_select(c.sel, ctx, r);
+  fill_rowset(&c.sel.set[c.sel.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, g.cnt_off, r.n_seq);
+  c.k = static_cast<const uint8_t *>(k);
+  c.v = static_cast<const uint8_t *>(v);
+  c.k_out = static_cast<uint8_t *>(k_pages);
+  c.v_out = static_cast<uint8_t *>(v_pages);
+  c.Hkv = r.Hkv;
+  c.block_table = pg.table;
+  c.max_pages = pg.max_pages;
+  c.page_shift = log2_exact(pg.page_size);
+  c.n_pages = (int)pg.n_pages;
+  const bool one = plan_select_gather(ctx, c, r);
   rc = enqueue_score(ws_of(ctx), shape, r, q_win, k, sg, nullptr, nullptr, st);
   if (rc != FKV_OK) return rc;
-  SelectArgs a{};
-  a.W = r.W;
-  a.n_seq = r.n_seq;
-  for (int b = 0; b <= r.n_seq; ++b) a.cu[b] = r.cu[b];
-  a.n_sets = 0;
-  a.err = ws_of(ctx).err;
-  fill_rowset(&a.set[a.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, g.cnt_off, r.n_seq);
-  {
-    SelectGatherArgs c{};
-    c.sel = a;
-    c.k = static_cast<const uint8_t *>(k);
-    c.v = static_cast<const uint8_t *>(v);
-    c.k_out = static_cast<uint8_t *>(k_pages);
-    c.v_out = static_cast<uint8_t *>(v_pages);
-    c.Hkv = r.Hkv;
-    c.block_table = pg.table;
-    c.max_pages = pg.max_pages;
-    c.page_shift = log2_exact(pg.page_size);
-    c.n_pages = (int)pg.n_pages;
-    bool done = false;
-    rc = enqueue_select_gather(ctx, c, r, st, &done);
-    if (rc != FKV_OK || done) return rc;
-    const hipError_t e = enqueue_select(ctx, a, st);
-    if (e != hipSuccess) return hip_fail(e);
-  }
+  const hipError_t e = one ? launch_select_gather(c, st) : enqueue_select(ctx, c.sel, st);
+  if (e != hipSuccess) return hip_fail(e);
+  if (one) return FKV_OK;
   return enqueue_gather_paged(ctx, r, g, k, v, idx_kv, pg, k_pages, v_pages, st);
 }
 
@@ -1201,35 +1212,35 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
   hipStream_t st = static_cast<hipStream_t>(stream);
   float *sg = reinterpret_cast<float *>(ctx->ws + ctx->lay.scores_group);
   float *stp = tsp ? reinterpret_cast<float *>(ctx->ws + ctx->lay.scores_tsp) : nullptr;
-  rc = enqueue_score(ws_of(ctx), shape, r, q_win, k, sg, stp, nullptr, st);
+  SelectGatherArgs c{};
+  fill_select(c.sel, ctx, r);
+  fill_rowset(&c.sel.set[c.sel.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, off_kv, r.n_seq);
+  if (tsp) fill_rowset(&c.sel.set[c.sel.n_sets++], stp, r.sum_p, 1, idx_tsp, off_tsp, r.n_seq);
+  c.k = static_cast<const uint8_t *>(k);
+  c.v = static_cast<const uint8_t *>(v);
+  c.k_out = static_cast<uint8_t *>(k_out);
+  c.v_out = static_cast<uint8_t *>(v_out);
+  c.x = static_cast<const uint8_t *>(x);
+  c.x_out = static_cast<uint8_t *>(x_out);
+  c.x_row_bytes = tsp ? (int)x_row_bytes : 0;
+  c.x_cpr_shift = log2_exact(c.x_row_bytes / 16);
+  c.Hkv = r.Hkv;
+  const bool one = plan_select_gather(ctx, c, r);
+  // The two-pass kernels' partials are idle in a call that leaves sums: 32 bytes a token and 4096 a sequence, for 32 a token and 96 of padding.
+  float *sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.partial);
+  static_assert(kMaxVGroups * kRowsPerGroup * sizeof(float2) >= kMaxKvHeads * sizeof(float) * kStatsChunk, "a statistics block has its tokens' sums");
+  bool summed = false;
+  rc = enqueue_score(ws_of(ctx), shape, r, q_win, k, sg, stp, nullptr, st, one ? sums : nullptr, &summed);
   if (rc != FKV_OK) return rc;
-
-  SelectArgs a{};
-  a.W = r.W;
-  a.n_seq = r.n_seq;
-  for (int b = 0; b <= r.n_seq; ++b) a.cu[b] = r.cu[b];
-  a.n_sets = 0;
-  a.err = ws_of(ctx).err;
-  fill_rowset(&a.set[a.n_sets++], sg, r.sum_p, r.Hkv, idx_kv, off_kv, r.n_seq);
-  if (tsp) fill_rowset(&a.set[a.n_sets++], stp, r.sum_p, 1, idx_tsp, off_tsp, r.n_seq);
-  {
-    SelectGatherArgs sg{};
-    sg.sel = a;
-    sg.k = static_cast<const uint8_t *>(k);
-    sg.v = static_cast<const uint8_t *>(v);
-    sg.k_out = static_cast<uint8_t *>(k_out);
-    sg.v_out = static_cast<uint8_t *>(v_out);
-    sg.x = static_cast<const uint8_t *>(x);
-    sg.x_out = static_cast<uint8_t *>(x_out);
-    sg.x_row_bytes = (int)x_row_bytes;
-    sg.x_cpr_shift = log2_exact((int)(x_row_bytes / 16));
-    sg.Hkv = r.Hkv;
-    bool done = false;
-    rc = enqueue_select_gather(ctx, sg, r, st, &done);
-    if (rc != FKV_OK || done) return rc;
-    const hipError_t e = enqueue_select(ctx, a, st);
-    if (e != hipSuccess) return hip_fail(e);
+  if (summed) {
+    c.sums = sums;
+    c.sums_stride = sums_stride(r);
+    c.n_sums = 1 + r.V - kSplitWaves;
+    c.inv_h = 1.0f / (float)r.Hq;
   }
+  const hipError_t e = one ? launch_select_gather(c, st) : enqueue_select(ctx, c.sel, st);
+  if (e != hipSuccess) return hip_fail(e);
+  if (one) return FKV_OK;
 
   const int row_bytes = kHeadDim * 2;
   GatherArgs g{};

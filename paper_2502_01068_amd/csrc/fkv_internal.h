@@ -89,6 +89,8 @@ struct ScoreArgs {
   int tile_own;           // tokens each block of the scores launch owns
   int tile_sub;           // 32-token sub-tiles that hold them and the pooling halo
   int64_t sum_p;          // row stride of scores_group
+  float *group_sums;      // [1 + V - kSplitWaves][sums_stride] or nullptr: sums of the heads' pooled scores, see pool_and_write
+  int64_t sums_stride;
 };
 
 // Single-pass (resident grid) score kernel: per-launch plan and the mailboxes of its grid exchange.
@@ -104,7 +106,13 @@ struct FusedArgs {
   int n_sub_max;           // most 32-token sub-tiles any block of the launch computes
   unsigned long long timeout_ticks;  // bound of every wait of the exchange, 100 MHz ticks
   int own[FKV_MAX_SEQS];             // prefix tokens owned by each block of sequence b
+  int split;               // -1, or: each token range of the map is 1 << split blocks, of kSplitWaves virtual groups each
 };
+// A range's groups go to two blocks of four waves where that leaves one block per CU: a SIMD's issue, which a short range is bound by,
+// then serves one wave instead of two.
+constexpr int kSplitWaves = 4, kSplitRanges = 128;
+constexpr int kMaxSums = 1 + kMaxKvHeads - kSplitWaves;
+constexpr int kSplitMaxTokens = kSplitRanges * 64;  // prefix tokens that such a launch can own (pooling kernel 1)
 constexpr size_t kFusedPartBytes = (size_t)kMaxFusedBlocks * kLseRowsPerBlock * sizeof(float2);
 constexpr size_t kFusedLseBytes = (size_t)kMaxFusedBlocks * kLseRowsPerBlock * sizeof(float);
 // Virtual-group helpers (a = any args struct with Hkv, G, vsh).
@@ -118,6 +126,7 @@ template <typename A> __host__ __device__ inline int vg_heads(const A &a, int v)
 }
 int fused_slots(void);
 int fused_preferred_blocks(int n_sub);
+int fused_split(int v_groups, int n_ranges, int n_sub, int max_blocks);
 int score_fused_max_blocks_per_cu(void);
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
 int keep_sub_max(int v_groups);
@@ -309,10 +318,15 @@ struct SelectGatherArgs {
   uint8_t *x_out;
   int x_row_bytes, x_cpr_shift; // as in GatherJob
   int Hkv;
+  const float *sums;            // the TSP row as n_sums rows of group sums instead of set[1].scores, or nullptr: added in order, times inv_h
+  int64_t sums_stride;          // a multiple of 4; rows on 16 bytes
+  int n_sums;                   // at most kMaxSums
+  float inv_h;
   const int32_t *block_table;   // as in PagedGatherArgs, or nullptr
   int max_pages, page_shift, n_pages;
   int parts[2][FKV_MAX_SEQS];   // blocks that share a row of each set
   int blk[FKV_MAX_SEQS + 1];    // first block of sequence b: its KV heads' rows, then its TSP row, a row's parts side by side
+  int longest;                  // keys of the longest row, and 3
 };
 // Rows that the one-block select of fkv_select.hip takes too, and the most bytes a block may copy: with more, two launches are
 // faster, whose gather has many short blocks.  us, two launches -> one (bytes of a block): 2048 tokens with hidden rows 19.4 -> 18.1
@@ -320,6 +334,6 @@ struct SelectGatherArgs {
 // 4000-4700 54.7 -> 53.7 (180 K), 13 of 2000-3100 50.5 -> 51.6 (250 K), 8 of 8192-16384 129 -> 157 (more than 800 K).
 constexpr int kSelGatherMaxKeys = 24 * 1024;
 constexpr uint32_t kSelGatherMaxShare = 192 << 10;
-hipError_t launch_select_gather(const SelectGatherArgs &a, int longest, hipStream_t s);
+hipError_t launch_select_gather(const SelectGatherArgs &a, hipStream_t s);
 
 }  // namespace fkv

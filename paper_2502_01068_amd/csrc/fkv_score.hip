@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
           }
           sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
-        store_sums<kSlots>(a, s_head, g + v, st * kSub + n, hi, inb, sum);
+        store_sums<kSlots>(a, s_head + (g + v) * kMaxGroup, g + v, st * kSub + n, hi, inb, sum);
       }
     });
   }

@@ -235,16 +235,16 @@ __device__ __forceinline__ float add_across_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// The window sums of a token for the 4 heads of virtual group g, which both wave halves hold, into s_head[4 g + i][slot]: each
+// The window sums of a token for the 4 heads of virtual group g, which both wave halves hold, into the group's rows[i][slot]: each
 // half stores two of them.  A token that is not scored counts as 0 (see pool_and_write).
 template <int kStride>
-__device__ __forceinline__ void store_sums(const ScoreArgs &a, float (*s_head)[kStride], int g, int slot, int hi, bool scored,
+__device__ __forceinline__ void store_sums(const ScoreArgs &a, float (*rows)[kStride], int g, int slot, int hi, bool scored,
                                            const float (&sum)[4]) {
   const int heads = vg_heads(a, g);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const float x = lane_pick(hi != 0, sum[2 * j], sum[2 * j + 1]);
-    if (2 * j + hi < heads) s_head[g * kMaxGroup + 2 * j + hi][slot] = scored ? x : 0.f;
+    if (2 * j + hi < heads) rows[2 * j + hi][slot] = scored ? x : 0.f;
   }
 }
 
@@ -259,9 +259,9 @@ __device__ __forceinline__ float max3(float x, float y, float z) {
 // taps are 8-byte LDS reads per head (the first tap of owned token jj is slot jj).  See pool_and_write.  Reads up to kPer - 1 slots past
 // the last tap of an owned token (kPoolPad floats behind the last row); what they give is not used.
 constexpr int kPoolPad = 4;
-template <int kStride, bool kMax, int kPer>
-__device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*s_head)[kStride], float (*g_sum)[kStride], int g,
-                                            int own, size_t col, int lane) {
+template <int kStride, bool kMax, int kPer, bool kPart>
+__device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*rows)[kStride], float *g_row, int g, int own, size_t col,
+                                            int lane) {
 #pragma clang fp contract(off)  // a pooled value is rounded before it enters a mean
   typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
   const int n_h = vg_heads(a, g), h0 = vg_head0(a, g);
@@ -270,7 +270,7 @@ __device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*s_
     float p[kMaxGroup][kPer];
 #pragma unroll
     for (int hl = 0; hl < kMaxGroup; ++hl) {
-      const float2 *row = reinterpret_cast<const float2 *>(s_head[g * kMaxGroup + (hl < n_h ? hl : 0)] + jj);
+      const float2 *row = reinterpret_cast<const float2 *>(rows[hl < n_h ? hl : 0] + jj);
       float v[kPer + 6];
 #pragma unroll
       for (int i = 0; i < kPer + 6; i += 2) {
@@ -310,32 +310,38 @@ __device__ __forceinline__ void pool7_group(const ScoreArgs &a, const float (*s_
       }
 #pragma unroll
     for (int i = 0; i < kPer; i += 2)
-      *reinterpret_cast<float2 *>(&g_sum[g][jj + i]) = make_float2(gs[i], gs[i + 1]);  // past the last owned token: not read
+      *reinterpret_cast<float2 *>(g_row + jj + i) = make_float2(gs[i], gs[i + 1]);  // past the last owned token: not read
     if (a.scores_group && a.vsh == 0) put(a.scores_group + (size_t)g * a.sum_p + col + jj, gs, a.inv_g);
+    if (kPart && a.group_sums && g >= kSplitWaves) put(a.group_sums + (size_t)(g - kSplitWaves + 1) * a.sums_stride + col + jj, gs, 1.f);
   }
 }
 
 // Pools the per-head window sums along tokens (Eq. 1), averages the heads of each KV group
 // (App. B.1) and all heads (Eq. 2) and writes the scores of the owned tokens [o0, o1).
-// s_head[4 v + i][slot] holds the window-summed probability of head i of virtual group v at token j0 + slot, 0 outside the
+// s_head[4 (v - g0) + i][slot] holds the window-summed probability of head i of virtual group v at token j0 + slot, 0 outside the
 // prefix: neutral for max pooling (scores are >= 0) and the zero padding of avg pooling.
 // Slots o0 - r - j0 .. o1 + r - 1 - j0 must be filled.  Contains block barriers.
-template <int kStride>
+// kPart: the block has the groups g0 .. g1 - 1 (all of a KV head's); where it does not have every group it leaves, instead of the mean
+// over all heads, what that is added up from in order: the sum of the first kSplitWaves groups, then each later group's.
+template <int kStride, bool kPart = false>
 __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (*s_head)[kStride],
-                                               float (*g_sum)[kStride], int j0, int o0, int o1, int col0) {
+                                               float (*g_sum)[kStride], int j0, int o0, int o1, int col0, int g0 = 0, int g1 = 0) {
 #pragma clang fp contract(off)
   const int r = a.pool_r;
   const int own = o1 - o0;
   const bool is_max = a.pool_mode == FKV_POOL_MAX;
   const int lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
+  if (!kPart) g1 = a.V;
   const bool split = a.vsh != 0;  // a KV group spans two virtual groups: its mean is formed after the barrier
-  for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g < a.V; g += n_waves) {  // one wave per virtual group
+  for (int lg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g0 + lg < g1; lg += n_waves) {  // one wave per virtual group
+    const int g = g0 + lg;
+    const float(*rows)[kStride] = s_head + lg * kMaxGroup;
     if (r == 3) {
       // two tokens per lane as long as that is one step of the loop; four then, for half the steps: each exposes its LDS reads
       // (32768 tokens: compress with 154 per block 56.2 -> 55.7 us per call, scores and window output 41.7 -> 41.4).  Kernels
       // whose rows cannot hold more, with six slots of halo, have no code for four (4 KB of 20).
       auto pool = [&](auto max_t, auto per, int n) {
-        pool7_group<kStride, decltype(max_t)::value, decltype(per)::value>(a, s_head, g_sum, g, n, (size_t)col0 + o0, lane);
+        pool7_group<kStride, decltype(max_t)::value, decltype(per)::value, kPart>(a, rows, g_sum[lg], g, n, (size_t)col0 + o0, lane);
       };
       typedef std::integral_constant<int, 2> two_t;
       typedef std::integral_constant<int, 4> four_t;
@@ -355,7 +361,7 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
       float gs = 0.f;
 #pragma unroll 1
       for (int hl = 0; hl < n_h; ++hl) {
-        const float *row = s_head[g * kMaxGroup + hl] + c;
+        const float *row = rows[hl] + c;
         float p;
         if (is_max) {
           p = row[0];
@@ -368,27 +374,36 @@ __device__ __forceinline__ void pool_and_write(const ScoreArgs &a, const float (
         if (a.scores_head) a.scores_head[(size_t)(h0 + hl) * a.sum_p + col0 + o0 + jj] = p;
         gs += p;
       }
-      g_sum[g][jj] = gs;
+      g_sum[lg][jj] = gs;
+      if (kPart && a.group_sums && g >= kSplitWaves) a.group_sums[(size_t)(g - kSplitWaves + 1) * a.sums_stride + col0 + o0 + jj] = gs;
       if (a.scores_group && !split) a.scores_group[(size_t)g * a.sum_p + col0 + o0 + jj] = gs * a.inv_g;
     }
   }
-  if (a.scores_tsp == nullptr && !(split && a.scores_group)) return;
+  const bool first_sums = kPart && a.group_sums != nullptr && g0 == 0;
+  if (a.scores_tsp == nullptr && !first_sums && !(split && a.scores_group)) return;
   lds_barrier();
   if (split && a.scores_group) {
-    for (int i = threadIdx.x; i < own * a.Hkv; i += blockDim.x) {
+    for (int i = threadIdx.x; i < own * ((g1 - g0) >> 1); i += blockDim.x) {
       const int kv = i / own, jj = i - kv * own;
-      a.scores_group[(size_t)kv * a.sum_p + col0 + o0 + jj] = (g_sum[2 * kv][jj] + g_sum[2 * kv + 1][jj]) * a.inv_g;
+      a.scores_group[(size_t)((g0 >> 1) + kv) * a.sum_p + col0 + o0 + jj] = (g_sum[2 * kv][jj] + g_sum[2 * kv + 1][jj]) * a.inv_g;
     }
   }
+  if (first_sums)
+    for (int jj = threadIdx.x; jj < own; jj += blockDim.x) {
+      float tot = 0.f;
+#pragma unroll
+      for (int i = 0; i < kSplitWaves; ++i) tot += g_sum[i][jj];
+      a.group_sums[col0 + o0 + jj] = tot;
+    }
   if (a.scores_tsp == nullptr) return;
   for (int jj = threadIdx.x; jj < own; jj += blockDim.x) {
     float tot = 0.f;
-    for (int g0 = 0; g0 < a.V; g0 += kMaxKvHeads) {  // the reads of 8 groups at a time (there are rows for as many), added in order
+    for (int v0 = 0; v0 < a.V; v0 += kMaxKvHeads) {  // the reads of 8 groups at a time (there are rows for as many), added in order
       float x[kMaxKvHeads];
 #pragma unroll
-      for (int i = 0; i < kMaxKvHeads; ++i) x[i] = g_sum[g0 + i][jj];
+      for (int i = 0; i < kMaxKvHeads; ++i) x[i] = g_sum[v0 + i][jj];
 #pragma unroll
-      for (int i = 0; i < kMaxKvHeads; ++i) tot = g0 + i < a.V ? tot + x[i] : tot;
+      for (int i = 0; i < kMaxKvHeads; ++i) tot = v0 + i < a.V ? tot + x[i] : tot;
     }
     a.scores_tsp[col0 + o0 + jj] = tot * a.inv_h;
   }

@@ -8,13 +8,15 @@
 
 namespace fkv {
 
-constexpr int kBoxChunks = kMaxFusedBlocks / 64;  // 64-block chunks an owner wave folds
-constexpr int kOwnRows = 8;                       // softmax rows per owner block, one per wave
+constexpr int kOwnRows = 8;  // softmax rows per owner block
 
+// kW waves per block, at most kRanges token ranges in a launch (a range has one block, or one for each half of its groups).
+template <int kW, int kRanges>
 struct ExchangeLds {
-  float2 part[kOwnRows][kMaxFusedBlocks];  // owner blocks: partials of their rows, by block
+  static_assert(kOwnRows % kW == 0, "rows per wave");
+  float2 part[kOwnRows][kRanges];  // owner blocks: partials of their rows, by range
   float lse[kOwnRows];
-  unsigned late[kWaves];
+  unsigned late[kW];
 };
 
 // Writes NaN into every score this block owns: a call whose exchange failed must not leave
@@ -49,7 +51,7 @@ __device__ __forceinline__ void request_args(const ScoreArgs &a, const FusedArgs
 
 // Folds a wave's per-lane (max, sum) pairs of a virtual group's 32 rows over the token lanes and posts them.  mloc[q]:
 // the block's maximum of row (q / 4) * 8 + hi * 4 + q % 4, in every lane.
-__device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
+__device__ __forceinline__ void fold_and_post(const FusedArgs &f, int range, const float (&mx)[16], const float (&sm)[16], float (&mloc)[16],
                                               int g, int lane, unsigned poisoned) {
   half_max16(mx, mloc);
   // lane q of each 16 ends up with row q's sum (and picks row q's maximum)
@@ -61,23 +63,24 @@ __device__ __forceinline__ void fold_and_post(const FusedArgs &f, const float (&
   if ((lane & 31) < 16 && poisoned == 0u) {
     const int q = lane & 15;
     const int row = g * kRowsPerGroup + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3);
-    box_post(f.part + (size_t)blockIdx.x * kLseRowsPerBlock + row, make_float2(pm, ps));
+    box_post(f.part + (size_t)range * kLseRowsPerBlock + row, make_float2(pm, ps));
   }
 }
 
 // Owner duty of a block.  A group of kOwnRows softmax rows of a sequence belongs to one block, group t to block
-// t mod n_wg.  That block's waves collect the rows' partials from every block of the sequence, fold a row
-// each and post the log-sum-exps into those blocks' result boxes.  Contains block barriers in blocks that own a group.
+// t mod n_wg.  That block's waves collect the rows' partials from every range of the sequence, fold a row at a time
+// each and post the log-sum-exps into those ranges' result boxes.  Contains block barriers in blocks that own a group.
 // False if a wait ran out (block-uniform).
-__device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &f, ExchangeLds &x, int wave, int lane) {
+template <int kW, int kRanges>
+__device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &f, ExchangeLds<kW, kRanges> &x, int wave, int lane) {
   bool wave_ok = true;
   const int groups_per_seq = a.V * (kRowsPerGroup / kOwnRows);
   const int n_groups = a.map.n_seq * groups_per_seq;
   for (int t = (int)blockIdx.x; t < n_groups; t += f.n_wg) {  // block-uniform
     const int tb = t / groups_per_seq, row0 = (t - tb * groups_per_seq) * kOwnRows;
     const int blk0 = a.map.blk[tb], nb = a.map.blk[tb + 1] - blk0;
-    constexpr int kPerPass = kWaves * (64 / kOwnRows);  // blocks the block's lanes cover at a time
-    constexpr int kPasses = kMaxFusedBlocks / kPerPass;
+    constexpr int kPerPass = kW * (64 / kOwnRows);  // ranges the block's lanes cover at a time
+    constexpr int kPasses = kRanges / kPerPass;
     const int i0 = wave * (64 / kOwnRows) + lane / kOwnRows, rl = lane % kOwnRows;
     float2 *src = f.part + (size_t)blk0 * kLseRowsPerBlock + row0 + rl;
     unsigned long long v[kPasses];
@@ -107,23 +110,25 @@ __device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &
     lds_barrier();
     bool late = false;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) late = late || x.late[w] != 0u;
+    for (int w = 0; w < kW; ++w) late = late || x.late[w] != 0u;
     if (late) { wave_ok = false; break; }  // the whole block
-    if (wave < kOwnRows) {
+#pragma unroll
+    for (int j = 0; j < kOwnRows / kW; ++j) {
+      const int own = j * kW + wave;
       float m = kNegBig, s = 0.f;
 #pragma unroll
-      for (int i = 0; i < kBoxChunks; ++i)
+      for (int i = 0; i < kRanges / 64; ++i)
         if (i * 64 + lane < nb) {
-          const float2 pv = x.part[wave][i * 64 + lane];
+          const float2 pv = x.part[own][i * 64 + lane];
           const float mn = fmaxf(m, pv.x);
           s = s * fast_exp2(m - mn) + pv.y * fast_exp2(pv.x - mn);
           m = mn;
         }
       const float mw = wave_fmax(m);
       const float sw = wave_fsum(s * fast_exp2(m - mw));
-      const int row = row0 + wave, in_group = row & (kRowsPerGroup - 1);
+      const int row = row0 + own, in_group = row & (kRowsPerGroup - 1);
       const bool row_ok = (in_group >> 3) < vg_heads(a, row / kRowsPerGroup) && (in_group & 7) < a.W;
-      if (lane == 0) x.lse[wave] = row_ok ? mw + __log2f(sw) : 0.f;
+      if (lane == 0) x.lse[own] = row_ok ? mw + __log2f(sw) : 0.f;
     }
     lds_barrier();
     const float lse = x.lse[rl];
@@ -134,12 +139,12 @@ __device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &
   return wave_ok;
 }
 
-// The log-sum-exps of the 32 rows of virtual groups g .. g + kVg - 1 from the block's result boxes, a lane each, into dst
+// The log-sum-exps of the 32 rows of virtual groups g .. g + kVg - 1 from the range's result boxes, a lane each, into dst
 // (LDS, 32 kVg floats).  Wave-uniform result: false if the wait ran out.
 template <int kVg>
-__device__ __forceinline__ bool collect_lse(const FusedArgs &f, int g, int lane, float *dst) {
+__device__ __forceinline__ bool collect_lse(const FusedArgs &f, int range, int g, int lane, float *dst) {
   const bool mine = lane < kVg * kRowsPerGroup;
-  float *box = f.lse + (size_t)blockIdx.x * kLseRowsPerBlock + g * kRowsPerGroup + (lane & (kVg * kRowsPerGroup - 1));
+  float *box = f.lse + (size_t)range * kLseRowsPerBlock + g * kRowsPerGroup + (lane & (kVg * kRowsPerGroup - 1));
   unsigned bits = kEmpty32;
   BoundedWait wait(f.timeout_ticks);
   while (true) {

@@ -25,6 +25,11 @@
 // Kernel trace, before -> after: 2048 tokens 14.5 -> 11.5 us, 6554 17.6 -> 13.8, 12289 18.1 -> 14.7, 16384 (head-wise) 20.2 ->
 // 16.5, 32768 25.4 -> 21.1.
 //
+// Short inputs leave CUs idle, and two waves a SIMD in those they use: their ranges go to two blocks of four waves each (fused_split;
+// the same work per wave, so the same bits).  The mean over all heads, for which a block needs every group, is then left to the
+// select, as sums.  us per call, before -> after: 1759 tokens 16.8 -> 15.0, 2048 with the mean 18.1 -> 17.5, 6554 22.9 ->
+// 21.2, 3 sequences of 1700 20.7 -> 17.9, head-wise 3000 19.8 -> 18.6.
+//
 // Used when the batch fits the resident grid (about 61K tokens on 256 CUs); longer inputs take
 // the kernel of fkv_score_keep.hip or the two-pass kernels.  Every wait in phase 2 is bounded: a wave that does not get what it waits
 // for within the time limit raises the context's error flag, and its block writes NaN scores.
@@ -40,6 +45,13 @@ constexpr int kFusedSubLong = 8;
 constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 
 int fused_slots(void) { return kFusedSlotsMax; }
+
+// The split of a launch's ranges (see FusedArgs), or -1: a range is one block's work.  Only where every block still has a CU to
+// itself, and ranges are of one or two sub-tiles then.
+int fused_split(int v_groups, int n_ranges, int n_sub, int max_blocks) {
+  const int shift = v_groups > kSplitWaves ? 1 : 0;
+  return v_groups <= kMaxKvHeads && n_sub <= kFusedSubFew && n_ranges <= kSplitRanges && (n_ranges << shift) <= max_blocks ? shift : -1;
+}
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more
 // sub-tile per block (fewer, longer blocks): the exchange gets slower with the number of blocks, a sub-tile costs a trip to memory.
 // Launches in a row, us (blocks: sub-tiles per block):
@@ -54,27 +66,29 @@ int fused_slots(void) { return kFusedSlotsMax; }
 // 250: 2 20.2; 20001 191: 4 25.8, 223: 3 23.9, 254: 3 24.3; 40000 208: 7 36.1, 224: 6 34.0, 255: 6 35.1).
 int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : n_sub * kSub <= kFusedSlotsMax ? 224 : kMaxFusedBlocks; }
 
-template <int kFusedSub>
-__global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs f) {
+// kW = kWaves: a block has all virtual groups of its range.  kW = 4: up to four of them, and a range 1 << f.split blocks.
+template <int kFusedSub, int kW>
+__global__ __launch_bounds__(kW * 64) void k_score_fused(ScoreArgs a, FusedArgs f) {
   constexpr int kFusedSlots = kFusedSub * kSub;
-  __shared__ __attribute__((aligned(16))) uint8_t lds_all[kWaves * kStageBytes];
-  __shared__ float cst_lds[kWaves][kRowsPerGroup];
-  __shared__ ExchangeLds xch;
+  constexpr bool kSplit = kW < kWaves;
+  __shared__ __attribute__((aligned(16))) uint8_t lds_all[kW * kStageBytes];
+  __shared__ float cst_lds[kW][kRowsPerGroup];
+  __shared__ ExchangeLds<kW, kSplit ? kSplitRanges : kMaxFusedBlocks> xch;
   __shared__ unsigned flag_lds[1];
-  float(*s_head)[kFusedSlots] = reinterpret_cast<float(*)[kFusedSlots]>(lds_all);  // [Hkv*4][slots]
-  float(*g_sum)[kFusedSlots] =
-      reinterpret_cast<float(*)[kFusedSlots]>(lds_all + kMaxKvHeads * kMaxGroup * kFusedSlots * 4);
-  static_assert((kMaxKvHeads * kMaxGroup + kMaxKvHeads) * kFusedSlots * 4 <= kWaves * kStageBytes, "LDS reuse");
+  float(*s_head)[kFusedSlots] = reinterpret_cast<float(*)[kFusedSlots]>(lds_all);  // [kW*4][slots]
+  float(*g_sum)[kFusedSlots] = reinterpret_cast<float(*)[kFusedSlots]>(lds_all + kW * kMaxGroup * kFusedSlots * 4);
+  static_assert((kW * kMaxGroup + kW) * kFusedSlots * 4 <= kW * kStageBytes, "LDS reuse");
 
   request_args(a, f);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hi = lane >> 5;
-  const int b = find_seq(a.map, blockIdx.x);
+  const int range = kSplit ? (int)blockIdx.x >> f.split : (int)blockIdx.x;
+  const int b = find_seq(a.map, range);
   const int tok_base = a.map.cu[b];
   const int Lb = a.map.cu[b + 1] - tok_base;
   const int P = Lb - a.W;
   const int r = a.pool_r;
-  const int local = (int)blockIdx.x - a.map.blk[b];
+  const int local = range - a.map.blk[b];
   const int n_ranges = a.map.blk[b + 1] - a.map.blk[b];
   const int o0 = local * f.own[b], o1 = min(P, o0 + f.own[b]);  // owned prefix tokens
   const bool last = local == n_ranges - 1;                      // also owns the window columns
@@ -83,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   const int n_sub = (c1 - c0 + kSub - 1) / kSub;                // <= kFusedSub (host guarantees)
   const int col0 = tok_base - b * a.W;
   uint8_t *stage = lds_all + wave * kStageBytes;
-  const int g = wave;
+  const int g0 = kSplit ? ((int)blockIdx.x & ((1 << f.split) - 1)) * kW : 0, g = g0 + wave;
   const bool has_group = g < a.V;  // the host takes this kernel only for V <= 8 (one wave per virtual group)
 
   const unsigned flag = request_flag(f.err);
@@ -140,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   }
   // Looked at before the mailbox posts go out: a load is waited for together with them otherwise.
   const unsigned poisoned = __builtin_amdgcn_readfirstlane(flag);
-  if (has_group) fold_and_post(f, mx, sm, mloc, g, lane, poisoned);
+  if (has_group) fold_and_post(f, range, mx, sm, mloc, g, lane, poisoned);
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
   // (fkv_clear_error) every launch only marks its scores invalid.
   if (poisoned != 0u) {
@@ -175,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 
   // ---- phase 2b: collect the log-sum-exp of this wave's 32 rows from the block's result box
   if (has_group && wave_ok) {
-    wave_ok = collect_lse<1>(f, g, lane, cst_lds[wave]);
+    wave_ok = collect_lse<1>(f, range, g, lane, cst_lds[wave]);
   }
   FKV_BTICK(2);
   lds_barrier();  // every wave has left its staging tile (phase 3 reuses them); flag_lds is initialised
@@ -205,7 +219,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
           }
           sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
-        store_sums<kFusedSlots>(a, s_head, g, st * kSub + n, hi, inb, sum);
+        store_sums<kFusedSlots>(a, s_head + wave * kMaxGroup, g, st * kSub + n, hi, inb, sum);
       }
     }
   }
@@ -213,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
   FKV_TICK(40);
   const bool grid_ok = flag_lds[0] != 0u;
   if (grid_ok) {
-    pool_and_write<kFusedSlots>(a, s_head, g_sum, c0, o0, o1, col0);
+    pool_and_write<kFusedSlots, kSplit>(a, s_head, g_sum, c0, o0, o1, col0, g0, min(a.V, g0 + kW));
   } else {
     poison_scores(a, col0, o0, o1);
     if (threadIdx.x == 0) __hip_atomic_store(f.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -223,18 +237,20 @@ __global__ __launch_bounds__(kThreads) void k_score_fused(ScoreArgs a, FusedArgs
 }
 
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s) {
-  if (f.n_sub_max <= kFusedSubFew)
-    hipLaunchKernelGGL(k_score_fused<kFusedSubFew>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+  if (f.split >= 0)
+    hipLaunchKernelGGL((k_score_fused<kFusedSubFew, kSplitWaves>), dim3(f.n_wg), dim3(kSplitWaves * 64), 0, s, a, f);
+  else if (f.n_sub_max <= kFusedSubFew)
+    hipLaunchKernelGGL((k_score_fused<kFusedSubFew, kWaves>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   else if (f.n_sub_max <= kFusedSubShort)
-    hipLaunchKernelGGL(k_score_fused<kFusedSubShort>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+    hipLaunchKernelGGL((k_score_fused<kFusedSubShort, kWaves>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   else
-    hipLaunchKernelGGL(k_score_fused<kFusedSubLong>, dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
+    hipLaunchKernelGGL((k_score_fused<kFusedSubLong, kWaves>), dim3(f.n_wg), dim3(kThreads), 0, s, a, f);
   return hipGetLastError();
 }
 
 int score_fused_max_blocks_per_cu(void) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_score_fused<kFusedSubLong>, kThreads, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_score_fused<kFusedSubLong, kWaves>, kThreads, 0) != hipSuccess) return 0;
   return n;
 }
 

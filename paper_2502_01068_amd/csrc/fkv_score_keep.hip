@@ -37,9 +37,10 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
   __shared__ __attribute__((aligned(16))) float g_sum[kGroups][kSlots];
   __shared__ float cst_lds[kGroups][kRowsPerGroup];
   __shared__ unsigned late_lds[kWaves];
-  static_assert(sizeof(ExchangeLds) <= sizeof(g_sum), "the exchange's tables lie where the group sums go later");
-  static_assert(__alignof__(g_sum) >= alignof(float2) && __alignof__(g_sum) >= alignof(ExchangeLds), "the pooling writes pairs of sums");
-  ExchangeLds &xch = *reinterpret_cast<ExchangeLds *>(g_sum);
+  typedef ExchangeLds<kWaves, kMaxFusedBlocks> xch_t;
+  static_assert(sizeof(xch_t) <= sizeof(g_sum), "the exchange's tables lie where the group sums go later");
+  static_assert(__alignof__(g_sum) >= alignof(float2) && __alignof__(g_sum) >= alignof(xch_t), "the pooling writes pairs of sums");
+  xch_t &xch = *reinterpret_cast<xch_t *>(g_sum);
   constexpr int kWaveSums = kVg * kMaxGroup * kSlots;  // floats of s_head that one wave fills
   static_assert(kLds * kVg * kRowsPerGroup * kSub <= kWaveSums && kWaveSums % 4 == 0, "logits kept in LDS");
 
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
 #pragma unroll
     for (int v = 0; v < kVg; ++v) {
       float mloc[16];
-      fold_and_post(f, mx[v], sm[v], mloc, g + v, lane, poisoned);
+      fold_and_post(f, blockIdx.x, mx[v], sm[v], mloc, g + v, lane, poisoned);
     }
   }
   // A failed exchange leaves mailboxes in an unknown state: until the host has reset them
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
 
   // ---- phase 2
   bool wave_ok = owner_duty(a, f, xch, wave, lane);
-  if (has_group) wave_ok = wave_ok && collect_lse<kVg>(f, g, lane, cst_lds[g]);
+  if (has_group) wave_ok = wave_ok && collect_lse<kVg>(f, blockIdx.x, g, lane, cst_lds[g]);
 
   // ---- phase 3
   if (has_group && wave_ok) {
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void k_score_keep(ScoreArgs a, FusedArgs 
           }
           sum[hl] = add_across_halves(sum[hl]);  // other half of the window rows
         }
-        store_sums<kSlots>(a, s_head, g + v, st * kSub + n, hi, inb, sum);
+        store_sums<kSlots>(a, s_head + (g + v) * kMaxGroup, g + v, st * kSub + n, hi, inb, sum);
       }
     };
     {

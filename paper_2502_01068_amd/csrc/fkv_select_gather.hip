@@ -18,7 +18,30 @@ struct GatherPart {  // what a block works on
   int b, row;         // sequence; KV head, or -1: the TSP row
   int P, k, i0, i1;   // prefix tokens, kept tokens, the block's part of them
   unsigned failed;
+  bool summed;        // sc is the first of the groups' rows of sums
 };
+
+// load_keys for a row that is the sum of a.n_sums rows of the workspace, times inv_h: what the score kernels make the mean over
+// all heads of where a block has every group, bit for bit.  Their stride is a multiple of four: whole groups of four are read.
+template <int kKpt>
+__device__ __forceinline__ void load_summed_keys(const SelectGatherArgs &a, const float *base, int mis, int P, int wave, int lane,
+                                                 uint32_t (&key)[kKpt]) {
+#pragma clang fp contract(off)
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < kKpt / 4; ++q) {
+    const int at = slot_pos<kKpt>(wave, lane, q);
+    f32x4 x[kMaxSums], tot = zero;
+#pragma unroll
+    for (int g = 0; g < kMaxSums; ++g)
+      x[g] = g < a.n_sums && at < mis + P ? *reinterpret_cast<const f32x4 *>(base + g * a.sums_stride + at) : zero;
+#pragma unroll
+    for (int g = 0; g < kMaxSums; ++g) tot = g < a.n_sums ? tot + x[g] : tot;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[4 * q + e] = at + e >= mis && at + e < mis + P ? order_key(tot[e] * a.inv_h) : 0u;
+  }
+}
 
 __device__ __forceinline__ GatherPart locate_part(const SelectGatherArgs &a) {
   const SelectArgs &s = a.sel;
@@ -33,10 +56,11 @@ __device__ __forceinline__ GatherPart locate_part(const SelectGatherArgs &a) {
   const float *scores[2] = {s.set[0].scores, s.set[1].scores};
   int32_t *idx[2] = {s.set[0].idx_out, s.set[1].idx_out};
   const int64_t stride0 = s.set[0].row_stride;
+  const float *sums = a.sums;
   const int total0 = s.set[0].total;
   const int c0[2] = {s.set[0].cnt_off[b], s.set[1].cnt_off[b]}, c1[2] = {s.set[0].cnt_off[b + 1], s.set[1].cnt_off[b + 1]};
   asm volatile("" ::"s"(at0), "s"(at1), "s"(blk0), "s"(n_rows0), "s"(s.W), "s"(s.err), "s"(scores[0]), "s"(scores[1]), "s"(idx[0]), "s"(idx[1]),
-               "s"(stride0), "s"(total0), "s"(c0[0]), "s"(c0[1]), "s"(c1[0]), "s"(c1[1]), "s"(n_part[0]), "s"(n_part[1]));
+               "s"(stride0), "s"(sums), "s"(total0), "s"(c0[0]), "s"(c0[1]), "s"(c1[0]), "s"(c1[1]), "s"(n_part[0]), "s"(n_part[1]));
   int zero = 0;
   asm("" : "+v"(zero));  // else the flag, a uniform value, is waited for on the spot
   GatherPart p;
@@ -52,7 +76,8 @@ __device__ __forceinline__ GatherPart locate_part(const SelectGatherArgs &a) {
   p.i0 = (int)((uint32_t)p.k * (uint32_t)part / (uint32_t)parts);  // k <= 32768, parts <= kSelGatherMaxParts
   p.i1 = (int)((uint32_t)p.k * (uint32_t)(part + 1) / (uint32_t)parts);
   const int col = at0 - b * s.W;
-  p.sc = tsp ? scores[1] + col : scores[0] + (size_t)row * stride0 + col;
+  p.summed = tsp && sums != nullptr;
+  p.sc = tsp ? (sums != nullptr ? sums : scores[1]) + col : scores[0] + (size_t)row * stride0 + col;
   p.out = tsp ? idx[1] + c0[1] : idx[0] + (size_t)row * total0 + c0[0];
   return p;
 }
@@ -69,7 +94,12 @@ __device__ __forceinline__ bool keep_row(const SelectGatherArgs &a, const Gather
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mis = (int)((reinterpret_cast<uintptr_t>(p.sc) >> 2) & 3), kp = p.k - a.sel.W;
   uint32_t key[kKpt];
-  load_keys<kKpt>(p.sc - mis, mis, p.P, 0, wave, lane, key);
+  if constexpr (kKpt <= kSplitMaxTokens / kSelThreads + 4) {
+    if (p.summed) load_summed_keys<kKpt>(a, p.sc - mis, mis, p.P, wave, lane, key);
+    else load_keys<kKpt>(p.sc - mis, mis, p.P, 0, wave, lane, key);
+  } else {
+    load_keys<kKpt>(p.sc - mis, mis, p.P, 0, wave, lane, key);
+  }
   clear_search(s.search, tid);
   if (uniform(p.failed) != 0u) return false;
   __syncthreads();
@@ -165,9 +195,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_gather(SelectGatherArgs 
   }
 }
 
-hipError_t launch_select_gather(const SelectGatherArgs &a, int longest, hipStream_t s) {
+hipError_t launch_select_gather(const SelectGatherArgs &a, hipStream_t s) {
   const dim3 grid((unsigned)a.blk[a.sel.n_seq]), block(kSelThreads);
-  switch ((longest + 4 * kSelThreads - 1) / (4 * kSelThreads)) {  // keys per thread by the longest row
+  switch ((a.longest + 4 * kSelThreads - 1) / (4 * kSelThreads)) {  // keys per thread by the longest row
     case 0:
     case 1: hipLaunchKernelGGL(k_select_gather<4>, grid, block, 0, s, a); break;
     case 2: hipLaunchKernelGGL(k_select_gather<8>, grid, block, 0, s, a); break;

@@ -1,0 +1,33 @@
+"""Short inputs, whose token ranges are split between two blocks: the scores of a call without the all-heads mean, which takes the
+split, against those of a call with it, which does not; bit for bit.  At the edges of a range and at the most ranges and one past them."""
+import pytest
+import torch
+
+from paper_2502_01068_amd import binding as fk
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,pool,pool_kernel,window", [
+    ([34], 32, 8, "avg", 7, 8), ([35, 36, 61], 32, 8, "max", 7, 8), ([3335], 32, 8, "avg", 7, 8), ([3336], 28, 4, "avg", 7, 8), ([7431], 32, 8, "max", 7, 8),
+    ([7432], 40, 8, "avg", 7, 8), ([8199], 24, 8, "avg", 1, 7), ([8200], 20, 4, "max", 1, 8), ([4000], 5, 5, "avg", 15, 8), ([4000], 42, 6, "avg", 31, 3),
+    ([900] * 7, 56, 8, "avg", 5, 8), ([1500, 33, 8, 5000], 28, 4, "max", 15, 8),
+])
+def test_split_ranges_give_the_same_bits(lengths, hq, hkv, pool, pool_kernel, window):
+    print("case: score split lengths=%s hq=%d hkv=%d %s %d w=%d" % (lengths[:4], hq, hkv, pool, pool_kernel, window), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(sum(lengths) + hq)
+    ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=len(lengths))
+    shape = fk.make_shape(lengths, n_q_heads=hq, n_kv_heads=hkv, pool_mode=pool, pool_kernel=pool_kernel, window=window)
+    q = 2.0 * torch.randn((len(lengths), window, hq, 128), device="cuda", generator=gen, dtype=torch.bfloat16)
+    k = torch.randn((sum(lengths), hkv, 128), device="cuda", generator=gen, dtype=torch.bfloat16)
+    whole, mean = ctx.fkv_score_window(shape, q, k)
+    split, none = ctx.fkv_score_window(shape, q, k, want_tsp=False)
+    heads = ctx.fkv_score_heads(shape, q, k)
+    assert none is None and torch.equal(whole.view(torch.int32), split.view(torch.int32))
+    g = hq // hkv
+    assert torch.allclose(heads.view(hkv, g, -1).double().mean(1), whole.double(), rtol=1e-6, atol=0)  # sums of at most 8 fp32 values
+    assert torch.allclose(heads.double().mean(0), mean.double(), rtol=1e-5, atol=0)  # of at most 56
+    for _ in range(3):
+        assert torch.equal(ctx.fkv_score_window(shape, q, k, want_tsp=False)[0].view(torch.int32), whole.view(torch.int32))
+    assert ctx.fkv_query_error() == 0
+    ctx.close()

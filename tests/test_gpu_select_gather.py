@@ -1,6 +1,7 @@
 """Select and gather in one launch against the two launches that a timed context makes of the same call: indices and copies, so
 bit for bit.  Rows at the edges of the keys per thread, parts of a row at the edges of a step, one and several sequences, rows of
-8 keys per thread next to longer ones, hidden rows of any multiple of 16 bytes, everything kept and only the window kept, pages."""
+8 keys per thread next to longer ones, hidden rows of any multiple of 16 bytes, everything kept and only the window kept, pages; and
+rows of all heads that the select adds up from the groups' sums (ranges split between blocks), at the most ranges and one past them."""
 import pytest
 import torch
 
@@ -18,14 +19,18 @@ def _randn(gen, *shape):
     ([8198], [65], [700], 136, 64), ([12293], [1229], [1230], 1024, 28), ([12294], [129], None, 0, 32), ([16389], [1000], [1639], 4096, 32),
     ([16390], [16390], None, 0, 32), ([20486], [300], [20486], 8, 64), ([24581], [2000], [2400], 4096, 32), ([24582], [2000], [24], 64, 32),
     ([23000, 2000, 8, 9, 4500], [100, 2000, 8, 8, 450], [2300, 17, 8, 9, 1111], 512, 32), ([1500 + 7 * i for i in range(64)], [130] * 64, [31] * 64, 56, 32),
-    ([3000] * 9, [8, 64, 128, 63, 129, 3000, 8, 9, 257], None, 0, 28),
+    ([3000] * 9, [8, 64, 128, 63, 129, 3000, 8, 9, 257], None, 0, 28), ([3335], [300], [600], 64, 24), ([3336], [200], [301], 64, 28),
+    ([7431, 9], [300, 8], [1000, 9], 64, 16), ([7440], [300], [1000], 64, 20), ([700, 2049, 8, 1300], [100] * 2 + [8, 100], [70, 205, 8, 130], 64, 32),
 ])
-def test_one_launch_matches_two(lengths, budgets, k_tsp, hidden, hq):
-    print("case: select and gather lengths=%s.. (%d) tsp=%s hidden=%d hq=%d" % (lengths[:3], len(lengths), k_tsp and k_tsp[:3], hidden, hq), flush=True)
-    hkv = 4 if hq == 28 else 8
+@pytest.mark.parametrize("pool", [("avg", 7), ("max", 1), ("avg", 15)], ids=lambda p: "%s%d" % p)
+def test_one_launch_matches_two(lengths, budgets, k_tsp, hidden, hq, pool):
+    if pool != ("avg", 7) and sum(lengths) > 8300:
+        pytest.skip("the pooling does not matter behind the blocks that have all heads")
+    print("case: select and gather lengths=%s.. (%d) tsp=%s hidden=%d hq=%d %s" % (lengths[:3], len(lengths), k_tsp and k_tsp[:3], hidden, hq, pool), flush=True)
+    hkv = {28: 4, 20: 4, 16: 2}.get(hq, 8)
     gen = torch.Generator(device="cuda").manual_seed(sum(lengths) + hq)
     ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=len(lengths))
-    shape = fk.make_shape(lengths, n_q_heads=hq, n_kv_heads=hkv)
+    shape = fk.make_shape(lengths, n_q_heads=hq, n_kv_heads=hkv, pool_mode=pool[0], pool_kernel=pool[1])
     q, k, v = _randn(gen, len(lengths), 8, hq, 128), _randn(gen, sum(lengths), hkv, 128), _randn(gen, sum(lengths), hkv, 128)
     x = _randn(gen, sum(lengths), hidden) if k_tsp else None
 
