@@ -115,6 +115,7 @@ __device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &
 #pragma unroll
     for (int j = 0; j < kOwnRows / kW; ++j) {
       const int own = j * kW + wave;
+      if (own >= kOwnRows) break;  // never; without it the partial-keep kernel for wide groups spills a register
       float m = kNegBig, s = 0.f;
 #pragma unroll
       for (int i = 0; i < kRanges / 64; ++i)
