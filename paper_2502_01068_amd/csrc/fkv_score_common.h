@@ -193,6 +193,16 @@ __device__ __forceinline__ void count_logit(float z, float one, float &mx, float
 // barrier that wait is pure latency.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// The first element of a row, whose (max, sum) is (kNegBig, 0) before it, makes it (z, one) where z is an ordinary number: what
+// count_logit gives, without its exponential.  True if that holds for every live lane's 16 logits of a tile (an infinite or
+// NaN one: false).  Wave-uniform.
+__device__ __forceinline__ bool ordinary_tile(const floatx16 &z, bool live) {
+  float s = 0.f;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) s += fabsf(z[q]);
+  return !__any(live && !(s < -kNegBig));
+}
+
 // Folds the per-lane running (max, sum) pairs of a wave's 32 softmax rows over the 32 token
 // lanes, through a wave-private LDS transpose (`scratch` >= 4480 bytes, 4-byte aligned).
 // In: mx[r], sm[r] of row m = (r/4)*8 + (lane/32)*4 + r%4 for token lane%32.

@@ -68,7 +68,7 @@ int fused_preferred_blocks(int n_sub) { return n_sub == 1 ? 128 : n_sub * kSub <
 
 // kW = kWaves: a block has all virtual groups of its range.  kW = 4: up to four of them, and a range 1 << f.split blocks.
 template <int kFusedSub, int kW>
-__global__ __launch_bounds__(kW * 64) void k_score_fused(ScoreArgs a, FusedArgs f) {
+__global__ __launch_bounds__(kW * 64, 2) void k_score_fused(ScoreArgs a, FusedArgs f) {
   constexpr int kFusedSlots = kFusedSub * kSub;
   constexpr bool kSplit = kW < kWaves;
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[kW * kStageBytes];
@@ -147,8 +147,18 @@ __global__ __launch_bounds__(kW * 64) void k_score_fused(ScoreArgs a, FusedArgs 
       // running reference = max over every logit that is counted or later scored, so that
       // 2^(z - reference) <= 1 for all of them; only counted keys enter the sum.  Masked window
       // keys and slots outside the sequence are neither: they must not move the reference.
+      // A row's first tile: with at most two tiles their instructions are what the stream takes (2048 tokens 17.66 -> 17.46 us per
+      // call, 6554 21.3 -> 21.1, 12289 24.9 -> 24.6); with more it is the memory, and the choice costs (16384 head-wise 31.9 -> 32.1).
+      if (kFusedSub <= kFusedSubFew && st == 0 && ordinary_tile(acc, counted | scored)) {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) count_logit(take[q & 3] ? acc[q] : kNegBig, one[q & 3], mx[q], sm[q]);
+        for (int q = 0; q < 16; ++q) {
+          mx[q] = take[q & 3] ? acc[q] : kNegBig;
+          sm[q] = one[q & 3];
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) count_logit(take[q & 3] ? acc[q] : kNegBig, one[q & 3], mx[q], sm[q]);
+      }
     }
     FKV_TICK(33);
   }

@@ -31,3 +31,30 @@ def test_split_ranges_give_the_same_bits(lengths, hq, hkv, pool, pool_kernel, wi
         assert torch.equal(ctx.fkv_score_window(shape, q, k, want_tsp=False)[0].view(torch.int32), whole.view(torch.int32))
     assert ctx.fkv_query_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("length", [34, 2048, 6554, 12289])
+def test_first_tile_without_finite_logits(length):
+    """Keys of a block's first tile whose logits are -inf count for nothing, as in the two-pass kernels; a NaN one takes its KV
+    head's scores with it and no other's."""
+    print("case: score first tile length=%d" % length, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(length)
+    ctx = fk.Context(max_total_tokens=length, max_seqs=1)
+    shape = fk.make_shape([length], pool_mode="avg")
+    q = 2.0 * torch.randn((1, 8, 32, 128), device="cuda", generator=gen, dtype=torch.bfloat16)
+    k = torch.randn((length, 8, 128), device="cuda", generator=gen, dtype=torch.bfloat16)
+    q[..., 0] = -1
+    plain = ctx.fkv_score_window(shape, q, k)[0].clone()
+    k[3, 2, 0] = float("inf")
+    got = ctx.fkv_score_window(shape, q, k)[0].clone()
+    short = ctx.fkv_score_window(shape, q, k, want_tsp=False)[0]
+    assert torch.equal(got, short)
+    ctx.fkv_set_score_path(1)
+    torch.testing.assert_close(got, ctx.fkv_score_window(shape, q, k)[0], rtol=2e-6, atol=1e-37)  # sums over other shares, as for finite inputs
+    ctx.fkv_set_score_path(0)
+    k[3, 2, 0] = float("nan")
+    bad = ctx.fkv_score_window(shape, q, k)[0]
+    assert torch.isnan(bad[2]).all()
+    others = [g for g in range(8) if g != 2]
+    assert torch.equal(bad[others], plain[others]) and torch.equal(got[others], plain[others])
+    ctx.close()
