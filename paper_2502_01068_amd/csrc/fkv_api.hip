@@ -40,7 +40,7 @@ WsLayout ws_layout(int64_t max_tokens, int32_t max_seqs) {
   w.dec_part = off;     off += align_up((size_t)2 * kDecodeMaxBlocks * kDecodeSlotFloats * sizeof(float));
   w.dec_count = off;    off += align_up((size_t)max_seqs * kMaxKvHeads * sizeof(unsigned));
   const size_t wout_slots = (size_t)kWoutBlocks + (size_t)kMaxVGroups * max_seqs;
-  w.wout_o = off;       off += align_up(wout_slots * kRowsPerGroup * kHeadDim * sizeof(float));
+  w.wout_o = off;       off += align_up(wout_slots * kRowsPerGroup * kHeadDim * sizeof(float)) + kWoSumBytes;  // the window sums first
   w.wout_ms = off;      off += align_up(wout_slots * kRowsPerGroup * sizeof(float2));
   w.total = off;
   return w;
@@ -120,6 +120,7 @@ struct fkv_ctx {
   int n_cu;            // compute units x resident blocks per CU of the single-pass score kernel
   int n_cu_keep;       // the same of the score kernel that keeps part of the logits (0: not available)
   int score_path;      // 0 auto, 1 two-pass kernels, 2 single-pass resident grid
+  int n_cu_wout;       // the same of the window output's kernel that leaves window sums
   int n_cu_select;     // resident blocks of the several-blocks-per-row select kernel (0: not available)
   int select_path;     // 0 auto, 1 never several blocks per row, 2 several blocks per row whenever the launch fits
   unsigned long long wait_ticks;  // bound of every wait inside a kernel, 100 MHz ticks
@@ -345,8 +346,12 @@ int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, Wout
   constexpr int kMergeUnits = 4;
   const int sub_max = r.V > kMaxKvHeads ? scores_sub_wide() : scores_sub_long();
   const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
-  const int units = wo ? wout_merge_units(*wo) : 0, beside = (units + kMergeUnits - 1) / kMergeUnits;
-  const bool merge = units > 0 && 8 * beside <= n_cu;
+  const int units = wo ? wout_merge_units(*wo) : 0;
+  // With the window sums the scores' blocks are short and leave a quarter of the CUs to the merge: 32768 tokens, 16 blocks of it
+  // 10.7 us, 64 of them 6.7; up to 8 units a block (8 sequences of 1500-2000 tokens 27.5 us per call, a launch of its own 28.5; 16 of
+  // 1200-1700, 16 units a block, 46.0 against 38.2).
+  const int beside = wo && wo->sums ? std::min(units, n_cu / 4) : (units + kMergeUnits - 1) / kMergeUnits;
+  const bool merge = units > 0 && (wo->sums ? units <= 2 * n_cu : 8 * beside <= n_cu);
   const int own = even_share(r, r.W, 2 * a.pool_r, merge ? n_cu - beside : n_cu, scores_sub_short(), sub_max);
   a.tile_own = own;
   a.tile_sub = (own + 2 * a.pool_r + 31) / 32;
@@ -367,7 +372,8 @@ int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, Wout
   if (nb > 0) {
     Timed t(w.prof, st, KID_SCORES);
     const int idle = std::max(beside, (n_cu - nb % n_cu) % n_cu);
-    e = merge ? launch_wout_scores(a, *wo, nb, std::min(idle, units), st) : launch_scores(a, nb, wo != nullptr, st);
+    if (merge || (wo && wo->sums)) e = launch_wout_scores(a, *wo, nb, merge ? std::min(idle, units) : 0, st);
+    else e = launch_scores(a, nb, wo != nullptr, st);
     if (e != hipSuccess) return hip_fail(e);
   }
   return FKV_OK;
@@ -677,6 +683,7 @@ int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_
     const int per_cu = score_fused_max_blocks_per_cu();
     c->n_cu = prop.multiProcessorCount * (per_cu > 0 ? 1 : 0);  // one resident block per CU
     c->n_cu_keep = prop.multiProcessorCount * (score_keep_max_blocks_per_cu() > 0 ? 1 : 0);
+    c->n_cu_wout = prop.multiProcessorCount * (wout_sums_max_blocks_per_cu() > 0 ? 1 : 0);
     c->n_cu_select = prop.multiProcessorCount * (select_coop_max_blocks_per_cu() > 0 ? 1 : 0);
   }
   c->select_path = 0;
@@ -952,7 +959,7 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   a.q_win = static_cast<const uint16_t *>(q_win);
   a.k = static_cast<const uint16_t *>(k);
   a.v = static_cast<const uint16_t *>(v);
-  a.part_o = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
+  a.part_o = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o + kWoSumBytes);
   a.part_ms = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.wout_ms);
   a.out = out;
   a.keep_k = keep_k;
@@ -968,6 +975,25 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   a.causal = shape->causal;
   const float scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.0f / sqrtf((float)shape->head_dim);
   a.scale_log2e = scale * 1.4426950408889634f;
+  // Where the blocks' logits fit the chip and all blocks are resident at once, the scores need no second pass over K (us per call, two
+  // passes -> one: 1500 tokens 19.8 -> 16.5, 8000 21.8 -> 20.4, 16384 27.9 -> 24.8, 32768 41.3 -> 35.5, 64 / 8 heads 16000 37.2 -> 30.1, 32
+  // sequences of 800-900 51.0 -> 47.0).  Not while several contexts exist on the device: resident launches of different contexts
+  // are chained, and not where the two-pass kernels are asked for.
+  const int blocks = a.n_split * r.V * r.n_seq, per = (tiles_max + a.n_split - 1) / a.n_split;
+  if (keep_k && ctx->score_path != 1 && !several_contexts(ctx->device) && per <= kWoKeepTiles * wout_tiles_per_block_min() &&
+      blocks <= std::min(ctx->n_cu_wout, kMaxFusedBlocks) && a.n_split <= kWoKeepSplits &&
+      r.sum_p * r.Hq * (int64_t)sizeof(float) <= (int64_t)kWoSumBytes) {
+    a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
+    a.sums_stride = r.sum_p;
+    a.boxes = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.fused_part);
+    a.err = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters) + kCtrError;
+    a.timeout_ticks = ctx->wait_ticks;
+    const hipError_t e = gated_launch(ctx->device, st, [&] {
+      Timed t(ctx, st, KID_WOUT);
+      return launch_wout(a, st);
+    });
+    return e == hipSuccess ? FKV_OK : hip_fail(e);
+  }
   Timed t(ctx, st, KID_WOUT);
   const hipError_t e = launch_wout(a, st);
   return e == hipSuccess ? FKV_OK : hip_fail(e);
@@ -1013,7 +1039,8 @@ int fkv_score_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_
   rc = enqueue_wout(ctx, shape, r, q_win, k, v, out, r.sum_p > 0, wo, st);
   if (rc != FKV_OK) return rc;
   if (r.sum_p == 0) return enqueue_wout_merge(ctx, wo, st);
-  // second pass over K (what the first pass left in the caches is reused): the scores, and the merge of the output
+  // the scores, from the window sums where that pass left them, else from a second pass over K (what the first left in the
+  // caches is reused), and the merge of the output
   ScoreArgs a{};
   fill_score_args(a, w, shape, r, q_win, k, scores_group, scores_tsp, nullptr);
   return enqueue_scores_pass2(w, a, r, &wo, st);

@@ -239,9 +239,20 @@ struct WoutArgs {
   float scale_log2e;
   float *rowstat;         // [n_seq][V*32] or nullptr: the merge leaves each softmax row's log-sum-exp (log2 units) here
   int keep_k;             // K is read with plain loads (it will be read again soon) instead of non-temporal ones
+  float *sums;            // [Hq][sums_stride] or nullptr: the blocks leave each prefix token's window-summed probability per head here
+  int64_t sums_stride;
+  float2 *boxes;          // [n_seq * V][n_split][32] mailboxes, empty before and (emptied by the scores' launch) after; with sums
+  const unsigned *err;    // the context's sticky error flag, with sums: the mailboxes may hold anything while it is set
+  unsigned long long timeout_ticks;
 };
+// Window sums that a block could not form (its normalisers did not come): the scores' launch reads K again for those tokens.
+constexpr unsigned kNoSum = 0xFFFFFFFFu;
+constexpr int kWoKeepTiles = 4;    // 32-token tiles per wave whose logits a block keeps
+constexpr int kWoKeepSplits = 32;  // most splits whose normalisers a block folds for itself
+constexpr size_t kWoSumBytes = (size_t)8 << 20;
 int wout_tiles_per_block_min(void);
 hipError_t launch_wout(const WoutArgs &a, hipStream_t s);        // the splits' partials
+int wout_sums_max_blocks_per_cu(void);
 hipError_t launch_wout_merge(const WoutArgs &a, hipStream_t s);  // the output from them
 int wout_merge_units(const WoutArgs &a);
 // The scores from those partials, whose normalisers every block folds for itself, in one launch; its first n_merge blocks

@@ -111,6 +111,38 @@ __global__ __launch_bounds__(256) void k_combine(ScoreArgs a) {
 
 struct NoWout {};
 
+// The window sums that k_wout_partial left for kVg groups of a block's tokens j0 .. j0 + n - 1, into its rows of s_head, 0 outside
+// the prefix.  False (wave-uniform) if some are missing.
+template <int kSlots, int kVg>
+__device__ __forceinline__ bool take_sums(const ScoreArgs &a, const WoutArgs &wo, float (*s_head)[kSlots], int g, int col0, int j0, int n, int P,
+                                          int lane) {
+  bool missing = false;
+  constexpr int kStep = 4;  // loads of a head's row in flight, of four heads
+  for (int v = 0; v < kVg; ++v) {
+    const int heads = vg_heads(a, g + v);
+    const float *src = wo.sums + (size_t)vg_head0(a, g + v) * wo.sums_stride + col0;
+    for (int s0 = lane; s0 < n; s0 += 64 * kStep) {
+      float x[kMaxGroup][kStep];
+#pragma unroll
+      for (int h = 0; h < kMaxGroup; ++h)
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+          const int tok = j0 + s0 + 64 * i;
+          x[h][i] = h < heads && s0 + 64 * i < n && tok >= 0 && tok < P ? src[(size_t)h * wo.sums_stride + tok] : 0.f;
+        }
+#pragma unroll
+      for (int h = 0; h < kMaxGroup; ++h)
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+          missing |= __float_as_uint(x[h][i]) == kNoSum;
+          if (h < heads && s0 + 64 * i < n) s_head[(g + v) * kMaxGroup + h][s0 + 64 * i] = x[h][i];
+        }
+    }
+  }
+  return !__any(missing);
+}
+
+// O = WoutArgs with window sums (wo.sums): those are pooled and averaged, K is read by blocks only that miss some of theirs.
 // kMaxSub 32-token sub-tiles per block at most.  A block owns a.tile_own tokens (host-chosen so that the
 // launch is one block per CU) and computes them and the pooling halo.  The window sums go straight into their own LDS array,
 // next to the waves' staging tiles.  O = WoutArgs: the row normalisers come from the splits of k_wout_partial, folded by
@@ -134,6 +166,11 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
         merge_output(wo, u / kUnits, (u % kUnits) * (kThreads / 4) + (threadIdx.x >> 2), threadIdx.x & 3);
       return;
     }
+    if (wo.sums != nullptr) {  // the mailboxes of k_wout_partial, for the next call
+      const int n_words = wo.n_seq * wo.V * wo.n_split * kRowsPerGroup;
+      for (int i = ((int)blockIdx.x - n_merge) * kThreads + threadIdx.x; i < n_words; i += ((int)gridDim.x - n_merge) * kThreads)
+        box_clear(wo.boxes + i);
+    }
   }
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -150,7 +187,9 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
 
   FKV_TICK(24);
   const int g = wave * kVg;
-  if (g < a.V) {
+  bool have = false;
+  if constexpr (kWout) have = wo.sums != nullptr && g < a.V && take_sums<kSlots, kVg>(a, wo, s_head, g, tok_base - b * a.W, j0, o1 + r - j0, P, lane);
+  if (g < a.V && !have) {
     const KTiles tiles(a, tok_base, vg_kv_head(a, g), j0, min(Lb, o1 + r), stage, lane);
     tiles.issue<kAux>(0);
     bf16x8 qa[kVg][8];

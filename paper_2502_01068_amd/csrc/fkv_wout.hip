@@ -55,8 +55,102 @@ __device__ __forceinline__ void read_v_half(u32x2 (&r)[8], uint32_t addr) {  // 
       : "memory");
 }
 
-template <bool kKeepK>
-__global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
+// The window sums of a block's tokens from its kept probabilities: per head, over the window rows, relative to the row's whole sum.
+// Every block of a group posts its rows' (max, sum) and reads the other splits', 32 blocks at most: one hop (an owner's fold and a
+// second hop, as in fkv_score_exchange.h, serve grids where everybody's partials are too much to read for everybody).  The
+// words are emptied by the scores' launch.  All blocks of the launch are resident at once (the host sees to it) and the wait is
+// bounded all the same: a block that does not get its words in time, or finds the context's error flag set, says so in its sums
+// (kNoSum).  Contains block barriers.
+__device__ __forceinline__ void leave_sums(const WoutArgs &a, uint8_t *lds, int b, int g, int t0, int t1, int tok_base, int P, unsigned poisoned,
+                                           const float (&kept)[kWoKeepTiles][16], const float (&kept_m)[kWoKeepTiles]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, hi = lane >> 5;
+  constexpr int kPolls = kWoKeepSplits * kRowsPerGroup / kWoThreads;
+  float2 *ms = reinterpret_cast<float2 *>(lds);  // [split][row]
+  unsigned *late = reinterpret_cast<unsigned *>(lds + kWoKeepSplits * kRowsPerGroup * sizeof(float2));
+  const float2 *box = a.boxes + ((size_t)b * a.V + g) * a.n_split * kRowsPerGroup;
+  const int n_words = a.n_split * kRowsPerGroup;
+  lds_barrier();  // the waves' states have been read
+  unsigned long long w[kPolls];
+#pragma unroll
+  for (int j = 0; j < kPolls; ++j) w[j] = kEmpty64;
+  bool ok = poisoned == 0u;
+  if (ok) {
+    BoundedWait wait(a.timeout_ticks);
+    while (true) {
+      bool missing = false;
+#pragma unroll
+      for (int j = 0; j < kPolls; ++j)
+        if (tid + j * kWoThreads < n_words && w[j] == kEmpty64) w[j] = box_peek(box + tid + j * kWoThreads);
+#pragma unroll
+      for (int j = 0; j < kPolls; ++j) missing |= tid + j * kWoThreads < n_words && w[j] == kEmpty64;
+      if (!__any(missing)) break;
+      if (wait.expired()) { ok = false; break; }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kPolls; ++j)
+    if (tid + j * kWoThreads < n_words) __builtin_memcpy(&ms[tid + j * kWoThreads], &w[j], sizeof w[j]);
+  if (lane == 0) late[wave] = ok ? 0u : 1u;
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < kWoWaves; ++i) ok = ok && late[i] == 0u;
+  // row n's normaliser: each half of the wave takes every other split
+  float2 st[kWoKeepSplits / 2];
+  float M = kNegBig, S = 0.f;
+#pragma unroll
+  for (int i = 0; i < kWoKeepSplits / 2; ++i) {
+    st[i] = ms[min(2 * i + hi, a.n_split - 1) * kRowsPerGroup + n];
+    M = fmaxf(M, st[i].x);
+  }
+  M = max_across_halves(M);
+#pragma unroll
+  for (int i = 0; i < kWoKeepSplits / 2; ++i) S += 2 * i + hi < a.n_split ? st[i].y * fast_exp2(st[i].x - M) : 0.f;
+  const float inv = 1.f / add_across_halves(S);
+  const int head = n >> 3, sub = n & 7;
+  const bool live = sub < a.W;
+  const bool writes = sub < 4 && head < vg_heads(a, g);
+  float *dst = a.sums + (size_t)(vg_head0(a, g) + (writes ? head : 0)) * a.sums_stride + (tok_base - b * a.W);
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+  for (int t = 0; t < kWoKeepTiles; ++t) {
+    const int tile = t0 + wave + t * kWoWaves;
+    if (tile < t1) {
+      const float shrink = fast_exp2(kept_m[t] - M) * inv;  // against 2^(logit - log-sum-exp) no rounding of a large exponent
+      float x[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        x[q] = live ? kept[t][q] * shrink : 0.f;
+        x[q] += dpp_f32<kDppQuadXor1>(0.f, x[q]);
+        x[q] += dpp_f32<kDppQuadXor2>(0.f, x[q]);
+        x[q] += dpp_f32<kDppHalfMirror>(0.f, x[q]);
+      }
+      // lane (head, sub < 4) stores tokens 8 sub + 4 hi .. + 3 of the tile
+      f32x4u v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = lane_pick((sub & 2) != 0, lane_pick((sub & 1) != 0, x[i], x[4 + i]), lane_pick((sub & 1) != 0, x[8 + i], x[12 + i]));
+        if (!ok) v[i] = __uint_as_float(kNoSum);
+      }
+      const int tok = tile * kSub + 8 * sub + 4 * hi;
+      if (writes) {
+        if (tok + 3 < P) *reinterpret_cast<f32x4u *>(dst + tok) = v;
+        else
+          for (int i = 0; i < 4; ++i)
+            if (tok + i < P) dst[tok + i] = v[i];
+      }
+    }
+  }
+}
+
+// kSums: the block also keeps its probabilities (at most kWoKeepTiles tiles a wave; relative to the running maximum of their tile,
+// which is kept with them) and, once it has its rows' partials of every split, leaves the window-summed probabilities of its tokens, so
+// that the scores need no second pass over K: 32768 tokens, K and V 24.8 + K again and scores 16.8 -> 28.7 + 6.7 us.  The stream
+// is the other form's with operands in two halves and addresses formed anew per tile (with those in registers 18 went to scratch, 33.4
+// us); the sums (exchange, 4 MB written) take 4 us.  A block posts its partials ahead of its output's merge, which the exchange hides
+// behind.  Logits instead of probabilities kept: an exponential per value more, and larger errors (a log-sum-exp's rounding).
+template <bool kKeepK, bool kSums>
+__global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[kWoWaves * kWoTileBytes];
   __shared__ float2 ms_lds[kWoWaves][kRowsPerGroup];
   typedef __attribute__((address_space(1))) const void *gptr_t;
@@ -91,7 +185,21 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   auto tile_of = [&](const uint16_t *x, int tile) {
     return reinterpret_cast<const uint8_t *>(x + ((size_t)(tok_base + tile * kSub) * a.Hkv + vg_kv_head(a, g)) * kHeadDim);
   };
+  // The kept logits leave no registers for addresses of every load: they are formed anew per tile.
+  auto form_addresses = [&] {
+    if constexpr (kSums) {
+      uint32_t base = tq * row;
+      asm("" : "+v"(base));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) row_at[i] = base + i * 4 * row;
+    }
+  };
+  const KTiles k_tiles(a, tok_base, vg_kv_head(a, g), (t0 + wave) * kSub, Lb, ktile, lane);
   auto issue_k = [&](int tile) {
+    if constexpr (kSums) {
+      k_tiles.issue<kPlain>(tile - t0 - wave);
+      return;
+    }
     const uint8_t *rows = tile_of(a.k, tile);
     const uint32_t last = (uint32_t)min(kSub - 1, Lb - 1 - tile * kSub) * row;
 #pragma unroll
@@ -100,6 +208,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   };
   auto issue_v = [&](int tile) {
     keep_access_order();  // the wait for a K tile leaves the 8 youngest loads in flight: these
+    form_addresses();
     const uint8_t *rows = tile_of(a.v, tile);
     const uint32_t last = (uint32_t)min(kSub - 1, Lb - 1 - tile * kSub) * row;
 #pragma unroll
@@ -121,6 +230,9 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   int tile = t0 + wave;
   bf16x8 qa[8];
   load_q(a, b, g, lane, qa);
+  float kept[kSums ? kWoKeepTiles : 1][16], kept_m[kSums ? kWoKeepTiles : 1];  // 2^(logit - kept_m), laid out as acc below
+  int step = 0;
+  const unsigned flag = kSums ? request_flag(a.err) : 0u;
   if (tile < t1) {
     issue_k(tile);
     issue_v(tile);
@@ -129,13 +241,26 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   for (; tile < t1; tile += kWoWaves) {
     const bool more = tile + kWoWaves < t1;
     __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8): the K tile has landed (V may still be on its way)
-    u32x4 kb[8];
-    read_operands<8>(kb, kaddr);
-    if (more) issue_k(tile + kWoWaves);
     floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    constexpr int kHalf = kSums ? 4 : 8;  // operands in registers at a time
 #pragma unroll
-    for (int s8 = 0; s8 < 8; ++s8)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kb[s8]), qa[s8], acc, 0, 0, 0);
+    for (int s0 = 0; s0 < 8; s0 += kHalf) {
+      u32x4 kb[kHalf];
+      if constexpr (kSums) {
+        uint32_t at = kaddr[0], col = ((hi * 8) ^ (n & 15)) << 4;
+        asm("" : "+v"(at), "+v"(col));
+        at -= col;
+#pragma unroll
+        for (int s = 0; s < kHalf; ++s) kaddr[1 + s] = at + (col ^ ((s0 + s) << 4));
+        read_operands<kHalf>(kb, kaddr + 1);
+      } else {
+        read_operands<kHalf>(kb, kaddr + s0);
+      }
+      if (s0 + kHalf == 8 && more) issue_k(tile + kWoWaves);
+#pragma unroll
+      for (int s8 = 0; s8 < kHalf; ++s8)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kb[s8]), qa[s0 + s8], acc, 0, 0, 0);
+    }
 
     // acc[q] = logit of softmax row n and token slot 8*(q/4) + 4*hi + q%4 of the tile
     const int tok0 = tile * kSub;
@@ -160,6 +285,17 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
       psum += z[q];
     }
     s = s * alpha + psum;
+    if constexpr (kSums) {
+#pragma unroll
+      for (int t = 0; t < kWoKeepTiles; ++t)
+        if (t == step) {
+          asm volatile("");  // a branch, not a choice per register for every t
+#pragma unroll
+          for (int q = 0; q < 16; ++q) kept[t][q] = z[q];
+          kept_m[t] = m_new;
+        }
+      ++step;
+    }
     if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -202,9 +338,11 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   // ---- the wave's state into its own (now idle) LDS tiles: O[row n][d], 16-byte chunks XOR-swizzled by row
   s = add_across_halves(s);
   float *ow = reinterpret_cast<float *>(ktile);
+  int at_hi = 4 * hi;
+  asm("" : "+v"(at_hi));  // else a row's number is kept through the loop, one register too many
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
-    const int mrow = 8 * (q >> 2) + 4 * hi + (q & 3);  // output row of the tiles; d = 4*mrow + tile
+    const int mrow = 8 * (q >> 2) + at_hi + (q & 3);  // output row of the tiles; d = 4*mrow + tile
     *reinterpret_cast<float4 *>(ow + n * kHeadDim + ((mrow ^ n) << 2)) = make_float4(o[0][q], o[1][q], o[2][q], o[3][q]);
   }
   if (hi == 0) ms_lds[wave][n] = make_float2(m, s);
@@ -212,8 +350,20 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   FKV_BTICK_AT(blk_id, 2);
 
   // ---- merge the waves in a fixed order and write the block's partial
+  const unsigned poisoned = kSums ? __builtin_amdgcn_readfirstlane(flag) : 0u;
   const size_t slot = ((size_t)b * a.V + g) * a.n_split + split;
   float *po = a.part_o + slot * kWoRowFloats;
+  if (threadIdx.x < kRowsPerGroup) {
+    const int row = threadIdx.x;
+    float M = ms_lds[0][row].x;
+#pragma unroll
+    for (int w = 1; w < kWoWaves; ++w) M = fmaxf(M, ms_lds[w][row].x);
+    float S = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWoWaves; ++w) S += ms_lds[w][row].y * fast_exp2(ms_lds[w][row].x - M);
+    a.part_ms[slot * kRowsPerGroup + row] = make_float2(M, S);
+    if (kSums && poisoned == 0u) box_post(a.boxes + slot * kRowsPerGroup + row, make_float2(M, S));
+  }
 #pragma unroll
   for (int j = 0; j < kWoRowFloats / 4 / kWoThreads; ++j) {
     const int idx = threadIdx.x + j * kWoThreads;
@@ -231,16 +381,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
     }
     *reinterpret_cast<float4 *>(po + row * kHeadDim + chunk * 4) = accv;
   }
-  if (threadIdx.x < kRowsPerGroup) {
-    const int row = threadIdx.x;
-    float M = ms_lds[0][row].x;
-#pragma unroll
-    for (int w = 1; w < kWoWaves; ++w) M = fmaxf(M, ms_lds[w][row].x);
-    float S = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWoWaves; ++w) S += ms_lds[w][row].y * fast_exp2(ms_lds[w][row].x - M);
-    a.part_ms[slot * kRowsPerGroup + row] = make_float2(M, S);
-  }
+  if constexpr (kSums) leave_sums(a, lds_all, b, g, t0, t1, tok_base, P, poisoned, kept, kept_m);
   FKV_BTICK_AT(blk_id, 3);
 }
 
@@ -250,11 +391,19 @@ __global__ __launch_bounds__(kWoMergeThreads) void k_wout_merge(WoutArgs a) {
 }
 
 hipError_t launch_wout(const WoutArgs &a, hipStream_t s) {
-  if (a.keep_k)
-    hipLaunchKernelGGL(k_wout_partial<true>, dim3(a.n_split, a.V, a.n_seq), dim3(kWoThreads), 0, s, a);
+  const dim3 grid(a.n_split, a.V, a.n_seq), block(kWoThreads);
+  if (a.sums != nullptr)
+    hipLaunchKernelGGL((k_wout_partial<true, true>), grid, block, 0, s, a);
+  else if (a.keep_k)
+    hipLaunchKernelGGL((k_wout_partial<true, false>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL(k_wout_partial<false>, dim3(a.n_split, a.V, a.n_seq), dim3(kWoThreads), 0, s, a);
+    hipLaunchKernelGGL((k_wout_partial<false, false>), grid, block, 0, s, a);
   return hipGetLastError();
+}
+int wout_sums_max_blocks_per_cu(void) {
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_wout_partial<true, true>, kWoThreads, 0) != hipSuccess) return 0;
+  return n;
 }
 hipError_t launch_wout_merge(const WoutArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_wout_merge, dim3(a.n_seq * a.V, kWoOutputs / (kWoMergeThreads / 4)), dim3(kWoMergeThreads), 0, s, a);

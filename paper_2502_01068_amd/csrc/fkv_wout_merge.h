@@ -2,7 +2,7 @@
 #pragma once
 
 #include "fkv_dpp.h"
-#include "fkv_score_common.h"
+#include "fkv_score_exchange.h"
 
 namespace fkv {
 
