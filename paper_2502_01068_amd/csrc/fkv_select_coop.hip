@@ -1,7 +1,7 @@
 // Top-k of long score rows with several blocks per row (Sec. 4.2: the same exact selection as
 // fkv_select.hip, window merged in, output ascending, equal scores to the lower index).
 //
-// A row is cut into at most 8 slices of 8192, 16384 or 32768 keys (by row length), one block each; the
+// A row is cut into at most 8 slices of 8192, 16384 or 32768 keys (by row length and number of rows), one block each; the
 // blocks of a row agree on the threshold key through tagged mailbox words (fkv_mailbox.h), all of them
 // resident at once.  Every step is the one-block kernel's, with an exchange where that kernel has a
 // block-wide reduction:
@@ -27,6 +27,8 @@
 // as failed; the block that finishes last then overwrites every index of the launch with -1.  So
 // that this overwrite is ordered after the other blocks' indices, all indices leave as agent-scope
 // stores and each block waits for their acknowledgement before it counts itself as finished.
+#include <algorithm>
+
 #include "fkv_mailbox.h"
 #include "fkv_select_common.h"
 
@@ -526,17 +528,25 @@ bool try_launch_select_coop(const SelectArgs &a, int rows, const SelectCoop &coo
   CoopArgs c{};
   int max_p = 0;
   for (int b = 0; b < a.n_seq; ++b) max_p = max(max_p, a.cu[b + 1] - a.cu[b] - a.W);
-  // keys per thread: the fewest that keep the longest row within kCoopMaxSlices blocks
-  int kpt = 8;
-  while (kpt < kMaxKpt && coop_slices(max_p, kSelThreads * kpt) > kCoopMaxSlices) kpt *= 2;
-  if (coop_slices(max_p, kSelThreads * kpt) > kCoopMaxSlices) return false;
+  // keys per thread: the fewest that keep the longest row within kCoopMaxSlices blocks and all rows within the resident grid (64
+  // rows of 39092 keys: 5 slices each would be 320 blocks; 3 of 16384 keys, 100.3 -> 83.2 us per head-wise call of 64 / 8 heads, against
+  // the six launches of fkv_select_long.hip)
   int64_t total = 0;
-  for (int b = 0; b < a.n_seq; ++b) {
-    const int P = a.cu[b + 1] - a.cu[b] - a.W;
-    if (coop.mode != 2 && P + 3 <= kCoopMinKeys) return false;
-    c.blk[b] = (int)total;
-    total += (int64_t)rows * coop_slices(P, kSelThreads * kpt);
-    if (total > coop.max_blocks) return false;
+  auto blocks = [&](int kpt) {
+    total = 0;
+    for (int b = 0; b < a.n_seq; ++b) {
+      c.blk[b] = (int)std::min<int64_t>(total, coop.max_blocks);
+      total += (int64_t)rows * coop_slices(a.cu[b + 1] - a.cu[b] - a.W, kSelThreads * kpt);
+    }
+    return total;
+  };
+  for (int b = 0; b < a.n_seq; ++b)
+    if (coop.mode != 2 && a.cu[b + 1] - a.cu[b] - a.W + 3 <= kCoopMinKeys) return false;
+  int kpt = 8;
+  while (coop_slices(max_p, kSelThreads * kpt) > kCoopMaxSlices || blocks(kpt) > coop.max_blocks) {
+    const bool fewer = coop_slices(max_p, kSelThreads * kpt) > kCoopMaxSlices || max_p + 3 > select_long_threshold();  // else one block a row
+    if (kpt == kMaxKpt || !fewer) return false;
+    kpt *= 2;
   }
   c.blk[a.n_seq] = (int)total;
   c.boxes = coop.boxes;

@@ -69,3 +69,21 @@ def test_select_mixed_lengths(lengths):
                 out += k
     assert ctx.fkv_query_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("n_rows,lengths", [(64, [32766]), (64, [39092]), (64, [65533]), (40, [33000, 34000]), (64, [70000]), (64, [24600, 33000])])
+def test_select_many_long_rows(n_rows, lengths):
+    """More slices of 8192 keys than blocks are resident: larger slices, or the launch chain.  The same indices from both."""
+    print("case: select %d rows of %s" % (n_rows, lengths), flush=True)
+    ctx = fk.Context(max_total_tokens=sum(lengths) + W * len(lengths), max_seqs=len(lengths))
+    shape = fk.make_shape([P + W for P in lengths], n_q_heads=64)
+    gen = torch.Generator(device="cuda").manual_seed(sum(lengths))
+    rows = torch.rand((n_rows, sum(lengths)), device="cuda", generator=gen)
+    rows[1] = (rows[1] * 64).round() / 64
+    counts = [W + P // 11 for P in lengths]
+    got = ctx.fkv_select_topk(shape, rows, counts).clone()
+    ctx.fkv_set_select_path(1)
+    assert torch.equal(got, ctx.fkv_select_topk(shape, rows, counts))
+    np.testing.assert_array_equal(got[1, :counts[0]].cpu().numpy(), oracle.select_topk(rows[1, :lengths[0]].cpu().numpy(), W, counts[0]))
+    assert ctx.fkv_query_error() == 0
+    ctx.close()
