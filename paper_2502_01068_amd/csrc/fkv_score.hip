@@ -110,6 +110,7 @@ __global__ __launch_bounds__(256) void k_combine(ScoreArgs a) {
 }
 
 struct NoWout {};
+struct WoutSums : WoutArgs {};  // with window sums; a type of its own: one kernel for both costs the others 0.4 us at 40000 tokens and more
 
 // The window sums that k_wout_partial left for kVg groups of a block's tokens j0 .. j0 + n - 1, into its rows of s_head, 0 outside
 // the prefix.  False (wave-uniform) if some are missing.
@@ -142,7 +143,7 @@ __device__ __forceinline__ bool take_sums(const ScoreArgs &a, const WoutArgs &wo
   return !__any(missing);
 }
 
-// O = WoutArgs with window sums (wo.sums): those are pooled and averaged, K is read by blocks only that miss some of theirs.
+// O = WoutSums: the window sums are pooled and averaged, K is read by blocks only that miss some of theirs.
 // kMaxSub 32-token sub-tiles per block at most.  A block owns a.tile_own tokens (host-chosen so that the
 // launch is one block per CU) and computes them and the pooling halo.  The window sums go straight into their own LDS array,
 // next to the waves' staging tiles.  O = WoutArgs: the row normalisers come from the splits of k_wout_partial, folded by
@@ -152,7 +153,7 @@ __device__ __forceinline__ bool take_sums(const ScoreArgs &a, const WoutArgs &wo
 template <int kMaxSub, int kVg, int kAux, typename O>
 __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_merge) {
   constexpr int kSlots = kMaxSub * kSub, kGroups = kWaves * kVg;
-  constexpr bool kWout = std::is_same<O, WoutArgs>::value;
+  constexpr bool kSums = std::is_same<O, WoutSums>::value, kWout = kSums || std::is_same<O, WoutArgs>::value;
   __shared__ __attribute__((aligned(16))) uint8_t stage_all[kWaves * kStageBytes];
   __shared__ __attribute__((aligned(16))) float s_head_all[kGroups * kMaxGroup * kSlots + kPoolPad];  // window-summed probabilities per head
   float(*s_head)[kSlots] = reinterpret_cast<float(*)[kSlots]>(s_head_all);
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
         merge_output(wo, u / kUnits, (u % kUnits) * (kThreads / 4) + (threadIdx.x >> 2), threadIdx.x & 3);
       return;
     }
-    if (wo.sums != nullptr) {  // the mailboxes of k_wout_partial, for the next call
+    if constexpr (kSums) {  // the mailboxes of k_wout_partial, for the next call
       const int n_words = wo.n_seq * wo.V * wo.n_split * kRowsPerGroup;
       for (int i = ((int)blockIdx.x - n_merge) * kThreads + threadIdx.x; i < n_words; i += ((int)gridDim.x - n_merge) * kThreads)
         box_clear(wo.boxes + i);
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
   FKV_TICK(24);
   const int g = wave * kVg;
   bool have = false;
-  if constexpr (kWout) have = wo.sums != nullptr && g < a.V && take_sums<kSlots, kVg>(a, wo, s_head, g, tok_base - b * a.W, j0, o1 + r - j0, P, lane);
+  if constexpr (kSums) have = g < a.V && take_sums<kSlots, kVg>(a, wo, s_head, g, tok_base - b * a.W, j0, o1 + r - j0, P, lane);
   if (g < a.V && !have) {
     const KTiles tiles(a, tok_base, vg_kv_head(a, g), j0, min(Lb, o1 + r), stage, lane);
     tiles.issue<kAux>(0);
@@ -272,7 +273,13 @@ int wout_merge_units(const WoutArgs &a) { return a.n_seq * a.V * (kWoOutputs / (
 
 hipError_t launch_wout_scores(const ScoreArgs &a, const WoutArgs &o, int n_blocks, int n_merge, hipStream_t s) {
   const dim3 grid(n_blocks + n_merge);
-  if (a.V > kMaxKvHeads)
+  if (o.sums != nullptr) {
+    const WoutSums sums{o};
+    if (a.V > kMaxKvHeads)
+      hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, WoutSums>), grid, dim3(kThreads), 0, s, a, sums, n_merge);
+    else
+      hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kPlain, WoutSums>), grid, dim3(kThreads), 0, s, a, sums, n_merge);
+  } else if (a.V > kMaxKvHeads)
     hipLaunchKernelGGL((k_scores<kScoresSubWide, 2, kOnce, WoutArgs>), grid, dim3(kThreads), 0, s, a, o, n_merge);
   else
     hipLaunchKernelGGL((k_scores<kScoresSubLong, 1, kPlain, WoutArgs>), grid, dim3(kThreads), 0, s, a, o, n_merge);
