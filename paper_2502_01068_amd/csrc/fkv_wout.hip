@@ -150,7 +150,7 @@ __device__ __forceinline__ void leave_sums(const WoutArgs &a, uint8_t *lds, int 
 // us); the sums (exchange, 4 MB written) take 4 us.  A block posts its partials ahead of its output's merge, which the exchange hides
 // behind.  Logits instead of probabilities kept: an exponential per value more, and larger errors (a log-sum-exp's rounding).
 template <bool kKeepK, bool kSums>
-__global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
+__global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[kWoWaves * kWoTileBytes];
   __shared__ float2 ms_lds[kWoWaves][kRowsPerGroup];
   typedef __attribute__((address_space(1))) const void *gptr_t;
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
   s = add_across_halves(s);
   float *ow = reinterpret_cast<float *>(ktile);
   int at_hi = 4 * hi;
-  asm("" : "+v"(at_hi));  // else a row's number is kept through the loop, one register too many
+  if constexpr (kSums) asm("" : "+v"(at_hi));  // else a row's number is kept through the loop, one register too many
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int mrow = 8 * (q >> 2) + at_hi + (q & 3);  // output row of the tiles; d = 4*mrow + tile
@@ -353,7 +353,8 @@ __global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
   const unsigned poisoned = kSums ? __builtin_amdgcn_readfirstlane(flag) : 0u;
   const size_t slot = ((size_t)b * a.V + g) * a.n_split + split;
   float *po = a.part_o + slot * kWoRowFloats;
-  if (threadIdx.x < kRowsPerGroup) {
+  auto leave_partials = [&] {
+    if (threadIdx.x >= kRowsPerGroup) return;
     const int row = threadIdx.x;
     float M = ms_lds[0][row].x;
 #pragma unroll
@@ -363,7 +364,8 @@ __global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
     for (int w = 0; w < kWoWaves; ++w) S += ms_lds[w][row].y * fast_exp2(ms_lds[w][row].x - M);
     a.part_ms[slot * kRowsPerGroup + row] = make_float2(M, S);
     if (kSums && poisoned == 0u) box_post(a.boxes + slot * kRowsPerGroup + row, make_float2(M, S));
-  }
+  };
+  if (kSums) leave_partials();  // the exchange is waited for
 #pragma unroll
   for (int j = 0; j < kWoRowFloats / 4 / kWoThreads; ++j) {
     const int idx = threadIdx.x + j * kWoThreads;
@@ -381,6 +383,7 @@ __global__ __launch_bounds__(kWoThreads, 2) void k_wout_partial(WoutArgs a) {
     }
     *reinterpret_cast<float4 *>(po + row * kHeadDim + chunk * 4) = accv;
   }
+  if (!kSums) leave_partials();
   if constexpr (kSums) leave_sums(a, lds_all, b, g, t0, t1, tok_base, P, poisoned, kept, kept_m);
   FKV_BTICK_AT(blk_id, 3);
 }
