@@ -341,7 +341,8 @@ int fkv_query_error(fkv_ctx *ctx, int32_t *flag_out);
  * device, empties the exchange's mailboxes (a failed exchange may leave values in them), zeroes the
  * decode kernel's counts of finished pieces (a launch that was cut short, or overlapped another one of
  * the context, may leave them off: later results of rows in pieces would be wrong without an error) and
- * resets the flag; the next call works again. */
+ * resets the flag; the next call works again.  (A fkv_score_window_output that returned FKV_EHIP may leave values in the mailboxes
+ * too, without a flag: until fkv_clear_error the context's scores come from the two-pass kernels.) */
 int fkv_set_wait_limit(fkv_ctx *ctx, int64_t microseconds);
 int fkv_clear_error(fkv_ctx *ctx);
 

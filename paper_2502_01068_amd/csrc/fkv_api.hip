@@ -124,6 +124,7 @@ struct fkv_ctx {
   int n_cu_select;     // resident blocks of the several-blocks-per-row select kernel (0: not available)
   int select_path;     // 0 auto, 1 never several blocks per row, 2 several blocks per row whenever the launch fits
   unsigned long long wait_ticks;  // bound of every wait inside a kernel, 100 MHz ticks
+  bool boxes_posted;   // a call posted into the score mailboxes and its launch that empties them failed: not to be read before fkv_clear_error
   bool prof_on;
   std::vector<EventPair> ev_pool;
   size_t ev_used;
@@ -303,7 +304,7 @@ ScoreWs ws_of(fkv_ctx *ctx) {
   w.partial = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.partial);
   w.partial_stride = ctx->lay.max_stat_blocks;
   w.rowstat = reinterpret_cast<float *>(ctx->ws + ctx->lay.rowstat);
-  w.fused_part = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.fused_part);
+  w.fused_part = ctx->boxes_posted ? nullptr : reinterpret_cast<float2 *>(ctx->ws + ctx->lay.fused_part);
   w.fused_lse = reinterpret_cast<float *>(ctx->ws + ctx->lay.fused_lse);
   w.err = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters) + kCtrError;
   w.n_cu = ctx->n_cu;
@@ -687,6 +688,7 @@ int fkv_create(fkv_ctx **out, int device, int64_t max_total_tokens, int32_t max_
     c->n_cu_select = prop.multiProcessorCount * (select_coop_max_blocks_per_cu() > 0 ? 1 : 0);
   }
   c->select_path = 0;
+  c->boxes_posted = false;
   c->prof_on = false;
   c->ev_used = 0;
   c->ev_prev = nullptr;
@@ -980,7 +982,7 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   // sequences of 800-900 51.0 -> 47.0).  Not while several contexts exist on the device: resident launches of different contexts
   // are chained, and not where the two-pass kernels are asked for.
   const int blocks = a.n_split * r.V * r.n_seq, per = (tiles_max + a.n_split - 1) / a.n_split;
-  if (keep_k && ctx->score_path != 1 && !several_contexts(ctx->device) && per <= kWoKeepTiles * wout_tiles_per_block_min() &&
+  if (keep_k && ctx->score_path != 1 && !ctx->boxes_posted && !several_contexts(ctx->device) && per <= kWoKeepTiles * wout_tiles_per_block_min() &&
       blocks <= std::min(ctx->n_cu_wout, kMaxFusedBlocks) && a.n_split <= kWoKeepSplits &&
       r.sum_p * r.Hq * (int64_t)sizeof(float) <= (int64_t)kWoSumBytes) {
     a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
@@ -1043,7 +1045,9 @@ int fkv_score_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_
   // caches is reused), and the merge of the output
   ScoreArgs a{};
   fill_score_args(a, w, shape, r, q_win, k, scores_group, scores_tsp, nullptr);
-  return enqueue_scores_pass2(w, a, r, &wo, st);
+  rc = enqueue_scores_pass2(w, a, r, &wo, st);
+  if (rc != FKV_OK && wo.sums) ctx->boxes_posted = true;
+  return rc;
 }
 
 int fkv_decode_attention(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const void *k, const void *v,
@@ -1394,6 +1398,7 @@ int fkv_clear_error(fkv_ctx *ctx) {
   if (e == hipSuccess) e = reset_decode_counts(ctx);
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.counters + kCtrError * sizeof(unsigned), 0, sizeof(unsigned));
   if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e == hipSuccess) ctx->boxes_posted = false;
   return e == hipSuccess ? FKV_OK : hip_fail(e);
 }
 

@@ -12,9 +12,12 @@ namespace fkv {
 // empty pattern back once it has the value.  Since the value itself is the signal, nothing has
 // to be ordered against anything else: no fences, no counters, no second location that could
 // become visible before the first (agent-scope fences would write back / invalidate a whole L2
-// on this multi-XCD part, tens of microseconds).  Each slot has one producer and one consumer per
-// launch; the empty pattern the consumer leaves behind is ordered before the next launch by the
-// kernel boundary.  Slots are touched by nothing else.
+// on this multi-XCD part, tens of microseconds).  In the score kernels' exchange (fkv_score_exchange.h) each slot has one producer
+// and one consumer per launch; the empty pattern the consumer leaves behind is ordered before the next launch by the
+// kernel boundary.  The window sums (fkv_wout.hip) use the same slots between two launches: one block posts a word, every block of its
+// (sequence, group) reads it and none empties it, and the scores' launch behind that one empties them all, which kernel boundaries
+// order on either side.  If that launch fails on the host, the words stay: the context reads no score mailbox then until
+// fkv_clear_error has emptied them.  Slots are touched by nothing else.
 constexpr unsigned long long kEmpty64 = ~0ull;
 constexpr unsigned kEmpty32 = ~0u;
 

@@ -1,0 +1,36 @@
+"""Which launches the calls make, and what the context does when one of them fails (no GPU; see launches.py)."""
+import pytest
+
+import launches
+
+EHIP, EUNSUPPORTED = -6, -4
+
+
+@pytest.fixture(scope="module")
+def calls(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("recorder")
+    return lambda *steps: launches.run([["create", {}]] + [list(s) for s in steps], tmp)[1:]
+
+
+def test_posted_mailboxes_are_not_read_after_a_failed_launch(calls):
+    """The window output's first launch posts into the score mailboxes, its second one empties them.  If that one fails, no kernel
+    that reads mailboxes may run before fkv_clear_error; the scores come from the two-pass kernels."""
+    window, score = ("window_output", {"lengths": [8192]}), ("score", {"lengths": [8192]})
+    got = calls(window, score, ("window_output", {"lengths": [8192], "refuse_launch": 1}), score, window,
+                ("compress", {"lengths": [8192], "budgets": [512], "k_tsp": [1638]}), ("set", {"what": "set_score_path", "value": 2}), score,
+                ("set", {"what": "set_score_path", "value": 0}), ("clear_error", {}), window, score)
+    before, failed, after = got[:2], got[2], got[3:6]
+    assert [launches.kernels(r)[0].split("<")[0] for r in before] == ["k_wout_partial", "k_score_fused"]
+    assert launches.kernels(before[0])[0] == "k_wout_partial<true, true>"
+    assert failed["value"] == EHIP and launches.kernels(failed) == ["k_wout_partial<true, true>"]
+    for r in after:
+        assert r["value"] == 0 and all(l["wait_ticks"] == 0 for l in r["launches"]), r
+    assert launches.kernels(after[0])[0].startswith("k_stats") and launches.kernels(after[2])[0].startswith("k_stats")
+    assert launches.kernels(after[1])[0] == "k_wout_partial<true, false>"
+    assert got[7]["value"] == EUNSUPPORTED  # the single-pass kernel and no other was asked for
+    assert [launches.kernels(r) for r in got[-2:]] == [launches.kernels(r) for r in before]
+
+
+def test_a_failed_first_launch_leaves_the_mailboxes_usable(calls):
+    got = calls(("window_output", {"lengths": [8192], "refuse_launch": 0}), ("score", {"lengths": [8192]}))
+    assert got[0]["value"] == EHIP and launches.kernels(got[1])[0].startswith("k_score_fused")
