@@ -25,7 +25,8 @@
  *     streams; while several contexts exist on a device, their single-pass score launches are
  *     chained on the GPU through an event (that event wait cannot be captured into a graph, and
  *     graphs that hold single-pass launches of different contexts must not be replayed
- *     concurrently; force the two-pass kernels with fkv_set_score_path for such use).
+ *     concurrently; force the two-pass kernels with fkv_set_score_path for such use; graphs that hold
+ *     fkv_score_window_output need no such care).
  *   - The calling thread's current HIP device must be the context's device and `stream` must
  *     belong to it; the compute calls do not switch devices (fkv_create makes `device` current for
  *     its own set-up and puts the caller's device back before it returns).
@@ -214,11 +215,15 @@ int fkv_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, c
 
 /* Scores and the window rows' attention output from one set of probabilities: what fkv_score_window
  * and fkv_window_output compute (Sec. 4.2 Eq. 1-2, App. B.1; Sec. 5.1: the layer's fused attention
- * kernel does not expose Att, so the estimation step recomputes it), in one call that reads V once and
- * K twice and needs no grid-wide exchange: the pass that forms the output also leaves every softmax
- * row's normaliser, and a second pass over K (largely served by the caches the first one filled)
- * turns logits into pooled, head-averaged scores.  Arguments and outputs as in the two calls;
- * scores_tsp may be NULL. */
+ * kernel does not expose Att, so the estimation step recomputes it), in one call that reads V once:
+ * the pass that forms the output also leaves what the scores need.  Where its blocks fit the device at once and can keep
+ * their probabilities (32768 tokens of 32 / 8 heads, 16384 of 64 / 8), and one context exists on the device, they exchange the
+ * softmax rows' normalisers and leave window sums; K is read once.  Elsewhere, and always under fkv_set_score_path(ctx, 1), they
+ * leave the normalisers, a second pass over K (largely served by the caches the first one filled) turns logits into scores, and no
+ * block waits for another.  The call does not depend on that exchange: a block waits at most 0.1 ms (and the limit of
+ * fkv_set_wait_limit), and what did not come, because kernels of another stream held compute units, is computed from K again.
+ * No error flag is raised or needed to be clear, and the scores are valid either way; between the two ways their last
+ * bits differ (fp32 summation order).  Arguments and outputs as in the two calls; scores_tsp may be NULL. */
 int fkv_score_window_output(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, const void *k, const void *v,
                             float *scores_group, float *scores_tsp, float *out, void *stream);
 
@@ -300,7 +305,7 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
  * exist on the device, the one that keeps the logits of part of the tokens and reads the rest of K again (about
  * 137K tokens; 72K with more than 4 query heads per KV head and more than 4 KV heads); else the two-pass kernels.
  * 1: always two-pass; 2: single-pass or FKV_EUNSUPPORTED.  All give the same scores up to fp32 summation
- * order.  What is said here about single-pass launches holds for both resident kernels. */
+ * order.  Mode 1 also keeps fkv_score_window_output free of waits between blocks.  What is said here about single-pass launches holds for both resident kernels. */
 int fkv_set_score_path(fkv_ctx *ctx, int mode);
 
 /* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 24573 keys
@@ -329,14 +334,14 @@ int fkv_score_plan(const fkv_shape *shape, int32_t max_blocks, int32_t *first_bl
  * 1 if a wave of a resident kernel (fkv_set_score_path, fkv_set_select_path) gave up waiting for the rest
  * of its grid (2 s bound).  Cannot happen while the library's launches are the only work competing for the
  * device's compute units for that long; a program whose own kernels may hold them, or their LDS, takes the
- * kernels that need no resident grid (mode 1 of both).  The failure is visible on the device without this call: the blocks that
+ * kernels that need no resident grid (mode 1 of both).  fkv_score_window_output never raises it.  The failure is visible on the device without this call: the blocks that
  * gave up write NaN scores, and while the flag is set every single-pass score launch of the context
  * writes only NaN scores, fkv_compress_kv / fkv_compress_kv_paged write -1 into every index and the
  * gathers copy nothing for those.  The flag stays set until fkv_clear_error. */
 int fkv_query_error(fkv_ctx *ctx, int32_t *flag_out);
 
 /* fkv_set_wait_limit: bound of every wait of the single-pass kernel's grid exchange in microseconds
- * (0 restores the 2 s default, at most 60 s).  A wave that gives up still leaves the kernel
+ * (0 restores the 2 s default, at most 60 s; fkv_score_window_output waits 0.1 ms at most whatever the limit).  A wave that gives up still leaves the kernel
  * normally; a tiny limit is how the failure path is exercised.  fkv_clear_error synchronises the
  * device, empties the exchange's mailboxes (a failed exchange may leave values in them), zeroes the
  * decode kernel's counts of finished pieces (a launch that was cut short, or overlapped another one of

@@ -462,7 +462,8 @@ class Context:
         return out
 
     def fkv_score_window_output(self, shape, q_win, k, v, scores_group=None, scores_tsp=None, out=None, want_tsp=True):
-        """Scores and the window rows' attention output in one call (V read once, K twice, no grid exchange)
+        """Scores and the window rows' attention output in one call (V read once; K once where
+        the pass's probabilities fit the device, else twice)
         -> (scores_group [Hkv, sum P], scores_tsp [sum P] or None, out [B,W,Hq,d] fp32)"""
         done = _native.score_window_output(self._h, self.device, shape, q_win, k, v, scores_group, scores_tsp, out, bool(want_tsp))
         if done is not None:

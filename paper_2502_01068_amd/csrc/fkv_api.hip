@@ -988,8 +988,8 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
     a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
     a.sums_stride = r.sum_p;
     a.boxes = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.fused_part);
-    a.err = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters) + kCtrError;
-    a.timeout_ticks = ctx->wait_ticks;
+    a.counters = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters);
+    a.timeout_ticks = std::min(ctx->wait_ticks, kWoWaitTicks);
     const hipError_t e = gated_launch(ctx->device, st, [&] {
       Timed t(ctx, st, KID_WOUT);
       return launch_wout(a, st);
@@ -1396,6 +1396,7 @@ int fkv_clear_error(fkv_ctx *ctx) {
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.fused_lse, 0xFF, kFusedLseBytes);
   if (e == hipSuccess) e = reset_select_exchange(ctx);
   if (e == hipSuccess) e = reset_decode_counts(ctx);
+  if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.counters + kCtrWoLate * sizeof(unsigned), 0, sizeof(unsigned));
   if (e == hipSuccess) e = hipMemset(ctx->ws + ctx->lay.counters + kCtrError * sizeof(unsigned), 0, sizeof(unsigned));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e == hipSuccess) ctx->boxes_posted = false;

@@ -176,6 +176,7 @@ constexpr int kCoopMinKeys = 24576;   // rows of up to 3 keys fewer stay on the 
 constexpr size_t kCoopBoxBytes = (size_t)kCoopMaxBlocks * kCoopWords * sizeof(unsigned long long);
 constexpr int kCtrSelEpoch = 1;       // context counters: epoch of the next launch (never 0),
 constexpr int kCtrSelDone = 2;        // finish count of the running launch
+constexpr int kCtrWoLate = 3;         // a block of the running window-sums launch has given up waiting
 struct CoopArgs {
   unsigned long long *boxes;  // [blocks][kCoopWords]
   unsigned *state;            // [0] epoch, [1] finish count (low half: blocks done, high half: blocks that failed)
@@ -242,13 +243,17 @@ struct WoutArgs {
   float *sums;            // [Hq][sums_stride] or nullptr: the blocks leave each prefix token's window-summed probability per head here
   int64_t sums_stride;
   float2 *boxes;          // [n_seq * V][n_split][32] mailboxes, empty before and (emptied by the scores' launch) after; with sums
-  const unsigned *err;    // the context's sticky error flag, with sums: the mailboxes may hold anything while it is set
+  unsigned *counters;     // the context's, with sums: [kCtrError] the mailboxes may hold anything while it is set, [kCtrWoLate]
   unsigned long long timeout_ticks;
 };
 // Window sums that a block could not form (its normalisers did not come): the scores' launch reads K again for those tokens.
 constexpr unsigned kNoSum = 0xFFFFFFFFu;
 constexpr int kWoKeepTiles = 4;    // 32-token tiles per wave whose logits a block keeps
 constexpr int kWoKeepSplits = 32;  // most splits whose normalisers a block folds for itself
+// How long a block waits for them, 100 MHz ticks (or the context's limit if that is shorter).  The words come within some 5 us when every
+// block has a CU, as the host plans; when a kernel of another stream holds CUs, blocks of this launch may start only once others
+// have left, and reading K again costs 10 us.
+constexpr unsigned long long kWoWaitTicks = 10000;
 constexpr size_t kWoSumBytes = (size_t)8 << 20;
 int wout_tiles_per_block_min(void);
 hipError_t launch_wout(const WoutArgs &a, hipStream_t s);        // the splits' partials

@@ -46,24 +46,25 @@ __device__ __forceinline__ void box_clear(float *slot) {
 }
 
 // Time limit of a polling loop.  Reading the clock costs a round trip through the scalar memory path
-// (comparable to the poll itself), so it is read only every 64th round, the first time to start
-// the interval; limits below 1 ms (how tests force the failure path) are checked on every round,
+// (comparable to the poll itself), so it is read only every 64th round (kEvery), the first time to start
+// the interval; limits below 1 ms (strict_below; how tests force the failure path) are checked on every round,
 // from a start time taken before the first poll.  Wave-uniform.
+template <unsigned kEvery = 64>
 struct BoundedWait {
   unsigned long long t0, limit;
   unsigned round;
   bool strict;
-  __device__ __forceinline__ explicit BoundedWait(unsigned long long limit_ticks)
-      : t0(0), limit(limit_ticks), round(0), strict(limit_ticks < 100000ull) {
+  __device__ __forceinline__ explicit BoundedWait(unsigned long long limit_ticks, unsigned long long strict_below = 100000ull)
+      : t0(0), limit(limit_ticks), round(0), strict(limit_ticks < strict_below) {
     if (strict) t0 = wall_clock64();
   }
   // Call after a poll that did not complete; true once the limit has passed.
   __device__ __forceinline__ bool expired() {
     ++round;
     if (strict) return wall_clock64() - t0 > limit;
-    if ((round & 63u) != 0u) return false;
+    if ((round & (kEvery - 1)) != 0u) return false;
     const unsigned long long now = wall_clock64();
-    if (round == 64u) { t0 = now; return false; }
+    if (round == kEvery) { t0 = now; return false; }
     return now - t0 > limit;
   }
 };

@@ -167,7 +167,9 @@ __global__ __launch_bounds__(kThreads) void k_scores(ScoreArgs a, O wo, int n_me
         merge_output(wo, u / kUnits, (u % kUnits) * (kThreads / 4) + (threadIdx.x >> 2), threadIdx.x & 3);
       return;
     }
-    if constexpr (kSums) {  // the mailboxes of k_wout_partial, for the next call
+    if constexpr (kSums) {  // the mailboxes of k_wout_partial and its mark, for the next call
+      if ((int)blockIdx.x == n_merge && threadIdx.x == 0)
+        __hip_atomic_store(wo.counters + kCtrWoLate, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int n_words = wo.n_seq * wo.V * wo.n_split * kRowsPerGroup;
       for (int i = ((int)blockIdx.x - n_merge) * kThreads + threadIdx.x; i < n_words; i += ((int)gridDim.x - n_merge) * kThreads)
         box_clear(wo.boxes + i);

@@ -86,7 +86,7 @@ __device__ __forceinline__ bool owner_duty(const ScoreArgs &a, const FusedArgs &
     unsigned long long v[kPasses];
 #pragma unroll
     for (int i = 0; i < kPasses; ++i) v[i] = kEmpty64;
-    BoundedWait wait(f.timeout_ticks);
+    BoundedWait<> wait(f.timeout_ticks);
     while (true) {
       bool missing = false;
 #pragma unroll
@@ -147,7 +147,7 @@ __device__ __forceinline__ bool collect_lse(const FusedArgs &f, int range, int g
   const bool mine = lane < kVg * kRowsPerGroup;
   float *box = f.lse + (size_t)range * kLseRowsPerBlock + g * kRowsPerGroup + (lane & (kVg * kRowsPerGroup - 1));
   unsigned bits = kEmpty32;
-  BoundedWait wait(f.timeout_ticks);
+  BoundedWait<> wait(f.timeout_ticks);
   while (true) {
     if (mine && bits == kEmpty32) bits = box_peek(box);
     if (!__any(mine && bits == kEmpty32)) break;

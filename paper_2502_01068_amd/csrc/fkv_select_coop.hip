@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_coop(SelectArgs a, CoopA
     // until all carry this launch's epoch; payloads to `got`.  Wave-uniform result.
     auto fetch = [&](auto slot, auto skip, auto &got) -> bool {
       constexpr int kN = (int)(sizeof(got) / sizeof(got[0]));
-      BoundedWait wait(c.timeout_ticks);
+      BoundedWait<> wait(c.timeout_ticks);
       if constexpr (kKpt >= 32 && kN > 4) {
         // 32 keys per thread leave few registers: four words in flight at a time
 #pragma unroll

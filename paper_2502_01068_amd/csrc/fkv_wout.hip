@@ -58,9 +58,9 @@ __device__ __forceinline__ void read_v_half(u32x2 (&r)[8], uint32_t addr) {  // 
 // The window sums of a block's tokens from its kept probabilities: per head, over the window rows, relative to the row's whole sum.
 // Every block of a group posts its rows' (max, sum) and reads the other splits', 32 blocks at most: one hop (an owner's fold and a
 // second hop, as in fkv_score_exchange.h, serve grids where everybody's partials are too much to read for everybody).  The
-// words are emptied by the scores' launch.  All blocks of the launch are resident at once (the host sees to it) and the wait is
-// bounded all the same: a block that does not get its words in time, or finds the context's error flag set, says so in its sums
-// (kNoSum).  Contains block barriers.
+// words are emptied by the scores' launch.  All blocks of the launch are resident at once where nothing else holds CUs (the host
+// plans for that), and nothing depends on it: a block that does not get its words within kWoWaitTicks, or finds the context's error flag
+// set, says so in its sums (kNoSum) and ends, and blocks that start after one has given up do not wait.  Contains block barriers.
 __device__ __forceinline__ void leave_sums(const WoutArgs &a, uint8_t *lds, int b, int g, int t0, int t1, int tok_base, int P, unsigned poisoned,
                                            const float (&kept)[kWoKeepTiles][16], const float (&kept_m)[kWoKeepTiles]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -76,7 +76,8 @@ __device__ __forceinline__ void leave_sums(const WoutArgs &a, uint8_t *lds, int 
   for (int j = 0; j < kPolls; ++j) w[j] = kEmpty64;
   bool ok = poisoned == 0u;
   if (ok) {
-    BoundedWait wait(a.timeout_ticks);
+    const unsigned late_before = request_flag(a.counters + kCtrWoLate);  // travels beside the first poll
+    BoundedWait<16> wait(a.timeout_ticks, kWoWaitTicks);
     while (true) {
       bool missing = false;
 #pragma unroll
@@ -85,8 +86,9 @@ __device__ __forceinline__ void leave_sums(const WoutArgs &a, uint8_t *lds, int 
 #pragma unroll
       for (int j = 0; j < kPolls; ++j) missing |= tid + j * kWoThreads < n_words && w[j] == kEmpty64;
       if (!__any(missing)) break;
-      if (wait.expired()) { ok = false; break; }
+      if (__builtin_amdgcn_readfirstlane(late_before) != 0u || wait.expired()) { ok = false; break; }
     }
+    if (!ok && lane == 0) __hip_atomic_store(a.counters + kCtrWoLate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 #pragma unroll
   for (int j = 0; j < kPolls; ++j)
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(kWoThreads) void k_wout_partial(WoutArgs a) {
   load_q(a, b, g, lane, qa);
   float kept[kSums ? kWoKeepTiles : 1][16], kept_m[kSums ? kWoKeepTiles : 1];  // 2^(logit - kept_m), laid out as acc below
   int step = 0;
-  const unsigned flag = kSums ? request_flag(a.err) : 0u;
+  const unsigned flag = kSums ? request_flag(a.counters + kCtrError) : 0u;
   if (tile < t1) {
     issue_k(tile);
     issue_v(tile);

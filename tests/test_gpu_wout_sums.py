@@ -47,23 +47,34 @@ def test_matches_two_passes(lengths, hq, hkv, pool, pool_kernel, window, causal)
 
 
 def test_without_the_sums_k_is_read_again():
-    """A wait limit of 1 us, and the error flag of another call: the scores come from a second pass then, and no flag is raised."""
+    """A wait limit of 1 us, which is less than the blocks of a long input end apart, and the error flag of another call: the scores
+    come from a second pass then, which shows in their last bits, and no flag is raised."""
     print("case: window sums that do not come", flush=True)
-    lengths = [8192]
-    ctx = fk.Context(max_total_tokens=8192, max_seqs=1)
+    lengths = [32768]
+    ctx = fk.Context(max_total_tokens=32768, max_seqs=1)
     shape = fk.make_shape(lengths, pool_mode="avg")
     q, k, v = _inputs(lengths, 32, 8)
     want = [t.clone() for t in ctx.fkv_score_window_output(shape, q, k, v)]
+
+    def read_again():
+        got = ctx.fkv_score_window_output(shape, q, k, v)
+        _check(got, want)
+        assert not torch.equal(got[0], want[0])
+
     ctx.fkv_set_wait_limit(1)
     for _ in range(3):
-        _check(ctx.fkv_score_window_output(shape, q, k, v), want)
+        read_again()
     assert ctx.fkv_query_error() == 0
+    ctx.fkv_set_wait_limit(0)  # the mark of the blocks that gave up is gone with their call: sums again
+    for _ in range(2):
+        assert all(torch.equal(x, y) for x, y in zip(ctx.fkv_score_window_output(shape, q, k, v), want))
+    ctx.fkv_set_wait_limit(1)
     for _ in range(3):
         ctx.fkv_score_window(shape, q, k)
     assert ctx.fkv_query_error() == 1
-    _check(ctx.fkv_score_window_output(shape, q, k, v), want)
+    read_again()
     ctx.fkv_set_wait_limit(0)
-    _check(ctx.fkv_score_window_output(shape, q, k, v), want)
+    read_again()
     ctx.fkv_clear_error()
     for _ in range(2):
         assert all(torch.equal(x, y) for x, y in zip(ctx.fkv_score_window_output(shape, q, k, v), want))

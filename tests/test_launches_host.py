@@ -34,3 +34,12 @@ def test_posted_mailboxes_are_not_read_after_a_failed_launch(calls):
 def test_a_failed_first_launch_leaves_the_mailboxes_usable(calls):
     got = calls(("window_output", {"lengths": [8192], "refuse_launch": 0}), ("score", {"lengths": [8192]}))
     assert got[0]["value"] == EHIP and launches.kernels(got[1])[0].startswith("k_score_fused")
+
+
+def test_window_sums_wait_no_longer_than_reading_k_again_is_worth(calls):
+    """A block of the window sums that misses another block's words is as well off reading K again: 0.1 ms at most, whatever the
+    context's limit; a shorter limit holds."""
+    window, limit = ("window_output", {"lengths": [8192]}), lambda us: ("set", {"what": "set_wait_limit", "value": us})
+    got = calls(window, limit(1000000), window, limit(5), window, limit(0), window)
+    ticks = [r["launches"][0]["wait_ticks"] for r in got if r["launches"]]
+    assert ticks == [10000, 10000, 500, 10000]  # of 10 ns
