@@ -349,9 +349,10 @@ int enqueue_scores_pass2(const ScoreWs &w, ScoreArgs &a, const Resolved &r, Wout
   const int n_cu = w.n_cu > 0 ? w.n_cu : 256;
   const int units = wo ? wout_merge_units(*wo) : 0;
   // With the window sums the scores' blocks are short and leave a quarter of the CUs to the merge: 32768 tokens, 16 blocks of it
-  // 10.7 us, 64 of them 6.7; up to 8 units a block (8 sequences of 1500-2000 tokens 27.5 us per call, a launch of its own 28.5; 16 of
-  // 1200-1700, 16 units a block, 46.0 against 38.2).
-  const int beside = wo && wo->sums ? std::min(units, n_cu / 4) : (units + kMergeUnits - 1) / kMergeUnits;
+  // 10.7 us, 64 of them 6.7.  From four units a block on they leave half of them: us per call at 64 and 128 blocks, 8 sequences of
+  // 3000 tokens 37.0 and 33.4 (28 / 4 heads; two passes over K 34.8), 4 of 6000 32.7 and 30.4, 16 of 3000 of 16 / 2 heads 40.2 and 32.8
+  // (two passes 34.3).  More than 4 units a block of those (16 sequences of 1200-1700) are a launch of their own: 46.0 against 38.2.
+  const int beside = wo && wo->sums ? std::min(units, units >= n_cu ? n_cu / 2 : n_cu / 4) : (units + kMergeUnits - 1) / kMergeUnits;
   const bool merge = units > 0 && (wo->sums ? units <= 2 * n_cu : 8 * beside <= n_cu);
   const int own = even_share(r, r.W, 2 * a.pool_r, merge ? n_cu - beside : n_cu, scores_sub_short(), sub_max);
   a.tile_own = own;
@@ -954,6 +955,21 @@ int decode_common(fkv_ctx *ctx, const fkv_shape *shape, const void *q, const voi
 }  // namespace
 
 namespace {
+// Whether window sums are faster than the scores' second pass over K.  They make the first launch some 2.6 us longer, with more splits
+// more; the second pass takes longer with the virtual groups of a block and with the tokens.  us per call, two passes and sums:
+// more than four groups: 20 / 5 heads 700 tokens 15.9, 14.3, 8000 18.1, 17.8; one tile 11.2, 12.5 (28 / 4 heads 12.5, 12.8);
+// up to four: with a merge that would be a launch of its own beside two passes and needs none beside sums, 32 sequences of 700 of
+// 4 / 1 heads 18.6, 17.0, 8 of 2500 of 16 / 4 23.8, 20.8; with many tokens, 4 sequences of 12000 of 16 / 4 heads 35.3, 31.5, 3 of 8000 of 12 / 3
+// 21.4, 19.9, but of 8 / 2, 32 splits, 16.2, 18.1; else only four groups in 2 to 15 splits: 16 / 4 heads 700 tokens 14.7, 14.0, 4000 (16 splits)
+// 15.4, 15.0 and of 4 / 4 heads 13.3, 13.7, 8000 16.1, 17.1; 8 / 1 heads 1500 tokens 13.9, 14.5, 8000 14.4, 16.5.
+bool wout_sums_pay(const WoutArgs &a, int tiles_max, int n_cu) {
+  if (a.V > kMaxGroup) return tiles_max > 1;
+  const int units = wout_merge_units(a);
+  if (2 * units > n_cu && units <= 2 * n_cu) return true;
+  if ((int64_t)a.V * a.cu[a.n_seq] >= 90000) return a.V > 2 || a.n_split < kWoKeepSplits;
+  return a.V == kMaxGroup && a.n_split > 1 && 2 * a.n_split < kWoKeepSplits && units <= n_cu;
+}
+
 // Launches the partials of the window rows' attention output and fills `a` for their merge; keep_k: K stays in the caches for
 // the score pass that follows.
 int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const void *q_win, const void *k, const void *v,
@@ -980,10 +996,10 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   // Where the blocks' logits fit the chip and all blocks are resident at once, the scores need no second pass over K (us per call, two
   // passes -> one: 1500 tokens 19.8 -> 16.5, 8000 21.8 -> 20.4, 16384 27.9 -> 24.8, 32768 41.3 -> 35.5, 64 / 8 heads 16000 37.2 -> 30.1, 32
   // sequences of 800-900 51.0 -> 47.0).  Not while several contexts exist on the device: resident launches of different contexts
-  // are chained, and not where the two-pass kernels are asked for.
+  // are chained, not where the two-pass kernels are asked for, and not where they are faster.
   const int blocks = a.n_split * r.V * r.n_seq, per = (tiles_max + a.n_split - 1) / a.n_split;
   if (keep_k && ctx->score_path != 1 && !ctx->boxes_posted && !several_contexts(ctx->device) && per <= kWoKeepTiles * wout_tiles_per_block_min() &&
-      blocks <= std::min(ctx->n_cu_wout, kMaxFusedBlocks) && a.n_split <= kWoKeepSplits &&
+      blocks <= std::min(ctx->n_cu_wout, kMaxFusedBlocks) && a.n_split <= kWoKeepSplits && wout_sums_pay(a, tiles_max, ctx->n_cu_wout) &&
       r.sum_p * r.Hq * (int64_t)sizeof(float) <= (int64_t)kWoSumBytes) {
     a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
     a.sums_stride = r.sum_p;

@@ -8,6 +8,20 @@ from paper_2502_01068_amd import binding as fk
 pytestmark = pytest.mark.gpu
 # A probability is 2^x; both forms round x (at most 32 in size here: 2^-20) twice on its way: 4 * 2^-20 * ln 2.
 TOL = dict(rtol=4e-6, atol=1e-37)
+# The last value: whether the first launch leaves window sums (test_launches_host.py looks at the launches of these calls).
+CASES = [
+    ([9], 32, 8, "avg", 7, 8, True, False), ([32], 28, 7, "avg", 7, 8, True, False), ([33], 32, 8, "max", 7, 8, True, True),
+    ([257], 28, 4, "avg", 15, 8, True, True), ([2048], 32, 8, "avg", 7, 3, True, True), ([8193], 32, 8, "max", 31, 8, False, True),
+    ([32767], 32, 8, "avg", 7, 8, True, True), ([32768], 28, 4, "max", 1, 5, True, True), ([32769], 32, 8, "avg", 7, 8, True, False),
+    ([16384], 64, 8, "avg", 7, 8, True, True), ([16385], 64, 8, "avg", 7, 8, True, False), ([4000], 56, 8, "max", 5, 7, True, True),
+    ([900], 4, 1, "avg", 7, 8, True, False), ([30000], 8, 1, "avg", 7, 8, True, False), ([256], 16, 4, "avg", 7, 8, True, False),
+    ([257], 16, 4, "max", 7, 8, True, True), ([3840], 16, 2, "avg", 7, 8, True, True), ([3841], 16, 2, "avg", 7, 8, True, False),
+    ([5000, 16000], 32, 8, "avg", 7, 8, True, True), ([700, 9, 1024], 32, 8, "max", 7, 8, True, True),
+    ([300 + 97 * i for i in range(8)], 64, 8, "avg", 3, 8, True, True), ([3000 - i for i in range(8)], 28, 4, "avg", 7, 8, True, True),
+    ([1500] * 16, 4, 1, "avg", 7, 8, True, False), ([1500, 700] * 8 + [9], 4, 1, "avg", 7, 8, True, True), ([3000] * 16, 8, 2, "max", 7, 8, True, True),
+    ([8000] * 3, 8, 2, "avg", 7, 8, True, False), ([12000, 9000, 9000], 12, 3, "avg", 7, 8, True, True), ([60] * 33, 8, 2, "avg", 7, 8, True, False),
+    ([1024] * 32, 32, 8, "avg", 7, 8, True, True), ([1025] + [600] * 31, 32, 8, "avg", 7, 8, True, False),
+]
 
 
 def _inputs(lengths, hq, hkv, window=8):
@@ -22,14 +36,8 @@ def _check(got, want):
     torch.testing.assert_close(got[1], want[1], **TOL)
 
 
-@pytest.mark.parametrize("lengths,hq,hkv,pool,pool_kernel,window,causal", [
-    ([9], 32, 8, "avg", 7, 8, True), ([33], 32, 8, "max", 7, 8, True), ([257], 28, 4, "avg", 15, 8, True), ([2048], 32, 8, "avg", 7, 3, True),
-    ([8193], 32, 8, "max", 31, 8, False), ([32767], 32, 8, "avg", 7, 8, True), ([32768], 28, 4, "max", 1, 5, True), ([32769], 32, 8, "avg", 7, 8, True),
-    ([16384], 64, 8, "avg", 7, 8, True), ([4000], 56, 8, "max", 5, 7, True), ([900], 4, 1, "avg", 7, 8, True), ([30000], 8, 1, "avg", 7, 8, True),
-    ([5000, 16000], 32, 8, "avg", 7, 8, True), ([700, 9, 1024], 32, 8, "max", 7, 8, True), ([300 + 97 * i for i in range(8)], 64, 8, "avg", 3, 8, True),
-    ([1024] * 32, 32, 8, "avg", 7, 8, True), ([1025] + [600] * 31, 32, 8, "avg", 7, 8, True),
-])
-def test_matches_two_passes(lengths, hq, hkv, pool, pool_kernel, window, causal):
+@pytest.mark.parametrize("lengths,hq,hkv,pool,pool_kernel,window,causal,sums", CASES)
+def test_matches_two_passes(lengths, hq, hkv, pool, pool_kernel, window, causal, sums):
     print("case: window sums lengths=%s.. (%d) hq=%d hkv=%d %s %d w=%d" % (lengths[:4], len(lengths), hq, hkv, pool, pool_kernel, window), flush=True)
     ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=len(lengths))
     shape = fk.make_shape(lengths, n_q_heads=hq, n_kv_heads=hkv, pool_mode=pool, pool_kernel=pool_kernel, window=window, causal=causal)
@@ -39,6 +47,8 @@ def test_matches_two_passes(lengths, hq, hkv, pool, pool_kernel, window, causal)
     ctx.fkv_set_score_path(0)
     first = ctx.fkv_score_window_output(shape, q, k, v)
     _check(first, want)
+    if not sums:
+        assert torch.equal(first[0], want[0])
     ctx.fkv_score_window(shape, q, k)  # shares the mailboxes
     again = ctx.fkv_score_window_output(shape, q, k, v)
     assert all(torch.equal(x, y) for x, y in zip(first, again))

@@ -2,6 +2,7 @@
 import pytest
 
 import launches
+import test_gpu_wout_sums
 
 EHIP, EUNSUPPORTED = -6, -4
 
@@ -43,3 +44,15 @@ def test_window_sums_wait_no_longer_than_reading_k_again_is_worth(calls):
     got = calls(window, limit(1000000), window, limit(5), window, limit(0), window)
     ticks = [r["launches"][0]["wait_ticks"] for r in got if r["launches"]]
     assert ticks == [10000, 10000, 500, 10000]  # of 10 ns
+
+
+def test_window_sums_where_they_are_faster(calls):
+    cases = test_gpu_wout_sums.CASES
+    got = calls(*[("window_output", {"lengths": c[0], "hq": c[1], "hkv": c[2], "pool_kernel": c[4], "window": c[5]}) for c in cases])
+    for c, r in zip(cases, got):
+        assert r["value"] == 0 and launches.kernels(r)[0] == ("k_wout_partial<true, true>" if c[-1] else "k_wout_partial<true, false>"), c
+
+
+def test_no_window_sums_beside_another_context(calls):
+    got = calls(("window_output", {"lengths": [8192]}), ("create", {}), ("window_output", {"lengths": [8192]}), ("destroy", {}), ("window_output", {"lengths": [8192]}))
+    assert [launches.kernels(r)[0] for r in got if r["launches"]] == ["k_wout_partial<true, %s>" % s for s in ("true", "false", "true")]
