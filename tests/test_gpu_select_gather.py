@@ -10,24 +10,30 @@ from paper_2502_01068_amd import binding as fk
 pytestmark = pytest.mark.gpu
 
 
+CASES = [
+    ([4101], [64], [512], 4096, 32), ([4102], [8], [8], 24, 32), ([9], [9], [8], 8, 32), ([8], [8], [8], 8, 32), ([8197], [2048], None, 0, 32),
+    ([8198], [65], [700], 136, 64), ([12293], [1229], [1230], 1024, 28), ([12294], [129], None, 0, 32), ([16389], [1000], [1639], 4096, 32),
+    ([16390], [11000], None, 0, 32), ([20486], [300], [20486], 8, 64), ([24581], [2000], [2400], 4096, 32), ([24580], [2000], [24], 64, 32),
+    ([23000, 2000, 8, 9, 4500], [100, 2000, 8, 8, 450], [2300, 17, 8, 9, 1111], 512, 32), ([1500 + 7 * i for i in range(64)], [130] * 64, [31] * 64, 56, 32),
+    ([3000] * 9, [8, 64, 128, 63, 129, 3000, 8, 9, 257], None, 0, 28), ([3335], [300], [600], 64, 24), ([3336], [200], [301], 64, 28),
+    ([7431, 9], [300, 8], [1000, 9], 64, 16), ([7440], [300], [1000], 64, 20), ([700, 2049, 8, 1300], [100] * 2 + [8, 100], [70, 205, 8, 130], 64, 32),
+    ([300 + i for i in range(10)], [30] * 10, [40] * 10, 24, 32), ([300] * 8 + [77], [65, 8] * 4 + [9], None, 0, 28), ([7000], [7000], [7000], 64, 32),
+]
+POOLS = [("avg", 7), ("max", 1), ("avg", 15)]  # the others where the select adds up group sums: the pooling does not matter behind blocks that have all heads
+
+
+def hkv_of(hq):
+    return {28: 4, 20: 4, 16: 2}.get(hq, 8)
+
+
 def _randn(gen, *shape):
     return torch.randn(shape, device="cuda", generator=gen, dtype=torch.bfloat16)
 
 
-@pytest.mark.parametrize("lengths,budgets,k_tsp,hidden,hq", [
-    ([4101], [64], [512], 4096, 32), ([4102], [8], [8], 24, 32), ([9], [9], [8], 8, 32), ([8], [8], [8], 8, 32), ([8197], [2048], None, 0, 32),
-    ([8198], [65], [700], 136, 64), ([12293], [1229], [1230], 1024, 28), ([12294], [129], None, 0, 32), ([16389], [1000], [1639], 4096, 32),
-    ([16390], [16390], None, 0, 32), ([20486], [300], [20486], 8, 64), ([24581], [2000], [2400], 4096, 32), ([24582], [2000], [24], 64, 32),
-    ([23000, 2000, 8, 9, 4500], [100, 2000, 8, 8, 450], [2300, 17, 8, 9, 1111], 512, 32), ([1500 + 7 * i for i in range(64)], [130] * 64, [31] * 64, 56, 32),
-    ([3000] * 9, [8, 64, 128, 63, 129, 3000, 8, 9, 257], None, 0, 28), ([3335], [300], [600], 64, 24), ([3336], [200], [301], 64, 28),
-    ([7431, 9], [300, 8], [1000, 9], 64, 16), ([7440], [300], [1000], 64, 20), ([700, 2049, 8, 1300], [100] * 2 + [8, 100], [70, 205, 8, 130], 64, 32),
-])
-@pytest.mark.parametrize("pool", [("avg", 7), ("max", 1), ("avg", 15)], ids=lambda p: "%s%d" % p)
+@pytest.mark.parametrize("lengths,budgets,k_tsp,hidden,hq,pool", [c + (p,) for c in CASES for p in POOLS if p == POOLS[0] or sum(c[0]) <= 8300])
 def test_one_launch_matches_two(lengths, budgets, k_tsp, hidden, hq, pool):
-    if pool != ("avg", 7) and sum(lengths) > 8300:
-        pytest.skip("the pooling does not matter behind the blocks that have all heads")
     print("case: select and gather lengths=%s.. (%d) tsp=%s hidden=%d hq=%d %s" % (lengths[:3], len(lengths), k_tsp and k_tsp[:3], hidden, hq, pool), flush=True)
-    hkv = {28: 4, 20: 4, 16: 2}.get(hq, 8)
+    hkv = hkv_of(hq)
     gen = torch.Generator(device="cuda").manual_seed(sum(lengths) + hq)
     ctx = fk.Context(max_total_tokens=sum(lengths), max_seqs=len(lengths))
     shape = fk.make_shape(lengths, n_q_heads=hq, n_kv_heads=hkv, pool_mode=pool[0], pool_kernel=pool[1])
