@@ -517,9 +517,11 @@ bool plan_select_gather(const fkv_ctx *ctx, SelectGatherArgs &g, const Resolved 
   }
   const int n_cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
   if (longest > kSelGatherMaxKeys || bytes > (int64_t)kSelGatherMaxShare * n_cu) return false;
-  // The smallest share of the bytes (in steps of an eighth) whose blocks fit the CUs once, at least one for every row.
   int rows = 0;
   for (int i = 0; i < a.n_sets; ++i) rows += a.set[i].n_rows * r.n_seq;
+  const bool mid = rows > n_cu || (a.n_sets > 1 && 2 * rows > n_cu) || (g.block_table != nullptr && longest <= kSelGatherMidKeys);
+  const uint32_t most = mid ? kSelGatherMidShare : kSelGatherMaxShare;
+  // The smallest share of the bytes (in steps of an eighth) whose blocks fit the CUs once, at least one for every row.
   uint32_t share = rows >= n_cu ? (uint32_t)bytes : std::max((uint32_t)bytes / (uint32_t)n_cu, 1u), heaviest;
   int nb;
   while (true) {
@@ -541,7 +543,7 @@ bool plan_select_gather(const fkv_ctx *ctx, SelectGatherArgs &g, const Resolved 
   }
   g.blk[r.n_seq] = nb;
   g.longest = longest;
-  return heaviest <= kSelGatherMaxShare;
+  return heaviest <= most;
 }
 
 void fill_rowset(SelectRowSet *rs, const float *scores, int64_t stride, int n_rows, int32_t *out,

@@ -349,7 +349,13 @@ struct SelectGatherArgs {
 // (22 K), 8192 29.9 -> 27.7 (91 K), 16384 38.2 -> 37.6 (146 K), 24000 46.9 -> 46.1 (191 K), 52.9 -> 54.1 (270 K); 8 sequences of
 // 4000-4700 54.7 -> 53.7 (180 K), 13 of 2000-3100 50.5 -> 51.6 (250 K), 8 of 8192-16384 129 -> 157 (more than 800 K).
 constexpr int kSelGatherMaxKeys = 24 * 1024;
-constexpr uint32_t kSelGatherMaxShare = 192 << 10;
+// Fewer bytes a block (us, two launches -> one) where more rows than CUs leave a last round of few blocks, 33 sequences of 3000 78.1 -> 80.5
+// (154 K; 48 of 2400 90.2 -> 88.3, 123 K); where many rows share the CUs with rows of hidden rows, which are cut into few parts then, 18
+// sequences of 900 37.2 -> 38.1 (131 K); and for pages from inputs whose select is short, since one head's rows of a slot are 256 B apart
+// from the next head's, while the gather of its own writes whole slots: 8192 tokens all kept 29.2 -> 31.2 (131 K), 20 sequences of 3000 48.6 ->
+// 50.0 (154 K), 8192 of which 5734 are kept 29.1 -> 27.8 (92 K).
+constexpr uint32_t kSelGatherMaxShare = 192 << 10, kSelGatherMidShare = 120 << 10;
+constexpr int kSelGatherMidKeys = 12 * 1024;
 hipError_t launch_select_gather(const SelectGatherArgs &a, hipStream_t s);
 
 }  // namespace fkv

@@ -2,6 +2,7 @@
 import pytest
 
 import launches
+import test_gpu_select_gather
 import test_gpu_wout_sums
 
 EHIP, EUNSUPPORTED = -6, -4
@@ -56,3 +57,36 @@ def test_window_sums_where_they_are_faster(calls):
 def test_no_window_sums_beside_another_context(calls):
     got = calls(("window_output", {"lengths": [8192]}), ("create", {}), ("window_output", {"lengths": [8192]}), ("destroy", {}), ("window_output", {"lengths": [8192]}))
     assert [launches.kernels(r)[0] for r in got if r["launches"]] == ["k_wout_partial<true, %s>" % s for s in ("true", "false", "true")]
+
+
+@pytest.mark.parametrize("paged", [False, True])
+def test_every_parity_case_of_the_one_launch_takes_it(calls, paged):
+    """And makes two launches of select and gather while launches are timed, which is what that test compares with."""
+    cases = [(c, p) for c in test_gpu_select_gather.CASES for p in test_gpu_select_gather.POOLS[:1]]
+    steps = [("compress", {"lengths": c[0], "budgets": c[1], "k_tsp": None if paged else c[2], "hidden": c[3], "hq": c[4],
+                           "hkv": test_gpu_select_gather.hkv_of(c[4]), "pool_kernel": p[1], "paged": paged}) for c, p in cases]
+    got = calls(*steps, ("set", {"what": "profile_enable", "value": 1}), *steps)
+    for (c, _), one, two in zip(cases, got, got[len(steps) + 1:]):
+        assert launches.kernels(one)[-1].startswith("k_select_gather<"), c
+        assert [k.split("<")[0] for k in launches.kernels(two)[-2:]] == ["k_select", "k_gather_paged" if paged else "k_gather"], c
+
+
+def _compress(n, length, budget, **kw):
+    return "compress", dict({"lengths": [length] * n, "budgets": [budget] * n}, **kw)
+
+
+def test_one_launch_where_it_is_faster(calls):
+    """Rows and bytes of a block on both sides of the rule's lines: long rows, a share of 192 KB, 120 KB for pages from short inputs, for
+    a last round of few blocks and for many rows beside hidden rows."""
+    steps = [(_compress(1, 24581, 2048), True), (_compress(1, 24582, 2048), False), (_compress(1, 12000, 12000), True), (_compress(1, 24500, 24500), False),
+             (_compress(1, 8192, 7500, paged=True), True), (_compress(1, 8192, 8192, paged=True), False), (_compress(1, 13000, 9000, paged=True), True),
+             (_compress(48, 2400, 240), True), (_compress(33, 3000, 300), False), (_compress(32, 3000, 300), True),
+             (_compress(18, 900, 90, k_tsp=[90] * 18), True), (_compress(18, 900, 90, k_tsp=[135] * 18), False), (_compress(8, 900, 90, k_tsp=[135] * 8), True)]
+    got = calls(*[s for s, _ in steps])
+    for (s, one), r in zip(steps, got):
+        assert r["value"] == 0 and launches.kernels(r)[-1].startswith("k_select_gather<") == one, s
+
+
+def test_one_launch_not_while_several_blocks_share_a_row(calls):
+    got = calls(("set", {"what": "set_select_path", "value": 2}), _compress(1, 2048, 256), ("set", {"what": "set_select_path", "value": 1}), _compress(1, 2048, 256))
+    assert [launches.kernels(r)[-1].split("<")[0] for r in got if r["launches"]] == ["k_gather", "k_select_gather"]
