@@ -431,7 +431,7 @@ int enqueue_score(const ScoreWs &w, const fkv_shape *sh, const Resolved &r, cons
       f.part = w.fused_part;
       f.lse = w.fused_lse;
       f.err = w.err;
-      f.split = keep ? -1 : fused_split(r.V, total, f.n_sub_max, max_blocks);
+      f.split = keep ? -1 : fused_split(r.V, r.n_seq, total, f.n_sub_max, max_blocks);
       if (f.split > 0 && scores_tsp) {  // no block sees every head
         if (group_sums) {
           a.scores_tsp = nullptr;

@@ -126,7 +126,7 @@ template <typename A> __host__ __device__ inline int vg_heads(const A &a, int v)
 }
 int fused_slots(void);
 int fused_preferred_blocks(int n_sub);
-int fused_split(int v_groups, int n_ranges, int n_sub, int max_blocks);
+int fused_split(int v_groups, int n_seq, int n_ranges, int n_sub, int max_blocks);
 int score_fused_max_blocks_per_cu(void);
 hipError_t launch_score_fused(const ScoreArgs &a, const FusedArgs &f, hipStream_t s);
 int keep_sub_max(int v_groups);

@@ -47,9 +47,12 @@ constexpr int kFusedSlotsMax = kFusedSubLong * kSub;
 int fused_slots(void) { return kFusedSlotsMax; }
 
 // The split of a launch's ranges (see FusedArgs), or -1: a range is one block's work.  Only where every block still has a CU to
-// itself, and ranges are of one or two sub-tiles then.
-int fused_split(int v_groups, int n_ranges, int n_sub, int max_blocks) {
+// itself, and ranges are of one or two sub-tiles then.  Blocks of four waves fold two softmax rows a wave for each group of rows they
+// own: up to four virtual groups, for which a range stays one block, that is slower where blocks own several (us per call, blocks of
+// eight waves and of four: 20 tokens of 16 / 4 heads 27.1, 28.6, 8 sequences of 40 16.8, 17.7, 24 of 900 13.0, 12.9).
+int fused_split(int v_groups, int n_seq, int n_ranges, int n_sub, int max_blocks) {
   const int shift = v_groups > kSplitWaves ? 1 : 0;
+  if (shift == 0 && n_seq * v_groups * (kRowsPerGroup / kOwnRows) > n_ranges) return -1;
   return v_groups <= kMaxKvHeads && n_sub <= kFusedSubFew && n_ranges <= kSplitRanges && (n_ranges << shift) <= max_blocks ? shift : -1;
 }
 // Block count up to which a layout of n_sub full sub-tiles per block is preferred over one more

@@ -2,6 +2,7 @@
 import pytest
 
 import launches
+import test_gpu_score_split
 import test_gpu_select_gather
 import test_gpu_wout_sums
 
@@ -90,3 +91,16 @@ def test_one_launch_where_it_is_faster(calls):
 def test_one_launch_not_while_several_blocks_share_a_row(calls):
     got = calls(("set", {"what": "set_select_path", "value": 2}), _compress(1, 2048, 256), ("set", {"what": "set_select_path", "value": 1}), _compress(1, 2048, 256))
     assert [launches.kernels(r)[-1].split("<")[0] for r in got if r["launches"]] == ["k_gather", "k_select_gather"]
+
+
+def test_ranges_split_between_blocks(calls):
+    """Without the mean over all heads; with it only where a block still sees every head, or the select adds the groups' sums up."""
+    cases = test_gpu_score_split.CASES
+    step = lambda c, mean: ("score", {"lengths": c[0], "hq": c[1], "hkv": c[2], "pool_kernel": c[4], "window": c[5], "mean": mean})
+    got = calls(*[step(c, mean) for c in cases for mean in (False, True)])
+    for c, split, mean in zip(cases, got[::2], got[1::2]):
+        groups = c[2] * (2 if c[1] // c[2] > 4 else 1)
+        assert (launches.kernels(split) == ["k_score_fused<2, 4>"]) == c[-1], c
+        assert (launches.kernels(mean) == ["k_score_fused<2, 4>"]) == (c[-1] and groups <= 4), c
+        if c[-1]:
+            assert split["launches"][0]["threads"] == 256 and split["launches"][0]["blocks"] <= 256
