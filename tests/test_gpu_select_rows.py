@@ -71,7 +71,14 @@ def test_select_mixed_lengths(lengths):
     ctx.close()
 
 
-@pytest.mark.parametrize("n_rows,lengths", [(64, [32766]), (64, [39092]), (64, [65533]), (40, [33000, 34000]), (64, [70000]), (64, [24600, 33000])])
+# The last value: keys per thread of the resident kernel, 0: the launch chain (test_launches_host.py looks at the launches).
+MANY_LONG_ROWS = [
+    (64, [32765], 8), (64, [32766], 16), (64, [39092], 16), (64, [65533], 16), (64, [65534], 32), (40, [33000, 34000], 16), (64, [70000], 32),
+    (64, [24600, 33000], 32), (64, [131069], 32), (64, [131070], 0), (64, [40000, 33000, 33000], 0),
+]
+
+
+@pytest.mark.parametrize("n_rows,lengths", [c[:-1] for c in MANY_LONG_ROWS])
 def test_select_many_long_rows(n_rows, lengths):
     """More slices of 8192 keys than blocks are resident: larger slices, or the launch chain.  The same indices from both."""
     print("case: select %d rows of %s" % (n_rows, lengths), flush=True)

@@ -4,6 +4,7 @@ import pytest
 import launches
 import test_gpu_score_split
 import test_gpu_select_gather
+import test_gpu_select_rows
 import test_gpu_wout_sums
 
 EHIP, EUNSUPPORTED = -6, -4
@@ -104,3 +105,11 @@ def test_ranges_split_between_blocks(calls):
         assert (launches.kernels(mean) == ["k_score_fused<2, 4>"]) == (c[-1] and groups <= 4), c
         if c[-1]:
             assert split["launches"][0]["threads"] == 256 and split["launches"][0]["blocks"] <= 256
+
+
+def test_slices_of_many_long_rows(calls):
+    cases = test_gpu_select_rows.MANY_LONG_ROWS
+    got = calls(*[("select", {"lengths": [P + 8 for P in lengths], "rows": n, "counts": [8 + P // 11 for P in lengths], "hq": 64}) for n, lengths, _ in cases])
+    for c, r in zip(cases, got):
+        name = launches.kernels(r)[0]
+        assert r["value"] == 0 and name.startswith("k_select_coop<%d," % c[2] if c[2] else "k_sel_long_prep"), (c, name)
