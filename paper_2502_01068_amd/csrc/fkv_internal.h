@@ -254,7 +254,7 @@ constexpr int kWoKeepSplits = 32;  // most splits whose normalisers a block fold
 // block has a CU, as the host plans; when a kernel of another stream holds CUs, blocks of this launch may start only once others
 // have left, and reading K again costs 10 us.
 constexpr unsigned long long kWoWaitTicks = 10000;
-constexpr size_t kWoSumBytes = (size_t)8 << 20;
+constexpr size_t kWoSumBytes = (size_t)8 << 20;  // most window sums of a call; a context has room for those of its tokens
 int wout_tiles_per_block_min(void);
 hipError_t launch_wout(const WoutArgs &a, hipStream_t s);        // the splits' partials
 int wout_sums_max_blocks_per_cu(void);

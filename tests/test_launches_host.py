@@ -113,3 +113,9 @@ def test_slices_of_many_long_rows(calls):
     for c, r in zip(cases, got):
         name = launches.kernels(r)[0]
         assert r["value"] == 0 and name.startswith("k_select_coop<%d," % c[2] if c[2] else "k_sel_long_prep"), (c, name)
+
+
+def test_workspace_holds_the_window_sums_of_its_tokens(calls):
+    """Up to 64 heads of 4 bytes a token, 8 MB at most: a context for short inputs does not pay for long ones."""
+    small, full, more = [r["value"] for r in calls(*[("workspace_bytes", {"tokens": n, "seqs": 1}) for n in (2048, 32768, 63488)])]
+    assert (full - small) - (more - full) == (8 << 20) - 2048 * 256  # what grows with the tokens is linear otherwise
