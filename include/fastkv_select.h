@@ -309,7 +309,7 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
 int fkv_set_score_path(fkv_ctx *ctx, int mode);
 
 /* Which kernels select the top-k of a score row (Sec. 4.2).  0 (default): rows of more than 24573 keys
- * are cut into at most 8 slices (8192, 16384 or 32768 keys each, by row length), one block per slice,
+ * are cut into at most 8 slices (8192, 16384 or 32768 keys each, by row length and number of rows), one block per slice,
  * and the blocks of a row agree on the threshold through device memory inside one launch, when every
  * block of the call can be resident at once (rows x slices x sequences <= compute units, rows up to
  * 262144 keys); other calls take one block per row (rows up to 32768 keys) or a chain of launches
@@ -358,8 +358,9 @@ int fkv_clear_error(fkv_ctx *ctx);
  * un-profiled time of the same call).  fkv_profile_read synchronises those events, writes
  * the accumulated milliseconds and launch counts of kernel ids 0 .. n-1 (n =
  * fkv_profile_kernels()) and clears the accumulators.  Calls that otherwise select and gather in one launch
- * (the compress calls on short rows) make two while timing is on, so that each has its own figure; their
- * results are the same.  Not for use under graph capture. */
+ * (the compress calls on short rows) make two while timing is on, so that each has its own figure, and with hidden rows
+ * their score launch then also forms the mean over all heads, which it leaves to the one launch otherwise: the figures of short
+ * calls are of more and longer launches than the untimed call makes.  The results are the same.  Not for use under graph capture. */
 int fkv_profile_kernels(void);
 const char *fkv_profile_kernel_name(int id);
 int fkv_profile_enable(fkv_ctx *ctx, int on);

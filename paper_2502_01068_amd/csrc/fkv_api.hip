@@ -505,7 +505,8 @@ void fill_select(SelectArgs &a, fkv_ctx *ctx, const Resolved &r) {  // the row s
 }
 
 // Whether select and gather of a compress call go in one launch, and its blocks: where every row is one block's work in the
-// select (fkv_select.hip).  While launches are timed they stay apart, so that each has a figure of its own.
+// select (fkv_select.hip).  While launches are timed they stay apart, so that each has a figure of its own (and the score launch is the
+// one that forms the mean over all heads, with blocks of eight waves): a kernel trace shows the launches of untimed calls.
 bool plan_select_gather(const fkv_ctx *ctx, SelectGatherArgs &g, const Resolved &r) {
   if (ctx->prof_on || ctx->select_path == 2) return false;
   const SelectArgs &a = g.sel;
@@ -1276,9 +1277,11 @@ int fkv_compress_kv(fkv_ctx *ctx, const fkv_shape *shape, const void *q_win, con
   c.x_cpr_shift = log2_exact(c.x_row_bytes / 16);
   c.Hkv = r.Hkv;
   const bool one = plan_select_gather(ctx, c, r);
-  // The two-pass kernels' partials are idle in a call that leaves sums: 32 bytes a token and 4096 a sequence, for 32 a token and 96 of padding.
+  // The two-pass kernels' partials are idle in a call that leaves sums.  A statistics block's share of them holds the sums of its tokens,
+  // and the one that every sequence has beside those of its whole chunks the rows' padding (kMaxSums rows, up to three floats each).
   float *sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.partial);
-  static_assert(kMaxVGroups * kRowsPerGroup * sizeof(float2) >= kMaxKvHeads * sizeof(float) * kStatsChunk, "a statistics block has its tokens' sums");
+  static_assert(kMaxVGroups * kRowsPerGroup * sizeof(float2) >= kMaxSums * sizeof(float) * kStatsChunk && kMaxVGroups * kRowsPerGroup * sizeof(float2) >= kMaxSums * 3 * sizeof(float),
+                "room for the group sums");
   bool summed = false;
   rc = enqueue_score(ws_of(ctx), shape, r, q_win, k, sg, stp, nullptr, st, one ? sums : nullptr, &summed);
   if (rc != FKV_OK) return rc;
