@@ -19,9 +19,13 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
-  size_t partial, rowstat, scores_group, scores_tsp, counters, fused_part, fused_lse, sel_long, sel_coop, dec_part, dec_count, wout_sums, wout_o, wout_ms, total;
+  size_t partial, rowstat, scores_group, scores_tsp, counters, fused_part, fused_lse, sel_long, sel_coop, dec_part, dec_count, wout_o, wout_ms, total;
   int max_stat_blocks;
 };
+
+size_t wout_sum_bytes(int64_t max_tokens) {  // of the calls that leave window sums
+  return align_up(std::min(kWoSumBytes, (size_t)max_tokens * kMaxKvHeads * kMaxReal * sizeof(float)));
+}
 
 WsLayout ws_layout(int64_t max_tokens, int32_t max_seqs) {
   WsLayout w{};
@@ -40,8 +44,7 @@ WsLayout ws_layout(int64_t max_tokens, int32_t max_seqs) {
   w.dec_part = off;     off += align_up((size_t)2 * kDecodeMaxBlocks * kDecodeSlotFloats * sizeof(float));
   w.dec_count = off;    off += align_up((size_t)max_seqs * kMaxKvHeads * sizeof(unsigned));
   const size_t wout_slots = (size_t)kWoutBlocks + (size_t)kMaxVGroups * max_seqs;
-  w.wout_sums = off;    off += align_up(std::min(kWoSumBytes, (size_t)max_tokens * kMaxKvHeads * kMaxReal * sizeof(float)));
-  w.wout_o = off;       off += align_up(wout_slots * kRowsPerGroup * kHeadDim * sizeof(float));
+  w.wout_o = off;       off += wout_sum_bytes(max_tokens) + align_up(wout_slots * kRowsPerGroup * kHeadDim * sizeof(float));  // the window sums first
   w.wout_ms = off;      off += align_up(wout_slots * kRowsPerGroup * sizeof(float2));
   w.total = off;
   return w;
@@ -981,7 +984,7 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   a.q_win = static_cast<const uint16_t *>(q_win);
   a.k = static_cast<const uint16_t *>(k);
   a.v = static_cast<const uint16_t *>(v);
-  a.part_o = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
+  a.part_o = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o + wout_sum_bytes(ctx->max_tokens));
   a.part_ms = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.wout_ms);
   a.out = out;
   a.keep_k = keep_k;
@@ -1005,7 +1008,7 @@ int enqueue_wout(fkv_ctx *ctx, const fkv_shape *shape, const Resolved &r, const 
   if (keep_k && ctx->score_path != 1 && !ctx->boxes_posted && !several_contexts(ctx->device) && per <= kWoKeepTiles * wout_tiles_per_block_min() &&
       blocks <= std::min(ctx->n_cu_wout, kMaxFusedBlocks) && a.n_split <= kWoKeepSplits && wout_sums_pay(a, tiles_max, ctx->n_cu_wout) &&
       r.sum_p * r.Hq * (int64_t)sizeof(float) <= (int64_t)kWoSumBytes) {
-    a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_sums);
+    a.sums = reinterpret_cast<float *>(ctx->ws + ctx->lay.wout_o);
     a.sums_stride = r.sum_p;
     a.boxes = reinterpret_cast<float2 *>(ctx->ws + ctx->lay.fused_part);
     a.counters = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.counters);
