@@ -15,6 +15,9 @@ PKG = os.path.join(ROOT, "paper_2502_01068_amd")
 
 
 def run(steps, tmp_path):
+    if not os.path.exists(os.path.join(PKG, "libfastkv_select.so")):
+        from paper_2502_01068_amd import build
+        build.build()
     recorder = os.path.join(str(tmp_path), "hip_recorder.so")
     if not os.path.exists(recorder):
         subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-attributes", "-D__HIP_PLATFORM_AMD__=1",
